@@ -1285,15 +1285,14 @@ static int step_body(coe_ctx* c, coe_step_stats& st)
     if (rc) return rc;
     const int32_t E = c->E;
 
-    // request arranging, index part
-    {
-        Span sp(c, COE_K_REGROUP_INDEX, (double)c->n_live * 16.0, c->sc);
-        HIPCHK(c, coe::k::regroup_index(c->d_cur, c->n_live, E, c->d_cnt, c->d_off, c->d_perm, c->d_inv, c->d_blockhist, c->sc));
-    }
+    // request arranging, index part (with an arranging window: the oldest queued request of every group, behind the counts)
     bool arranging = false;
     for (const ArchPlan& a : c->archs) arranging = arranging || a.arr_wait > 0;
-    if (arranging)   // the oldest queued request of every group, behind the counts
-        HIPCHK(c, coe::k::group_heads(c->d_perm, c->d_off, c->d_cnt, E, c->d_cnt + E, c->sc));
+    {
+        Span sp(c, COE_K_REGROUP_INDEX, (double)c->n_live * 16.0, c->sc);
+        HIPCHK(c, coe::k::regroup_index(c->d_cur, c->n_live, E, c->d_cnt, c->d_off, c->d_perm, c->d_inv, c->d_blockhist,
+                                        arranging ? c->d_cnt + E : nullptr, c->sc));
+    }
     HIPCHK(c, hipMemcpyAsync(c->h_cnt, c->d_cnt, (size_t)E * 4 * (arranging ? 2 : 1), hipMemcpyDeviceToHost, c->sc));
     HIPCHK(c, hipStreamSynchronize(c->sc));
     auto t0 = std::chrono::steady_clock::now();
@@ -1762,7 +1761,7 @@ int coe_debug_regroup(coe_ctx* c, int32_t n, const int32_t* cur, int32_t E, int3
     if (n > c->cfg.max_requests) return fail(c, COE_ERANGE, "more keys than max_requests");
     if (c->n_live > 0) return fail(c, COE_ESTATE, "requests are live");
     if (n) HIPCHK(c, hipMemcpy(c->d_cur, cur, (size_t)n * 4, hipMemcpyHostToDevice));
-    HIPCHK(c, coe::k::regroup_index(c->d_cur, n, E, c->d_cnt, c->d_off, c->d_perm, c->d_inv, c->d_blockhist, c->sc));
+    HIPCHK(c, coe::k::regroup_index(c->d_cur, n, E, c->d_cnt, c->d_off, c->d_perm, c->d_inv, c->d_blockhist, nullptr, c->sc));
     HIPCHK(c, hipStreamSynchronize(c->sc));
     std::vector<int32_t> hoff(E + 1);
     HIPCHK(c, hipMemcpy(hoff.data(), c->d_off, ((size_t)E + 1) * 4, hipMemcpyDeviceToHost));

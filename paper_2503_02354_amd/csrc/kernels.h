@@ -9,7 +9,7 @@
 namespace coe {
 namespace k {
 
-constexpr int kRegroupTile = 256;     // requests per workgroup in the regroup kernels
+constexpr int kRegroupTile = 256;     // the histogram scratch is sized for one histogram per so many requests
 constexpr int kRegroupMaxExperts = 2048;
 
 // Routing epilogue arguments.  slot == nullptr: row i writes logits row i and nothing else (plain forward).
@@ -28,9 +28,10 @@ struct RouteArgs {
 
 // Request arranging, index part: per-expert histogram, prefix scan, stable scatter of request indices.
 // cur[n]: expert id in [0,E) = pending, anything else = not pending.  cnt[E], off[E+1], perm[<=n], inv[n].
-// blockhist: scratch of ceil(n/kRegroupTile)*E int32.
+// blockhist: scratch of ceil(n/kRegroupTile)*E int32.  heads, if not null: heads[e] = perm[off[e]] (the oldest queued
+// request of expert e: the regroup is stable) or -1 for an empty group.
 hipError_t regroup_index(const int32_t* cur, int32_t n, int32_t E, int32_t* cnt, int32_t* off, int32_t* perm,
-                         int32_t* inv, int32_t* blockhist, hipStream_t stream);
+                         int32_t* inv, int32_t* blockhist, int32_t* heads, hipStream_t stream);
 
 // The same with the histogram scratch in a static device array of kRegroupStaticInts int32 (no allocation anywhere on the
 // path): hipErrorInvalidValue when ceil(n / kRegroupTile) * E exceeds it.  Runs on the current device; calls on one device
@@ -40,9 +41,6 @@ hipError_t regroup_index_static(const int32_t* cur, int32_t n, int32_t E, int32_
                                 int32_t* inv, hipStream_t stream);
 
 // Request arranging, activation part: dst row i = src row perm[i]; rows of row_bytes (multiple of 4) bytes.
-// heads[e] = perm[off[e]] (the oldest queued request of expert e: the regroup is stable) or -1 for an empty group
-hipError_t group_heads(const int32_t* perm, const int32_t* off, const int32_t* cnt, int32_t E, int32_t* heads,
-                       hipStream_t stream);
 hipError_t gather_rows(const void* src, const int32_t* perm, int32_t n_rows, size_t row_bytes, void* dst,
                        hipStream_t stream);
 

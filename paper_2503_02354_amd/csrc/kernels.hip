@@ -43,22 +43,35 @@ __device__ __forceinline__ float apply_act(float v, int act)
 }
 
 // -------------------------------------------------------------------------------------------------------------
-// regroup, index part
+// regroup, index part: a stable counting sort of the request indices by expert id
 // -------------------------------------------------------------------------------------------------------------
-// Pass 1: per-workgroup histogram of the pending requests' expert ids.
-__global__ __launch_bounds__(kRegroupTile) void regroup_count_kernel(const int32_t* __restrict__ cur, int32_t n,
-                                                                     int32_t E, int32_t* __restrict__ blockhist)
+// A workgroup owns a contiguous range of the keys and every wavefront a contiguous eighth of it, so the order inside a
+// group is: earlier workgroups, earlier wavefronts, earlier 64-key trips, lower lanes.  Two launches: every workgroup
+// writes the histogram of its range; then every workgroup adds up the columns of all histograms for itself (its own
+// group starts), counts its wavefronts' keys again and places them.  One launch when a single workgroup holds all keys.
+// What bounds it is latency: 0.4 MB of keys are read twice.  The former three launches spent 92 of 103 us in a scan by one
+// workgroup that walked 391 histograms of 256 keys one load after the other (100,003 keys, 370 experts); wide ranges
+// leave 49 histograms and all workgroups walk them at once with eight loads in flight.  That call: 96.4 -> 12.0 us, launches
+// included.
+constexpr int kPlaceThreads = 512;
+constexpr int kPlaceWaves = kPlaceThreads / kWave;
+constexpr int kPlaceRange = 2048;        // keys of a workgroup at least: 256 per wavefront, four trips
+constexpr int kPlaceMaxBlocks = 128;     // every workgroup reads every histogram: their number is bounded, ranges grow instead
+
+// Pass 1: histogram of a workgroup's range.
+__global__ __launch_bounds__(kPlaceThreads) void regroup_count_kernel(const int32_t* __restrict__ cur, int32_t n, int32_t E,
+                                                                      int32_t range, int32_t* __restrict__ blockhist)
 {
     extern __shared__ int32_t hist[];
-    for (int e = threadIdx.x; e < E; e += kRegroupTile) hist[e] = 0;
+    for (int e = threadIdx.x; e < E; e += kPlaceThreads) hist[e] = 0;
     __syncthreads();
-    int i = blockIdx.x * kRegroupTile + threadIdx.x;
-    if (i < n) {
-        int key = cur[i];
+    const int lo = blockIdx.x * range, hi = min(n, lo + range);
+    for (int i = lo + threadIdx.x; i < hi; i += kPlaceThreads) {
+        const int key = cur[i];
         if (key >= 0 && key < E) atomicAdd(&hist[key], 1);
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < E; e += kRegroupTile) blockhist[(size_t)blockIdx.x * E + e] = hist[e];
+    for (int e = threadIdx.x; e < E; e += kPlaceThreads) blockhist[(size_t)blockIdx.x * E + e] = hist[e];
 }
 
 // inclusive prefix sum across one wavefront
@@ -73,89 +86,121 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
     return v;
 }
 
-// Pass 2 (one workgroup): column sums of blockhist -> cnt; blockhist becomes the exclusive prefix down each column;
-// exclusive scan of cnt over experts -> off.
-constexpr int kScanThreads = 1024;
-__global__ __launch_bounds__(kScanThreads) void regroup_scan_kernel(int32_t* __restrict__ blockhist, int32_t nblocks,
-                                                                    int32_t E, int32_t* __restrict__ cnt,
-                                                                    int32_t* __restrict__ off)
+// Pass 2: group starts (written out by workgroup 0) and stable placement of the workgroup's range.  heads, if not null:
+// heads[e] = the first request of group e or -1.
+__global__ __launch_bounds__(kPlaceThreads) void regroup_place_kernel(const int32_t* __restrict__ cur, int32_t n, int32_t E,
+                                                                      int32_t range, int32_t key_bits,
+                                                                      const int32_t* __restrict__ blockhist,
+                                                                      int32_t* __restrict__ cnt, int32_t* __restrict__ off,
+                                                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv,
+                                                                      int32_t* __restrict__ heads)
 {
-    __shared__ int32_t wave_tot[kScanThreads / kWave];
-    __shared__ int32_t carry;
-    if (threadIdx.x == 0) carry = 0;
+    extern __shared__ int32_t lds[];
+    __shared__ int32_t wave_tot[kPlaceWaves];
+    int32_t* const wcount = lds;                       // [waves][E]: keys of every wavefront, then where its next one goes
+    int32_t* const total = lds + kPlaceWaves * E;      // [E]: keys of all workgroups, then the group's start
+    int32_t* const before = total + E;                 // [E]: keys of earlier workgroups
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    const int nblocks = gridDim.x, block = blockIdx.x;
+    for (int j = tid; j < (kPlaceWaves + 2) * E; j += kPlaceThreads) lds[j] = 0;
     __syncthreads();
-    int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    for (int base = 0; base < E; base += kScanThreads) {
-        int e = base + threadIdx.x;
-        int total = 0;
-        if (e < E) {
-            for (int b = 0; b < nblocks; ++b) {
-                int t = blockhist[(size_t)b * E + e];
-                blockhist[(size_t)b * E + e] = total;
-                total += t;
-            }
-            cnt[e] = total;
-        }
-        int incl = wave_inclusive_scan(total);
-        if (lane == kWave - 1) wave_tot[wid] = incl;
-        __syncthreads();
-        if (wid == 0) {
-            int t = lane < kScanThreads / kWave ? wave_tot[lane] : 0;
-            int s = wave_inclusive_scan(t);
-            if (lane < kScanThreads / kWave) wave_tot[lane] = s - t;   // exclusive offset of each wave
-        }
-        __syncthreads();
-        int c = carry;
-        int excl = c + wave_tot[wid] + incl - total;
-        if (e < E) off[e] = excl;
-        __syncthreads();
-        if (threadIdx.x == kScanThreads - 1) carry = excl + total;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) off[E] = carry;
-}
 
-// Pass 3: stable scatter.  Position of request i = off[key] + (requests with that key in earlier workgroups)
-// + (in earlier wavefronts of this workgroup) + (in lower lanes of this wavefront).
-__global__ __launch_bounds__(kRegroupTile) void regroup_scatter_kernel(const int32_t* __restrict__ cur, int32_t n,
-                                                                       int32_t E, const int32_t* __restrict__ blockhist,
-                                                                       const int32_t* __restrict__ off,
-                                                                       int32_t* __restrict__ perm,
-                                                                       int32_t* __restrict__ inv)
-{
-    extern __shared__ int32_t wcount[];   // [waves][E]
-    constexpr int kWaves = kRegroupTile / kWave;
-    for (int j = threadIdx.x; j < kWaves * E; j += kRegroupTile) wcount[j] = 0;
-    __syncthreads();
-    int i = blockIdx.x * kRegroupTile + threadIdx.x;
-    int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    int key = -1;
-    if (i < n) {
-        key = cur[i];
-        if (key < 0 || key >= E) key = -1;
+    const int per_wave = range / kPlaceWaves;          // a multiple of the wavefront size
+    const int lo = block * range + wid * per_wave, hi = min(n, lo + per_wave);
+    int32_t* const mine = wcount + wid * E;
+    for (int i = lo + lane; i < hi; i += kWave) {
+        const int key = cur[i];
+        if (key >= 0 && key < E) atomicAdd(&mine[key], 1);
     }
-    unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-    unsigned long long remaining = __ballot(key >= 0);
-    int rank = 0;
-    while (remaining) {
-        int leader = __ffsll((long long)remaining) - 1;
-        int lk = __shfl(key, leader, kWave);
-        unsigned long long peers = __ballot(key == lk);
-        if (key == lk) {
-            rank = __popcll(peers & lt_mask);
-            if (lane == leader) wcount[wid * E + lk] = __popcll(peers);
+    if (nblocks > 1) {
+        // column sums: as many threads per expert as fit, each over every so many-th histogram
+        const int cols = E < kPlaceThreads ? E : kPlaceThreads, parts = kPlaceThreads / cols;
+        const int part = tid / cols;
+        if (part < parts)
+            for (int e = tid % cols; e < E; e += cols) {
+                int t = 0, b4 = 0;
+#pragma unroll 8
+                for (int b = part; b < nblocks; b += parts) {
+                    const int v = blockhist[(size_t)b * E + e];
+                    t += v;
+                    b4 += b < block ? v : 0;
+                }
+                if (t) atomicAdd(&total[e], t);
+                if (b4) atomicAdd(&before[e], b4);
+            }
+    }
+    __syncthreads();
+    if (nblocks == 1) {
+        for (int e = tid; e < E; e += kPlaceThreads) {
+            int t = 0;
+#pragma unroll
+            for (int w = 0; w < kPlaceWaves; ++w) t += wcount[w * E + e];
+            total[e] = t;
         }
-        remaining &= ~peers;
+        __syncthreads();
     }
+    // exclusive scan of the totals: consecutive experts per thread
+    const int per = (E + kPlaceThreads - 1) / kPlaceThreads;
+    int sum = 0;
+    for (int j = 0; j < per; ++j) {
+        const int e = tid * per + j;
+        if (e < E) sum += total[e];
+    }
+    const int incl = wave_inclusive_scan(sum);
+    if (lane == kWave - 1) wave_tot[wid] = incl;
     __syncthreads();
-    if (key >= 0) {
-        int before = 0;
-        for (int w = 0; w < wid; ++w) before += wcount[w * E + key];
-        int pos = off[key] + blockhist[(size_t)blockIdx.x * E + key] + before + rank;
-        perm[pos] = i;
-        inv[i] = pos;
-    } else if (i < n) {
-        inv[i] = -1;
+    int start = incl - sum, all = 0;
+#pragma unroll
+    for (int w = 0; w < kPlaceWaves; ++w) {
+        if (w < wid) start += wave_tot[w];
+        all += wave_tot[w];
+    }
+    for (int j = 0; j < per; ++j) {
+        const int e = tid * per + j;
+        if (e >= E) break;
+        const int t = total[e];
+        if (block == 0) {
+            cnt[e] = t;
+            off[e] = start;
+            if (heads && t == 0) heads[e] = -1;
+        }
+        total[e] = start;
+        int at = start + before[e];
+#pragma unroll
+        for (int w = 0; w < kPlaceWaves; ++w) {
+            const int c = wcount[w * E + e];
+            wcount[w * E + e] = at;
+            at += c;
+        }
+        start += t;
+    }
+    if (block == 0 && tid == 0) off[E] = all;
+    __syncthreads();
+
+    // a wavefront places 64 keys a trip: the lanes with the same key find each other by one ballot per key bit, the lowest
+    // of them moves the wavefront's position for that key on
+    const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+    for (int base = lo; base < hi; base += kWave) {
+        const int i = base + lane;
+        int key = i < hi ? cur[i] : -1;
+        const bool live = key >= 0 && key < E;
+        unsigned long long peers = __ballot(live);
+        for (int b = 0; b < key_bits; ++b) {
+            const bool bit = (key >> b) & 1;
+            const unsigned long long set = __ballot(bit);
+            peers &= bit ? set : ~set;
+        }
+        if (live) {
+            const int pos = mine[key] + __popcll(peers & lt_mask);
+            perm[pos] = i;
+            inv[i] = pos;
+            if (heads && pos == total[key]) heads[key] = i;
+        } else if (i < hi) {
+            inv[i] = -1;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (live && (peers & lt_mask) == 0) mine[key] += __popcll(peers);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 
@@ -558,17 +603,23 @@ __global__ __launch_bounds__(kHeadThreads) void head_det_kernel(const uint16_t* 
 // launchers
 // -------------------------------------------------------------------------------------------------------------
 hipError_t regroup_index(const int32_t* cur, int32_t n, int32_t E, int32_t* cnt, int32_t* off, int32_t* perm,
-                         int32_t* inv, int32_t* blockhist, hipStream_t stream)
+                         int32_t* inv, int32_t* blockhist, int32_t* heads, hipStream_t stream)
 {
     if (n < 0 || E <= 0 || E > kRegroupMaxExperts) return hipErrorInvalidValue;
-    int nblocks = (n + kRegroupTile - 1) / kRegroupTile;
-    if (nblocks > 0)
-        hipLaunchKernelGGL(regroup_count_kernel, dim3(nblocks), dim3(kRegroupTile), sizeof(int32_t) * E, stream, cur, n, E,
+    const int32_t share = (int32_t)(((long long)n + kPlaceMaxBlocks - 1) / kPlaceMaxBlocks);
+    const int32_t range = share <= kPlaceRange ? kPlaceRange : (share + kPlaceThreads - 1) / kPlaceThreads * kPlaceThreads;
+    const int32_t nblocks = n <= range ? 1 : (n + range - 1) / range;
+    int32_t key_bits = 0;
+    while ((1 << key_bits) < E) ++key_bits;
+    if (nblocks > 1)
+        hipLaunchKernelGGL(regroup_count_kernel, dim3(nblocks), dim3(kPlaceThreads), sizeof(int32_t) * E, stream, cur, n, E, range,
                            blockhist);
-    hipLaunchKernelGGL(regroup_scan_kernel, dim3(1), dim3(kScanThreads), 0, stream, blockhist, nblocks, E, cnt, off);
-    if (nblocks > 0)
-        hipLaunchKernelGGL(regroup_scatter_kernel, dim3(nblocks), dim3(kRegroupTile),
-                           sizeof(int32_t) * E * (kRegroupTile / kWave), stream, cur, n, E, blockhist, off, perm, inv);
+    const size_t lds = sizeof(int32_t) * (size_t)E * (kPlaceWaves + 2);
+    static const hipError_t configured = hipFuncSetAttribute((const void*)regroup_place_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                             (int)(sizeof(int32_t) * kRegroupMaxExperts * (kPlaceWaves + 2)));
+    if (configured != hipSuccess) return configured;
+    hipLaunchKernelGGL(regroup_place_kernel, dim3(nblocks), dim3(kPlaceThreads), lds, stream, cur, n, E, range, key_bits, blockhist,
+                       cnt, off, perm, inv, heads);
     return hipGetLastError();
 }
 
@@ -608,24 +659,8 @@ hipError_t regroup_index_static(const int32_t* cur, int32_t n, int32_t E, int32_
         }
         ptr = g_scratch_ptr[dev];
     }
-    // every histogram entry the scan and the scatter read is written by the count kernel of the same call: nothing has to
-    // start at zero
-    return regroup_index(cur, n, E, cnt, off, perm, inv, ptr, stream);
-}
-
-__global__ void group_heads_kernel(const int32_t* __restrict__ perm, const int32_t* __restrict__ off,
-                                   const int32_t* __restrict__ cnt, int32_t E, int32_t* __restrict__ heads)
-{
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < E) heads[e] = cnt[e] > 0 ? perm[off[e]] : -1;
-}
-
-hipError_t group_heads(const int32_t* perm, const int32_t* off, const int32_t* cnt, int32_t E, int32_t* heads,
-                       hipStream_t stream)
-{
-    if (E <= 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(group_heads_kernel, dim3((E + 255) / 256), dim3(256), 0, stream, perm, off, cnt, E, heads);
-    return hipGetLastError();
+    // every histogram entry the placement reads is written by the count kernel of the same call: nothing has to start at zero
+    return regroup_index(cur, n, E, cnt, off, perm, inv, ptr, nullptr, stream);
 }
 
 hipError_t gather_rows(const void* src, const int32_t* perm, int32_t n_rows, size_t row_bytes, void* dst,
