@@ -66,9 +66,15 @@ struct GroupRoutes {
     int32_t slot_off[kMaxGroups];         // offset of the group's first request in RouteArgs::slot
 };
 
-// Plain convolution kernel for any shape, fp32 or bf16 storage, fp32 FMA accumulation.
+// Convolution of any shape, fp32 or bf16 storage, fp32 accumulation: conv_f32 where it supports the shape, else a plain
+// kernel with one thread per output.
 hipError_t conv_direct(int dtype, const void* x, const void* w, const float* bias, const void* res, void* y,
                        const ConvShape& s, hipStream_t stream);
+
+// fp32 convolution on the matrix cores: any shape whose patch and filters of one channel block fit LDS.
+bool conv_f32_supported(const ConvShape& s);
+hipError_t conv_f32(const void* x, const void* w, const float* bias, const void* res, void* y, const ConvShape& s,
+                    hipStream_t stream);
 
 // bf16 implicit-GEMM convolution on the matrix cores.  Requires C % 32 == 0 and K % 32 == 0 (N is not looked at).
 // The filters must have been repacked with pack_filters_mfma (host): w is [K][red] with red = R*S*C, out has the

@@ -691,6 +691,7 @@ hipError_t conv_direct(int dtype, const void* x, const void* w, const float* bia
 {
     size_t total = (size_t)s.N * s.P * s.Q * s.K;
     if (total == 0) return hipSuccess;
+    if (dtype == 0 && conv_f32_supported(s)) return conv_f32(x, w, bias, res, y, s, stream);
     size_t blocks = (total + 255) / 256;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (dtype == 1)

@@ -28,3 +28,36 @@ def test_regroup_range_edges(B, oracle, n, E):
     want = oracle.regroup(np.where(cur < E, cur, -1).astype(np.int32), E)
     for k in ("cnt", "off", "perm", "inv"):
         assert np.array_equal(got[k], want[k]), k
+
+
+@pytest.mark.parametrize("n,H,Wd,C,K,R,stride,pad,use_res,act", [
+    (2, 64, 64, 3, 16, 3, 1, 1, False, 1),        # contiguous patch rows, fewer than 32 filters
+    (3, 17, 15, 16, 32, 3, 1, 1, True, 0),        # one block of 16 channels, ragged tiles
+    (2, 33, 20, 32, 64, 3, 1, 1, False, 1),       # two filter blocks
+    (600, 7, 7, 64, 128, 3, 1, 1, True, 1),       # more tiles than resident workgroups, several channel blocks
+    (700, 5, 9, 8, 40, 3, 1, 1, False, 0),        # resident workgroups walk several tiles and two filter tiles of 64
+    (2, 31, 31, 24, 66, 3, 2, 1, True, 3),        # channels in blocks of 8, stride 2, filters not a multiple of 4
+    (2, 40, 37, 3, 64, 7, 2, 3, False, 2),        # 7x7 stride 2 on an image
+    (1, 6, 5, 5, 7, 1, 1, 0, True, 1),            # 1x1, odd everything
+    (1, 3, 3, 256, 10, 3, 1, 1, False, 0),        # one small tile
+])
+def test_conv_f32_elementwise(B, oracle, n, H, Wd, C, K, R, stride, pad, use_res, act):
+    rng = np.random.default_rng(n * 1000 + H * 10 + K)
+    x = rng.standard_normal((n, H, Wd, C)).astype(np.float32)
+    w = (rng.standard_normal((K, R, R, C)) * np.sqrt(2.0 / (R * R * C))).astype(np.float32)
+    bias = rng.standard_normal(K).astype(np.float32)
+    P = (H + 2 * pad - R) // stride + 1; Q = (Wd + 2 * pad - R) // stride + 1
+    res = rng.standard_normal((n, P, Q, K)).astype(np.float32) if use_res else None
+    ctx = B.Context(max_requests=1)
+    got, _ = ctx.coe_debug_conv(0, x, w, bias, res, stride, pad, act)
+    ctx.close()
+    some = range(n) if n <= 8 else sorted(set([0, 1, n - 1] + list(rng.integers(0, n, 20))))
+    for i in some:
+        r = None if res is None else res[i]
+        want = oracle.conv2d(x[i], w, bias, r, stride, pad, act, 0)
+        # a sum of m fp32 products in any order is off by at most m * 2^-24 times the sum of the absolute products (first
+        # order); bias and residual are two terms more; the activations' slopes stay below 1.13, their own evaluation adds
+        # a few roundings of the result
+        mag = oracle.conv2d(np.abs(x[i]), np.abs(w), np.abs(bias), None if r is None else np.abs(r), stride, pad, 0, 0)
+        bound = 1.13 * (R * R * C + 2) * 2.0 ** -24 * mag + 8 * 2.0 ** -24 * np.abs(want) + (1e-6 * mag if act >= 2 else 0)
+        assert np.all(np.abs(got[i] - want) <= bound), float((np.abs(got[i] - want) / bound).max())
