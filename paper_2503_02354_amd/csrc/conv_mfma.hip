@@ -699,7 +699,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv3x3_slab_kernel
     // compute unit is in its epilogue.  The filters then have to be in LDS one step earlier: four stages, loads three
     // steps ahead.
     constexpr bool kDeep = MB <= 2;
-    constexpr int kStagesB = kDeep ? 4 : 3;
 
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // 2 slabs | spare block | 3 or 4 filter stages
 
@@ -994,6 +993,256 @@ hipError_t launch_slab(const void* x, const void* wp, const float* bias, const v
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------------------------------
+// Few output tiles: with a handful of requests the kernels above leave most of the chip idle (512 filters over the 49
+// pixels of one 7 x 7 image are four 256 x 128 tiles) and each of their few workgroups walks the whole reduction with
+// its loads only two short steps ahead.  Splitting the reduction would change the order of the sums, and with it the
+// bits of a request's result with the number of requests that happen to run beside it; so the tile shrinks instead and
+// the loads run further ahead.  Same operands, same instruction and same order of accumulation as the kernel that the
+// shape otherwise takes (slab_order: channel blocks outside, window positions inside), hence the same bits.
+//   * STAGES stages of UN 32-channel steps each in LDS, all but two of them in flight; one barrier per stage.
+//   * operands of a stage are read into registers while the stage before it is multiplied.
+//   * row tiles run fastest: the workgroups of one XCD take all rows of a few filter tiles, so filters - most of the
+//     bytes here - come from memory once and not once per XCD.
+// ---------------------------------------------------------------------------------------------------------------
+template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel(const uint16_t* __restrict__ x,
+                                                                   const uint16_t* __restrict__ wp_all,
+                                                                   const float* __restrict__ bias_all,
+                                                                   const uint16_t* __restrict__ res,
+                                                                   uint16_t* __restrict__ y, ConvShape s, int M,
+                                                                   int tiles_n, GroupTable gt, uint32_t off_w, uint32_t off_b)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int BK = 32, KS = 2;
+    constexpr int NW = WAVES_M * WAVES_N;
+    constexpr int WM = 32 * MB, WN = 32 * NB, BM = WM * WAVES_M, BN = WN * WAVES_N;
+    constexpr int FA = BM / 16, FB = BN / 32 * KS;            // 1 KiB blocks per step
+    static_assert(FA % NW == 0 && FB % NW == 0, "every wave issues the same number of loads");
+    constexpr int A_PER_WAVE = FA / NW, B_PER_WAVE = FB / NW;
+    constexpr int LOADS = UN * (A_PER_WAVE + B_PER_WAVE);     // of a wave and stage
+    constexpr int FRAG = 512;                                 // elements per 1 KiB block
+    constexpr int STEP = (FA + FB) * FRAG, STAGE = UN * STEP;
+    static_assert(STAGES >= 3 && (STAGES - 2) * LOADS <= 63, "what is in flight at a wait fits its counter");
+
+    extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // STAGES * STAGE elements
+
+    int tile;
+    {
+        int L = blockIdx.x, total = gridDim.x;
+        int xcd = L % kXcds, slot = L / kXcds;
+        int base = total / kXcds, rem = total % kXcds;
+        tile = xcd * base + (xcd < rem ? xcd : rem) + slot;
+    }
+    const int PQ = s.P * s.Q;
+    int m_first = 0;
+    const uint16_t* wp = wp_all;
+    const float* bias = bias_all;
+    int g = 0, tiles_m = (M + BM - 1) / BM;
+    if (gt.n > 0) {
+        for (;; ++g) {                                        // the launch has exactly sum-of-tiles workgroups
+            tiles_m = ((gt.first_row[g + 1] - gt.first_row[g]) * PQ + BM - 1) / BM;
+            if (tile < tiles_m * tiles_n || g + 1 >= gt.n) break;
+            tile -= tiles_m * tiles_n;
+        }
+        m_first = gt.first_row[g] * PQ;
+        M = gt.first_row[g + 1] * PQ;
+        wp = (const uint16_t*)((const char*)gt.weights[g] + off_w);
+        bias = (const float*)((const char*)gt.weights[g] + off_b);
+    }
+    const int m0 = m_first + (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wid / WAVES_N, wn = wid % WAVES_N;
+
+    const int cblocks = s.C / BK;
+    const int RS = s.R * s.S;
+    const int ks16_total = RS * cblocks * KS;
+
+    const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(x, (uint32_t)s.N * (uint32_t)(s.H * s.W * s.C) * 2u);
+    const __amdgpu_buffer_rsrc_t w_rsrc = make_rsrc(wp, (uint32_t)s.K * (uint32_t)(RS * s.C) * 2u);
+
+    auto swz = [](int r16) { return ((r16 >> 1) & 3) ^ (r16 >> 3); };
+    // Byte offset of this lane's piece of an activation row, out of range where the window position is outside the image:
+    // for all nine positions at once in slab order, else for the position that is being fetched.  The channel block is
+    // a scalar offset, so a load needs no vector arithmetic (a wave's instruction issue is what bounds these tiles).
+    constexpr int kPos = SLAB_ORDER ? 9 : 1;
+    static_assert(!SLAB_ORDER || UN == 3, "three stages per channel block");
+    uint32_t a_at[A_PER_WAVE][kPos];
+    int32_t a_off[A_PER_WAVE], a_ih[A_PER_WAVE], a_iw[A_PER_WAVE];
+    auto place = [&](int j, int rr, int tt) __attribute__((always_inline)) -> uint32_t {
+        const bool in = (unsigned)(a_ih[j] + rr) < (unsigned)s.H && (unsigned)(a_iw[j] + tt) < (unsigned)s.W;
+        return in ? (uint32_t)(a_off[j] + (rr * s.W + tt) * s.C * 2) : kOutOfRange;
+    };
+    {
+        const int chunk = (lane & 3) ^ swz(lane >> 2);
+#pragma unroll
+        for (int j = 0; j < A_PER_WAVE; ++j) {
+            const int m = m0 + (wid * A_PER_WAVE + j) * 16 + (lane >> 2);
+            const bool ok = m < M;
+            const int mm = ok ? m : 0;
+            const int n = mm / PQ, pq = mm % PQ;
+            const int p = pq / s.Q, q = pq % s.Q;
+            a_ih[j] = ok ? p * s.stride - s.pad : -0x10000;    // a row past the end: no position is inside
+            a_iw[j] = q * s.stride - s.pad;
+            a_off[j] = ((n * s.H + p * s.stride - s.pad) * s.W + a_iw[j]) * s.C * 2 + chunk * 16;
+#pragma unroll
+            for (int k = 0; k < kPos; ++k) a_at[j][k] = place(j, k / 3, k % 3);
+        }
+    }
+    uint32_t b_off[B_PER_WAVE];
+#pragma unroll
+    for (int j = 0; j < B_PER_WAVE; ++j) {
+        int fb = wid * B_PER_WAVE + j;
+        b_off[j] = (uint32_t)((((n0 / 32 + fb / KS) * ks16_total + fb % KS) * FRAG + lane * 8) * 2);
+    }
+
+    // the stage that is fetched next: scalar offsets of its first channel block in a row and of its first filter fragment
+    uint32_t f_c = 0, f_w = 0, r_pos = 0, t_pos = 0;
+    const uint32_t c_end = (uint32_t)s.C * 2, tap_w = (uint32_t)cblocks * (KS * FRAG * 2);
+    // part (slab order): which three of the nine positions
+    auto issue = [&](auto part_c, int stage) __attribute__((always_inline)) {
+        constexpr int part = decltype(part_c)::value;
+        uint16_t* const st = lds + stage * STAGE;
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+#pragma unroll
+            for (int j = 0; j < A_PER_WAVE; ++j)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void*)(st + u * STEP + (wid * A_PER_WAVE + j) * FRAG), 16,
+                                                         a_at[j][SLAB_ORDER ? part * 3 + u : 0], SLAB_ORDER ? f_c : f_c + u * (BK * 2), 0, 0);
+#pragma unroll
+            for (int j = 0; j < B_PER_WAVE; ++j)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void*)(st + u * STEP + (FA + wid * B_PER_WAVE + j) * FRAG), 16, b_off[j],
+                                                         SLAB_ORDER ? f_w + (part * 3 + u) * tap_w : f_w + u * (KS * FRAG * 2), 0, 0);
+        }
+        // past the last stage the position stays put: what is fetched there is never used
+        if (SLAB_ORDER) {
+            if (part == 2 && f_c + BK * 2 < c_end) { f_c += BK * 2; f_w += KS * FRAG * 2; }
+        } else if (f_c + UN * BK * 2 < c_end) {
+            f_c += UN * BK * 2;
+            f_w += UN * KS * FRAG * 2;
+        } else {                                              // on to the next window position
+            const bool row_end = t_pos + 1 == (uint32_t)s.S;
+            if (!row_end || r_pos + 1 < (uint32_t)s.R) {
+                t_pos = row_end ? 0 : t_pos + 1;
+                r_pos = row_end ? r_pos + 1 : r_pos;
+                f_c = 0;
+                f_w += UN * KS * FRAG * 2;
+#pragma unroll
+                for (int j = 0; j < A_PER_WAVE; ++j) a_at[j][0] = place(j, r_pos, t_pos);
+            }
+        }
+    };
+
+    f32x16 acc[MB][NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    const int rd_row = lane & 31;
+    const int rd0 = (rd_row >> 4) * FRAG + ((rd_row & 15) * 4 + ((lane >> 5) ^ swz(rd_row & 15))) * 8;
+    bf16x8 af[2][UN][KS][MB], bfr[2][UN][KS][NB];             // [stage parity]
+    auto read = [&](auto set_c, int stage) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_c)::value;
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const uint16_t* a_lds = lds + stage * STAGE + u * STEP + (wm * MB * 2) * FRAG;
+            const uint16_t* b_lds = lds + stage * STAGE + u * STEP + (FA + wn * NB * KS) * FRAG + lane * 8;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+                for (int i = 0; i < MB; ++i) af[set][u][ks][i] = *(const bf16x8*)(a_lds + i * 2 * FRAG + (rd0 ^ (ks * 16)));
+#pragma unroll
+                for (int j = 0; j < NB; ++j) bfr[set][u][ks][j] = *(const bf16x8*)(b_lds + (j * KS + ks) * FRAG);
+            }
+        }
+    };
+    auto multiply = [&](auto set_c, int u) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_c)::value;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][u][ks][j], af[set][u][ks][i], acc[i][j], 0, 0, 0);
+    };
+
+    typedef std::integral_constant<int, 0> c0;
+    typedef std::integral_constant<int, 1> c1;
+    typedef std::integral_constant<int, 2> c2;
+    // stages are fetched in order; in slab order stage k holds positions 3 (k % 3) .. + 2
+#pragma unroll
+    for (int k = 0; k < STAGES - 1; ++k) {
+        if (SLAB_ORDER && k % 3 == 1) issue(c1{}, k);
+        else if (SLAB_ORDER && k % 3 == 2) issue(c2{}, k);
+        else issue(c0{}, k);
+    }
+    wait_before_barrier<(STAGES - 2) * LOADS>();
+    __builtin_amdgcn_s_barrier();
+    read(c0{}, 0);
+    // body of stage i: the loads of stage i + 1 have landed (its successors may be in flight) | barrier | stage i + STAGES - 1
+    // goes where stage i - 1 was: every wave has its operands in registers since before this barrier | operands of stage
+    // i + 1 | products of stage i.  Past the end stale stages are read into registers that nothing uses.
+    int next = 1, fill = STAGES - 1;
+    auto body = [&](auto part_c, auto cur_c, auto nxt_c) __attribute__((always_inline)) {
+        constexpr int part = decltype(part_c)::value;
+        wait_before_barrier<(STAGES - 3) * LOADS>();
+        __builtin_amdgcn_s_barrier();
+        read(nxt_c, next);
+        issue(std::integral_constant<int, SLAB_ORDER ? (part + STAGES - 1) % 3 : 0>{}, fill);
+#pragma unroll
+        for (int u = 0; u < UN; ++u) multiply(cur_c, u);
+        next = next == STAGES - 1 ? 0 : next + 1;
+        fill = fill == STAGES - 1 ? 0 : fill + 1;
+    };
+    if constexpr (SLAB_ORDER) {
+        for (int cb = 0; cb < cblocks; cb += 2) {
+            body(c0{}, c0{}, c1{});
+            body(c1{}, c1{}, c0{});
+            body(c2{}, c0{}, c1{});
+            if (cb + 1 == cblocks) break;
+            body(c0{}, c1{}, c0{});
+            body(c1{}, c0{}, c1{});
+            body(c2{}, c1{}, c0{});
+        }
+    } else {
+        const int n_stages = RS * cblocks / UN;               // the launcher picks UN so that it divides the channel blocks
+        for (int i = 0; i < n_stages; i += 2) {
+            body(c0{}, c0{}, c1{});
+            if (i + 1 == n_stages) break;
+            body(c0{}, c1{}, c0{});
+        }
+    }
+    wait_before_barrier<0>();
+    __builtin_amdgcn_s_barrier();        // every wave is done with the operand stages: LDS is free for the epilogue
+    store_tile_via_lds<MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
+#endif
+}
+
+template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES>
+hipError_t launch_ring(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
+                       hipStream_t stream, const Grouping& grp = Grouping())
+{
+    constexpr int BM = 32 * MB * WAVES_M, BN = 32 * NB * WAVES_N;
+    long long M = (long long)s.N * s.P * s.Q;
+    int tiles_n = s.K / BN;
+    long long total = count_tiles(M, (long long)s.P * s.Q, BM, tiles_n, grp.table);
+    if (total > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    if (total == 0) return hipSuccess;
+    constexpr size_t kLdsBytes = STAGES * UN * (size_t)(BM + BN) * 32 * sizeof(uint16_t);
+    static_assert(kLdsBytes <= 160 * 1024 && kLdsBytes >= (size_t)WAVES_M * WAVES_N * 32 * (32 * NB + 8) * 2, "operand stages and epilogue rows");
+    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES>,
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+    if (configured != hipSuccess) return configured;
+    hipLaunchKernelGGL((conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES>), dim3((unsigned)total), dim3(64 * WAVES_M * WAVES_N),
+                       kLdsBytes, stream, (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M,
+                       tiles_n, grp.table, grp.off_w, grp.off_b);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 bool conv_mfma_uses_slab(const ConvShape& s)
@@ -1002,6 +1251,38 @@ bool conv_mfma_uses_slab(const ConvShape& s)
 }
 
 namespace {
+
+// Launches with few output tiles go to conv_igemm_ring_kernel (same bits).  Measured on single launches, microseconds
+// with 4-5 of launch and event overhead (kernel the shape otherwise takes / 32 x 32 tiles / 64 x 64 tiles):
+//   512 -> 512, 3x3, 7 x 7:   1 image 54 / 13 / 16,  30 images 58 / 20 / 17,  100 images 61 / 63 / 46
+//   256 -> 256, 3x3, 14 x 14: 1 image 32 / 9 / 11,   20 images 33 / 18 / 12,  30 images 34 / 23 / 19
+//   128 -> 128, 3x3, 28 x 28: 1 image 20 / 7 / 9,    30 images 22 / 27 / 20
+//   64 -> 64, 3x3, 56 x 56:   1 image 10 / 6 / 7,    30 images 16 / 36 / 27
+//   3072 -> 768, 1x1, 197 positions: 1 image 34 / 14 / 17,  5 images 35 / 26 / 18
+//   768 -> 2304, 1x1, 197 positions: 1 image 13 / 8 / 9,    5 images 14 / 20 / 15
+// A single wavefront per 32 x 32 tile is ahead while the chip holds all tiles at once at two per compute unit; 64 x 64
+// tiles, which share operands between four wavefronts, while there are about two of them (three: 3x3) per compute unit.
+constexpr long long kRingTiles32 = 512, kRingTiles64 = 512, kRingTiles64Slab = 768;
+
+// hipErrorNotSupported: not a launch for these tiles
+hipError_t conv_ring(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
+                     hipStream_t stream, const Grouping& grp = Grouping())
+{
+    const bool slab = conv_mfma_uses_slab(s);
+    const int cblocks = s.C / 32;
+    if (!slab && cblocks % 2) return hipErrorNotSupported;       // a stage holds channel blocks of one window position
+    const long long M = (long long)s.N * s.P * s.Q, PQ = (long long)s.P * s.Q;
+    if (count_tiles(M, PQ, 32, s.K / 32, grp.table) <= kRingTiles32) {
+        if (slab) return launch_ring<true, 1, 1, 1, 1, 3, 4>(x, wp, bias, res, y, s, stream, grp);
+        if (cblocks % 4 == 0) return launch_ring<false, 1, 1, 1, 1, 4, 4>(x, wp, bias, res, y, s, stream, grp);
+        return launch_ring<false, 1, 1, 1, 1, 2, 6>(x, wp, bias, res, y, s, stream, grp);
+    }
+    if (s.K % 64 == 0 && count_tiles(M, PQ, 64, s.K / 64, grp.table) <= (slab ? kRingTiles64Slab : kRingTiles64)) {
+        if (slab) return launch_ring<true, 1, 1, 2, 2, 3, 3>(x, wp, bias, res, y, s, stream, grp);
+        return launch_ring<false, 1, 1, 2, 2, 2, 5>(x, wp, bias, res, y, s, stream, grp);
+    }
+    return hipErrorNotSupported;
+}
 
 template <int BK>
 hipError_t pick_tile(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
@@ -1042,6 +1323,8 @@ hipError_t conv_mfma(const void* x, const void* wp, const float* bias, const voi
     if ((long long)s.N * s.H * s.W * s.C * 2 >= 0x7FFFFFFFll || (long long)s.K * s.R * s.S * s.C * 2 >= 0x7FFFFFFFll ||
         M >= 0x7FFFFFFFll - 256)
         return hipErrorInvalidValue;
+    const hipError_t ring = conv_ring(x, wp, bias, res, y, s, stream);
+    if (ring != hipErrorNotSupported) return ring;
     // 32-channel steps everywhere: measured equal or better than 64-channel steps on every ResNet layer shape
     if (conv_mfma_uses_slab(s)) {
         // 256-row and 128-row tiles measured within a few percent of each other on every ResNet-18 layer shape
@@ -1077,6 +1360,8 @@ hipError_t conv_mfma_grouped(const void* x, const GroupTable& groups, size_t off
     grp.table = groups;
     grp.off_w = (uint32_t)off_w;
     grp.off_b = (uint32_t)off_b;
+    const hipError_t ring = conv_ring(x, nullptr, nullptr, res, y, s, stream, grp);
+    if (ring != hipErrorNotSupported) return ring;
     // every group starts a fresh row of tiles: 128-row tiles waste fewer rows past the end of a small group, 256-row
     // tiles (twice the accumulator rows per wave and operand read) are the faster ones where that waste stays small
     if (conv_mfma_uses_slab(s)) {

@@ -61,3 +61,45 @@ def test_conv_f32_elementwise(B, oracle, n, H, Wd, C, K, R, stride, pad, use_res
         mag = oracle.conv2d(np.abs(x[i]), np.abs(w), np.abs(bias), None if r is None else np.abs(r), stride, pad, 0, 0)
         bound = 1.13 * (R * R * C + 2) * 2.0 ** -24 * mag + 8 * 2.0 ** -24 * np.abs(want) + (1e-6 * mag if act >= 2 else 0)
         assert np.all(np.abs(got[i] - want) <= bound), float((np.abs(got[i] - want) / bound).max())
+
+
+def _bf16(rng, *shape, scale=1.0):
+    return W.f32_to_bf16_bits((rng.standard_normal(shape) * scale).astype(np.float32)).reshape(shape)
+
+
+@pytest.mark.parametrize("H,Wd,C,K,R,stride,pad,act,few,some,many", [
+    (7, 7, 64, 128, 3, 1, 1, 1, 1, 200, 1200),        # slab order: 32 x 32 tiles, 64 x 64 tiles, 256-row tiles
+    (9, 11, 32, 64, 3, 1, 1, 0, 3, 300, 1200),        # one channel block (the loop over block pairs ends in its middle)
+    (14, 13, 96, 192, 3, 1, 1, 3, 1, 60, 400),        # three channel blocks, filters not a multiple of 128
+    (15, 15, 64, 128, 3, 2, 1, 1, 2, 250, 1300),      # stride 2: window positions outside, two channel blocks a stage
+    (14, 14, 128, 256, 1, 2, 0, 0, 1, 200, 1400),     # 1x1 projection, four channel blocks a stage
+    (50, 1, 192, 64, 1, 1, 0, 2, 3, 600, 2400),       # token GEMM, odd number of stages
+    (10, 10, 64, 96, 1, 1, 0, 0, 2, 0, 500),          # filters not a multiple of 64: no 64 x 64 tiles
+    (12, 12, 64, 64, 5, 1, 2, 1, 1, 200, 900),        # 5x5 window
+])
+def test_few_tiles_give_the_bits_of_many(B, oracle, H, Wd, C, K, R, stride, pad, act, few, some, many):
+    """Launches with few output tiles run on smaller tiles.  A request's result must not depend on how many requests run
+    beside it: the same images alone, among some and among many give the same bits, and those of a few are the oracle's."""
+    rng = np.random.default_rng(H * 100 + C + R)
+    x = _bf16(rng, few + 1, H, Wd, C)
+    w = _bf16(rng, K, R, R, C, scale=np.sqrt(2.0 / (R * R * C)))
+    bias = (0.1 * rng.standard_normal(K)).astype(np.float32)
+    P = (H + 2 * pad - R) // stride + 1; Q = (Wd + 2 * pad - R) // stride + 1
+    res = _bf16(rng, few + 1, P, Q, K)
+    ctx = B.Context(max_requests=1)
+    outs = {}
+    for n in (few, some, many):
+        if n:
+            idx = np.arange(n) % (few + 1)
+            outs[n], _ = ctx.coe_debug_conv(1, x[idx], w, bias, res[idx], stride, pad, act)
+    ctx.close()
+    for n, y in outs.items():
+        for r in range(1 if n > few else 0, n // (few + 1)):
+            assert np.array_equal(y[r * (few + 1):(r + 1) * (few + 1)], y[:few + 1]), (n, r)
+        assert np.array_equal(y[:few], outs[few]), n
+    xf, wf, rf = (W.bf16_bits_to_f32(a).reshape(a.shape) for a in (x, w, res))
+    want = np.stack([oracle.conv2d(xf[i], wf, bias, rf[i], stride, pad, act, 1) for i in range(few)])
+    got = W.bf16_bits_to_f32(outs[few]).reshape(want.shape)
+    # one bf16 ulp where fp32 and fp64 sums round to different sides; 1e-5 absolute where the terms cancel (the fp32 error
+    # of a sum of up to 1600 terms of size ~0.05)
+    assert np.all(np.abs(got - want) <= np.maximum(np.abs(want) * 2.0 ** -7, 1e-5))
