@@ -1005,6 +1005,14 @@ hipError_t launch_slab(const void* x, const void* wp, const float* bias, const v
 //   * row tiles run fastest: the workgroups of one XCD take all rows of a few filter tiles, so filters - most of the
 //     bytes here - come from memory once and not once per XCD.
 // ---------------------------------------------------------------------------------------------------------------
+template <int BEGIN, int END, typename F> __device__ __forceinline__ void static_for(F&& f)
+{
+    if constexpr (BEGIN < END) {
+        f(std::integral_constant<int, BEGIN>{});
+        static_for<BEGIN + 1, END>(f);
+    }
+}
+
 template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel(const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ wp_all,
@@ -1066,7 +1074,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
     // for all nine positions at once in slab order, else for the position that is being fetched.  The channel block is
     // a scalar offset, so a load needs no vector arithmetic (a wave's instruction issue is what bounds these tiles).
     constexpr int kPos = SLAB_ORDER ? 9 : 1;
-    static_assert(!SLAB_ORDER || UN == 3, "three stages per channel block");
+    constexpr int kParts = SLAB_ORDER ? 9 / UN : 1;           // stages per channel block (slab order)
+    static_assert(!SLAB_ORDER || 9 % UN == 0, "whole stages per channel block");
     uint32_t a_at[A_PER_WAVE][kPos];
     int32_t a_off[A_PER_WAVE], a_ih[A_PER_WAVE], a_iw[A_PER_WAVE];
     auto place = [&](int j, int rr, int tt) __attribute__((always_inline)) -> uint32_t {
@@ -1099,7 +1108,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
     // the stage that is fetched next: scalar offsets of its first channel block in a row and of its first filter fragment
     uint32_t f_c = 0, f_w = 0, r_pos = 0, t_pos = 0;
     const uint32_t c_end = (uint32_t)s.C * 2, tap_w = (uint32_t)cblocks * (KS * FRAG * 2);
-    // part (slab order): which three of the nine positions
+    // part (slab order): which UN of the nine positions
     auto issue = [&](auto part_c, int stage) __attribute__((always_inline)) {
         constexpr int part = decltype(part_c)::value;
         uint16_t* const st = lds + stage * STAGE;
@@ -1108,15 +1117,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
 #pragma unroll
             for (int j = 0; j < A_PER_WAVE; ++j)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void*)(st + u * STEP + (wid * A_PER_WAVE + j) * FRAG), 16,
-                                                         a_at[j][SLAB_ORDER ? part * 3 + u : 0], SLAB_ORDER ? f_c : f_c + u * (BK * 2), 0, 0);
+                                                         a_at[j][SLAB_ORDER ? part * UN + u : 0], SLAB_ORDER ? f_c : f_c + u * (BK * 2), 0, 0);
 #pragma unroll
             for (int j = 0; j < B_PER_WAVE; ++j)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void*)(st + u * STEP + (FA + wid * B_PER_WAVE + j) * FRAG), 16, b_off[j],
-                                                         SLAB_ORDER ? f_w + (part * 3 + u) * tap_w : f_w + u * (KS * FRAG * 2), 0, 0);
+                                                         SLAB_ORDER ? f_w + (part * UN + u) * tap_w : f_w + u * (KS * FRAG * 2), 0, 0);
         }
         // past the last stage the position stays put: what is fetched there is never used
         if (SLAB_ORDER) {
-            if (part == 2 && f_c + BK * 2 < c_end) { f_c += BK * 2; f_w += KS * FRAG * 2; }
+            if (part == kParts - 1 && f_c + BK * 2 < c_end) { f_c += BK * 2; f_w += KS * FRAG * 2; }
         } else if (f_c + UN * BK * 2 < c_end) {
             f_c += UN * BK * 2;
             f_w += UN * KS * FRAG * 2;
@@ -1172,14 +1181,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
 
     typedef std::integral_constant<int, 0> c0;
     typedef std::integral_constant<int, 1> c1;
-    typedef std::integral_constant<int, 2> c2;
-    // stages are fetched in order; in slab order stage k holds positions 3 (k % 3) .. + 2
-#pragma unroll
-    for (int k = 0; k < STAGES - 1; ++k) {
-        if (SLAB_ORDER && k % 3 == 1) issue(c1{}, k);
-        else if (SLAB_ORDER && k % 3 == 2) issue(c2{}, k);
-        else issue(c0{}, k);
-    }
+    // stages are fetched in order; in slab order stage k holds part k % kParts of channel block k / kParts
+    static_for<0, STAGES - 1>([&](auto k) __attribute__((always_inline)) {
+        issue(std::integral_constant<int, decltype(k)::value % kParts>{}, decltype(k)::value);
+    });
     wait_before_barrier<(STAGES - 2) * LOADS>();
     __builtin_amdgcn_s_barrier();
     read(c0{}, 0);
@@ -1192,21 +1197,23 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
         wait_before_barrier<(STAGES - 3) * LOADS>();
         __builtin_amdgcn_s_barrier();
         read(nxt_c, next);
-        issue(std::integral_constant<int, SLAB_ORDER ? (part + STAGES - 1) % 3 : 0>{}, fill);
+        issue(std::integral_constant<int, (part + STAGES - 1) % kParts>{}, fill);
 #pragma unroll
         for (int u = 0; u < UN; ++u) multiply(cur_c, u);
         next = next == STAGES - 1 ? 0 : next + 1;
         fill = fill == STAGES - 1 ? 0 : fill + 1;
     };
     if constexpr (SLAB_ORDER) {
-        for (int cb = 0; cb < cblocks; cb += 2) {
-            body(c0{}, c0{}, c1{});
-            body(c1{}, c1{}, c0{});
-            body(c2{}, c0{}, c1{});
+        for (int cb = 0; cb < cblocks; cb += 2) {             // kParts is odd: register sets swap roles from block to block
+            static_for<0, kParts>([&](auto k) __attribute__((always_inline)) {
+                constexpr int set = decltype(k)::value & 1;
+                body(k, std::integral_constant<int, set>{}, std::integral_constant<int, set ^ 1>{});
+            });
             if (cb + 1 == cblocks) break;
-            body(c0{}, c1{}, c0{});
-            body(c1{}, c0{}, c1{});
-            body(c2{}, c1{}, c0{});
+            static_for<0, kParts>([&](auto k) __attribute__((always_inline)) {
+                constexpr int set = decltype(k)::value & 1;
+                body(k, std::integral_constant<int, set ^ 1>{}, std::integral_constant<int, set>{});
+            });
         }
     } else {
         const int n_stages = RS * cblocks / UN;               // the launcher picks UN so that it divides the channel blocks
@@ -1273,12 +1280,17 @@ hipError_t conv_ring(const void* x, const void* wp, const float* bias, const voi
     if (!slab && cblocks % 2) return hipErrorNotSupported;       // a stage holds channel blocks of one window position
     const long long M = (long long)s.N * s.P * s.Q, PQ = (long long)s.P * s.Q;
     if (count_tiles(M, PQ, 32, s.K / 32, grp.table) <= kRingTiles32) {
-        if (slab) return launch_ring<true, 1, 1, 1, 1, 3, 4>(x, wp, bias, res, y, s, stream, grp);
+        if (slab) return launch_ring<true, 1, 1, 1, 1, 3, 6>(x, wp, bias, res, y, s, stream, grp);
         if (cblocks % 4 == 0) return launch_ring<false, 1, 1, 1, 1, 4, 4>(x, wp, bias, res, y, s, stream, grp);
         return launch_ring<false, 1, 1, 1, 1, 2, 6>(x, wp, bias, res, y, s, stream, grp);
     }
-    if (s.K % 64 == 0 && count_tiles(M, PQ, 64, s.K / 64, grp.table) <= (slab ? kRingTiles64Slab : kRingTiles64)) {
-        if (slab) return launch_ring<true, 1, 1, 2, 2, 3, 3>(x, wp, bias, res, y, s, stream, grp);
+    const long long tiles64 = count_tiles(M, PQ, 64, s.K / 64, grp.table);
+    if (s.K % 64 == 0 && tiles64 <= (slab ? kRingTiles64Slab : kRingTiles64)) {
+        // 3x3: one workgroup per compute unit has its LDS to itself, with more tiles than that two share it.  Nine steps in
+        // three stages (72 KB) were too shallow for filters that come from memory: 512 -> 512 over 29 images of 15 groups
+        // took 42 us, with five stages or nine single-step ones in flight 22.
+        if (slab && tiles64 <= 256) return launch_ring<true, 1, 1, 2, 2, 3, 5>(x, wp, bias, res, y, s, stream, grp);
+        if (slab) return launch_ring<true, 1, 1, 2, 2, 1, 10>(x, wp, bias, res, y, s, stream, grp);
         return launch_ring<false, 1, 1, 2, 2, 2, 5>(x, wp, bias, res, y, s, stream, grp);
     }
     return hipErrorNotSupported;
