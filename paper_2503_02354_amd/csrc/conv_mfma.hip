@@ -1250,6 +1250,309 @@ hipError_t launch_ring(const void* x, const void* wp, const float* bias, const v
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------------------------------
+// Long GEMM-like launches (token GEMMs, 1x1 and strided convolutions with long reductions): 256 x 256 tiles of eight
+// wavefronts, 128 x 64 each, by workgroups that stay for several tiles, one per compute unit.
+// What bounds it: with 0.75 KiB of operand reads per matrix-core instruction the LDS moves 96 B/clk of reads and 32 B/clk of
+// arriving loads when the matrix cores run at their full rate, which is all it can do; timing copies on 3072 -> 768 over
+// 76,633 rows (us): matrix cores only 207, with operand reads 288, with loads 310, with both 380, so what counts is that
+// the three overlap.  A wave issues in order and stalls where a queue is full: a run of reads or loads in front of the
+// matrix-core instructions leaves these waiting.  Hence the fixed order inside a half step (one read or load after each
+// matrix-core instruction), and loads of filters and of pixel rows in different halves.
+//   * A step is 32 channels, its two 16-channel halves alternate: the operands of one are read while the other is
+//     multiplied; in the middle of a step one barrier says that the next stage has landed and this one has been read.
+//   * Three stages; the fetches run on into the next tile, so a tile starts with its operands in LDS and the epilogue
+//     of the tile before, with the stores still on their way, costs no pipeline start.
+// Measured, us (128 x 128 tiles of conv_igemm_dma_kernel / here), 76,633 rows: 768 -> 2304 434 / 324 (0.84 PFLOP/s),
+// 768 -> 768 with residual 154 / 122, 3072 -> 768 with residual 447 / 337 (1.07 PFLOP/s); 25,216 rows: 768 -> 2304 112 / 87;
+// 256 images: 1x1 1024 -> 256 on 14 x 14 39 / 30; 3x3 stride 2, 512 images: 256 -> 512 on 14 x 14 78 / 58.
+// ---------------------------------------------------------------------------------------------------------------
+// Epilogue with an exact number of memory operations: MB * T stores (and loads, with a residual) per wave, rows past the end
+// dropped by the buffer's range check.
+template <int MB, int NB, int ACT, bool RES>
+__device__ __forceinline__ void store_tile_counted_act(f32x16 (&acc)[MB][NB], uint16_t* stage, const float* __restrict__ bias,
+                                                       __amdgpu_buffer_rsrc_t res, __amdgpu_buffer_rsrc_t y, int m_wave, int n_wave,
+                                                       int M, int K, int lane)
+{
+    constexpr int WN = NB * 32, ROW = WN + 8;
+    constexpr int CPR = WN / 8;
+    constexpr int T = 32 * CPR / 64;
+    const int frag_row = lane & 31, f_hi = (lane >> 5) * 4;
+    auto at = [&](int i, int t) -> uint32_t {
+        const int idx = lane + 64 * t, mo = m_wave + i * 32 + idx / CPR;
+        return mo < M ? ((uint32_t)mo * (uint32_t)K + (uint32_t)(n_wave + (idx % CPR) * 8)) * 2u : kOutOfRange;
+    };
+    float* const bl = (float*)(stage + 32 * ROW);             // the wave's bias values, next to its rows
+    static_assert(WN == 64, "one bias value per lane");
+    bl[lane] = bias[n_wave + lane];
+    u32x4 rres[2][T];
+    if (RES) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) rres[0][t] = __builtin_amdgcn_raw_buffer_load_b128(res, at(0, t), 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+        if (RES) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int idx = lane + 64 * t;
+                *(u32x4*)(stage + (idx / CPR) * ROW + (idx % CPR) * 8) = rres[i & 1][t];
+                if (i + 1 < MB) rres[(i + 1) & 1][t] = __builtin_amdgcn_raw_buffer_load_b128(res, at(i + 1, t), 0, 0);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int nl = j * 32 + 8 * g + f_hi;
+                uint2* cell = (uint2*)(stage + frag_row * ROW + nl);
+                const float4 bv = *(const float4*)(bl + nl);
+                float v0 = acc[i][j][4 * g + 0] + bv.x, v1 = acc[i][j][4 * g + 1] + bv.y;
+                float v2 = acc[i][j][4 * g + 2] + bv.z, v3 = acc[i][j][4 * g + 3] + bv.w;
+                if (RES) {
+                    const uint2 rv = *cell;
+                    v0 += bf16_to_f32(rv.x & 0xFFFFu); v1 += bf16_to_f32(rv.x >> 16);
+                    v2 += bf16_to_f32(rv.y & 0xFFFFu); v3 += bf16_to_f32(rv.y >> 16);
+                }
+                uint2 o;
+                o.x = pack_bf16(act_fn(v0, ACT), act_fn(v1, ACT));
+                o.y = pack_bf16(act_fn(v2, ACT), act_fn(v3, ACT));
+                *cell = o;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int idx = lane + 64 * t;
+            const u32x4 v = *(const u32x4*)(stage + (idx / CPR) * ROW + (idx % CPR) * 8);
+            __builtin_amdgcn_raw_buffer_store_b128(v, y, at(i, t), 0, 0);
+        }
+    }
+}
+
+template <bool ROWS, int MB, int NB, int WAVES_M, int WAVES_N>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_gemm_persistent_kernel(const uint16_t* __restrict__ x,
+                                                                   const uint16_t* __restrict__ wp_all,
+                                                                   const float* __restrict__ bias_all,
+                                                                   const uint16_t* __restrict__ res,
+                                                                   uint16_t* __restrict__ y, ConvShape s, int M_all,
+                                                                   int tiles_n, int total, GroupTable gt, uint32_t off_w, uint32_t off_b)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int BK = 32, KS = 2, STAGES = 3;
+    constexpr int NW = WAVES_M * WAVES_N;
+    constexpr int WM = 32 * MB, WN = 32 * NB, BM = WM * WAVES_M, BN = WN * WAVES_N;
+    constexpr int FA = BM / 16, FB = BN / 32 * KS;
+    static_assert(FA % NW == 0 && FB % NW == 0, "every wave issues the same number of loads");
+    constexpr int A_PER_WAVE = FA / NW, B_PER_WAVE = FB / NW, LOADS = A_PER_WAVE + B_PER_WAVE;
+    constexpr int FRAG = 512;
+    constexpr int STAGE = (FA + FB) * FRAG;
+    constexpr int kStores = MB * NB * 2;                      // of a wave's epilogue
+    extern __shared__ __attribute__((aligned(16))) uint16_t lds[];   // STAGES * STAGE | rows of the epilogue per wave
+
+    // every XCD takes a contiguous range of tiles (filter tiles fastest), its workgroups take turns
+    const int xcd = blockIdx.x % kXcds, n_x = (gridDim.x - xcd + kXcds - 1) / kXcds;
+    const int t_begin = xcd * (total / kXcds) + (xcd < total % kXcds ? xcd : total % kXcds);
+    const int t_end = t_begin + total / kXcds + (xcd < total % kXcds ? 1 : 0);
+    int tile = t_begin + blockIdx.x / kXcds;
+    if (tile >= t_end) return;
+
+    const int PQ = s.P * s.Q;
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wid / WAVES_N, wn = wid % WAVES_N;
+    const int cblocks = s.C / BK;
+    const int RS = s.R * s.S;
+    const int nsteps = RS * cblocks;
+    const int ks16_total = nsteps * KS;
+    const __amdgpu_buffer_rsrc_t x_rsrc = make_rsrc(x, (uint32_t)s.N * (uint32_t)(s.H * s.W * s.C) * 2u);
+    const __amdgpu_buffer_rsrc_t y_rsrc = make_rsrc(y, (uint32_t)s.N * (uint32_t)(PQ * s.K) * 2u);
+    const __amdgpu_buffer_rsrc_t r_rsrc = make_rsrc(res, res ? (uint32_t)s.N * (uint32_t)(PQ * s.K) * 2u : 0u);
+    auto swz = [](int r16) { return ((r16 >> 1) & 3) ^ (r16 >> 3); };
+
+    // ---- what is fetched: tile f_tile, position (r_pos, t_pos), channel offset f_c, filter offset f_w ----
+    uint32_t a_at[A_PER_WAVE], b_off[B_PER_WAVE];
+    int32_t a_off[A_PER_WAVE], a_ih[A_PER_WAVE], a_iw[A_PER_WAVE];
+    __amdgpu_buffer_rsrc_t w_rsrc;
+    uint32_t f_c = 0, f_w = 0;
+    int r_pos = 0, t_pos = 0;
+    const uint32_t c_end = (uint32_t)s.C * 2;
+    auto place = [&](int j, int rr, int tt) __attribute__((always_inline)) -> uint32_t {
+        const bool in = (unsigned)(a_ih[j] + rr) < (unsigned)s.H && (unsigned)(a_iw[j] + tt) < (unsigned)s.W;
+        return in ? (uint32_t)(a_off[j] + (rr * s.W + tt) * s.C * 2) : kOutOfRange;
+    };
+    auto fetch_tile = [&](int t) __attribute__((always_inline)) {
+        const TileOrigin o = locate_tile<BM>(t, tiles_n, PQ, M_all, wp_all, bias_all, gt, off_w, off_b);
+        w_rsrc = make_rsrc(o.wp, (uint32_t)s.K * (uint32_t)(RS * s.C) * 2u);
+        const int chunk = (lane & 3) ^ swz(lane >> 2);
+#pragma unroll
+        for (int j = 0; j < A_PER_WAVE; ++j) {
+            const int m = o.m0 + (wid * A_PER_WAVE + j) * 16 + (lane >> 2);
+            const bool ok = m < o.m_end;
+            if (ROWS) {
+                a_at[j] = ok ? (uint32_t)(m * s.C * 2 + chunk * 16) : kOutOfRange;
+            } else {
+                const int mm = ok ? m : 0;
+                const int n = mm / PQ, pq = mm - n * PQ, p = pq / s.Q, q = pq - p * s.Q;
+                a_ih[j] = ok ? p * s.stride - s.pad : -0x10000;
+                a_iw[j] = q * s.stride - s.pad;
+                a_off[j] = ((n * s.H + p * s.stride - s.pad) * s.W + a_iw[j]) * s.C * 2 + chunk * 16;
+                a_at[j] = place(j, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < B_PER_WAVE; ++j) {
+            const int fb = wid * B_PER_WAVE + j;
+            b_off[j] = (uint32_t)((((o.tile_n * BN / 32 + fb / KS) * ks16_total + fb % KS) * FRAG + lane * 8) * 2);
+        }
+        f_c = f_w = 0;
+        r_pos = t_pos = 0;
+    };
+    auto issue_a = [&](int stage, auto j_c) __attribute__((always_inline)) {
+        constexpr int j = decltype(j_c)::value;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void*)(lds + stage * STAGE + (wid * A_PER_WAVE + j) * FRAG), 16, a_at[j], f_c, 0, 0);
+    };
+    auto issue_b = [&](int stage, auto j_c) __attribute__((always_inline)) {
+        constexpr int j = decltype(j_c)::value;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void*)(lds + stage * STAGE + (FA + wid * B_PER_WAVE + j) * FRAG), 16, b_off[j], f_w, 0, 0);
+    };
+    auto advance = [&]() __attribute__((always_inline)) {     // never past the tile's last step
+        f_w += KS * FRAG * 2;
+        if (ROWS || f_c + BK * 2 < c_end) {
+            f_c += BK * 2;
+        } else {
+            const bool row_end = t_pos + 1 == s.S;
+            t_pos = row_end ? 0 : t_pos + 1;
+            r_pos = row_end ? r_pos + 1 : r_pos;
+            f_c = 0;
+#pragma unroll
+            for (int j = 0; j < A_PER_WAVE; ++j) a_at[j] = place(j, r_pos, t_pos);
+        }
+    };
+
+    f32x16 acc[MB][NB];
+    auto clear = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    };
+    const int rd_row = lane & 31;
+    const int rd0 = (rd_row >> 4) * FRAG + ((rd_row & 15) * 4 + ((lane >> 5) ^ swz(rd_row & 15))) * 8;
+    bf16x8 af[KS][MB], bfr[KS][NB];
+    // operand k of a half step: filters first, then pixel rows
+    auto read_one = [&](auto ks_c, auto k_c, int stage) __attribute__((always_inline)) {
+        constexpr int ks = decltype(ks_c)::value, k = decltype(k_c)::value;
+        if constexpr (k < NB) bfr[ks][k] = *(const bf16x8*)(lds + stage * STAGE + (FA + (wn * NB + k) * KS + ks) * FRAG + lane * 8);
+        else af[ks][k - NB] = *(const bf16x8*)(lds + stage * STAGE + (wm * MB * 2) * FRAG + (rd0 ^ (ks * 16)) + (k - NB) * 2 * FRAG);
+    };
+    typedef std::integral_constant<int, 0> c0;
+    typedef std::integral_constant<int, 1> c1;
+    // Half a step: the products of half MUL with the operands of the other half (of stage rd) and `loads` loads of a stage
+    // slipped in between, in this very order: a wave issues in order, and with its reads and loads in one run the
+    // matrix core would idle while they queue.
+    auto half = [&](auto mul_c, int rd, auto n_loads_c, auto&& load) __attribute__((always_inline)) {
+        constexpr int mul = decltype(mul_c)::value, n_loads = decltype(n_loads_c)::value, kMfma = MB * NB, kReads = MB + NB;
+        static_assert(kReads <= kMfma && n_loads <= kMfma, "");
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<0, kMfma>([&](auto t) __attribute__((always_inline)) {
+            constexpr int k = decltype(t)::value;
+            constexpr int upto = (k + 1) * n_loads / kMfma, from = k * n_loads / kMfma;
+            acc[k / NB][k % NB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[mul][k % NB], af[mul][k / NB], acc[k / NB][k % NB], 0, 0, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            if constexpr (k < kReads) {
+                read_one(std::integral_constant<int, mul ^ 1>{}, t, rd);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            if constexpr (upto > from) {
+                load(std::integral_constant<int, from>{});
+                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            }
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int cur = 0;
+    // Step u multiplies stage u and fetches stage u + 3: its pixel rows in the second half, once everybody has read stage u,
+    // its filters in the first half of step u + 1.  SWITCH: the fetches go on with the next tile.  LAST: all loads in the
+    // second half (they are older than the epilogue's stores then), FIRST: none in the first half.  EXTRA: stores that
+    // may still be outstanding.
+    auto step = [&](auto first_c, auto last_c, auto switch_c, auto extra_c) __attribute__((always_inline)) {
+        constexpr bool first = decltype(first_c)::value, last = decltype(last_c)::value, swt = decltype(switch_c)::value;
+        constexpr int extra = decltype(extra_c)::value;
+        const int nxt = cur == STAGES - 1 ? 0 : cur + 1, prv = cur == 0 ? STAGES - 1 : cur - 1;
+        half(c0{}, cur, std::integral_constant<int, first ? 0 : B_PER_WAVE>{}, [&](auto k) __attribute__((always_inline)) { issue_b(prv, k); });
+        if (swt) fetch_tile(tile + n_x < t_end ? tile + n_x : tile);      // (after the last tile: loads that nobody uses)
+        else if (!first) advance();
+        wait_before_barrier<(STAGES - 2) * LOADS + extra>();
+        __builtin_amdgcn_s_barrier();
+        half(c1{}, nxt, std::integral_constant<int, last ? LOADS : A_PER_WAVE>{}, [&](auto k) __attribute__((always_inline)) {
+            if constexpr (decltype(k)::value < A_PER_WAVE) issue_a(cur, k);
+            else issue_b(cur, std::integral_constant<int, decltype(k)::value - A_PER_WAVE>{});
+        });
+        if (last) advance();
+        cur = nxt;
+    };
+    typedef std::integral_constant<bool, true> yes;
+    typedef std::integral_constant<bool, false> no;
+    typedef std::integral_constant<int, kStores> stores;
+
+    fetch_tile(tile);
+#pragma unroll
+    for (int k = 0; k < STAGES; ++k) {
+        static_for<0, A_PER_WAVE>([&](auto j) __attribute__((always_inline)) { issue_a(k, j); });
+        static_for<0, B_PER_WAVE>([&](auto j) __attribute__((always_inline)) { issue_b(k, j); });
+        advance();
+    }
+    wait_before_barrier<(STAGES - 1) * LOADS>();
+    __builtin_amdgcn_s_barrier();
+    static_for<0, MB + NB>([&](auto k) __attribute__((always_inline)) { read_one(c0{}, k, 0); });
+    clear();
+    step(yes{}, no{}, no{}, c0{});
+    step(no{}, no{}, no{}, c0{});
+    for (;;) {                                                // at least five steps: the launcher sees to it
+        for (int u = 2; u < nsteps - 3; ++u) step(no{}, no{}, no{}, c0{});
+        step(no{}, no{}, yes{}, c0{});
+        step(no{}, no{}, no{}, c0{});
+        step(no{}, yes{}, no{}, c0{});
+        const TileOrigin o = locate_tile<BM>(tile, tiles_n, PQ, M_all, wp_all, bias_all, gt, off_w, off_b);
+        uint16_t* const stage = lds + STAGES * STAGE + wid * (32 * (WN + 8) + 128);
+        with_activation(s.act, [&](auto a) {
+            constexpr int ACT = decltype(a)::value;
+            const int m = o.m0 + wm * WM, n = o.tile_n * BN + wn * WN;
+            if (res) store_tile_counted_act<MB, NB, ACT, true>(acc, stage, o.bias, r_rsrc, y_rsrc, m, n, o.m_end, s.K, lane);
+            else store_tile_counted_act<MB, NB, ACT, false>(acc, stage, o.bias, r_rsrc, y_rsrc, m, n, o.m_end, s.K, lane);
+        });
+        tile += n_x;
+        if (tile >= t_end) break;
+        clear();
+        step(yes{}, no{}, no{}, stores{});
+        step(no{}, no{}, no{}, stores{});
+    }
+    wait_vmcnt<0>();                                          // no load may land in LDS after the workgroup has ended
+#endif
+}
+
+template <bool ROWS, int MB, int NB, int WAVES_M, int WAVES_N>
+hipError_t launch_gemm_persistent(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
+                       hipStream_t stream, const Grouping& grp = Grouping())
+{
+    constexpr int BM = 32 * MB * WAVES_M, BN = 32 * NB * WAVES_N;
+    long long M = (long long)s.N * s.P * s.Q;
+    int tiles_n = s.K / BN;
+    long long total = count_tiles(M, (long long)s.P * s.Q, BM, tiles_n, grp.table);
+    if (total > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    if (total == 0) return hipSuccess;
+    constexpr size_t kLdsBytes = (3 * (size_t)(BM + BN) * 32 + WAVES_M * WAVES_N * (32 * (32 * NB + 8) + 128)) * sizeof(uint16_t);
+    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N>,
+                                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+    if (configured != hipSuccess) return configured;
+    const unsigned grid = (unsigned)(total < 256 ? total : 256);
+    hipLaunchKernelGGL((conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N>), dim3(grid), dim3(64 * WAVES_M * WAVES_N),
+                       kLdsBytes, stream, (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M,
+                       tiles_n, (int)total, grp.table, grp.off_w, grp.off_b);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 bool conv_mfma_uses_slab(const ConvShape& s)
@@ -1270,6 +1573,24 @@ namespace {
 // A single wavefront per 32 x 32 tile is ahead while the chip holds all tiles at once at two per compute unit; 64 x 64
 // tiles, which share operands between four wavefronts, while there are about two of them (three: 3x3) per compute unit.
 constexpr long long kRingTiles32 = 512, kRingTiles64 = 512, kRingTiles64Slab = 768;
+
+// 256 x 256 tiles where a workgroup's turns fill: 256 * ceil(tiles / 256) at most a third more than there are tiles (98
+// tiles: 88 us against 66 on 128 x 128 tiles; 297: 136 against 133; 392: 65 against 73; 900: 337 against 447), and where
+// the reduction is long enough for the tile's epilogue (14 x 14, 256 -> 1024, eight steps: 66 against 52).
+bool conv_persistent_pays(const ConvShape& s, const GroupTable& gt)
+{
+    if (s.K % 256 || s.R * s.S * s.C < 16 * 32) return false;
+    if ((long long)s.N * s.P * s.Q * s.K * 2 >= 0x7FFFFFFFll) return false;      // 31-bit offsets into the output as well
+    const long long tiles = count_tiles((long long)s.N * s.P * s.Q, (long long)s.P * s.Q, 256, s.K / 256, gt);
+    return tiles * 4 >= (tiles + 255) / 256 * 256 * 3;
+}
+hipError_t conv_persistent(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
+                           hipStream_t stream, const Grouping& grp = Grouping())
+{
+    if (s.R == 1 && s.S == 1 && s.stride == 1 && s.pad == 0)
+        return launch_gemm_persistent<true, 4, 2, 2, 4>(x, wp, bias, res, y, s, stream, grp);
+    return launch_gemm_persistent<false, 4, 2, 2, 4>(x, wp, bias, res, y, s, stream, grp);
+}
 
 // hipErrorNotSupported: not a launch for these tiles
 hipError_t conv_ring(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
@@ -1343,6 +1664,7 @@ hipError_t conv_mfma(const void* x, const void* wp, const float* bias, const voi
         if (s.K % 128 == 0) return launch_slab<256, 128, 2, 2>(x, wp, bias, res, y, s, stream);
         return launch_slab<256, 64, 4, 1>(x, wp, bias, res, y, s, stream);
     }
+    if (conv_persistent_pays(s, GroupTable{})) return conv_persistent(x, wp, bias, res, y, s, stream);
     // 128-row tiles: three workgroups per compute unit; measured ahead of 256-row tiles on the ResNet layer shapes
     if (s.K % 128 == 0) return launch_dma<128, 128, 2, 2>(x, wp, bias, res, y, s, stream);
     if (s.K % 64 == 0) return launch_dma<128, 64, 2, 2>(x, wp, bias, res, y, s, stream);
@@ -1385,6 +1707,7 @@ hipError_t conv_mfma_grouped(const void* x, const GroupTable& groups, size_t off
         return tall ? launch_slab<256, 64, 4, 1>(x, nullptr, nullptr, res, y, s, stream, grp)
                     : launch_slab<128, 64, 4, 1>(x, nullptr, nullptr, res, y, s, stream, grp);
     }
+    if (conv_persistent_pays(s, groups)) return conv_persistent(x, nullptr, nullptr, res, y, s, stream, grp);
     if (s.K % 128 == 0) return launch_dma<128, 128, 2, 2>(x, nullptr, nullptr, res, y, s, stream, grp);
     return launch_dma<128, 64, 2, 2>(x, nullptr, nullptr, res, y, s, stream, grp);
 }

@@ -76,6 +76,10 @@ def _bf16(rng, *shape, scale=1.0):
     (50, 1, 192, 64, 1, 1, 0, 2, 3, 600, 2400),       # token GEMM, odd number of stages
     (10, 10, 64, 96, 1, 1, 0, 0, 2, 0, 500),          # filters not a multiple of 64: no 64 x 64 tiles
     (12, 12, 64, 64, 5, 1, 2, 1, 1, 200, 900),        # 5x5 window
+    (14, 14, 512, 256, 1, 1, 0, 1, 1, 129, 255),      # 256 x 256 tiles: 16 steps, 196 tiles, the last one ragged
+    (50, 1, 768, 512, 1, 1, 0, 2, 2, 400, 2995),      # GELU, workgroups with four and with five tiles, two filter tiles
+    (15, 13, 64, 256, 3, 2, 1, 3, 1, 300, 931),       # stride 2 at odd sizes, two channel blocks a window position
+    (14, 14, 544, 256, 1, 2, 0, 0, 1, 400, 1045),     # strided rows, 17 steps
 ])
 def test_few_tiles_give_the_bits_of_many(B, oracle, H, Wd, C, K, R, stride, pad, act, few, some, many):
     """Launches with few output tiles run on smaller tiles.  A request's result must not depend on how many requests run
