@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint32_t* __restri
     }
 }
 
-// ---- attention, one workgroup per (head, request), head width 64, up to 224 tokens --------------------------------
+// ---- attention, head width 64, up to 224 tokens ---------------------------------------------------------------------
 // Scores are computed transposed, S^T = K Q^T, with the key fragment as the first matrix-core operand: a lane then
 // owns ONE query (column l%32) and, per 32-key block, the keys 8*(v/4) + 4*(l/32) + v%4.  Softmax statistics of a
 // query therefore live in two lanes (l and l^32), and the exponentials, rounded to bf16, are already laid out as the
@@ -118,138 +118,190 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint32_t* __restri
 // accumulator quad and stores 8 bytes at a time.
 // Numerics: scores in fp32, e = exp(s - max), probabilities p = e / sum(e) rounded to bf16 (they are a tensor of their
 // own in storage precision), output = sum_j p_j v_j accumulated in fp32 and rounded to bf16.
+// What bounds it: q, k, v and the output through HBM, 0.47 GB for 389 requests of 197 tokens and 12 heads (98 us at the
+// 4.8 TB/s a large copy reaches); the softmax is about 80 us of vector instructions.  A head of a request is a load of
+// 75 KB and a few microseconds of work, so what counts is that loads are always in flight: workgroups of eight wavefronts
+// stay, one per compute unit; K and V of the next unit of work come by DMA into a second buffer, its queries into
+// registers, while every wavefront does one block of 32 queries of this one.  V stays as it is in memory: the transposing
+// LDS read (four rows of sixteen 16-bit elements per 16 lanes, a lane gets one column) delivers V^T.  With fewer than five
+// 32-token blocks a unit of work is several heads.
+// Measured there: 380 us (two workgroups of four wavefronts per compute unit, each loading and transposing its K and V
+// through registers, then two rounds of query blocks) -> 140 us; 12 heads of one request 17 -> 9 us.
 constexpr int kDh = 64;
 constexpr int kMaxKeyBlocks = 7;
-constexpr int kKStride = kDh + 8;                 // K tile row stride (elements): conflict-free 16-byte reads
-constexpr int kVStride = kMaxKeyBlocks * 32 + 8;  // V^T row stride
-__global__ __launch_bounds__(256) void attention_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ out, int T,
-                                                        int D, float scale)
+constexpr int kAttnWaves = 8;
+typedef __attribute__((address_space(3))) void lds_void;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+[[maybe_unused]] constexpr uint32_t kOutOfRange = 0x80000000u;   // buffer offset beyond any tensor: loads return zeros, stores are dropped
+
+template <int TB>
+__global__ __launch_bounds__(64 * kAttnWaves, 2) void attention_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ out,
+                                                                       int N, int T, int D, int heads, float scale)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t Kl[kMaxKeyBlocks * 32 * kKStride];
-    __shared__ __attribute__((aligned(16))) uint16_t Vt[kDh * kVStride];
-    const int head = blockIdx.x, n = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int TB = (T + 31) / 32;
-    const size_t row_stride = (size_t)3 * D;
-    const uint16_t* base = qkv + (size_t)n * T * row_stride + (size_t)head * kDh;
-
-    // K as it is, V transposed; two tokens per thread so that the transposed stores are 4 bytes (token pairs)
-    for (int c = tid; c < TB * 16 * 8; c += 256) {
-        const int t = (c >> 3) * 2, part = c & 7;
-        uint4 kv[2], vv[2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            kv[j] = make_uint4(0, 0, 0, 0);
-            vv[j] = make_uint4(0, 0, 0, 0);
-            if (t + j < T) {
-                kv[j] = *(const uint4*)(base + (size_t)(t + j) * row_stride + D + part * 8);
-                vv[j] = *(const uint4*)(base + (size_t)(t + j) * row_stride + 2 * D + part * 8);
-            }
-            *(uint4*)(Kl + (t + j) * kKStride + part * 8) = kv[j];
-        }
-        const uint32_t w0[4] = {vv[0].x, vv[0].y, vv[0].z, vv[0].w}, w1[4] = {vv[1].x, vv[1].y, vv[1].z, vv[1].w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            *(uint32_t*)(Vt + (part * 8 + 2 * i) * kVStride + t) = (w0[i] & 0xFFFFu) | (w1[i] << 16);
-            *(uint32_t*)(Vt + (part * 8 + 2 * i + 1) * kVStride + t) = (w0[i] >> 16) | (w1[i] & 0xFFFF0000u);
-        }
-    }
-    __syncthreads();
-
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int kHeads = kAttnWaves / TB;           // heads per unit of work
+    constexpr int kRows8 = 4 * TB;                    // 1 KiB blocks of eight 128-byte rows in K, the same in V
+    constexpr int kBuf = kHeads * 2 * kRows8 * 1024;  // bytes; a wavefront loads kHeads * TB blocks of it
+    extern __shared__ __attribute__((aligned(1024))) char lds[];      // two buffers
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, half = lane >> 5;
+    const int items = N * heads, units = (items + kHeads - 1) / kHeads;
+    const uint32_t row_bytes = (uint32_t)D * 6u;      // a token of qkv
+    const __amdgpu_buffer_rsrc_t in_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(qkv), 0, (int)((uint32_t)N * (uint32_t)T * row_bytes), 0x00020000);
+    const __amdgpu_buffer_rsrc_t out_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(out, 0, (int)((uint32_t)N * (uint32_t)T * (uint32_t)D * 2u), 0x00020000);
+
+    // Row r of K keeps its 16-byte chunk c in slot c ^ ((r >> 1) & 7), row r of V in slot c ^ (r & 7): operand reads (32 rows
+    // of one chunk; four rows of sixteen channels) then spread over the LDS banks.  Lane i of a load fills slot i % 8 of row
+    // i / 8 and fetches the chunk that belongs there.
+    const int ld_row = lane >> 3, ld_slot = lane & 7;
+    auto load_unit = [&](int unit, int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < kHeads * TB; ++j) {
+            const int blk = wid + kAttnWaves * j, in_item = blk % (2 * kRows8), b = in_item % kRows8;
+            const int item = unit * kHeads + blk / (2 * kRows8), is_v = in_item / kRows8;
+            const int n = item / heads, head = item - n * heads;
+            const int chunk = ld_slot ^ (is_v ? ld_row : ((b & 1) * 4 + (ld_row >> 1)));
+            const bool ok = item < items && 8 * b + ld_row < T;
+            const uint32_t at = ok ? (uint32_t)ld_row * row_bytes + (uint32_t)chunk * 16u : kOutOfRange;
+            const uint32_t base = ((uint32_t)n * (uint32_t)T + 8u * b) * row_bytes + (uint32_t)((1 + is_v) * D + head * kDh) * 2u;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(in_rsrc, (lds_void*)(lds + buf * kBuf + blk * 1024), 16, at,
+                                                     __builtin_amdgcn_readfirstlane(base), 0, 0);
+        }
+    };
+    const int sub = wid / TB, qb = wid % TB;          // this wavefront's head of the unit and block of queries
+    const bool works = wid < kHeads * TB;
+    const int query = qb * 32 + l32;
+    u32x4 q_next[kDh / 16];
+    auto load_queries = [&](int unit) __attribute__((always_inline)) {
+        const int item = unit * kHeads + sub, n = item / heads, head = item - n * heads;
+        const uint32_t at = item < items && query < T ? (uint32_t)l32 * row_bytes + (uint32_t)half * 16u : kOutOfRange;
+        const uint32_t base = __builtin_amdgcn_readfirstlane(((uint32_t)n * (uint32_t)T + 32u * qb) * row_bytes + (uint32_t)(head * kDh) * 2u);
+#pragma unroll
+        for (int ks = 0; ks < kDh / 16; ++ks) q_next[ks] = __builtin_amdgcn_raw_buffer_load_b128(in_rsrc, at, base + ks * 32, 0);
+    };
+
+    // operand addresses inside a buffer (bytes): K, for the low bit of the 16-channel step; V, for the two 32-channel halves
+    const char* const item_lds = lds + (works ? sub : 0) * (2 * kRows8 * 1024);
+    uint32_t k_at[kDh / 16], v_at[2];
+#pragma unroll
+    for (int ks = 0; ks < kDh / 16; ++ks) k_at[ks] = (uint32_t)(l32 * 128 + (((ks * 2 + half) ^ ((l32 >> 1) & 7)) * 16));
+#pragma unroll
+    for (int db = 0; db < 2; ++db) {
+        const int r = 4 * half + ((lane >> 2) & 3), chunk = db * 4 + ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);
+        v_at[db] = (uint32_t)(kRows8 * 1024 + r * 128 + ((chunk ^ r) * 16) + (lane & 1) * 8);
+    }
     const float scale2 = scale * 1.44269504088896340736f;
-    for (int qb = wid; qb < TB; qb += 4) {
-        const int query = qb * 32 + l32;
+
+    int buf = 0;
+    bool stored = false;
+    load_unit(blockIdx.x, 0);
+    if (works) load_queries(blockIdx.x);
+    for (int unit = blockIdx.x; unit < units; unit += gridDim.x) {
+        // this unit's loads have landed; the eight stores of the unit before, if any, are younger and may be on their way
+        if (works && stored) __builtin_amdgcn_s_waitcnt(8 | (7 << 4) | (0 << 8));
+        else __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0 << 8));
+        __builtin_amdgcn_s_barrier();
         bf16x8 qf[kDh / 16];
 #pragma unroll
-        for (int ks = 0; ks < kDh / 16; ++ks) {
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (query < T) v = *(const uint4*)(base + (size_t)query * row_stride + ks * 16 + half * 8);
-            qf[ks] = __builtin_bit_cast(bf16x8, v);
+        for (int ks = 0; ks < kDh / 16; ++ks) qf[ks] = __builtin_bit_cast(bf16x8, q_next[ks]);
+        if (unit + (int)gridDim.x < units) {
+            load_unit(unit + gridDim.x, buf ^ 1);
+            if (works) load_queries(unit + gridDim.x);
         }
-        f32x16 sc[kMaxKeyBlocks];
-        float m = -INFINITY;
+        if (works) {
+            const char* const kv = item_lds + buf * kBuf;
+            f32x16 sc[TB];
+            float m = -INFINITY;
 #pragma unroll
-        for (int kb = 0; kb < kMaxKeyBlocks; ++kb) {
-            if (kb < TB) {
+            for (int kb = 0; kb < TB; ++kb) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) sc[kb][v] = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < kDh / 16; ++ks) {
-                    bf16x8 kf = *(const bf16x8*)(Kl + (kb * 32 + l32) * kKStride + ks * 16 + half * 8);
+                    const bf16x8 kf = *(const bf16x8*)(kv + k_at[ks] + kb * 4096);
                     sc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[ks], sc[kb], 0, 0, 0);
                 }
+                if (kb == TB - 1) {                   // the last block may hold rows past the last token
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        if (kb * 32 + 8 * (v >> 2) + 4 * half + (v & 3) >= T) sc[kb][v] = -INFINITY;
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) m = fmaxf(m, sc[kb][v]);
+            }
+            m = fmaxf(m, __shfl_xor(m, 32, 64));
+            const float m2 = m * scale2;              // scores in units of ln 2
+            float lsum = 0.f;
+#pragma unroll
+            for (int kb = 0; kb < TB; ++kb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    int key = kb * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                    float s = key < T ? sc[kb][v] * scale2 : -INFINITY;       // scores in units of ln 2
-                    sc[kb][v] = s;
-                    m = fmaxf(m, s);
-                }
-            }
-        }
-        m = fmaxf(m, __shfl_xor(m, 32, 64));
-        float lsum = 0.f;
-        uint32_t pw[kMaxKeyBlocks][8];          // bf16 pairs: [kb][2*g + j/2] = keys 8g + 4*half + (j, j+1)
-#pragma unroll
-        for (int kb = 0; kb < kMaxKeyBlocks; ++kb) {
-            if (kb < TB) {
-#pragma unroll
-                for (int v = 0; v < 16; v += 2) {
                     // 2^x on the transcendental unit (one instruction; exp(s - max) = 2^((s - max) / ln 2))
-                    float e0 = __builtin_amdgcn_exp2f(sc[kb][v] - m), e1 = __builtin_amdgcn_exp2f(sc[kb][v + 1] - m);
-                    lsum += e0 + e1;
-                    sc[kb][v] = e0;
-                    sc[kb][v + 1] = e1;
+                    sc[kb][v] = __builtin_amdgcn_exp2f(fmaf(sc[kb][v], scale2, -m2));
+                    lsum += sc[kb][v];
                 }
-            }
-        }
-        lsum += __shfl_xor(lsum, 32, 64);
-        const float inv = 1.f / lsum;
+            lsum += __shfl_xor(lsum, 32, 64);
+            const float inv = 1.f / lsum;
+            f32x16 oacc[2];
 #pragma unroll
-        for (int kb = 0; kb < kMaxKeyBlocks; ++kb) {
-            if (kb < TB) {
+            for (int db = 0; db < 2; ++db)
 #pragma unroll
-                for (int v = 0; v < 16; v += 2) pw[kb][v >> 1] = pack_bf16(sc[kb][v] * inv, sc[kb][v + 1] * inv);
-            }
-        }
-
-        f32x16 oacc[kDh / 32];
+                for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
 #pragma unroll
-        for (int db = 0; db < kDh / 32; ++db)
+            for (int kb = 0; kb < TB; ++kb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
+                for (int t2 = 0; t2 < 2; ++t2) {      // 16 keys per matrix-core step: accumulator quads 2 t2 and 2 t2 + 1
+                    const int v0 = 8 * t2;
+                    u32x4 pv;
 #pragma unroll
-        for (int kb = 0; kb < kMaxKeyBlocks; ++kb) {
-            if (kb < TB) {
+                    for (int e = 0; e < 4; ++e) pv[e] = pack_bf16(sc[kb][v0 + 2 * e] * inv, sc[kb][v0 + 2 * e + 1] * inv);
+                    const bf16x8 pf = __builtin_bit_cast(bf16x8, pv);
 #pragma unroll
-                for (int t2 = 0; t2 < 2; ++t2) {          // 16 keys per matrix-core step: quads g = 2*t2 and 2*t2 + 1
-                    const int g = 2 * t2;
-                    uint4 pv = make_uint4(pw[kb][2 * g], pw[kb][2 * g + 1], pw[kb][2 * g + 2], pw[kb][2 * g + 3]);
-                    bf16x8 pf = __builtin_bit_cast(bf16x8, pv);
-#pragma unroll
-                    for (int db = 0; db < kDh / 32; ++db) {
-                        const uint16_t* vp = Vt + (db * 32 + l32) * kVStride + kb * 32 + 4 * half;
-                        uint2 a = *(const uint2*)(vp + 8 * g), b = *(const uint2*)(vp + 8 * (g + 1));
-                        bf16x8 vf = __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, b.x, b.y));
+                    for (int db = 0; db < 2; ++db) {
+                        const char* vp = kv + v_at[db] + kb * 4096 + t2 * 2048;
+                        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp));
+                        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp + 1024));
+                        const bf16x8 vf = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
                         oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, oacc[db], 0, 0, 0);
                     }
                 }
-            }
-        }
-        if (query < T) {
-            uint16_t* op = out + ((size_t)n * T + query) * D + (size_t)head * kDh;
+            const int item = unit * kHeads + sub, n = item / heads, head = item - n * heads;
+            const uint32_t at = item < items && query < T ? (uint32_t)l32 * (uint32_t)(D * 2) + (uint32_t)half * 8u : kOutOfRange;
+            const uint32_t base =
+                __builtin_amdgcn_readfirstlane(((uint32_t)n * (uint32_t)T + 32u * qb) * (uint32_t)(D * 2) + (uint32_t)(head * kDh) * 2u);
 #pragma unroll
-            for (int db = 0; db < kDh / 32; ++db)
+            for (int db = 0; db < 2; ++db)
 #pragma unroll
                 for (int gq = 0; gq < 4; ++gq) {
-                    uint2 o;
-                    o.x = pack_bf16(oacc[db][4 * gq], oacc[db][4 * gq + 1]);
-                    o.y = pack_bf16(oacc[db][4 * gq + 2], oacc[db][4 * gq + 3]);
-                    *(uint2*)(op + db * 32 + 8 * gq + 4 * half) = o;
+                    u32x2 o;
+                    o[0] = pack_bf16(oacc[db][4 * gq], oacc[db][4 * gq + 1]);
+                    o[1] = pack_bf16(oacc[db][4 * gq + 2], oacc[db][4 * gq + 3]);
+                    __builtin_amdgcn_raw_buffer_store_b64(o, out_rsrc, at, base + db * 64 + gq * 16, 0);
                 }
         }
+        stored = true;
+        buf ^= 1;
     }
+#endif
+}
+
+template <int TB>
+hipError_t launch_attention(const void* qkv, void* out, int32_t N, int32_t T, int32_t D, int32_t heads, hipStream_t stream)
+{
+    constexpr int kHeads = kAttnWaves / TB;
+    constexpr size_t kLds = 2 * (size_t)kHeads * 8 * TB * 1024;
+    static const hipError_t configured =
+        hipFuncSetAttribute((const void*)attention_kernel<TB>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
+    if (configured != hipSuccess) return configured;
+    const long long units = ((long long)N * heads + kHeads - 1) / kHeads;
+    hipLaunchKernelGGL(attention_kernel<TB>, dim3((unsigned)(units < 256 ? units : 256)), dim3(64 * kAttnWaves), kLds, stream,
+                       (const uint16_t*)qkv, (uint16_t*)out, N, T, D, heads, 1.0f / sqrtf((float)kDh));
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -299,10 +351,16 @@ hipError_t attention(const void* qkv, void* out, int32_t N, int32_t T, int32_t D
 {
     if (!attention_supported(T, D, heads)) return hipErrorInvalidValue;
     if (N == 0) return hipSuccess;
-    if (N > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(attention_kernel, dim3(heads, N), dim3(256), 0, stream, (const uint16_t*)qkv, (uint16_t*)out, T, D,
-                       1.0f / sqrtf((float)kDh));
-    return hipGetLastError();
+    if ((long long)N * T * D * 6 >= 0x7FFFFFFFll) return hipErrorInvalidValue;      // 31-bit byte offsets inside the kernel
+    switch ((T + 31) / 32) {
+    case 1: return launch_attention<1>(qkv, out, N, T, D, heads, stream);
+    case 2: return launch_attention<2>(qkv, out, N, T, D, heads, stream);
+    case 3: return launch_attention<3>(qkv, out, N, T, D, heads, stream);
+    case 4: return launch_attention<4>(qkv, out, N, T, D, heads, stream);
+    case 5: return launch_attention<5>(qkv, out, N, T, D, heads, stream);
+    case 6: return launch_attention<6>(qkv, out, N, T, D, heads, stream);
+    default: return launch_attention<7>(qkv, out, N, T, D, heads, stream);
+    }
 }
 
 }  // namespace k

@@ -107,3 +107,33 @@ def test_few_tiles_give_the_bits_of_many(B, oracle, H, Wd, C, K, R, stride, pad,
     # one bf16 ulp where fp32 and fp64 sums round to different sides; 1e-5 absolute where the terms cancel (the fp32 error
     # of a sum of up to 1600 terms of size ~0.05)
     assert np.all(np.abs(got - want) <= np.maximum(np.abs(want) * 2.0 ** -7, 1e-5))
+
+
+@pytest.mark.parametrize("T,heads,n", [(17, 12, 5), (31, 3, 1), (33, 2, 3), (65, 12, 2), (97, 1, 5), (129, 3, 2), (160, 2, 1), (192, 1, 3),
+                                       (193, 3, 2), (197, 12, 29)])
+def test_attention_block_counts(B, oracle, T, heads, n):
+    """Every number of 32-token blocks: heads packed into one unit of work (with an incomplete last one), workgroups that
+    do one unit and several, ragged last blocks."""
+    D = 64 * heads
+    rng = np.random.default_rng(T * 10 + heads)
+    x = _bf16(rng, n, T, 3 * D)
+    p = W._Prog(T, 1, 3 * D)
+    p.raw([W.OP_ATTENTION, 0, 1, -1, D, 0, 0, 0, 0, 0, heads, 0])
+    p.shape[1] = (T, 1, D)
+    p.head(1, 4)
+    arch = W.Arch("attention", W.DT_BF16, T, 1, 3 * D, 4, np.array(p.layers, dtype=np.int32), p.gains)
+    import torch
+    dev = torch.from_numpy(x.view(np.int16)).cuda()
+    ctx = B.Context(max_requests=n, max_batch=n)
+    aid = ctx.coe_register_arch(arch)
+    ctx.coe_register_expert(0, aid, W.make_expert_blob(arch, 3, 0), 1.0)
+    got = W.bf16_bits_to_f32(ctx.coe_debug_layer_output(0, n, dev.data_ptr(), 0, (n, T, D), np.uint16)).reshape(n, T, D)
+    ctx.close()
+    xf = W.bf16_bits_to_f32(x).reshape(n, T, 3 * D)
+    for i in sorted({0, n - 1, n // 2}):
+        want = oracle.attention(xf[i], heads, 1)
+        # the output is one rounding (2^-8 of a value at most) of sum_j p_j v_j; an fp32 and an fp64 softmax may round a few
+        # p_j to neighbouring bf16 values, 2^-8 p_j each: at most 2^-8 sum_j p_j |v_j| in all, and |v| < 5 here
+        assert np.all(np.abs(got[i] - want) <= 2.0 ** -8 * (np.abs(want) + 5.0))
+        assert np.sqrt(np.mean((got[i] - want) ** 2)) <= 2.0 ** -8 * np.sqrt(np.mean(want ** 2))
+        assert np.mean(got[i] == want) > 0.9
