@@ -1272,8 +1272,8 @@ hipError_t launch_ring(const void* x, const void* wp, const float* bias, const v
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Long GEMM-like launches (token GEMMs, 1x1 and strided convolutions with long reductions): 256 x 256 tiles of eight
-// wavefronts, 128 x 64 each, by workgroups that stay for several tiles, one per compute unit.
+// Long GEMM-like launches (token GEMMs, 1x1 and strided convolutions with long reductions): tiles of 64 MB x 256 of eight
+// wavefronts, 32 MB x 64 each (MB = 4: 256 x 256), by workgroups that stay for several tiles, one per compute unit.
 // What bounds it: with 0.75 KiB of operand reads per matrix-core instruction the LDS moves 96 B/clk of reads and 32 B/clk of
 // arriving loads when the matrix cores run at their full rate, which is all it can do; timing copies on 3072 -> 768 over
 // 76,633 rows (us): matrix cores only 207, with operand reads 288, with loads 310, with both 380, so what counts is that
@@ -1362,9 +1362,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_gemm_persisten
     constexpr int BK = 32, KS = 2, STAGES = 3;
     constexpr int NW = WAVES_M * WAVES_N;
     constexpr int WM = 32 * MB, WN = 32 * NB, BM = WM * WAVES_M, BN = WN * WAVES_N;
-    constexpr int FA = BM / 16, FB = BN / 32 * KS;
-    static_assert(FA % NW == 0 && FB % NW == 0, "every wave issues the same number of loads");
-    constexpr int A_PER_WAVE = FA / NW, B_PER_WAVE = FB / NW, LOADS = A_PER_WAVE + B_PER_WAVE;
+    // every wave issues the same number of loads; blocks of rows past the tile's last read nothing and fill spare LDS
+    constexpr int A_PER_WAVE = (BM / 16 + NW - 1) / NW, FA = A_PER_WAVE * NW, FB = BN / 32 * KS;
+    static_assert(FB % NW == 0, "");
+    constexpr int B_PER_WAVE = FB / NW, LOADS = A_PER_WAVE + B_PER_WAVE;
     constexpr int FRAG = 512;
     constexpr int STAGE = (FA + FB) * FRAG;
     constexpr int kStores = MB * NB * 2;                      // of a wave's epilogue
@@ -1407,7 +1408,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_gemm_persisten
 #pragma unroll
         for (int j = 0; j < A_PER_WAVE; ++j) {
             const int m = o.m0 + (wid * A_PER_WAVE + j) * 16 + (lane >> 2);
-            const bool ok = m < o.m_end;
+            const bool ok = m < o.m_end && (FA * 16 == BM || m < o.m0 + BM);
             if (ROWS) {
                 a_at[j] = ok ? (uint32_t)(m * s.C * 2 + chunk * 16) : kOutOfRange;
             } else {
@@ -1474,17 +1475,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_gemm_persisten
     // matrix core would idle while they queue.
     auto half = [&](auto mul_c, int rd, auto n_loads_c, auto&& load) __attribute__((always_inline)) {
         constexpr int mul = decltype(mul_c)::value, n_loads = decltype(n_loads_c)::value, kMfma = MB * NB, kReads = MB + NB;
-        static_assert(kReads <= kMfma && n_loads <= kMfma, "");
+        static_assert(n_loads <= kMfma, "");
         __builtin_amdgcn_sched_barrier(0);
         static_for<0, kMfma>([&](auto t) __attribute__((always_inline)) {
             constexpr int k = decltype(t)::value;
             constexpr int upto = (k + 1) * n_loads / kMfma, from = k * n_loads / kMfma;
             acc[k / NB][k % NB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[mul][k % NB], af[mul][k / NB], acc[k / NB][k % NB], 0, 0, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if constexpr (k < kReads) {
-                read_one(std::integral_constant<int, mul ^ 1>{}, t, rd);
+            constexpr int r0 = k * kReads / kMfma, r1 = (k + 1) * kReads / kMfma;
+            if constexpr (r1 > r0) {
+                read_one(std::integral_constant<int, mul ^ 1>{}, std::integral_constant<int, r0>{}, rd);
                 __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             }
+            static_assert(r1 - r0 <= 1, "at most one read after each product");
             if constexpr (upto > from) {
                 load(std::integral_constant<int, from>{});
                 __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
@@ -1563,7 +1566,8 @@ hipError_t launch_gemm_persistent(const void* x, const void* wp, const float* bi
     long long total = count_tiles(M, (long long)s.P * s.Q, BM, tiles_n, grp.table);
     if (total > 0x7FFFFFFFll) return hipErrorInvalidValue;
     if (total == 0) return hipSuccess;
-    constexpr size_t kLdsBytes = (3 * (size_t)(BM + BN) * 32 + WAVES_M * WAVES_N * (32 * (32 * NB + 8) + 128)) * sizeof(uint16_t);
+    constexpr int NW = WAVES_M * WAVES_N, kRowsLds = (BM / 16 + NW - 1) / NW * NW * 16;
+    constexpr size_t kLdsBytes = (3 * (size_t)(kRowsLds + BN) * 32 + WAVES_M * WAVES_N * (32 * (32 * NB + 8) + 128)) * sizeof(uint16_t);
     static const hipError_t configured = hipFuncSetAttribute((const void*)conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
     if (configured != hipSuccess) return configured;
@@ -1595,22 +1599,48 @@ namespace {
 // tiles, which share operands between four wavefronts, while there are about two of them (three: 3x3) per compute unit.
 constexpr long long kRingTiles32 = 512, kRingTiles64 = 512, kRingTiles64Slab = 768;
 
-// 256 x 256 tiles where a workgroup's turns fill: 256 * ceil(tiles / 256) at most a third more than there are tiles (98
-// tiles: 88 us against 66 on 128 x 128 tiles; 297: 136 against 133; 392: 65 against 73; 900: 337 against 447), and where
-// the reduction is long enough for the tile's epilogue (14 x 14, 256 -> 1024, eight steps: 66 against 52).
-bool conv_persistent_pays(const ConvShape& s, const GroupTable& gt)
+// Which tiles a long GEMM-like launch takes: height / 64 of conv_gemm_persistent_kernel's tiles, or 0 for the 128 x 128 tiles of
+// conv_igemm_dma_kernel.  The unit is the time of one turn of 256 x 256 tiles on all 256 compute units; a turn of 192- and
+// 128-row tiles measured 0.72-0.84 and 0.53-0.58 of it (their operand reads per product are more), 128 x 128 tiles, three
+// workgroups per compute unit that share it as they come, 0.5 for up to 256 and one more per 681.  What decides is how
+// well the turns fill; us at 4 / 3 / 2 / 0: 25,216 rows 3072 -> 768 137 / 115 / 122 / 134; 5910 rows 768 -> 2304 25 / 32 / 29 / 33,
+// 3072 -> 768 59 / 49 / 39 / 44; 12,544 rows 2048 -> 512 42 / 36 / 31 / 33; 11,760 rows 3x3 128 -> 256 26 / 22 / 17 / 17.
+// Short reductions stay on the 128 x 128 tiles: eight steps, 256 -> 1024 on 14 x 14, 64 / 59 / 52 / 52 (bound by memory).
+int persistent_height(const ConvShape& s, const GroupTable& gt)
 {
-    if (s.K % 256 || s.R * s.S * s.C < 16 * 32) return false;
-    if ((long long)s.N * s.P * s.Q * s.K * 2 >= 0x7FFFFFFFll) return false;      // 31-bit offsets into the output as well
-    const long long tiles = count_tiles((long long)s.N * s.P * s.Q, (long long)s.P * s.Q, 256, s.K / 256, gt);
-    return tiles * 4 >= (tiles + 255) / 256 * 256 * 3;
+    if (s.K % 256 || s.R * s.S * s.C < 16 * 32) return 0;
+    const long long PQ = (long long)s.P * s.Q, M = s.N * PQ;
+    if (M * s.K * 2 >= 0x7FFFFFFFll) return 0;                // 31-bit offsets into the output as well
+    const long long small = count_tiles(M, PQ, 128, s.K / 128, gt);
+    double best = 0.5 + (small > 256 ? (double)(small - 256) / 681.0 : 0.0);
+    int height = 0;
+    const double turn[5] = {0.0, 0.0, 0.54, 0.80, 1.0};
+    for (int h = 2; h <= 4; ++h) {
+        const double cost = (double)((count_tiles(M, PQ, 64 * h, s.K / 256, gt) + 255) / 256) * turn[h];
+        if (cost <= best) { best = cost; height = h; }
+    }
+    return height;
 }
+template <int MB>
 hipError_t conv_persistent(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
-                           hipStream_t stream, const Grouping& grp = Grouping())
+                           hipStream_t stream, const Grouping& grp)
 {
     if (s.R == 1 && s.S == 1 && s.stride == 1 && s.pad == 0)
-        return launch_gemm_persistent<true, 4, 2, 2, 4>(x, wp, bias, res, y, s, stream, grp);
-    return launch_gemm_persistent<false, 4, 2, 2, 4>(x, wp, bias, res, y, s, stream, grp);
+        return launch_gemm_persistent<true, MB, 2, 2, 4>(x, wp, bias, res, y, s, stream, grp);
+    return launch_gemm_persistent<false, MB, 2, 2, 4>(x, wp, bias, res, y, s, stream, grp);
+}
+// the launches that neither the slab kernel nor few-tile kernels take
+hipError_t conv_gemm(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s, hipStream_t stream,
+                     const Grouping& grp = Grouping())
+{
+    switch (persistent_height(s, grp.table)) {
+    case 4: return conv_persistent<4>(x, wp, bias, res, y, s, stream, grp);
+    case 3: return conv_persistent<3>(x, wp, bias, res, y, s, stream, grp);
+    case 2: return conv_persistent<2>(x, wp, bias, res, y, s, stream, grp);
+    }
+    // 128-row tiles: three workgroups per compute unit; measured ahead of 256-row tiles on the ResNet layer shapes
+    if (s.K % 128 == 0) return launch_dma<128, 128, 2, 2>(x, wp, bias, res, y, s, stream, grp);
+    return launch_dma<128, 64, 2, 2>(x, wp, bias, res, y, s, stream, grp);
 }
 
 // hipErrorNotSupported: not a launch for these tiles
@@ -1685,10 +1715,7 @@ hipError_t conv_mfma(const void* x, const void* wp, const float* bias, const voi
         if (s.K % 128 == 0) return launch_slab<256, 128, 2, 2>(x, wp, bias, res, y, s, stream);
         return launch_slab<256, 64, 4, 1>(x, wp, bias, res, y, s, stream);
     }
-    if (conv_persistent_pays(s, GroupTable{})) return conv_persistent(x, wp, bias, res, y, s, stream);
-    // 128-row tiles: three workgroups per compute unit; measured ahead of 256-row tiles on the ResNet layer shapes
-    if (s.K % 128 == 0) return launch_dma<128, 128, 2, 2>(x, wp, bias, res, y, s, stream);
-    if (s.K % 64 == 0) return launch_dma<128, 64, 2, 2>(x, wp, bias, res, y, s, stream);
+    if (s.K % 64 == 0) return conv_gemm(x, wp, bias, res, y, s, stream);
     // filter counts that are not a multiple of 64: the register-staged kernel
     return pick_tile<32>(x, wp, bias, res, y, s, stream);
 }
@@ -1728,9 +1755,7 @@ hipError_t conv_mfma_grouped(const void* x, const GroupTable& groups, size_t off
         return tall ? launch_slab<256, 64, 4, 1>(x, nullptr, nullptr, res, y, s, stream, grp)
                     : launch_slab<128, 64, 4, 1>(x, nullptr, nullptr, res, y, s, stream, grp);
     }
-    if (conv_persistent_pays(s, groups)) return conv_persistent(x, nullptr, nullptr, res, y, s, stream, grp);
-    if (s.K % 128 == 0) return launch_dma<128, 128, 2, 2>(x, nullptr, nullptr, res, y, s, stream, grp);
-    return launch_dma<128, 64, 2, 2>(x, nullptr, nullptr, res, y, s, stream, grp);
+    return conv_gemm(x, nullptr, nullptr, res, y, s, stream, grp);
 }
 
 }  // namespace k

@@ -80,6 +80,9 @@ def _bf16(rng, *shape, scale=1.0):
     (50, 1, 768, 512, 1, 1, 0, 2, 2, 400, 2995),      # GELU, workgroups with four and with five tiles, two filter tiles
     (15, 13, 64, 256, 3, 2, 1, 3, 1, 300, 931),       # stride 2 at odd sizes, two channel blocks a window position
     (14, 14, 544, 256, 1, 2, 0, 0, 1, 400, 1045),     # strided rows, 17 steps
+    (14, 14, 512, 256, 1, 1, 0, 1, 1, 120, 180),      # 192 x 256 tiles (184 of them) and 128 x 256 ones
+    (50, 1, 512, 768, 1, 1, 0, 2, 2, 190, 514),       # 192 x 256 tiles in two turns, three filter tiles; 128 x 256 ones
+    (9, 9, 64, 256, 3, 1, 0, 0, 1, 220, 480),         # 3x3 without padding, the same two heights
 ])
 def test_few_tiles_give_the_bits_of_many(B, oracle, H, Wd, C, K, R, stride, pad, act, few, some, many):
     """Launches with few output tiles run on smaller tiles.  A request's result must not depend on how many requests run
