@@ -888,13 +888,20 @@ int run_group_set(coe_ctx* c, Lane& ln, const std::vector<SetMember>& set, const
                 Span sp(c, coe::k::conv_mfma_uses_slab(s) ? COE_K_CONV_SLAB : COE_K_CONV_MFMA, flops, ln.s);
                 HIPCHK(c, coe::k::conv_mfma_grouped(buf(l.src), gt, L.off[0], L.off[1], res, buf(l.dst), s, ln.s));
             } else {
-                // few input channels (the stem): the filters live in LDS for a whole launch, so one launch per group,
-                // each writing its rows of the shared activation buffer
+                // few input channels (the stem): one launch where the kernel takes a group table, else, with filters that live in
+                // LDS for a whole launch, one per group, each writing its rows of the shared activation buffer
                 const bool fused = L.fuse_pool;
                 const LayerPlan& outL = fused ? *(&L + 1) : L;
                 const size_t in_row = (size_t)L.H * L.W * L.C * a.elem();
                 const size_t out_row = (size_t)outL.P * outL.Q * outL.K * a.elem();
                 Span sp(c, COE_K_CONV_STEM, flops, ln.s);
+                if (coe::k::conv_smallc_groupable(s, fused)) {
+                    int32_t first_in[coe::k::kMaxGroups];
+                    for (size_t g = 0; g < set.size(); ++g) first_in[g] = l.src == 0 ? set[g].first : gt.first_row[g];
+                    HIPCHK(c, coe::k::conv_smallc_grouped(l.src == 0 ? staged : buf(l.src), first_in, gt, L.off[0], L.off[1],
+                                                          buf(outL.d.dst), s, fused, ln.s, l.src == 0 ? rows : nullptr));
+                    break;
+                }
                 for (size_t g = 0; g < set.size(); ++g) {
                     coe::k::ConvShape sg = s;
                     sg.N = set[g].count;

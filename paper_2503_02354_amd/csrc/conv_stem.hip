@@ -314,6 +314,293 @@ __global__ __launch_bounds__(kThreads, 4) void conv_smallc_bf16_kernel(const uin
     }
 }
 
+// ---------------------------------------------------------------------------------------------------------------
+// The 7x7/2 stem on three channels with ReLU and the fused 3x3/2 pool, as every ResNet-shaped expert begins: no tiles in
+// LDS and no barriers.  A wavefront walks down a strip of 32 conv columns (15 pooled ones at most) and keeps in registers
+//   * the operands of four pairs of input rows, (2i + 1, 2i + 2) for i = p - 2 .. p + 1, which are what conv row p needs
+//     (its window rows are 2p - 3 .. 2p + 3; the last row of the last pair is left out).  A window row is the 24 elements of
+//     columns 2q - 4 .. 2q + 3, three chunks of 8 that a lane loads straight from the image, 16 bytes each; column 2q - 4
+//     and whatever lies left or right of the image is masked to zero.  The next pair is loaded into the registers of the
+//     pair that has just been used for the last time, a whole conv row before it is needed;
+//   * the running maximum of a pooled row's conv rows, after the bias.
+// The filters are packed into LDS in fragment order once per workgroup and read again for every conv row.  (In registers,
+// as far as they fit, they gain nothing: 1.39 ms per 4096 images with one to four of the eleven steps resident; with five and
+// six the compiler spills: 1.68 and 2.12 ms.)
+// Lanes 0-15 of a half hold the odd conv columns 2b - 1, lanes 16-31 the even ones 2b (b = pooled column), so that the
+// horizontal maximum is one row swap and one shift within 16 lanes, after which all lanes hold results; swapping halves
+// then gives a lane 8 consecutive channels to store.  ReLU and rounding are monotonic: they come after the vertical maximum
+// (fp32), the horizontal one compares non-negative bf16 as integers.
+// Bound by the matrix cores and the vector instructions between them: 44 of 32 cycles per strip and pooled row beside about
+// 220 of 4 cycles, which the second wavefront of the SIMD overlaps in part.  Groups with filters of their own share a launch.
+// Measured, 224 x 224: 4096 images 2.60 ms with 16 x 16 tiles in LDS (conv_smallc_bf16_kernel), 1.39 here (0.7 for the matrix
+// instructions alone at their full rate, 0.55 for the bytes); 29 images in 15 groups 15 launches of 17 us, now one of 21.
+// ---------------------------------------------------------------------------------------------------------------
+constexpr int kStripPooled = 15;      // pooled columns per strip: 2 * 15 + 1 conv columns of 32
+constexpr int kStripWaves = 4;
+constexpr int kStripSlots = 2048;     // wavefronts the chip holds at two per SIMD
+constexpr int kStemSteps = 11;
+constexpr int kStemResident = 2;      // steps whose filter fragments stay in registers: a conv row begins without waiting for LDS
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+struct StripGeom {
+    int PP, PQ;                       // pooled size
+    int strips, strip_cols;           // strips per image, pooled columns of a strip
+    int segs, seg_rows;               // segments of a strip, pooled rows of a segment
+};
+// Groups with filters of their own: a workgroup belongs to one of them
+struct StripGroups {
+    int n;
+    int first_wg[kMaxGroups + 1];     // first workgroup of each group
+    int out[kMaxGroups + 1];          // first image of each group in the output
+    int in[kMaxGroups];               // first image (or row table entry) of each group in the input
+    const void* weights[kMaxGroups];
+    int64_t off_w, off_b;             // bytes from there to the filters and the bias
+};
+
+__global__ __launch_bounds__(64 * kStripWaves, 2) void conv_stem_strip_kernel(const uint16_t* __restrict__ x,
+                                                                              uint16_t* __restrict__ y, ConvShape s, StripGeom g,
+                                                                              StripGroups gr, const int32_t* __restrict__ rows)
+{
+    constexpr int kFrags = 2 * kStemSteps;
+    __shared__ __attribute__((aligned(16))) uint16_t wpack[kFrags * 512];     // [step][filter block][lane][8]
+    __shared__ float4 lbias[32];                               // the bias; minus infinity, for a conv row that does not exist
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5;
+    int grp = 0;
+    while (grp + 1 < gr.n && (int)blockIdx.x >= gr.first_wg[grp + 1]) ++grp;
+    const int wg = blockIdx.x - gr.first_wg[grp], wgs = gr.first_wg[grp + 1] - gr.first_wg[grp];
+    const int tasks = (gr.out[grp + 1] - gr.out[grp]) * g.segs * g.strips;
+    const uint16_t* const w = (const uint16_t*)((const char*)gr.weights[grp] + gr.off_w);
+    const float* const bias = (const float*)((const char*)gr.weights[grp] + gr.off_b);
+
+    // chunk c of window row r is elements 8c - 3 .. 8c + 4 of its 21 (zero outside); lanes 0-31 of step j take chunk 2j,
+    // lanes 32-63 chunk 2j + 1, counted over all rows
+    constexpr int kChunks = kFrags * 64, kPerThread = (kChunks + 64 * kStripWaves - 1) / (64 * kStripWaves);
+    uint32_t packed[kPerThread][4];                            // (all loads in flight at once)
+#pragma unroll
+    for (int t = 0; t < kPerThread; ++t) {
+        const int idx = tid + t * 64 * kStripWaves, l = idx & 63, f = idx >> 6;
+        const int k = (f & 1) * 32 + (l & 31), chunk = (f >> 1) * 2 + (l >> 5);
+        const int r = chunk / 3, e0 = chunk % 3 * 8 - 3;
+        const bool row_ok = idx < kChunks && r < 7;
+        uint32_t v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const bool ok = row_ok && (unsigned)(e0 + i) < 21u;
+            const uint32_t loaded = w[ok ? (k * 7 + r) * 21 + e0 + i : 0];
+            v[i] = ok ? loaded : 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) packed[t][i] = v[2 * i] | v[2 * i + 1] << 16;
+    }
+#pragma unroll
+    for (int t = 0; t < kPerThread; ++t)
+        if (tid + t * 64 * kStripWaves < kChunks) *(u32x4*)(wpack + (tid + t * 64 * kStripWaves) * 8) = u32x4{packed[t][0], packed[t][1], packed[t][2], packed[t][3]};
+    if (tid < 16) lbias[tid] = *(const float4*)(bias + 4 * tid);
+    else if (tid < 32) lbias[tid] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+    __syncthreads();
+    bf16x8 fil[kStemResident][2];
+#pragma unroll
+    for (int j = 0; j < kStemResident; ++j)
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) fil[j][nb] = *(const bf16x8*)(wpack + ((j * 2 + nb) * 64 + lane) * 8);
+
+    const int H = s.H, WC = s.W * 3, row_bytes = WC * 2;
+    const int col = lane & 15, even = (lane >> 4) & 1;
+    // step ks of a pair: chunks (0 | 1) of its first row, (2 of the first | 0 of the second), (1 | 2) of the second
+    for (int task = wg * kStripWaves + wid; task < tasks; task += wgs * kStripWaves) {
+        const int strip = task % g.strips, seg = task / g.strips % g.segs, image = task / g.strips / g.segs;
+        const int n = gr.out[grp] + image;
+        const int b0 = strip * g.strip_cols, cols = g.PQ - b0 < g.strip_cols ? g.PQ - b0 : g.strip_cols;
+        const int a0 = seg * g.seg_rows, a_end = a0 + g.seg_rows < g.PP ? a0 + g.seg_rows : g.PP;
+        const int q = 2 * (b0 + col) - 1 + even;
+        const uint32_t col_mask = (unsigned)q < (unsigned)s.Q ? ~0u : 0u;       // a column that does not exist is 0: never more than the maximum after ReLU
+        const int e_q = 6 * q - 12;
+        const int e_of[3] = {e_q + 8 * half, half ? e_q : e_q + 16, e_q + 8 + 8 * half};
+        u32x4 mask[3];
+#pragma unroll
+        for (int ks = 0; ks < 3; ++ks)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int e = e_of[ks] + 2 * d, lo = e_q + 3 > 0 ? e_q + 3 : 0;
+                mask[ks][d] = (e >= lo && e < WC ? 0x0000FFFFu : 0u) | (e + 1 >= lo && e + 1 < WC ? 0xFFFF0000u : 0u);
+            }
+        const int n_src = rows ? __builtin_amdgcn_readfirstlane(rows[gr.in[grp] + image]) : gr.in[grp] + image;
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x + (size_t)n_src * H * WC), 0, H * row_bytes, 0x00020000);
+        const int off[3] = {e_of[0] * 2, e_of[1] * 2 + half * row_bytes, e_of[2] * 2 + row_bytes};
+
+        u32x4 in[4][3];                                        // [pair][step]
+        // Offsets before the image (as unsigned) and behind it read as zero, and what a lane reads beyond a row's ends is
+        // masked; only a chunk that begins left of the image's first row and reaches into it needs the other form.
+        auto load_pair = [&](u32x4 (&to)[3], int i) __attribute__((always_inline)) {
+#pragma unroll
+            for (int ks = 0; ks < 3; ++ks) to[ks] = __builtin_amdgcn_raw_buffer_load_b128(rs, off[ks] + (2 * i + 1) * row_bytes, 0, 0);
+        };
+        auto load_first_pair = [&](u32x4 (&to)[3]) __attribute__((always_inline)) {     // rows -1 and 0
+#pragma unroll
+            for (int ks = 0; ks < 3; ++ks) {
+                const bool row = ks == 2 || (ks == 1 && half);
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const int e = e_of[ks] + 2 * d;
+                    to[ks][d] = __builtin_amdgcn_raw_buffer_load_b32(rs, row && (unsigned)e < (unsigned)WC ? e * 2 : (int)0x80000000, 0, 0);
+                }
+            }
+        };
+        auto mask_pair = [&](u32x4 (&v)[3]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int ks = 0; ks < 3; ++ks) v[ks] &= mask[ks];
+        };
+        f32x16 acc[2];
+        // conv row p, its pairs in slots base .. base + 3; the next pair goes to slot base
+        auto conv_row = [&](auto base_c, int p) __attribute__((always_inline)) {
+            constexpr int base = decltype(base_c)::value;
+            acc[0] = f32x16{};
+            acc[1] = f32x16{};
+            int fil_at = lane * 8;
+            asm volatile("" : "+v"(fil_at));                   // (not kept across conv rows)
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                u32x4(&pair)[3] = in[(base + j) & 3];
+                if (j == 3) mask_pair(pair);
+#pragma unroll
+                for (int ks = 0; ks < 3; ++ks) {
+                    if (j == 3 && ks == 2) continue;           // the eighth row
+                    u32x4 v = pair[ks];
+                    if (j == 3 && ks == 1) v = half ? u32x4{0u, 0u, 0u, 0u} : v;
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) {
+                        const int step = 3 * j + ks;
+                        const bf16x8 f = step < kStemResident ? fil[step < kStemResident ? step : 0][nb]
+                                                              : *(const bf16x8*)(wpack + (step * 2 + nb) * 512 + fil_at);
+                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, __builtin_bit_cast(bf16x8, v), acc[nb], 0, 0, 0);
+                    }
+                }
+                if (j == 0) load_pair(pair, p + 2);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        float top[2][16];                                      // running maximum of the pooled row
+        // f(nb, element, conv output with its bias)
+        auto each = [&](int p, auto&& f) __attribute__((always_inline)) {
+            int at = half + ((unsigned)p < (unsigned)s.P ? 0 : 16);
+            asm volatile("" : "+v"(at));                       // (read again each time: 32 registers less)
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq) {
+                    const float4 bv = lbias[at + nb * 8 + gq * 2];
+                    f(nb, gq * 4 + 0, acc[nb][gq * 4 + 0] + bv.x);
+                    f(nb, gq * 4 + 1, acc[nb][gq * 4 + 1] + bv.y);
+                    f(nb, gq * 4 + 2, acc[nb][gq * 4 + 2] + bv.z);
+                    f(nb, gq * 4 + 3, acc[nb][gq * 4 + 3] + bv.w);
+                }
+        };
+        uint16_t* y_at = y + ((size_t)(n * (size_t)g.PP + a0) * g.PQ + b0 + col) * 64 + 8 * (2 * half + even);
+        // pooled row a from conv rows 2a - 1 (in `top`), 2a and 2a + 1
+        auto pooled_row = [&](auto base_c, int a) __attribute__((always_inline)) {
+            constexpr int base = decltype(base_c)::value;
+            conv_row(std::integral_constant<int, base>{}, 2 * a);
+            each(2 * a, [&](int nb, int v, float t) __attribute__((always_inline)) { top[nb][v] = fmaxf(top[nb][v], t); });
+            conv_row(std::integral_constant<int, (base + 1) & 3>{}, 2 * a + 1);
+            u16x2 m[2][4][2];                                  // [filter block][quad][channel pair]
+            float out[2][16];
+            each(2 * a + 1, [&](int nb, int v, float t) __attribute__((always_inline)) {
+                out[nb][v] = fmaxf(fmaxf(top[nb][v], t), 0.f);
+                top[nb][v] = t;
+            });
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                for (int v = 0; v < 16; v += 2) {
+                    const uint32_t o = pack_bf16(out[nb][v], out[nb][v + 1]) & col_mask;
+                    m[nb][v / 4][v % 4 / 2] = __builtin_bit_cast(u16x2, o);
+                }
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+                uint32_t r[2][2];                              // [quad pair][channel pair]
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int d = 0; d < 2; ++d) {
+                        // odd columns of both quads, then even columns of both
+                        const auto sw = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, m[nb][2 * h][d]),
+                                                                         __builtin_bit_cast(uint32_t, m[nb][2 * h + 1][d]), false, false);
+                        const uint32_t right = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sw[0], 0x101, 0xF, 0xF, true);   // row_shl:1
+                        const u16x2 c = __builtin_elementwise_max(__builtin_bit_cast(u16x2, (uint32_t)sw[0]), __builtin_bit_cast(u16x2, (uint32_t)sw[1]));
+                        r[h][d] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(c, __builtin_bit_cast(u16x2, right)));
+                    }
+                const auto s0 = __builtin_amdgcn_permlane32_swap(r[0][0], r[1][0], false, false);
+                const auto s1 = __builtin_amdgcn_permlane32_swap(r[0][1], r[1][1], false, false);
+                if (col < cols) *(u32x4*)(y_at + nb * 32) = u32x4{(uint32_t)s0[0], (uint32_t)s1[0], (uint32_t)s0[1], (uint32_t)s1[1]};
+            }
+            y_at += (size_t)g.PQ * 64;
+        };
+
+        const int p0 = 2 * a0 - 1;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) load_pair(in[j], p0 - 2 + j);
+        if (p0 == -1) load_first_pair(in[2]);
+        if (p0 == 1) load_first_pair(in[0]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) mask_pair(in[j]);
+        conv_row(std::integral_constant<int, 0>{}, p0);
+        each(p0, [&](int nb, int v, float t) __attribute__((always_inline)) { top[nb][v] = t; });
+        for (int a = a0;;) {
+            pooled_row(std::integral_constant<int, 1>{}, a);
+            if (++a == a_end) break;
+            pooled_row(std::integral_constant<int, 3>{}, a);
+            if (++a == a_end) break;
+        }
+    }
+}
+
+// the shapes of conv_stem_strip_kernel (for any number of images: a request's bits do not depend on what runs beside it)
+bool strip_supported(const ConvShape& s)
+{
+    return s.C == 3 && s.K == 64 && s.R == 7 && s.S == 7 && s.stride == 2 && s.pad == 3 && s.act == 1 && s.W % 2 == 0 && s.P >= 2 &&
+           s.Q >= 2 && (long long)s.H * s.W * s.C * 2 < 0x3FFFFFFFll;
+}
+
+// Launches the strips of all groups of gr (n, out, in, weights and offsets set).  Segments: what matters is the number of conv rows
+// of the wavefront that has the most; a segment has two per pooled row, one above, and the time of about three until its first
+// loads are there.  All workgroups are resident at once.
+hipError_t launch_strip(const void* x, void* y, const ConvShape& s, StripGroups& gr, hipStream_t stream, const int32_t* rows)
+{
+    StripGeom g{};
+    g.PP = (s.P + 2 - 3) / 2 + 1;
+    g.PQ = (s.Q + 2 - 3) / 2 + 1;
+    g.strips = (g.PQ + kStripPooled - 1) / kStripPooled;
+    g.strip_cols = (g.PQ + g.strips - 1) / g.strips;
+    long long best = 0, best_each = 0;
+    for (int r = 1; r <= g.PP; ++r) {
+        const int segs = (g.PP + r - 1) / r;
+        const long long per_image = (long long)g.strips * segs;
+        if ((long long)s.N * per_image > 0x3FFFFFFFll) continue;
+        // strips a wavefront takes, so that the workgroups of all groups fit the chip
+        long long each = ((long long)s.N * per_image + kStripSlots - 1) / kStripSlots, wgs;
+        do {
+            wgs = 0;
+            for (int i = 0; i < gr.n; ++i) wgs += ((gr.out[i + 1] - gr.out[i]) * per_image + kStripWaves * each - 1) / (kStripWaves * each);
+        } while (wgs > kStripSlots / kStripWaves && ++each);
+        const long long cost = each * (2 * r + 4);
+        if (best == 0 || cost < best) { best = cost; best_each = each; g.segs = segs; g.seg_rows = r; }
+    }
+    if (best == 0) return hipErrorInvalidValue;
+    gr.first_wg[0] = 0;
+    for (int i = 0; i < gr.n; ++i)
+        gr.first_wg[i + 1] = gr.first_wg[i] + (int)(((long long)(gr.out[i + 1] - gr.out[i]) * g.strips * g.segs + kStripWaves * best_each - 1) /
+                                                    (kStripWaves * best_each));
+    if (gr.first_wg[gr.n] == 0) return hipSuccess;
+    hipLaunchKernelGGL(conv_stem_strip_kernel, dim3(gr.first_wg[gr.n]), dim3(64 * kStripWaves), 0, stream, (const uint16_t*)x, (uint16_t*)y,
+                       s, g, gr, rows);
+    return hipGetLastError();
+}
+
 bool geometry(const ConvShape& s, bool pool, StemGeom& g, size_t& smem)
 {
     if (s.K != 32 && s.K != 64) return false;
@@ -389,13 +676,45 @@ hipError_t conv_smallc(const void* x, const void* w, const float* bias, void* y,
     if (!geometry(s, fused_pool, g, smem)) return hipErrorInvalidValue;
     if (g.total_tiles == 0) return hipSuccess;
     if (s.K == 64) {
-        if (fused_pool && g.cpr == 3 && s.R == 7)         // the ResNet stem: reduction loop unrolled with constant offsets
+        if (fused_pool && strip_supported(s)) {
+            StripGroups gr{};
+            gr.n = 1;
+            gr.out[1] = s.N;
+            gr.weights[0] = w;
+            gr.off_b = (const char*)bias - (const char*)w;
+            return launch_strip(x, y, s, gr, stream, rows);
+        }
+        if (fused_pool && g.cpr == 3 && s.R == 7)         // reduction loop unrolled with constant offsets
             return launch<2, true, 3, 7>(x, w, bias, y, s, g, smem, stream, rows);
         return fused_pool ? launch<2, true, 0, 0>(x, w, bias, y, s, g, smem, stream, rows)
                           : launch<2, false, 0, 0>(x, w, bias, y, s, g, smem, stream, rows);
     }
     return fused_pool ? launch<1, true, 0, 0>(x, w, bias, y, s, g, smem, stream, rows)
                       : launch<1, false, 0, 0>(x, w, bias, y, s, g, smem, stream, rows);
+}
+
+bool conv_smallc_groupable(const ConvShape& s, bool fused_pool)
+{
+    return fused_pool && strip_supported(s);
+}
+
+hipError_t conv_smallc_grouped(const void* x, const int32_t* first_in, const GroupTable& groups, size_t off_w, size_t off_b, void* y,
+                               const ConvShape& s, bool fused_pool, hipStream_t stream, const int32_t* rows)
+{
+    if (!conv_smallc_groupable(s, fused_pool) || groups.n <= 0 || groups.n > kMaxGroups || groups.first_row[0] != 0 ||
+        groups.first_row[groups.n] != s.N || off_w > 0x7FFFFFFFull || off_b > 0x7FFFFFFFull)
+        return hipErrorInvalidValue;
+    StripGroups gr{};
+    gr.n = groups.n;
+    for (int i = 0; i < groups.n; ++i) {
+        if (groups.first_row[i + 1] < groups.first_row[i] || !groups.weights[i]) return hipErrorInvalidValue;
+        gr.out[i + 1] = groups.first_row[i + 1];
+        gr.in[i] = first_in[i];
+        gr.weights[i] = groups.weights[i];
+    }
+    gr.off_w = (int64_t)off_w;
+    gr.off_b = (int64_t)off_b;
+    return launch_strip(x, y, s, gr, stream, rows);
 }
 
 }  // namespace k

@@ -99,6 +99,11 @@ hipError_t conv_mfma_grouped(const void* x, const GroupTable& groups, size_t off
 bool conv_smallc_supported(const ConvShape& s, bool has_res, bool fused_pool);
 hipError_t conv_smallc(const void* x, const void* w, const float* bias, void* y, const ConvShape& s, bool fused_pool,
                        hipStream_t stream, const int32_t* rows = nullptr);
+// Grouped form, for the shapes conv_smallc_groupable names (7x7 stride 2 on three channels with ReLU and the fused pool): group g's
+// images start at image (or row table entry) first_in[g], its filters sit at weights[g] + off_w, its bias at weights[g] + off_b.
+bool conv_smallc_groupable(const ConvShape& s, bool fused_pool);
+hipError_t conv_smallc_grouped(const void* x, const int32_t* first_in, const GroupTable& groups, size_t off_w, size_t off_b, void* y,
+                               const ConvShape& s, bool fused_pool, hipStream_t stream, const int32_t* rows = nullptr);
 
 hipError_t maxpool(int dtype, const void* x, void* y, int32_t N, int32_t H, int32_t W, int32_t C, int32_t R, int32_t S,
                    int32_t stride, int32_t pad, int32_t P, int32_t Q, hipStream_t stream);

@@ -140,3 +140,56 @@ def test_attention_block_counts(B, oracle, T, heads, n):
         assert np.all(np.abs(got[i] - want) <= 2.0 ** -8 * (np.abs(want) + 5.0))
         assert np.sqrt(np.mean((got[i] - want) ** 2)) <= 2.0 ** -8 * np.sqrt(np.mean(want ** 2))
         assert np.mean(got[i] == want) > 0.9
+
+
+@pytest.mark.parametrize("H,Wd,n", [
+    (224, 224, 3),        # the image of most experts: four strips of 14 pooled columns
+    (64, 64, 1300),       # two strips of 8; wavefronts that take several strips
+    (38, 58, 2),          # one full strip of 15
+    (33, 62, 2),          # 31 conv columns and 17 rows, both odd: a column and a row that do not exist
+    (35, 60, 20),         # one strip of 15, its last column's right neighbour does not exist; 18 rows
+    (224, 120, 1),        # two full strips
+    (21, 122, 3),         # three strips, the last one narrower
+    (5, 6, 4),            # three conv rows, segments of one pooled row
+    (1, 4, 1), (9, 2, 2), # fewer rows and columns than the window: only the general kernels take some of these
+])
+def test_stem_with_pool(B, oracle, H, Wd, n):
+    """7x7 stride 2 on three channels, ReLU, 3x3 stride 2 max pool: pooled values read back through an identity convolution
+    (bit-exact), images at both ends of the batch against the oracle and equal images equal everywhere."""
+    import torch
+    rng = np.random.default_rng(H * 1000 + Wd)
+    few = min(n, 3)
+    x = _bf16(rng, few, H, Wd, 3)
+    p = W._Prog(H, Wd, 3)
+    p.conv(0, 1, 64, 7, 2, 3, W.ACT_RELU)
+    p.maxpool(1, 2, 3, 2, 1)
+    p.conv(2, 3, 64, 1, 1, 0, 0)
+    p.head(3, 4)
+    arch = W.Arch("stem", W.DT_BF16, H, Wd, 3, 4, np.array(p.layers, dtype=np.int32), p.gains)
+    w = _bf16(rng, 64, 7, 7, 3, scale=np.sqrt(2.0 / 147))
+    bias = (0.3 * rng.standard_normal(64)).astype(np.float32)
+    blob = W.make_expert_blob(arch, 5, 0).copy()
+    for sp in W.blob_layout(arch)[0]:
+        value = {(0, "w"): w, (0, "b"): bias, (2, "w"): W.f32_to_bf16_bits(np.eye(64, dtype=np.float32)),
+                 (2, "b"): np.zeros(64, np.float32)}.get((sp.layer, sp.name))
+        if value is not None:
+            blob[sp.offset:sp.offset + sp.nbytes] = np.ascontiguousarray(value).view(np.uint8).reshape(-1)
+    P, Q = p.shape[1][:2]
+    PP, PQ = p.shape[2][:2]
+    idx = np.arange(n) % few
+    dev = torch.from_numpy(x[idx].view(np.int16)).cuda()
+    ctx = B.Context(max_requests=n, max_batch=n)
+    aid = ctx.coe_register_arch(arch)
+    ctx.coe_register_expert(0, aid, blob, 1.0)
+    got = W.bf16_bits_to_f32(ctx.coe_debug_layer_output(0, n, dev.data_ptr(), 2, (n, PP, PQ, 64), np.uint16)).reshape(n, PP, PQ, 64)
+    ctx.close()
+    assert np.array_equal(got, got[idx])
+    xf, wf = W.bf16_bits_to_f32(x).reshape(x.shape), W.bf16_bits_to_f32(w).reshape(w.shape)
+    for i in range(few):
+        conv = oracle.conv2d(xf[i], wf, bias, None, 2, 3, 1, 1)
+        wide = np.full((2 * PP + 1, 2 * PQ + 1, 64), -np.inf, np.float32)
+        wide[1:P + 1, 1:Q + 1] = conv
+        want = np.max([wide[r:r + 2 * PP - 1:2, c:c + 2 * PQ - 1:2] for r in range(3) for c in range(3)], axis=0)
+        # one bf16 ulp where fp32 and fp64 sums round to different sides, 1e-5 where the terms cancel; rounding and the
+        # maximum are monotonic, so the pool adds nothing
+        assert np.all(np.abs(got[i] - want) <= np.maximum(np.abs(want) * 2.0 ** -7, 1e-5)), i
