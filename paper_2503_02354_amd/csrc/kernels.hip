@@ -357,6 +357,32 @@ template <typename T> __host__ __device__ inline bool head_vector_path(int C)
     return sizeof(T) == 2 && C >= 64 && C % 8 == 0 && kHeadThreads % (C / 8) == 0;
 }
 
+// The same for fp32: C a multiple of 4 with C/4 dividing the block.  One 4-byte load at a time kept a workgroup waiting for
+// memory: 256 requests of 64 x 64 images with 64 channels, two stages in four launches of 279 us; that pass 2.40 -> 1.43 ms.
+template <typename T> __host__ __device__ inline bool head_vector4_path(int C)
+{
+    return sizeof(T) == 4 && C >= 16 && C % 4 == 0 && kHeadThreads % (C / 4) == 0;
+}
+// position groups of the pooling phase, whose partial sums meet in LDS
+template <typename T> __host__ __device__ inline int head_groups(int C)
+{
+    if (head_vector_path<T>(C)) return kHeadThreads / (C / 8);
+    if (head_vector4_path<T>(C)) return kHeadThreads / (C / 4);
+    return C < kHeadThreads ? kHeadThreads / C : 1;
+}
+// LDS, in floats: feat[C], then the partial sums; the logits after them, on the fp32 path over those of the later position
+// groups (nobody reads them any more)
+template <typename T> __host__ __device__ inline size_t head_logit_at(int C)
+{
+    const int before = head_vector4_path<T>(C) ? (C < kHeadThreads ? kHeadThreads / C : 1) : head_groups<T>(C);
+    return (size_t)C + (size_t)before * C;
+}
+template <typename T> size_t head_lds_bytes(int C, int ncls)
+{
+    const size_t sums = (size_t)C + (size_t)head_groups<T>(C) * C, logits = head_logit_at<T>(C) + (size_t)ncls;
+    return sizeof(float) * (sums > logits ? sums : logits);
+}
+
 template <typename T>
 __global__ __launch_bounds__(kHeadThreads) void head_gap_fc_kernel(const T* __restrict__ x, const T* __restrict__ w,
                                                                    const float* __restrict__ b, int HW, int C, int ncls,
@@ -378,11 +404,10 @@ __global__ __launch_bounds__(kHeadThreads) void head_gap_fc_kernel(const T* __re
         if (r.slot) r.slot = r.slot + (gr.slot_off[g] - gt.first_row[g]);
     }
     const T* xp = x + (size_t)row * HW * C;
-    int groups = C < kHeadThreads ? kHeadThreads / C : 1;      // position groups when there are few channels
-    if (head_vector_path<T>(C)) groups = kHeadThreads / (C / 8);
+    const int groups = head_groups<T>(C);
     float* feat = smem;
     float* part = smem + C;
-    float* logit = part + (size_t)groups * C;
+    float* logit = smem + head_logit_at<T>(C);
     // phase 1: per-channel sums, lanes run along channels (contiguous in NHWC)
     if (head_vector_path<T>(C)) {
         // bf16, C a multiple of 8 with C/8 dividing the block: 16-byte loads, 8 channels per thread, the positions
@@ -401,6 +426,32 @@ __global__ __launch_bounds__(kHeadThreads) void head_gap_fc_kernel(const T* __re
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) part[pg * C + chunk * 8 + e] = a8[e];
+        __syncthreads();
+        for (int c2 = threadIdx.x; c2 < C; c2 += kHeadThreads) {
+            float a = 0.f;
+            for (int g2 = 0; g2 < G; ++g2) a += part[g2 * C + c2];
+            feat[c2] = a / (float)HW;
+        }
+    } else if (head_vector4_path<T>(C)) {
+        // sixteen 16-byte loads in flight per thread: one workgroup streams a whole image
+        constexpr int kFlight = 16;
+        const int cpb = C / 4, G = groups;
+        const int chunk = threadIdx.x % cpb, pg = threadIdx.x / cpb;
+        const float* const at = (const float*)xp + chunk * 4;
+        float4 a4 = make_float4(0.f, 0.f, 0.f, 0.f);
+        int i = pg;
+        for (; i + (kFlight - 1) * G < HW; i += kFlight * G) {
+            float4 v[kFlight];
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) v[u] = *(const float4*)(at + (size_t)(i + u * G) * C);
+#pragma unroll
+            for (int u = 0; u < kFlight; ++u) { a4.x += v[u].x; a4.y += v[u].y; a4.z += v[u].z; a4.w += v[u].w; }
+        }
+        for (; i < HW; i += G) {
+            const float4 v = *(const float4*)(at + (size_t)i * C);
+            a4.x += v.x; a4.y += v.y; a4.z += v.z; a4.w += v.w;
+        }
+        *(float4*)(part + pg * C + chunk * 4) = a4;
         __syncthreads();
         for (int c2 = threadIdx.x; c2 < C; c2 += kHeadThreads) {
             float a = 0.f;
@@ -730,9 +781,7 @@ hipError_t head_gap_fc(int dtype, const void* x, const void* w, const float* b, 
                        int32_t ncls, const RouteArgs& r, hipStream_t stream)
 {
     if (N <= 0) return hipSuccess;
-    int groups = C < kHeadThreads ? kHeadThreads / C : 1;
-    if (dtype == 1 && head_vector_path<uint16_t>(C)) groups = kHeadThreads / (C / 8);      // partial sums of the 16-byte path
-    size_t smem = sizeof(float) * ((size_t)C + (size_t)groups * C + (size_t)ncls);
+    const size_t smem = dtype == 1 ? head_lds_bytes<uint16_t>(C, ncls) : head_lds_bytes<float>(C, ncls);
     if (smem > 60 * 1024) return hipErrorInvalidValue;
     const GroupTable gt{};
     const GroupRoutes gr{};
@@ -753,9 +802,7 @@ hipError_t head_gap_fc_grouped(int dtype, const void* x, const GroupTable& group
     if (groups.n <= 0 || groups.n > kMaxGroups || groups.first_row[0] != 0 || groups.first_row[groups.n] != N ||
         off_w > 0x7FFFFFFFull || off_b > 0x7FFFFFFFull)
         return hipErrorInvalidValue;
-    int pgroups = C < kHeadThreads ? kHeadThreads / C : 1;
-    if (dtype == 1 && head_vector_path<uint16_t>(C)) pgroups = kHeadThreads / (C / 8);
-    size_t smem = sizeof(float) * ((size_t)C + (size_t)pgroups * C + (size_t)ncls);
+    const size_t smem = dtype == 1 ? head_lds_bytes<uint16_t>(C, ncls) : head_lds_bytes<float>(C, ncls);
     if (smem > 60 * 1024) return hipErrorInvalidValue;
     if (dtype == 1)
         hipLaunchKernelGGL(head_gap_fc_kernel<uint16_t>, dim3(N), dim3(kHeadThreads), smem, stream, (const uint16_t*)x,

@@ -193,3 +193,34 @@ def test_stem_with_pool(B, oracle, H, Wd, n):
         # one bf16 ulp where fp32 and fp64 sums round to different sides, 1e-5 where the terms cancel; rounding and the
         # maximum are monotonic, so the pool adds nothing
         assert np.all(np.abs(got[i] - want) <= np.maximum(np.abs(want) * 2.0 ** -7, 1e-5)), i
+
+
+@pytest.mark.parametrize("H,Wd,C", [(64, 64, 64), (33, 31, 512), (16, 16, 16), (1, 1, 64), (3, 5, 1024), (255, 1, 64), (257, 1, 32),
+                                    (20, 13, 48), (9, 9, 12)])
+def test_fp32_head_pooling(B, H, Wd, C):
+    """Average pool and classifier of fp32 experts: sixteen positions in flight per thread and their remainders, one position,
+    one position group (1024 channels), and channel counts that keep the plain loads (48, 12)."""
+    import torch
+    n = 3
+    p = W._Prog(H, Wd, C)
+    p.head(0, 5)
+    arch = W.Arch("head", W.DT_F32, H, Wd, C, 5, np.array(p.layers, dtype=np.int32), p.gains)
+    blob = W.make_expert_blob(arch, 7, 0)
+    rng = np.random.default_rng(H * 7 + C)
+    x = rng.standard_normal((n, H, Wd, C)).astype(np.float32)
+    dev = torch.from_numpy(x).cuda()
+    ctx = B.Context(max_requests=n, max_stages=1, max_batch=n)
+    aid = ctx.coe_register_arch(arch)
+    ctx.coe_register_expert(0, aid, blob, 1.0)
+    g = W.graph_from_lists([[]])
+    ctx.coe_set_dependency_graph(g.succ_off, g.succ)
+    ctx.coe_submit(n, dev.data_ptr(), True)
+    while ctx.coe_step()[0] != B.COE_DONE:
+        pass
+    _, logits, _ = ctx.coe_collect(n)
+    ctx.close()
+    w, b = W.blob_tensor(arch, blob, 0, "w").astype(np.float64).reshape(5, C), W.blob_tensor(arch, blob, 0, "b").astype(np.float64)
+    want = x.astype(np.float64).mean((1, 2)) @ w.T + b
+    # first order: HW - 1 additions, a division, C products and additions, each 2^-24 of the absolute terms
+    bound = (H * Wd + 2 * C + 4) * 2.0 ** -24 * (np.abs(x).astype(np.float64).mean((1, 2)) @ np.abs(w).T + np.abs(b))
+    assert np.all(np.abs(logits[:, :5] - want) <= bound)
