@@ -224,3 +224,28 @@ def test_fp32_head_pooling(B, H, Wd, C):
     # first order: HW - 1 additions, a division, C products and additions, each 2^-24 of the absolute terms
     bound = (H * Wd + 2 * C + 4) * 2.0 ** -24 * (np.abs(x).astype(np.float64).mean((1, 2)) @ np.abs(w).T + np.abs(b))
     assert np.all(np.abs(logits[:, :5] - want) <= bound)
+
+
+@pytest.mark.parametrize("n", [341, 342, 700])
+def test_pageable_inputs_arrive_whole(B, n):
+    """Inputs from pageable memory (below 16 MB by the runtime's copy, from there through the pinned ring: eight chunks and a
+    remainder, more chunks than the ring holds) and from pinned memory give the bits of inputs in device memory, twice over."""
+    import torch
+    arch = W.tiny_cnn(4, 64)
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal((n, 64, 64, 3)).astype(np.float32)
+    pinned = torch.from_numpy(x).pin_memory()
+    ctx = B.Context(max_requests=n, max_stages=1, max_batch=256)
+    aid = ctx.coe_register_arch(arch)
+    ctx.coe_register_expert(0, aid, W.make_expert_blob(arch, 7, 0), 1.0)
+    g = W.graph_from_lists([[]])
+    ctx.coe_set_dependency_graph(g.succ_off, g.succ)
+    dev = torch.from_numpy(x).cuda()
+    out = []
+    for src, on_device in ((dev.data_ptr(), True), (x, False), (x[::-1].copy(), False), (pinned.numpy(), False)):
+        ctx.coe_submit(n, src, on_device)
+        while ctx.coe_step()[0] != B.COE_DONE:
+            pass
+        out.append(ctx.coe_collect(n)[1])
+    ctx.close()
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2][::-1]) and np.array_equal(out[0], out[3])
