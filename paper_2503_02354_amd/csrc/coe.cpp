@@ -50,6 +50,7 @@ struct ArchPlan {
     size_t buf_elems[kMaxBufs] = {0};   // per request
     size_t patch_elems = 0;             // per request: rows of the largest patch-gathered conv
     bool groupable = false;             // every layer can run several experts' small groups in one launch
+    bool token_ops = false;             // transformer-shaped
     int32_t row_cap = INT32_MAX;        // most requests one launch may cover: the kernels address a tensor with 31-bit byte offsets
     int32_t arr_min_res = 0, arr_min_miss = 0, arr_wait = 0;   // arranging window (coe_set_arranging); arr_wait 0 = off
     bool gathers_input = false;         // the only reader of the input is a few-channel conv kernel, which can follow a row table
@@ -420,18 +421,24 @@ int plan_arch(coe_ctx* c, const coe_arch_desc* d, ArchPlan& a)
         a.gathers_input = readers == 1 && L0.d.op == COE_OP_CONV && L0.d.src == 0 && a.dtype == COE_DT_BF16 && !L0.packed &&
                           (L0.fuse_pool || coe::k::conv_smallc_supported(cs, L0.d.res >= 0, false));
     }
-    // grouped launches: matrix-core convs with K % 64 == 0 take a group table; few-channel convs run once per group;
-    // pools have no weights; the pooled head takes a group table.  Anything else keeps one launch per group.
+    // grouped launches: matrix-core convs with K % 64 == 0 take a group table; few-channel convs run once per group where their
+    // kernel takes none; patches are gathered once per group; pools and attention have no weights; token ops, layer norms and
+    // the pooled and class-token heads take a group table.  Anything else keeps one launch per group.
     a.groupable = a.dtype == COE_DT_BF16;
     for (const LayerPlan& L : a.layers) {
         const coe_layer& l = L.d;
         coe::k::ConvShape cs{1, L.H, L.W, L.C, L.K, l.r, l.s, l.stride, l.pad, L.P, L.Q, l.act};
         const bool reads_input = l.src == 0 || l.res == 0;
-        if (reads_input && !(l.op == COE_OP_CONV && !L.packed && l.res != 0)) a.groupable = false;   // only the per-group stem may
+        // only the per-group stem and the per-group patches may
+        if (reads_input && !(l.op == COE_OP_CONV && (!L.packed || L.patchify) && l.res != 0)) a.groupable = false;
         if (l.op == COE_OP_CONV) {
-            if (L.patchify) a.groupable = false;
-            else if (L.packed) a.groupable = a.groupable && coe::k::conv_mfma_groupable(cs);
+            if (L.patchify) {
+                coe::k::ConvShape gs{1, L.P, L.Q, l.r * l.s * L.C, L.K, 1, 1, 1, 0, L.P, L.Q, l.act};
+                a.groupable = a.groupable && coe::k::conv_mfma_groupable(gs);
+            } else if (L.packed) a.groupable = a.groupable && coe::k::conv_mfma_groupable(cs);
             else if (!L.fuse_pool && !coe::k::conv_smallc_supported(cs, l.res >= 0, false)) a.groupable = false;
+        } else if (l.op == COE_OP_TOKENS || l.op == COE_OP_LAYERNORM || l.op == COE_OP_ATTENTION || l.op == COE_OP_HEAD_CLS) {
+            a.token_ops = true;
         } else if (l.op != COE_OP_MAXPOOL && l.op != COE_OP_HEAD) {
             a.groupable = false;
         }
@@ -886,7 +893,21 @@ int run_group_set(coe_ctx* c, Lane& ln, const std::vector<SetMember>& set, const
         case COE_OP_CONV: {
             coe::k::ConvShape s{n, L.H, L.W, L.C, L.K, l.r, l.s, l.stride, l.pad, L.P, L.Q, l.act};
             double flops = 2.0 * L.macs * n;
-            if (L.packed) {
+            if (L.patchify) {
+                const size_t patch_row = (size_t)L.P * L.Q * l.r * l.s * L.C * a.elem(), in_row = (size_t)L.H * L.W * L.C * a.elem();
+                {
+                    double bytes = 2.0 * n * (double)L.H * L.W * L.C * a.elem();
+                    Span sp(c, COE_K_TOKEN_OPS, bytes, ln.s);
+                    for (size_t g = 0; g < set.size(); ++g) {
+                        const uint8_t* in = l.src == 0 ? staged + (size_t)set[g].first * ib : buf(l.src) + (size_t)gt.first_row[g] * in_row;
+                        HIPCHK(c, coe::k::patchify(in, (uint8_t*)ln.d_patch + (size_t)gt.first_row[g] * patch_row, set[g].count, L.H, L.W,
+                                                   L.C, l.r, l.s, ln.s));
+                    }
+                }
+                coe::k::ConvShape gs{n, L.P, L.Q, l.r * l.s * L.C, L.K, 1, 1, 1, 0, L.P, L.Q, l.act};
+                Span sp(c, COE_K_CONV_MFMA, flops, ln.s);
+                HIPCHK(c, coe::k::conv_mfma_grouped(ln.d_patch, gt, L.off[0], L.off[1], nullptr, buf(l.dst), gs, ln.s));
+            } else if (L.packed) {
                 if (l.src == 0) return fail(c, COE_ESTATE, "internal: grouped matrix-core conv on the raw input");
                 const void* res = l.res >= 0 ? buf(l.res) : nullptr;
                 Span sp(c, coe::k::conv_mfma_uses_slab(s) ? COE_K_CONV_SLAB : COE_K_CONV_MFMA, flops, ln.s);
@@ -935,6 +956,35 @@ int run_group_set(coe_ctx* c, Lane& ln, const std::vector<SetMember>& set, const
                                 c->max_classes};
             Span sp(c, COE_K_HEAD, bytes, ln.s);
             HIPCHK(c, coe::k::head_gap_fc_grouped(a.dtype, buf(l.src), gt, L.off[0], L.off[1], n, L.H * L.W, L.C, L.K, r, gr, ln.s));
+            break;
+        }
+        case COE_OP_TOKENS: {
+            if (l.src == 0) return fail(c, COE_ESTATE, "internal: grouped token op on the raw input");
+            double bytes = (double)n * ((double)L.H * L.W + L.P) * L.C * a.elem();
+            Span sp(c, COE_K_TOKEN_OPS, bytes, ln.s);
+            HIPCHK(c, coe::k::tokens_grouped(buf(l.src), gt, L.off[0], L.off[1], buf(l.dst), n, L.P, L.C, ln.s));
+            break;
+        }
+        case COE_OP_LAYERNORM: {
+            if (l.src == 0) return fail(c, COE_ESTATE, "internal: grouped layer norm on the raw input");
+            double bytes = 2.0 * n * (double)L.H * L.W * L.C * a.elem();
+            Span sp(c, COE_K_TOKEN_OPS, bytes, ln.s);
+            HIPCHK(c, coe::k::layernorm_grouped(buf(l.src), gt, L.off[0], L.off[1], buf(l.dst), n, L.H * L.W, L.C, ln.s));
+            break;
+        }
+        case COE_OP_ATTENTION: {
+            if (l.src == 0) return fail(c, COE_ESTATE, "internal: grouped attention on the raw input");
+            Span sp(c, COE_K_ATTENTION, 2.0 * L.macs * n, ln.s);
+            HIPCHK(c, coe::k::attention(buf(l.src), buf(l.dst), n, L.H * L.W, L.K, l.aux0, ln.s));
+            break;
+        }
+        case COE_OP_HEAD_CLS: {
+            if (l.src == 0) return fail(c, COE_ESTATE, "internal: grouped head on the raw input");
+            double bytes = (double)n * L.C * a.elem();
+            coe::k::RouteArgs r{c->d_perm, 0, c->d_succ, 0, c->d_cur, c->d_depth, c->d_path, c->cfg.max_stages, c->d_logits,
+                                c->max_classes};
+            Span sp(c, COE_K_HEAD, bytes, ln.s);
+            HIPCHK(c, coe::k::head_cls_grouped(buf(l.src), gt, L.off, n, L.H * L.W, L.C, L.K, r, gr, ln.s));
             break;
         }
         default:
@@ -1527,12 +1577,16 @@ static int step_body(coe_ctx* c, coe_step_stats& st)
         // a group that has run only frees its expert earlier).
         std::vector<SetMember> set;
         if (small(e)) {
+            const ArchPlan& a = c->archs[x.arch];
             set.push_back({e, off[e], c->h_cnt[e]});
             int32_t rows = c->h_cnt[e];
             for (size_t j = i + 1; j < order.size() && (int32_t)set.size() < coe::k::kMaxGroups; ++j) {
                 const int32_t f = order[j];
                 if (launched[f] || !small(f) || c->experts[f].arch != x.arch) continue;
                 if (!c->experts[f].buf) continue;              // its switch has not been issued yet
+                // transformer-shaped weights take longer to arrive than a small group to run (170 MB, 3 ms): nothing waits
+                // for another group's copy
+                if (a.token_ops && (x.load_pending || c->experts[f].load_pending)) continue;
                 if (rows + c->h_cnt[f] > chunk_rows(c, c->archs[x.arch])) continue;
                 set.push_back({f, off[f], c->h_cnt[f]});
                 rows += c->h_cnt[f];

@@ -133,14 +133,23 @@ hipError_t head_det(const void* m0, int32_t hw0, const void* m1, int32_t hw1, in
 hipError_t patchify(const void* x, void* out, int32_t N, int32_t H, int32_t W, int32_t C, int32_t R, int32_t S, hipStream_t stream);
 // out[n][0] = cls + pos[0]; out[n][1+i] = x[n][i] + pos[1+i]; T = tokens of out; D % 8 == 0.
 hipError_t tokens(const void* x, const void* cls, const void* pos, void* out, int32_t N, int32_t T, int32_t D, hipStream_t stream);
+// grouped form: group g's class token and positions at weights[g] + off_cls, + off_pos
+hipError_t tokens_grouped(const void* x, const GroupTable& groups, size_t off_cls, size_t off_pos, void* out, int32_t N, int32_t T,
+                          int32_t D, hipStream_t stream);
 // layer norm over D channels of `rows` tokens, eps 1e-6, D even and <= 2048.
 hipError_t layernorm(const void* x, const float* gamma, const float* beta, void* y, int64_t rows, int32_t D, hipStream_t stream);
+// grouped form over N images of T tokens: gamma at weights[g] + off_gamma, beta at + off_beta
+hipError_t layernorm_grouped(const void* x, const GroupTable& groups, size_t off_gamma, size_t off_beta, void* y, int32_t N, int32_t T,
+                             int32_t D, hipStream_t stream);
 // qkv [N][T][3D] (q | k | v) -> out [N][T][D]; head width must be 64, T <= 224.
 bool attention_supported(int32_t T, int32_t D, int32_t heads);
 hipError_t attention(const void* qkv, void* out, int32_t N, int32_t T, int32_t D, int32_t heads, hipStream_t stream);
 // logits = FC(layer norm(token 0 of x [N][T][D])), then routing like head_gap_fc.
 hipError_t head_cls(const void* x, const float* gamma, const float* beta, const void* w, const float* b, int32_t N, int32_t T,
                     int32_t D, int32_t ncls, const RouteArgs& r, hipStream_t stream);
+// grouped form: the four tensors at weights[g] + off[0..3]; r and routes as in head_gap_fc_grouped
+hipError_t head_cls_grouped(const void* x, const GroupTable& groups, const size_t off[4], int32_t N, int32_t T, int32_t D, int32_t ncls,
+                            const RouteArgs& r, const GroupRoutes& routes, hipStream_t stream);
 
 }  // namespace k
 }  // namespace coe

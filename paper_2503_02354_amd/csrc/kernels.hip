@@ -532,13 +532,28 @@ __global__ __launch_bounds__(kHeadThreads) void head_gap_fc_kernel(const T* __re
 // class-token head: layer norm of token 0 (rounded to bf16 like every stored activation), FC, routing
 __global__ __launch_bounds__(kHeadThreads) void head_cls_kernel(const uint16_t* __restrict__ x, const float* __restrict__ gamma,
                                                                 const float* __restrict__ beta, const uint16_t* __restrict__ w,
-                                                                const float* __restrict__ b, int T, int D, int ncls, RouteArgs r)
+                                                                const float* __restrict__ b, int T, int D, int ncls, RouteArgs r,
+                                                                GroupTable gt, GroupRoutes gr, uint4 off)
 {
     extern __shared__ float smem[];          // feat[D] | red[8] | logit[ncls]
     float* feat = smem;
     float* red = smem + D;
     float* logit = red + 8;
     const int row = blockIdx.x;
+    if (gt.n > 0) {
+        // grouped launch: this request's group decides the weights and the routing rule
+        int g = 0;
+        while (g + 1 < gt.n && row >= gt.first_row[g + 1]) ++g;
+        const char* base = (const char*)gt.weights[g];
+        gamma = (const float*)(base + off.x);
+        beta = (const float*)(base + off.y);
+        w = (const uint16_t*)(base + off.z);
+        b = (const float*)(base + off.w);
+        r.expert = gr.expert[g];
+        r.succ = r.succ + gr.succ_off[g];
+        r.n_route = gr.n_route[g];
+        if (r.slot) r.slot = r.slot + (gr.slot_off[g] - gt.first_row[g]);
+    }
     const uint16_t* xp = x + (size_t)row * T * D;     // token 0
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     float sum = 0.f;
@@ -855,7 +870,22 @@ hipError_t head_cls(const void* x, const float* gamma, const float* beta, const 
     size_t smem = sizeof(float) * ((size_t)D + 8 + (size_t)ncls);
     if (smem > 60 * 1024) return hipErrorInvalidValue;
     hipLaunchKernelGGL(head_cls_kernel, dim3(N), dim3(kHeadThreads), smem, stream, (const uint16_t*)x, gamma, beta,
-                       (const uint16_t*)w, b, T, D, ncls, r);
+                       (const uint16_t*)w, b, T, D, ncls, r, GroupTable{}, GroupRoutes{}, make_uint4(0, 0, 0, 0));
+    return hipGetLastError();
+}
+
+hipError_t head_cls_grouped(const void* x, const GroupTable& groups, const size_t off[4], int32_t N, int32_t T, int32_t D, int32_t ncls,
+                            const RouteArgs& r, const GroupRoutes& routes, hipStream_t stream)
+{
+    if (N <= 0) return hipSuccess;
+    if (groups.n <= 0 || groups.n > kMaxGroups || groups.first_row[0] != 0 || groups.first_row[groups.n] != N) return hipErrorInvalidValue;
+    for (int i = 0; i < 4; ++i)
+        if (off[i] > 0x7FFFFFFFull) return hipErrorInvalidValue;
+    size_t smem = sizeof(float) * ((size_t)D + 8 + (size_t)ncls);
+    if (smem > 60 * 1024) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(head_cls_kernel, dim3(N), dim3(kHeadThreads), smem, stream, (const uint16_t*)x, (const float*)nullptr,
+                       (const float*)nullptr, (const uint16_t*)nullptr, (const float*)nullptr, T, D, ncls, r, groups, routes,
+                       make_uint4((uint32_t)off[0], (uint32_t)off[1], (uint32_t)off[2], (uint32_t)off[3]));
     return hipGetLastError();
 }
 

@@ -47,9 +47,19 @@ __global__ __launch_bounds__(256) void patchify_kernel(const uint4* __restrict__
     out[idx] = x[src];
 }
 
+// first tensor of the group that image n belongs to, `off` bytes into its expert's weights
+__device__ __forceinline__ const void* group_tensor(const GroupTable& gt, int n, uint32_t off)
+{
+    int g = 0;
+    while (g + 1 < gt.n && n >= gt.first_row[g + 1]) ++g;
+    return (const char*)gt.weights[g] + off;
+}
+
 // ---- class token + position embedding: out[n][0] = cls + pos[0]; out[n][1+i] = x[n][i] + pos[1+i] -----------------
+template <bool GROUPED>
 __global__ __launch_bounds__(256) void tokens_kernel(const uint4* __restrict__ x, const uint4* __restrict__ cls,
-                                                     const uint4* __restrict__ pos, uint4* __restrict__ out, int N, int T, int D8)
+                                                     const uint4* __restrict__ pos, uint4* __restrict__ out, int N, int T, int D8,
+                                                     GroupTable gt, uint32_t off_cls, uint32_t off_pos)
 {
     size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
     size_t total = (size_t)N * T * D8;
@@ -58,6 +68,10 @@ __global__ __launch_bounds__(256) void tokens_kernel(const uint4* __restrict__ x
     size_t r = idx / D8;
     int t = (int)(r % T);
     int n = (int)(r / T);
+    if (GROUPED) {
+        cls = (const uint4*)group_tensor(gt, n, off_cls);
+        pos = (const uint4*)group_tensor(gt, n, off_pos);
+    }
     uint4 a = t == 0 ? cls[c] : x[((size_t)n * (T - 1) + (t - 1)) * D8 + c];
     uint4 p = pos[(size_t)t * D8 + c];
     uint4 o;
@@ -70,12 +84,18 @@ __global__ __launch_bounds__(256) void tokens_kernel(const uint4* __restrict__ x
 
 // ---- layer norm over channels, one wavefront per token, the token held in registers ---------------------------------
 constexpr int kLnMaxPairs = 16;     // D <= 64 lanes * 2 * 16 = 2048
+template <bool GROUPED>
 __global__ __launch_bounds__(256) void layernorm_kernel(const uint32_t* __restrict__ x, const float* __restrict__ gamma,
                                                         const float* __restrict__ beta, uint32_t* __restrict__ y, int rows,
-                                                        int D2 /* pairs per token */)
+                                                        int D2 /* pairs per token */, GroupTable gt, int tokens_per_image,
+                                                        uint32_t off_gamma, uint32_t off_beta)
 {
-    int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    int row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (row >= rows) return;
+    if (GROUPED) {
+        gamma = (const float*)group_tensor(gt, row / tokens_per_image, off_gamma);
+        beta = (const float*)group_tensor(gt, row / tokens_per_image, off_beta);
+    }
     int lane = threadIdx.x & 63;
     const uint32_t* xp = x + (size_t)row * D2;
     float v[2 * kLnMaxPairs];
@@ -319,27 +339,65 @@ hipError_t patchify(const void* x, void* out, int32_t N, int32_t H, int32_t W, i
     return hipGetLastError();
 }
 
-hipError_t tokens(const void* x, const void* cls, const void* pos, void* out, int32_t N, int32_t T, int32_t D, hipStream_t stream)
+namespace {
+
+template <bool GROUPED>
+hipError_t launch_tokens(const void* x, const void* cls, const void* pos, void* out, int32_t N, int32_t T, int32_t D,
+                         const GroupTable& gt, uint32_t off_cls, uint32_t off_pos, hipStream_t stream)
 {
     if (D % 8) return hipErrorInvalidValue;
     size_t total = (size_t)N * T * (D / 8);
     if (total == 0) return hipSuccess;
     size_t blocks = (total + 255) / 256;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(tokens_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint4*)x, (const uint4*)cls,
-                       (const uint4*)pos, (uint4*)out, N, T, D / 8);
+    hipLaunchKernelGGL(tokens_kernel<GROUPED>, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint4*)x, (const uint4*)cls,
+                       (const uint4*)pos, (uint4*)out, N, T, D / 8, gt, off_cls, off_pos);
     return hipGetLastError();
 }
 
-hipError_t layernorm(const void* x, const float* gamma, const float* beta, void* y, int64_t rows, int32_t D, hipStream_t stream)
+template <bool GROUPED>
+hipError_t launch_layernorm(const void* x, const float* gamma, const float* beta, void* y, int64_t rows, int32_t D, const GroupTable& gt,
+                            int32_t tokens_per_image, uint32_t off_gamma, uint32_t off_beta, hipStream_t stream)
 {
     if (D % 2 || D > 128 * kLnMaxPairs) return hipErrorInvalidValue;
     if (rows == 0) return hipSuccess;
     int64_t blocks = (rows + 3) / 4;
     if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(layernorm_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint32_t*)x, gamma, beta,
-                       (uint32_t*)y, (int)rows, D / 2);
+    hipLaunchKernelGGL(layernorm_kernel<GROUPED>, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint32_t*)x, gamma, beta,
+                       (uint32_t*)y, (int)rows, D / 2, gt, tokens_per_image, off_gamma, off_beta);
     return hipGetLastError();
+}
+
+bool table_ok(const GroupTable& groups, int32_t N, size_t off_a, size_t off_b)
+{
+    return groups.n > 0 && groups.n <= kMaxGroups && groups.first_row[0] == 0 && groups.first_row[groups.n] == N &&
+           off_a <= 0x7FFFFFFFull && off_b <= 0x7FFFFFFFull;
+}
+
+}  // namespace
+
+hipError_t tokens(const void* x, const void* cls, const void* pos, void* out, int32_t N, int32_t T, int32_t D, hipStream_t stream)
+{
+    return launch_tokens<false>(x, cls, pos, out, N, T, D, GroupTable{}, 0, 0, stream);
+}
+
+hipError_t tokens_grouped(const void* x, const GroupTable& groups, size_t off_cls, size_t off_pos, void* out, int32_t N, int32_t T,
+                          int32_t D, hipStream_t stream)
+{
+    if (!table_ok(groups, N, off_cls, off_pos)) return hipErrorInvalidValue;
+    return launch_tokens<true>(x, nullptr, nullptr, out, N, T, D, groups, (uint32_t)off_cls, (uint32_t)off_pos, stream);
+}
+
+hipError_t layernorm(const void* x, const float* gamma, const float* beta, void* y, int64_t rows, int32_t D, hipStream_t stream)
+{
+    return launch_layernorm<false>(x, gamma, beta, y, rows, D, GroupTable{}, 1, 0, 0, stream);
+}
+
+hipError_t layernorm_grouped(const void* x, const GroupTable& groups, size_t off_gamma, size_t off_beta, void* y, int32_t N, int32_t T,
+                             int32_t D, hipStream_t stream)
+{
+    if (!table_ok(groups, N, off_gamma, off_beta) || T <= 0) return hipErrorInvalidValue;
+    return launch_layernorm<true>(x, nullptr, nullptr, y, (int64_t)N * T, D, groups, T, (uint32_t)off_gamma, (uint32_t)off_beta, stream);
 }
 
 bool attention_supported(int32_t T, int32_t D, int32_t heads)

@@ -249,3 +249,37 @@ def test_pageable_inputs_arrive_whole(B, n):
         out.append(ctx.coe_collect(n)[1])
     ctx.close()
     assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2][::-1]) and np.array_equal(out[0], out[3])
+
+
+@pytest.mark.parametrize("n,experts,cap", [(30, 6, 0), (300, 9, 0), (60, 8, 5)])
+def test_grouped_transformers_give_the_same_bits(B, n, experts, cap):
+    """Small groups of several transformer-shaped experts share launches: same logits, routes and switches, bit for bit, as one
+    launch per group."""
+    import torch
+    from oracle import guard as G
+    wl = W.config5(n, hw=64, n_experts=experts, cap=cap, dim=128, depth=2, heads=2, mlp=256, calibrated=False)
+    G.calibrate_workload(wl, n_cal=48)        # spreads the routes
+    blobs = [wl.blob(e) for e in range(experts)]
+    x = wl.inputs(range(n))
+    dev = torch.from_numpy(x.view(np.int16)).cuda()
+    out = {}
+    for small in (-1, 0):
+        ctx = B.Context(max_requests=n, max_stages=2, max_batch=256, cache_cap_experts=cap, group_small=small)
+        B.setup_workload(ctx, wl, blobs)
+        runs = []
+        for _ in range(2):                    # the first pass waits for the experts' first copies
+            ctx.coe_submit(n, dev.data_ptr(), True)
+            stats = []
+            while True:
+                rc, st = ctx.coe_step()
+                if rc == B.COE_DONE:
+                    break
+                stats.append(st)
+            _, logits, path = ctx.coe_collect(n)
+            runs.append((logits, path, [st.n_groups for st in stats], [st.n_misses for st in stats], sum(st.n_grouped for st in stats)))
+        ctx.close()
+        out[small] = runs
+    for a, b in zip(out[-1], out[0]):
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and a[2:4] == b[2:4]
+        assert a[4] == 0
+    assert out[0][1][4] >= 2
