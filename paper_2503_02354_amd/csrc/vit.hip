@@ -21,6 +21,12 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     f32x2 f = {lo, hi};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));   // round to nearest even
 }
+// a product that is rounded before it is used (not contracted into a multiply-add)
+__device__ __forceinline__ float scaled(float a, float b)
+{
+#pragma clang fp contract(off)
+    return a * b;
+}
 __device__ __forceinline__ float wave_sum(float v)
 {
 #pragma unroll
@@ -252,18 +258,21 @@ __global__ __launch_bounds__(64 * kAttnWaves, 2) void attention_kernel(const uin
                         if (kb * 32 + 8 * (v >> 2) + 4 * half + (v & 3) >= T) sc[kb][v] = -INFINITY;
                 }
 #pragma unroll
-                for (int v = 0; v < 16; ++v) m = fmaxf(m, sc[kb][v]);
+                for (int v = 0; v < 16; ++v) {
+                    sc[kb][v] = scaled(sc[kb][v], scale2);    // scores in units of ln 2
+                    m = fmaxf(m, sc[kb][v]);
+                }
             }
             m = fmaxf(m, __shfl_xor(m, 32, 64));
-            const float m2 = m * scale2;              // scores in units of ln 2
             float lsum = 0.f;
 #pragma unroll
             for (int kb = 0; kb < TB; ++kb)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
+                for (int v = 0; v < 16; v += 2) {
                     // 2^x on the transcendental unit (one instruction; exp(s - max) = 2^((s - max) / ln 2))
-                    sc[kb][v] = __builtin_amdgcn_exp2f(fmaf(sc[kb][v], scale2, -m2));
-                    lsum += sc[kb][v];
+                    sc[kb][v] = __builtin_amdgcn_exp2f(sc[kb][v] - m);
+                    sc[kb][v + 1] = __builtin_amdgcn_exp2f(sc[kb][v + 1] - m);
+                    lsum += sc[kb][v] + sc[kb][v + 1];
                 }
             lsum += __shfl_xor(lsum, 32, 64);
             const float inv = 1.f / lsum;
