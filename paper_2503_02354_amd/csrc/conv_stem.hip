@@ -318,10 +318,12 @@ __global__ __launch_bounds__(kThreads, 4) void conv_smallc_bf16_kernel(const uin
 // The 7x7/2 stem on three channels with ReLU and the fused 3x3/2 pool, as every ResNet-shaped expert begins: no tiles in
 // LDS and no barriers.  A wavefront walks down a strip of 32 conv columns (15 pooled ones at most) and keeps in registers
 //   * the operands of four pairs of input rows, (2i + 1, 2i + 2) for i = p - 2 .. p + 1, which are what conv row p needs
-//     (its window rows are 2p - 3 .. 2p + 3; the last row of the last pair is left out).  A window row is the 24 elements of
-//     columns 2q - 4 .. 2q + 3, three chunks of 8 that a lane loads straight from the image, 16 bytes each; column 2q - 4
-//     and whatever lies left or right of the image is masked to zero.  The next pair is loaded into the registers of the
-//     pair that has just been used for the last time, a whole conv row before it is needed;
+//     (its window rows are 2p - 3 .. 2p + 3; the last row of the last pair is left out).  A window row is the 21 elements of
+//     columns 2q - 3 .. 2q + 3 in three chunks of 8, as in conv_smallc_bf16_kernel: the sums run in its order and give its bits.
+//     A window begins at an odd element, so a lane loads a chunk straight from the image as the five dwords around it, 16 + 4
+//     bytes, and one byte permutation per dword moves it into place and puts zeros for what lies left or right of the image
+//     or behind the window.  The next pair is loaded into the registers of the pair that has just been used for the last
+//     time, a whole conv row before it is needed;
 //   * the running maximum of a pooled row's conv rows, after the bias.
 // The filters are packed into LDS in fragment order once per workgroup and read again for every conv row.  (In registers,
 // as far as they fit, they gain nothing: 1.39 ms per 4096 images with one to four of the eleven steps resident; with five and
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void conv_stem_strip_kernel(co
     const uint16_t* const w = (const uint16_t*)((const char*)gr.weights[grp] + gr.off_w);
     const float* const bias = (const float*)((const char*)gr.weights[grp] + gr.off_b);
 
-    // chunk c of window row r is elements 8c - 3 .. 8c + 4 of its 21 (zero outside); lanes 0-31 of step j take chunk 2j,
+    // chunk c of window row r is elements 8c .. 8c + 7 of its 21 (zero behind them); lanes 0-31 of step j take chunk 2j,
     // lanes 32-63 chunk 2j + 1, counted over all rows
     constexpr int kChunks = kFrags * 64, kPerThread = (kChunks + 64 * kStripWaves - 1) / (64 * kStripWaves);
     uint32_t packed[kPerThread][4];                            // (all loads in flight at once)
@@ -383,12 +385,12 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void conv_stem_strip_kernel(co
     for (int t = 0; t < kPerThread; ++t) {
         const int idx = tid + t * 64 * kStripWaves, l = idx & 63, f = idx >> 6;
         const int k = (f & 1) * 32 + (l & 31), chunk = (f >> 1) * 2 + (l >> 5);
-        const int r = chunk / 3, e0 = chunk % 3 * 8 - 3;
+        const int r = chunk / 3, e0 = chunk % 3 * 8;
         const bool row_ok = idx < kChunks && r < 7;
         uint32_t v[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const bool ok = row_ok && (unsigned)(e0 + i) < 21u;
+            const bool ok = row_ok && e0 + i < 21;
             const uint32_t loaded = w[ok ? (k * 7 + r) * 21 + e0 + i : 0];
             v[i] = ok ? loaded : 0u;
         }
@@ -417,43 +419,55 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void conv_stem_strip_kernel(co
         const int a0 = seg * g.seg_rows, a_end = a0 + g.seg_rows < g.PP ? a0 + g.seg_rows : g.PP;
         const int q = 2 * (b0 + col) - 1 + even;
         const uint32_t col_mask = (unsigned)q < (unsigned)s.Q ? ~0u : 0u;       // a column that does not exist is 0: never more than the maximum after ReLU
-        const int e_q = 6 * q - 12;
+        const int e_q = 6 * q - 9, e_end = e_q + 21 < WC ? e_q + 21 : WC;           // the window's elements of an image row
         const int e_of[3] = {e_q + 8 * half, half ? e_q : e_q + 16, e_q + 8 + 8 * half};
-        u32x4 mask[3];
+        // selectors of the byte permutations: the upper half of one dword and the lower half of the next, or zeros
+        u32x4 pick[3];
 #pragma unroll
         for (int ks = 0; ks < 3; ++ks)
 #pragma unroll
             for (int d = 0; d < 4; ++d) {
-                const int e = e_of[ks] + 2 * d, lo = e_q + 3 > 0 ? e_q + 3 : 0;
-                mask[ks][d] = (e >= lo && e < WC ? 0x0000FFFFu : 0u) | (e + 1 >= lo && e + 1 < WC ? 0xFFFF0000u : 0u);
+                const int e = e_of[ks] + 2 * d;
+                pick[ks][d] = (e >= 0 && e < e_end ? 0x0302u : 0x0C0Cu) | (e + 1 >= 0 && e + 1 < e_end ? 0x05040000u : 0x0C0C0000u);
             }
         const int n_src = rows ? __builtin_amdgcn_readfirstlane(rows[gr.in[grp] + image]) : gr.in[grp] + image;
         const __amdgpu_buffer_rsrc_t rs =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x + (size_t)n_src * H * WC), 0, H * row_bytes, 0x00020000);
-        const int off[3] = {e_of[0] * 2, e_of[1] * 2 + half * row_bytes, e_of[2] * 2 + row_bytes};
+        // the dword that holds the element before a chunk and its first one
+        const int off[3] = {e_of[0] * 2 - 2, e_of[1] * 2 - 2 + half * row_bytes, e_of[2] * 2 - 2 + row_bytes};
 
-        u32x4 in[4][3];                                        // [pair][step]
+        u32x4 in[4][3];                                        // [pair][step]; as loaded without the fifth dwords
+        struct Fifth { uint32_t d[3]; };
         // Offsets before the image (as unsigned) and behind it read as zero, and what a lane reads beyond a row's ends is
-        // masked; only a chunk that begins left of the image's first row and reaches into it needs the other form.
-        auto load_pair = [&](u32x4 (&to)[3], int i) __attribute__((always_inline)) {
+        // not picked; only a chunk that begins left of the image's first row and reaches into it needs the other form.
+        auto load_pair = [&](u32x4 (&to)[3], Fifth& fifth, int i) __attribute__((always_inline)) {
 #pragma unroll
-            for (int ks = 0; ks < 3; ++ks) to[ks] = __builtin_amdgcn_raw_buffer_load_b128(rs, off[ks] + (2 * i + 1) * row_bytes, 0, 0);
+            for (int ks = 0; ks < 3; ++ks) {
+                to[ks] = __builtin_amdgcn_raw_buffer_load_b128(rs, off[ks] + (2 * i + 1) * row_bytes, 0, 0);
+                fifth.d[ks] = __builtin_amdgcn_raw_buffer_load_b32(rs, off[ks] + (2 * i + 1) * row_bytes + 16, 0, 0);
+            }
         };
-        auto load_first_pair = [&](u32x4 (&to)[3]) __attribute__((always_inline)) {     // rows -1 and 0
+        auto load_first_pair = [&](u32x4 (&to)[3], Fifth& fifth) __attribute__((always_inline)) {     // rows -1 and 0
 #pragma unroll
             for (int ks = 0; ks < 3; ++ks) {
                 const bool row = ks == 2 || (ks == 1 && half);
 #pragma unroll
-                for (int d = 0; d < 4; ++d) {
-                    const int e = e_of[ks] + 2 * d;
-                    to[ks][d] = __builtin_amdgcn_raw_buffer_load_b32(rs, row && (unsigned)e < (unsigned)WC ? e * 2 : (int)0x80000000, 0, 0);
+                for (int d = 0; d < 5; ++d) {
+                    const int e = e_of[ks] - 1 + 2 * d;
+                    const uint32_t v = __builtin_amdgcn_raw_buffer_load_b32(rs, row && (unsigned)e < (unsigned)WC ? e * 2 : (int)0x80000000, 0, 0);
+                    if (d < 4) to[ks][d] = v;
+                    else fifth.d[ks] = v;
                 }
             }
         };
-        auto mask_pair = [&](u32x4 (&v)[3]) __attribute__((always_inline)) {
+        auto place_pair = [&](u32x4 (&v)[3], const Fifth& fifth) __attribute__((always_inline)) {
 #pragma unroll
-            for (int ks = 0; ks < 3; ++ks) v[ks] &= mask[ks];
+            for (int ks = 0; ks < 3; ++ks)
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    v[ks][d] = __builtin_amdgcn_perm(d < 3 ? v[ks][d < 3 ? d + 1 : 3] : fifth.d[ks], v[ks][d], pick[ks][d]);
         };
+        Fifth fifth[2];                                        // of the pair that is on its way and of the one before it
         f32x16 acc[2];
         // conv row p, its pairs in slots base .. base + 3; the next pair goes to slot base
         auto conv_row = [&](auto base_c, int p) __attribute__((always_inline)) {
@@ -466,7 +480,7 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void conv_stem_strip_kernel(co
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 u32x4(&pair)[3] = in[(base + j) & 3];
-                if (j == 3) mask_pair(pair);
+                if (j == 3) place_pair(pair, fifth[(base + 1) & 1]);
 #pragma unroll
                 for (int ks = 0; ks < 3; ++ks) {
                     if (j == 3 && ks == 2) continue;           // the eighth row
@@ -480,7 +494,7 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void conv_stem_strip_kernel(co
                         acc[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, __builtin_bit_cast(bf16x8, v), acc[nb], 0, 0, 0);
                     }
                 }
-                if (j == 0) load_pair(pair, p + 2);
+                if (j == 0) load_pair(pair, fifth[base & 1], p + 2);
             }
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -542,12 +556,14 @@ __global__ __launch_bounds__(64 * kStripWaves, 2) void conv_stem_strip_kernel(co
         };
 
         const int p0 = 2 * a0 - 1;
+        Fifth first[3];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) load_pair(in[j], p0 - 2 + j);
-        if (p0 == -1) load_first_pair(in[2]);
-        if (p0 == 1) load_first_pair(in[0]);
+        for (int j = 0; j < 3; ++j) load_pair(in[j], first[j], p0 - 2 + j);
+        load_pair(in[3], fifth[1], p0 + 1);
+        if (p0 == -1) load_first_pair(in[2], first[2]);
+        if (p0 == 1) load_first_pair(in[0], first[0]);
 #pragma unroll
-        for (int j = 0; j < 3; ++j) mask_pair(in[j]);
+        for (int j = 0; j < 3; ++j) place_pair(in[j], first[j]);
         conv_row(std::integral_constant<int, 0>{}, p0);
         each(p0, [&](int nb, int v, float t) __attribute__((always_inline)) { top[nb][v] = t; });
         for (int a = a0;;) {

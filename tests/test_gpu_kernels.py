@@ -195,6 +195,46 @@ def test_stem_with_pool(B, oracle, H, Wd, n):
         assert np.all(np.abs(got[i] - want) <= np.maximum(np.abs(want) * 2.0 ** -7, 1e-5)), i
 
 
+@pytest.mark.parametrize("H,Wd,n", [(224, 224, 2), (64, 64, 300), (38, 58, 2), (33, 62, 2), (35, 60, 5), (21, 122, 3), (5, 6, 4), (4, 4, 1)])
+def test_stem_with_pool_gives_the_bits_of_the_general_kernel(B, H, Wd, n):
+    """The fused stem adds the products of a window in the order of the general few-channel kernel: its pooled values are the
+    maxima of that kernel's convolution, bit for bit."""
+    import torch
+    rng = np.random.default_rng(H * 100 + Wd)
+    few = min(n, 3)
+    x = _bf16(rng, few, H, Wd, 3)
+    w = _bf16(rng, 64, 7, 7, 3, scale=np.sqrt(2.0 / 147))
+    bias = (0.3 * rng.standard_normal(64)).astype(np.float32)
+    p = W._Prog(H, Wd, 3)
+    p.conv(0, 1, 64, 7, 2, 3, W.ACT_RELU)
+    p.maxpool(1, 2, 3, 2, 1)
+    p.conv(2, 3, 64, 1, 1, 0, 0)
+    p.head(3, 4)
+    arch = W.Arch("stem", W.DT_BF16, H, Wd, 3, 4, np.array(p.layers, dtype=np.int32), p.gains)
+    blob = W.make_expert_blob(arch, 5, 0).copy()
+    for sp in W.blob_layout(arch)[0]:
+        value = {(0, "w"): w, (0, "b"): bias, (2, "w"): W.f32_to_bf16_bits(np.eye(64, dtype=np.float32)),
+                 (2, "b"): np.zeros(64, np.float32)}.get((sp.layer, sp.name))
+        if value is not None:
+            blob[sp.offset:sp.offset + sp.nbytes] = np.ascontiguousarray(value).view(np.uint8).reshape(-1)
+    P, Q = p.shape[1][:2]
+    PP, PQ = p.shape[2][:2]
+    idx = np.arange(n) % few
+    dev = torch.from_numpy(x[idx].view(np.int16)).cuda()
+    ctx = B.Context(max_requests=n, max_batch=n)
+    aid = ctx.coe_register_arch(arch)
+    ctx.coe_register_expert(0, aid, blob, 1.0)
+    got = ctx.coe_debug_layer_output(0, n, dev.data_ptr(), 2, (n, PP, PQ, 64), np.uint16).reshape(n, PP, PQ, 64)
+    conv, cls = ctx.coe_debug_conv(1, x, w, bias, None, 2, 3, W.ACT_RELU)
+    ctx.close()
+    assert cls == B.K_CONV_STEM
+    wide = np.zeros((few, 2 * PP + 1, 2 * PQ + 1, 64), np.uint16)         # after ReLU bf16 orders like its bits, 0 is the least
+    wide[:, 1:P + 1, 1:Q + 1] = conv
+    want = np.max([wide[:, r:r + 2 * PP - 1:2, c:c + 2 * PQ - 1:2] for r in range(3) for c in range(3)], axis=0)
+    # (the identity convolution turns -0 into 0; there is none after ReLU)
+    assert np.array_equal(got, want[idx])
+
+
 @pytest.mark.parametrize("H,Wd,C", [(64, 64, 64), (33, 31, 512), (16, 16, 16), (1, 1, 64), (3, 5, 1024), (255, 1, 64), (257, 1, 32),
                                     (20, 13, 48), (9, 9, 12)])
 def test_fp32_head_pooling(B, H, Wd, C):
