@@ -53,17 +53,18 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     f32x2 f = {lo, hi};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));   // round to nearest even
 }
-// x Phi(x) = max(x, 0) - |x| Q(|x|).  From 1 on Q(a) = exp(-a^2 / 2) h(a), h(a) = erfcx(a / sqrt 2) / 2 as t times a polynomial
-// of degree 8 in t = 1 / (1 + 0.26 a): a weighted least-squares fit, iterated towards equal relative error on 0 <= a <= 14.5
-// (7e-8 with the coefficients in fp32).  Below 1, where the roundings of those factors would show, Q(a) = 1/2 - a g(a^2), g of
-// degree 5 (Chebyshev interpolation, 4e-8).  Error of the result against 64 bits, 2-norm, normal arguments of standard deviation
-// 0.25 / 1 / 3: 3.2e-8 / 3.0e-8 / 2.2e-8; 0.5 x erfcf(-x / sqrt 2): 4.9e-8 / 3.4e-8 / 2.6e-8.  A third of its instructions: with
-// erfcf the epilogue of a 768 -> 3072 token GEMM took as long as half its products (chain of 777 transformer requests 78.6 ms
-// with erfcf, 72.4 with this).
-__device__ __forceinline__ float gelu(float x)
+// GELU as every kernel of this library defines it
+__device__ __forceinline__ float gelu_erfc(float x)
 {
-    const float a0 = fabsf(x), a = a0 > 64.f ? 64.f : a0;
-    const float t = __builtin_amdgcn_rcpf(fmaf(0.26f, a, 1.f));
+    return 0.5f * x * erfcf(-x * 0.70710678118654752440f);
+}
+// The same within ten units in the last place of fp32, for x > -12 and NaN: max(x, 0) - |x| Q(|x|), Q(a) = exp(-a^2 / 2) h(a),
+// h(a) = erfcx(a / sqrt 2) / 2 as t times a polynomial of degree 8 in t = 1 / (1 + 0.26 a): a weighted least-squares fit, iterated
+// towards equal relative error on 0 <= a <= 14.5 (7e-8 with the coefficients in fp32).  The exponent is the square of the rounded
+// argument that gelu_erfc passes on, to twice the precision: the rounding of that argument weighs far out.
+__device__ __forceinline__ float gelu_fast(float x)
+{
+    const float a = fabsf(x > 64.f ? 64.f : x), t = __builtin_amdgcn_rcpf(fmaf(0.26f, a, 1.f));
     float p = 0.0302301552f;
     p = fmaf(p, t, -0.151493773f);
     p = fmaf(p, t, 0.248731926f);
@@ -73,23 +74,63 @@ __device__ __forceinline__ float gelu(float x)
     p = fmaf(p, t, 0.102788605f);
     p = fmaf(p, t, 0.103050984f);
     p = fmaf(p, t, 0.103757024f);
-    const float z = a * a;
-    const float tail = __builtin_amdgcn_exp2f(z * -0.72134752044448170368f) * t * p;
-    float g = -7.662608e-06f;
-    g = fmaf(g, z, 0.00011350748f);
-    g = fmaf(g, z, -0.0011863485f);
-    g = fmaf(g, z, 0.00997333f);
-    g = fmaf(g, z, -0.06649036f);
-    g = fmaf(g, z, 0.3989423f);
-    const float q = a < 1.f ? fmaf(-a, g, 0.5f) : tail;
-    return fmaf(-a, q, fmaxf(x, 0.f));
+    constexpr float kLog2e = -1.44269504088896340736f, kLog2eLow = (float)(-1.44269504088896340736 - (double)kLog2e);
+    const float y = a * 0.70710678118654752440f, z = y * y, h = z * kLog2e;
+    const float low = fmaf(fmaf(z, kLog2eLow, fmaf(z, kLog2e, -h)), 0.69314718055994530942f, -fmaf(y, y, -z));
+    const float e = __builtin_amdgcn_exp2f(h);
+    return fmaf(-a, fmaf(e, low, e) * t * p, fmaxf(x, -0.f));
+}
+// GELU of values that are rounded to bf16 next, with the bits that gelu_erfc gives: the fast form decides unless it is so close to
+// the middle between two bf16 values that ten units of fp32 could tip it (a value in 3000), or far out.  Those lanes evaluate
+// gelu_erfc.  Compared over all 2^32 arguments: distance at most 10 for x > -12, the same bf16 everywhere, NaN for NaN and for
+// minus infinity.  (Which way single roundings fall moves the logits after twelve transformer layers by 1 %.)  Its time is near
+// that of the fast form alone: chain of 777 transformer requests 91.8 ms with the 128 x 128 tiles and erfcf throughout, 78.6 with
+// today's tiles and erfcf, 74.4 with a fast form that differed in one rounding of 10,000, 76.4 with this (77.4 in groups of four
+// values, 81.1 of sixteen: too many registers).
+template <int N> __device__ __forceinline__ void gelu_for_bf16(float (&v)[N])
+{
+    constexpr uint32_t kDistance = 10;
+    float x[N];
+    uint16_t off[N], nearest = 0xFFFF;
+    float lowest = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        x[i] = v[i];
+        v[i] = gelu_fast(x[i]);
+        off[i] = (uint16_t)(__float_as_uint(v[i]) - (0x8000u - kDistance));
+        nearest = min(nearest, off[i]);
+        lowest = fminf(lowest, x[i]);
+    }
+    if (nearest <= 2 * kDistance || lowest <= -12.f) {
+        uint32_t open = 0;                                    // a bit per value
+#pragma unroll
+        for (int i = 0; i < N; ++i) open |= off[i] <= 2 * kDistance || x[i] <= -12.f ? 1u << i : 0u;
+        do {
+            const uint32_t one = open & (0u - open);
+            float at = x[0];
+#pragma unroll
+            for (int i = 1; i < N; ++i) at = one == 1u << i ? x[i] : at;
+            const float r = gelu_erfc(at);
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[i] = one == 1u << i ? r : v[i];
+            open ^= one;
+        } while (open);
+    }
 }
 __device__ __forceinline__ float act_fn(float v, int act)
 {
     if (act == 1) return v > 0.f ? v : 0.f;
-    if (act == 2) return gelu(v);
     if (act == 3) return v / (1.f + expf(-v));
     return v;
+}
+template <int ACT, int N> __device__ __forceinline__ void activate(float (&v)[N])
+{
+    if (ACT == 2) {
+        gelu_for_bf16(v);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = act_fn(v[i], ACT);
+    }
 }
 // The activation is a launch parameter, but an epilogue that tests it per element compiles into hundreds of
 // branches: dispatch ONCE per wave to a body specialised for the activation.
@@ -318,10 +359,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_bf16_kernel
                     v0 += bf16_to_f32(rv.x & 0xFFFFu); v1 += bf16_to_f32(rv.x >> 16);
                     v2 += bf16_to_f32(rv.y & 0xFFFFu); v3 += bf16_to_f32(rv.y >> 16);
                 }
-                uint2 o;
-                o.x = pack_bf16(act_fn(v0, ACT), act_fn(v1, ACT));
-                o.y = pack_bf16(act_fn(v2, ACT), act_fn(v3, ACT));
-                *(uint2*)(y + orow + n) = o;
+                float v[4] = {v0, v1, v2, v3};
+                activate<ACT>(v);
+                *(uint2*)(y + orow + n) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
             }
         }
     }
@@ -420,6 +460,7 @@ __device__ __forceinline__ void store_tile_via_lds_act(f32x16 (&acc)[MB][NB], ui
     constexpr int WN = NB * 32, ROW = WN + 8;             // elements; 16 bytes of padding per staged row
     constexpr int CPR = WN / 8;                            // 16-byte chunks per row
     constexpr int T = 32 * CPR / 64;                       // chunks per lane and 32-row block
+    constexpr int kQuads = ACT == 2 ? 2 : 1;               // GELU: eight values share its test
     const int frag_row = lane & 31, f_hi = (lane >> 5) * 4;
     // the residual takes the same road in the other direction: row-contiguous 16-byte loads (all issued up front),
     // staged in LDS, picked up in the accumulator layout
@@ -446,21 +487,25 @@ __device__ __forceinline__ void store_tile_via_lds_act(f32x16 (&acc)[MB][NB], ui
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int nl = j * 32 + 8 * g + f_hi;
-                uint2* cell = (uint2*)(stage + frag_row * ROW + nl);
-                const float4 bv = *(const float4*)(bias + n_wave + nl);
-                float v0 = acc[i][j][4 * g + 0] + bv.x, v1 = acc[i][j][4 * g + 1] + bv.y;
-                float v2 = acc[i][j][4 * g + 2] + bv.z, v3 = acc[i][j][4 * g + 3] + bv.w;
-                if (RES) {
-                    const uint2 rv = *cell;
-                    v0 += bf16_to_f32(rv.x & 0xFFFFu); v1 += bf16_to_f32(rv.x >> 16);
-                    v2 += bf16_to_f32(rv.y & 0xFFFFu); v3 += bf16_to_f32(rv.y >> 16);
+            for (int g = 0; g < 4; g += kQuads) {             // accumulator quads that are finished together
+                float v[4 * kQuads];
+#pragma unroll
+                for (int h = 0; h < kQuads; ++h) {
+                    const int nl = j * 32 + 8 * (g + h) + f_hi;
+                    const float4 bv = *(const float4*)(bias + n_wave + nl);
+                    v[4 * h] = acc[i][j][4 * (g + h)] + bv.x; v[4 * h + 1] = acc[i][j][4 * (g + h) + 1] + bv.y;
+                    v[4 * h + 2] = acc[i][j][4 * (g + h) + 2] + bv.z; v[4 * h + 3] = acc[i][j][4 * (g + h) + 3] + bv.w;
+                    if (RES) {
+                        const uint2 rv = *(const uint2*)(stage + frag_row * ROW + nl);
+                        v[4 * h] += bf16_to_f32(rv.x & 0xFFFFu); v[4 * h + 1] += bf16_to_f32(rv.x >> 16);
+                        v[4 * h + 2] += bf16_to_f32(rv.y & 0xFFFFu); v[4 * h + 3] += bf16_to_f32(rv.y >> 16);
+                    }
                 }
-                uint2 o;
-                o.x = pack_bf16(act_fn(v0, ACT), act_fn(v1, ACT));
-                o.y = pack_bf16(act_fn(v2, ACT), act_fn(v3, ACT));
-                *cell = o;
+                activate<ACT>(v);
+#pragma unroll
+                for (int h = 0; h < kQuads; ++h)
+                    *(uint2*)(stage + frag_row * ROW + j * 32 + 8 * (g + h) + f_hi) =
+                        make_uint2(pack_bf16(v[4 * h], v[4 * h + 1]), pack_bf16(v[4 * h + 2], v[4 * h + 3]));
             }
         }
 #pragma unroll
@@ -1308,6 +1353,7 @@ __device__ __forceinline__ void store_tile_counted_act(f32x16 (&acc)[MB][NB], ui
     constexpr int WN = NB * 32, ROW = WN + 8;
     constexpr int CPR = WN / 8;
     constexpr int T = 32 * CPR / 64;
+    constexpr int kQuads = ACT == 2 ? 2 : 1;               // GELU: eight values share its test
     const int frag_row = lane & 31, f_hi = (lane >> 5) * 4;
     auto at = [&](int i, int t) -> uint32_t {
         const int idx = lane + 64 * t, mo = m_wave + i * 32 + idx / CPR;
@@ -1334,21 +1380,25 @@ __device__ __forceinline__ void store_tile_counted_act(f32x16 (&acc)[MB][NB], ui
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int nl = j * 32 + 8 * g + f_hi;
-                uint2* cell = (uint2*)(stage + frag_row * ROW + nl);
-                const float4 bv = *(const float4*)(bl + nl);
-                float v0 = acc[i][j][4 * g + 0] + bv.x, v1 = acc[i][j][4 * g + 1] + bv.y;
-                float v2 = acc[i][j][4 * g + 2] + bv.z, v3 = acc[i][j][4 * g + 3] + bv.w;
-                if (RES) {
-                    const uint2 rv = *cell;
-                    v0 += bf16_to_f32(rv.x & 0xFFFFu); v1 += bf16_to_f32(rv.x >> 16);
-                    v2 += bf16_to_f32(rv.y & 0xFFFFu); v3 += bf16_to_f32(rv.y >> 16);
+            for (int g = 0; g < 4; g += kQuads) {             // accumulator quads that are finished together
+                float v[4 * kQuads];
+#pragma unroll
+                for (int h = 0; h < kQuads; ++h) {
+                    const int nl = j * 32 + 8 * (g + h) + f_hi;
+                    const float4 bv = *(const float4*)(bl + nl);
+                    v[4 * h] = acc[i][j][4 * (g + h)] + bv.x; v[4 * h + 1] = acc[i][j][4 * (g + h) + 1] + bv.y;
+                    v[4 * h + 2] = acc[i][j][4 * (g + h) + 2] + bv.z; v[4 * h + 3] = acc[i][j][4 * (g + h) + 3] + bv.w;
+                    if (RES) {
+                        const uint2 rv = *(const uint2*)(stage + frag_row * ROW + nl);
+                        v[4 * h] += bf16_to_f32(rv.x & 0xFFFFu); v[4 * h + 1] += bf16_to_f32(rv.x >> 16);
+                        v[4 * h + 2] += bf16_to_f32(rv.y & 0xFFFFu); v[4 * h + 3] += bf16_to_f32(rv.y >> 16);
+                    }
                 }
-                uint2 o;
-                o.x = pack_bf16(act_fn(v0, ACT), act_fn(v1, ACT));
-                o.y = pack_bf16(act_fn(v2, ACT), act_fn(v3, ACT));
-                *cell = o;
+                activate<ACT>(v);
+#pragma unroll
+                for (int h = 0; h < kQuads; ++h)
+                    *(uint2*)(stage + frag_row * ROW + j * 32 + 8 * (g + h) + f_hi) =
+                        make_uint2(pack_bf16(v[4 * h], v[4 * h + 1]), pack_bf16(v[4 * h + 2], v[4 * h + 3]));
             }
         }
 #pragma unroll

@@ -112,6 +112,28 @@ def test_few_tiles_give_the_bits_of_many(B, oracle, H, Wd, C, K, R, stride, pad,
     assert np.all(np.abs(got - want) <= np.maximum(np.abs(want) * 2.0 ** -7, 1e-5))
 
 
+@pytest.mark.parametrize("C,pixels", [(64, 200), (64, 6000), (64, 40000), (96, 3000), (512, 33000)])
+def test_gelu_rounds_like_the_fp32_path(B, C, pixels):
+    """GELU in the bf16 epilogues (32 x 32 tiles, 64 x 64 tiles, 128 x 64 tiles, the register-staged kernel, persistent tiles) gives the
+    rounded value of the plain formula, which fp32 experts evaluate, bit for bit: an identity convolution, so that the value before
+    the activation is one fp32 sum of a bf16 number and a bias on both paths."""
+    rng = np.random.default_rng(C + pixels)
+    scale = np.exp(rng.uniform(np.log(1e-3), np.log(6.0), (1, pixels, 1, C)))
+    x = W.f32_to_bf16_bits((rng.standard_normal((1, pixels, 1, C)) * scale).astype(np.float32)).reshape(1, pixels, 1, C)
+    bias = rng.standard_normal(C).astype(np.float32)
+    bias[:10] = [-np.inf, np.inf, np.nan, -13.0, -12.0, -30.0, 80.0, 1e30, -1e30, 0.0]
+    eye = np.eye(C, dtype=np.float32).reshape(C, 1, 1, C)
+    ctx = B.Context(max_requests=1)
+    got, _ = ctx.coe_debug_conv(1, x, W.f32_to_bf16_bits(eye).reshape(eye.shape), bias, None, 1, 0, W.ACT_GELU)
+    plain, _ = ctx.coe_debug_conv(0, W.bf16_bits_to_f32(x).reshape(x.shape), eye, bias, None, 1, 0, W.ACT_GELU)
+    ctx.close()
+    nan = np.isnan(plain)
+    assert nan[..., 0].all() and nan[..., 2].all() and not nan[..., 3:].any()          # -inf * 0, as in the plain formula
+    assert np.array_equal(np.isnan(W.bf16_bits_to_f32(got).reshape(got.shape)), nan)
+    want = W.f32_to_bf16_bits(np.where(nan, 0, plain)).reshape(got.shape)
+    assert int(np.sum((got != want) & ~nan)) == 0
+
+
 @pytest.mark.parametrize("T,heads,n", [(17, 12, 5), (31, 3, 1), (33, 2, 3), (65, 12, 2), (97, 1, 5), (129, 3, 2), (160, 2, 1), (192, 1, 3),
                                        (193, 3, 2), (197, 12, 29)])
 def test_attention_block_counts(B, oracle, T, heads, n):
