@@ -63,6 +63,71 @@ def test_conv_f32_elementwise(B, oracle, n, H, Wd, C, K, R, stride, pad, use_res
         assert np.all(np.abs(got[i] - want) <= bound), float((np.abs(got[i] - want) / bound).max())
 
 
+def _spread(bad, R, stride, pad, P, Q):
+    """Outputs whose window holds one of the image positions `bad` (h, w)."""
+    hit = np.zeros((P, Q), bool)
+    for h, w in bad:
+        for p in range(P):
+            for q in range(Q):
+                hit[p, q] |= 0 <= h - (p * stride - pad) < R and 0 <= w - (q * stride - pad) < R
+    return hit
+
+
+@pytest.mark.parametrize("H,Wd,C,K,R,stride,pad,act", [
+    (20, 21, 3, 16, 3, 1, 1, 0), (20, 21, 3, 40, 3, 1, 1, 1), (19, 33, 5, 7, 3, 1, 1, 0), (18, 18, 5, 64, 5, 1, 2, 1),
+    (40, 37, 3, 64, 7, 2, 3, 1), (9, 9, 3, 8, 1, 1, 0, 0), (17, 18, 16, 32, 3, 1, 1, 0), (17, 18, 8, 64, 3, 2, 1, 1),
+])
+def test_conv_f32_keeps_non_finite_pixels_to_their_windows(B, oracle, H, Wd, C, K, R, stride, pad, act):
+    """An infinite or NaN pixel reaches the outputs whose window holds it and no other: those have the bits they have with
+    the pixel replaced."""
+    rng = np.random.default_rng(H * 10 + C)
+    x = rng.standard_normal((1, H, Wd, C)).astype(np.float32)
+    w = (rng.standard_normal((K, R, R, C)) * np.sqrt(2.0 / (R * R * C))).astype(np.float32)
+    bias = rng.standard_normal(K).astype(np.float32)
+    P = (H + 2 * pad - R) // stride + 1; Q = (Wd + 2 * pad - R) // stride + 1
+    bad = [(3, 5), (H - 1, Wd - 1), (0, Wd // 2), (H // 2, 0)]
+    ctx = B.Context(max_requests=1)
+    base, _ = ctx.coe_debug_conv(0, x, w, bias, None, stride, pad, act)
+    for value in (np.inf, -np.inf, np.nan):
+        xb = x.copy()
+        for i, (h, wd) in enumerate(bad):
+            xb[0, h, wd, i % C] = value
+        got, _ = ctx.coe_debug_conv(0, xb, w, bias, None, stride, pad, act)
+        hit = _spread(bad, R, stride, pad, P, Q)
+        assert np.array_equal(got[0][~hit], base[0][~hit]), value
+        if act == 0:
+            want = oracle.conv2d(xb[0], w, bias, None, stride, pad, act, 0)
+            assert np.array_equal(np.isnan(got[0][hit]), np.isnan(want[hit])) and np.array_equal(got[0][hit] > 0, want[hit] > 0)
+            assert not np.isfinite(got[0][hit]).any()
+    ctx.close()
+
+
+@pytest.mark.parametrize("H,Wd,C,K,R,stride,pad,act", [
+    (20, 21, 3, 40, 3, 1, 1, 0), (33, 18, 16, 64, 3, 1, 1, 1), (40, 37, 3, 64, 7, 2, 3, 2), (50, 50, 136, 32, 3, 1, 1, 0),
+])
+def test_conv_f32_keeps_non_finite_filters_off_the_padding(B, oracle, H, Wd, C, K, R, stride, pad, act):
+    """A filter value that is not finite does not reach outputs for which it falls on the zero padding."""
+    rng = np.random.default_rng(H * 10 + C)
+    x = rng.standard_normal((2, H, Wd, C)).astype(np.float32)
+    w = (rng.standard_normal((K, R, R, C)) * np.sqrt(2.0 / (R * R * C))).astype(np.float32)
+    w[1, 0, 1, C - 1], w[K - 1, R - 1, R - 1, 0] = np.inf, np.nan
+    bias = rng.standard_normal(K).astype(np.float32)
+    ctx = B.Context(max_requests=1)
+    got, _ = ctx.coe_debug_conv(0, x, w, bias, None, stride, pad, act)
+    ctx.close()
+    for i in range(2):
+        want = oracle.conv2d(x[i], w, bias, None, stride, pad, act, 0)
+        finite = np.isfinite(want)
+        assert finite[0, :, 1].all() and finite[-1, :, K - 1].all()
+        assert not np.isfinite(want[2, 2, [1, K - 1]]).any() or act
+        assert np.array_equal(np.isnan(got[i]), np.isnan(want)) and np.array_equal(np.isinf(got[i]), np.isinf(want))
+        wf = np.where(np.isfinite(w), np.abs(w), 0)
+        mag = oracle.conv2d(np.abs(x[i]), wf, np.abs(bias), None, stride, pad, 0, 0)
+        # as in test_conv_f32_elementwise
+        bound = 1.13 * (R * R * C + 2) * 2.0 ** -24 * mag + 8 * 2.0 ** -24 * np.abs(want) + (1e-6 * mag if act >= 2 else 0)
+        assert np.all(np.abs(got[i] - want)[finite] <= bound[finite])
+
+
 def _bf16(rng, *shape, scale=1.0):
     return W.f32_to_bf16_bits((rng.standard_normal(shape) * scale).astype(np.float32)).reshape(shape)
 
