@@ -99,6 +99,7 @@ struct Expert {
     int32_t cls = 0;                 // size class of its blob in the expert arena
     DevBuf* buf = nullptr;           // arena slot that holds the device copy when resident
     hipEvent_t loaded = nullptr;     // recorded on the copy stream after the switch
+    bool finite_filters = true;      // fp32: no filter of a convolution is infinite or NaN
     bool load_pending = false;       // compute stream has not yet waited for `loaded`
     int64_t file_off = -1;           // host tier: where the blob sits in the backing file
     HostSlot* hslot = nullptr;       // host tier: the pinned slot that holds it, if any
@@ -791,7 +792,8 @@ int run_expert(coe_ctx* c, Lane& ln, const Expert& x, const void* weights, const
                                               l.src == 0 ? rows : nullptr));
             } else {
                 Span sp(c, COE_K_CONV_DIRECT, flops, ln.s);
-                HIPCHK(c, coe::k::conv_direct(a.dtype, buf(l.src), wb + L.off[0], (const float*)(wb + L.off[1]), res, buf(l.dst), s, ln.s));
+                HIPCHK(c, coe::k::conv_direct(a.dtype, buf(l.src), wb + L.off[0], (const float*)(wb + L.off[1]), res, buf(l.dst), s,
+                                              x.finite_filters, ln.s));
             }
             break;
         }
@@ -1191,8 +1193,11 @@ int coe_register_expert(coe_ctx* c, int32_t id, int32_t arch_id, const void* w, 
     std::memcpy(x.host, w, nbytes);
     // filters of the layers that run on the matrix cores are kept in fragment order from here on
     {
+        x.finite_filters = true;
         std::vector<uint16_t> tmp;
         for (const LayerPlan& L : c->archs[arch_id].layers) {
+            if (c->archs[arch_id].dtype == COE_DT_F32 && L.d.op == COE_OP_CONV)
+                x.finite_filters = x.finite_filters && coe::k::all_finite((const float*)((const uint8_t*)x.host + L.off[0]), (size_t)L.K * L.d.r * L.d.s * L.C);
             if (!L.packed) continue;
             const int red = L.d.r * L.d.s * L.C;
             const size_t n = (size_t)L.K * red;
@@ -1946,6 +1951,7 @@ int coe_debug_conv(coe_ctx* c, int32_t dtype, const void* x, const void* w, cons
     hipError_t he = hipSuccess;
     auto ok = [&](hipError_t e) { if (he == hipSuccess) he = e; return he == hipSuccess; };
     std::vector<uint16_t> packed;
+    const bool finite = dtype == COE_DT_F32 && coe::k::all_finite((const float*)w, nw);
     const void* wsrc = w;
     if (mfma) {
         packed.resize(nw);
@@ -1962,7 +1968,7 @@ int coe_debug_conv(coe_ctx* c, int32_t dtype, const void* x, const void* w, cons
             Span sp(c, cls, flops, c->sc);
             if (mfma) ok(coe::k::conv_mfma(dx, dw, db, dres, dy, cs, c->sc));
             else if (smallc) ok(coe::k::conv_smallc(dx, dw, db, dy, cs, false, c->sc));
-            else ok(coe::k::conv_direct(dtype, dx, dw, db, dres, dy, cs, c->sc));
+            else ok(coe::k::conv_direct(dtype, dx, dw, db, dres, dy, cs, finite, c->sc));
         }
         ok(hipStreamSynchronize(c->sc));
         ok(hipMemcpy(y, dy, ny * eb, hipMemcpyDeviceToHost));

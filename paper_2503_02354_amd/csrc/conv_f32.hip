@@ -8,8 +8,7 @@
 //     16-byte reads of 16 neighbouring pixels on different banks.
 //   other C (images): patch rows are contiguous, a chunk is 8 of the S*C elements of a window row, zeros on both sides where
 //     it overhangs (what lies there in the patch are the next pixels, and zero times an infinite one is not zero).
-// Zero padding is multiplied like any pixel.  Where a filter is not finite, outputs of a tile that touches the padding are
-// summed one by one instead, over the window positions inside the image only.
+// Zero padding is multiplied like any pixel, so the filters have to be finite (conv_direct's caller says whether they are).
 // Bound: the fp32 matrix cores (157 TFLOP/s; a large library product reaches 153).  An instruction takes 64 cycles and the
 // operands of four take one LDS read each, so neither LDS nor L2 is near its limit; two workgroups per compute unit (LDS
 // up to 78 KB each) keep the matrix cores busy while the other one stages.
@@ -52,11 +51,6 @@ struct Geom {
     int sub, chunks;              // a window row is `sub` runs (px floats apart) of `chunks` 8-element chunks
 };
 
-__device__ __forceinline__ bool touches_padding(const ConvShape& s, const Geom& g, int ih0, int iw0)
-{
-    return ih0 < 0 || iw0 < 0 || ih0 + g.patch_rows > s.H || iw0 + g.patch_cols > s.W;
-}
-
 template <int NB, bool CHAN8>
 __global__ __launch_bounds__(kThreads, 4) void conv_f32_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                                const float* __restrict__ bias, const float* __restrict__ res,
@@ -71,9 +65,7 @@ __global__ __launch_bounds__(kThreads, 4) void conv_f32_kernel(const float* __re
     const float* const a_src = patch + prow * s.stride * g.row + pcol * s.stride * g.px + 4 * half;
     const float* const b_src = wl + lane * 4;
 
-    __shared__ int wild[kWaves];                                       // wavefronts that staged a filter value that is not finite
     int staged = -1;
-    bool finite = true, again = false;                                 // all filters of the tile; tiles left for the second pass
     const int total = g.pixel_tiles * g.ktiles;
     for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
         const int kt = tile / g.pixel_tiles, pt = tile % g.pixel_tiles;
@@ -88,9 +80,7 @@ __global__ __launch_bounds__(kThreads, 4) void conv_f32_kernel(const float* __re
             for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
 
         for (int cb = 0; cb < g.cblocks; ++cb) {
-            const bool stage = staged != kt || g.cblocks > 1;
-            if (stage) {
-                float zero = 0.f;                                      // NaN once a value is not finite
+            if (staged != kt || g.cblocks > 1) {
                 const int pieces = s.R * g.sub * g.chunks * NB * 64;
                 for (int i = tid; i < pieces; i += kThreads) {
                     const int l = i & 63, j = (i >> 6) % NB, c = (i >> 6) / NB;
@@ -106,12 +96,8 @@ __global__ __launch_bounds__(kThreads, 4) void conv_f32_kernel(const float* __re
                                 if (e + t < sc) v[t] = w[((size_t)f * s.R + r) * sc + e + t];
                         }
                     }
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) zero = fmaf(v[t], 0.f, zero);
                     *(f32x4*)(wl + (size_t)i * 4) = v;
                 }
-                const bool any = __any(zero != 0.f);
-                if (lane == 0) wild[wid] = any;
                 staged = kt;
             }
             if (CHAN8) {
@@ -135,12 +121,6 @@ __global__ __launch_bounds__(kThreads, 4) void conv_f32_kernel(const float* __re
                 }
             }
             __syncthreads();
-            if (stage) {
-                int any = 0;
-#pragma unroll
-                for (int i = 0; i < kWaves; ++i) any |= wild[i];
-                finite = (cb == 0 || finite) && __builtin_amdgcn_readfirstlane(any) == 0;
-            }
             const float* bp = b_src;
             for (int r = 0; r < s.R; ++r)
                 for (int t = 0; t < g.sub; ++t) {
@@ -166,10 +146,6 @@ __global__ __launch_bounds__(kThreads, 4) void conv_f32_kernel(const float* __re
             __syncthreads();      // the next block (or tile) overwrites patch and filters
         }
 
-        if (!finite && touches_padding(s, g, ih0, iw0)) {
-            again = true;
-            continue;
-        }
         // filters are the first operand: accumulator element v of lane l belongs to pixel l % 32 and filter
         // 8 * (v / 4) + 4 * (l / 32) + v % 4 of its 32
         const int p = tp * kTile + prow, q = tq * kTile + pcol;
@@ -204,42 +180,6 @@ __global__ __launch_bounds__(kThreads, 4) void conv_f32_kernel(const float* __re
         else if (s.act == 2) store(std::integral_constant<int, 2>{});
         else if (s.act == 3) store(std::integral_constant<int, 3>{});
         else store(std::integral_constant<int, 0>{});
-    }
-    if (!again) return;
-
-    // the tiles that were left out above (in a pass of its own, so that it costs the one above no registers)
-    for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-        const int kt = tile / g.pixel_tiles, pt = tile % g.pixel_tiles;
-        const int n = pt / (g.tiles_p * g.tiles_q), tp = (pt / g.tiles_q) % g.tiles_p, tq = pt % g.tiles_q;
-        if (!touches_padding(s, g, tp * kTile * s.stride - s.pad, tq * kTile * s.stride - s.pad)) continue;
-        const int first = kt * NB * 32, last = first + NB * 32 < s.K ? first + NB * 32 : s.K;
-        const size_t per_filter = (size_t)s.R * s.S * s.C, end = last * per_filter;
-        bool any = false;
-        for (size_t i = first * per_filter + tid; i < end; i += kThreads) any = any || (__float_as_uint(w[i]) & 0x7F800000u) == 0x7F800000u;
-        any = __any(any);
-        __syncthreads();
-        if (lane == 0) wild[wid] = any;
-        __syncthreads();
-        int some = 0;
-        for (int i = 0; i < kWaves; ++i) some |= wild[i];
-        if (some == 0) continue;
-        const int p = tp * kTile + prow, q = tq * kTile + pcol;
-        if (p >= s.P || q >= s.Q) continue;
-        const size_t at = (((size_t)n * s.P + p) * s.Q + q) * s.K;
-        for (int f = first + half; f < last; f += 2) {
-            float v = 0.f;
-            for (int r = 0; r < s.R; ++r)
-                for (int t = 0; t < s.S; ++t) {
-                    const int ih = p * s.stride - s.pad + r, iw = q * s.stride - s.pad + t;
-                    if ((unsigned)ih >= (unsigned)s.H || (unsigned)iw >= (unsigned)s.W) continue;
-                    const float* const xp = x + (((size_t)n * s.H + ih) * s.W + iw) * s.C;
-                    const float* const wp = w + (((size_t)f * s.R + r) * s.S + t) * s.C;
-                    for (int c = 0; c < s.C; ++c) v = fmaf(xp[c], wp[c], v);
-                }
-            v += bias[f];
-            if (res) v += res[at + f];
-            y[at + f] = s.act == 1 ? act_fn<1>(v) : s.act == 2 ? act_fn<2>(v) : s.act == 3 ? act_fn<3>(v) : v;
-        }
     }
 }
 

@@ -66,10 +66,12 @@ struct GroupRoutes {
     int32_t slot_off[kMaxGroups];         // offset of the group's first request in RouteArgs::slot
 };
 
-// Convolution of any shape, fp32 or bf16 storage, fp32 accumulation: conv_f32 where it supports the shape, else a plain
-// kernel with one thread per output.
+// Convolution of any shape, fp32 or bf16 storage, fp32 accumulation: conv_f32 where it supports the shape and the filters are
+// known to be finite (it multiplies them by the zero padding), else a plain kernel with one thread per output.
 hipError_t conv_direct(int dtype, const void* x, const void* w, const float* bias, const void* res, void* y,
-                       const ConvShape& s, hipStream_t stream);
+                       const ConvShape& s, bool finite_filters, hipStream_t stream);
+// host: every one of n fp32 values is finite
+bool all_finite(const float* v, size_t n);
 
 // fp32 convolution on the matrix cores: any shape whose patch and filters of one channel block fit LDS.
 bool conv_f32_supported(const ConvShape& s);

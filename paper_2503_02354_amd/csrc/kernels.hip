@@ -2,6 +2,8 @@
 // Wavefronts are 64 lanes wide throughout.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cstring>
 #include <mutex>
 
 #include "kernels.h"
@@ -752,12 +754,23 @@ hipError_t gather_rows(const void* src, const int32_t* perm, int32_t n_rows, siz
     return hipGetLastError();
 }
 
+bool all_finite(const float* v, size_t n)
+{
+    uint32_t largest = 0;                     // exponent bits
+    for (size_t i = 0; i < n; ++i) {
+        uint32_t bits;
+        std::memcpy(&bits, v + i, sizeof bits);
+        largest = std::max(largest, bits & 0x7F800000u);
+    }
+    return largest != 0x7F800000u;
+}
+
 hipError_t conv_direct(int dtype, const void* x, const void* w, const float* bias, const void* res, void* y,
-                       const ConvShape& s, hipStream_t stream)
+                       const ConvShape& s, bool finite_filters, hipStream_t stream)
 {
     size_t total = (size_t)s.N * s.P * s.Q * s.K;
     if (total == 0) return hipSuccess;
-    if (dtype == 0 && conv_f32_supported(s)) return conv_f32(x, w, bias, res, y, s, stream);
+    if (dtype == 0 && finite_filters && conv_f32_supported(s)) return conv_f32(x, w, bias, res, y, s, stream);
     size_t blocks = (total + 255) / 256;
     if (blocks > 0x7FFFFFFFull) return hipErrorInvalidValue;
     if (dtype == 1)

@@ -128,6 +128,33 @@ def test_conv_f32_keeps_non_finite_filters_off_the_padding(B, oracle, H, Wd, C, 
         assert np.all(np.abs(got[i] - want)[finite] <= bound[finite])
 
 
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_expert_with_a_non_finite_filter(B, oracle, value):
+    """The same through an expert that is registered with such a filter, beside one without."""
+    import torch
+    arch = W.tiny_cnn(4, 32)
+    blob = W.make_expert_blob(arch, 7, 0).copy()
+    sp = next(sp for sp in W.blob_layout(arch)[0] if sp.layer == 0 and sp.name == "w")
+    clean = blob.copy()
+    w = blob[sp.offset:sp.offset + sp.nbytes].view(np.float32).reshape(sp.shape)
+    w[2, 0, 0, 1] = value
+    x = np.random.default_rng(3).standard_normal((2, 32, 32, 3)).astype(np.float32)
+    dev = torch.from_numpy(x).cuda()
+    ctx = B.Context(max_requests=2, max_batch=2)
+    aid = ctx.coe_register_arch(arch)
+    ctx.coe_register_expert(0, aid, blob, 1.0)
+    ctx.coe_register_expert(1, aid, clean, 1.0)
+    shape = (2, 32, 32, sp.shape[0])
+    got = [ctx.coe_debug_layer_output(e, 2, dev.data_ptr(), 0, shape, np.float32).reshape(shape) for e in (0, 1)]
+    ctx.close()
+    act = int(arch.layers[0][9])
+    for i in range(2):
+        want = oracle.conv2d(x[i], w, W.blob_tensor(arch, blob, 0, "b"), None, 1, 1, act, 0)
+        assert np.isfinite(want[0, :, 2]).all() and np.array_equal(np.isfinite(got[0][i]), np.isfinite(want))
+        np.testing.assert_allclose(np.where(np.isfinite(want), got[0][i], 0), np.where(np.isfinite(want), want, 0), rtol=1e-5, atol=1e-5)
+        assert np.isfinite(got[1][i]).all()
+
+
 def _bf16(rng, *shape, scale=1.0):
     return W.f32_to_bf16_bits((rng.standard_normal(shape) * scale).astype(np.float32)).reshape(shape)
 
