@@ -12,8 +12,11 @@
 // Bound: the fp32 matrix cores (157 TFLOP/s; a large library product reaches 153).  An instruction takes 64 cycles and the
 // operands of four take one LDS read each, so neither LDS nor L2 is near its limit; two workgroups per compute unit (LDS
 // up to 78 KB each) keep the matrix cores busy while the other one stages.
-// Measured on 256 requests through two experts of 3->16->32->64 channels, 3x3, 64x64 images (98 GFLOP): 86.6 ms with one
-// thread per output and scalar loads, 2.40 ms here, read-out included.
+// Measured on 256 requests through two experts of 3->16->32->64 channels, 3x3, 64x64 images (98 GFLOP), the whole pass: 86.6 ms
+// with one thread per output and scalar loads, 1.37 here.
+// Small maps: a wavefront whose two tile rows lie below the map has no products to add, and a launch of at most 256 tiles of 64 filters
+// takes tiles of 32.  us, plain kernel / without these two / with them: 2x2 map, 512 -> 512, 3x3, 64 images 559 / 657 / 305,
+// 512 images 7467 / 4833 / 2218; 2x2, 64 -> 64, 3x3, 64 images 40 / 48 / 21; 28x28, 3 -> 64, 3x3, one image 7.8 / 11.4 / 9.1.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -72,6 +75,7 @@ __global__ __launch_bounds__(kThreads, 4) void conv_f32_kernel(const float* __re
         const int n = pt / (g.tiles_p * g.tiles_q), tp = (pt / g.tiles_q) % g.tiles_p, tq = pt % g.tiles_q;
         const int ih0 = tp * kTile * s.stride - s.pad, iw0 = tq * kTile * s.stride - s.pad;
         const float* const img = x + (size_t)n * s.H * s.W * s.C;
+        const bool works = tp * kTile + 2 * wid < s.P;                 // this wavefront's rows exist (on small maps most do not)
 
         f32x16 acc[NB];
 #pragma unroll
@@ -122,7 +126,8 @@ __global__ __launch_bounds__(kThreads, 4) void conv_f32_kernel(const float* __re
             }
             __syncthreads();
             const float* bp = b_src;
-            for (int r = 0; r < s.R; ++r)
+            const int rows = works ? s.R : 0;
+            for (int r = 0; r < rows; ++r)
                 for (int t = 0; t < g.sub; ++t) {
                     const float* ap = a_src + r * g.row + t * g.px;
                     for (int c = 0; c < g.chunks; ++c) {
@@ -225,6 +230,15 @@ bool geometry(const ConvShape& s, int NB, Geom& g, size_t& lds)
     return false;
 }
 
+// Tiles of 32 filters instead of 64, for launches whose tiles of 64 leave compute units idle.  The channel blocks, and with them the
+// order of the sums, stay those of 64: a request's bits do not depend on how many run beside it.
+constexpr int kTiles64 = 256;
+void halve_tiles(const ConvShape& s, Geom& g, size_t& lds)
+{
+    lds -= (size_t)s.R * g.sub * g.chunks * 256 * sizeof(float);
+    g.ktiles = (s.K + 31) / 32;
+}
+
 template <int NB, bool CHAN8>
 hipError_t launch(const float* x, const float* w, const float* bias, const float* res, float* y, const ConvShape& s, const Geom& g,
                   size_t lds, hipStream_t stream)
@@ -243,6 +257,13 @@ hipError_t launch(const float* x, const float* w, const float* bias, const float
 
 bool conv_f32_supported(const ConvShape& s)
 {
+    // An output of one pixel, most of whose window lies on the padding: the plain kernel leaves that out.  us, plain kernel / tiles:
+    // 1 x 1 map, 512 -> 512, 3x3, pad 1, one image 74 / 137, 512 images 276 / 2312.  With a whole window the tiles are ahead or
+    // close: 3 x 3 map without padding, 512 -> 512, 683 / 135 and 2300 / 2217; 1x1, 256 -> 256, 39 / 20 and 75 / 107.
+    if (s.P * s.Q == 1) {
+        const int rows = (s.R < s.H + s.pad ? s.R : s.H + s.pad) - s.pad, cols = (s.S < s.W + s.pad ? s.S : s.W + s.pad) - s.pad;
+        if (2 * rows * cols <= s.R * s.S) return false;
+    }
     Geom g;
     size_t lds;
     return geometry(s, s.K > 32 ? 2 : 1, g, lds);
@@ -253,9 +274,13 @@ hipError_t conv_f32(const void* x, const void* w, const float* bias, const void*
 {
     Geom g;
     size_t lds = 0;
-    const int nb = s.K > 32 ? 2 : 1;
+    int nb = s.K > 32 ? 2 : 1;
     if (!geometry(s, nb, g, lds)) return hipErrorInvalidValue;
     if (g.pixel_tiles == 0) return hipSuccess;
+    if (nb == 2 && (long long)g.pixel_tiles * g.ktiles <= kTiles64) {
+        halve_tiles(s, g, lds);
+        nb = 1;
+    }
     const float *xf = (const float*)x, *wf = (const float*)w, *rf = (const float*)res;
     const bool c8 = s.C % 8 == 0;
     if (nb == 2) return c8 ? launch<2, true>(xf, wf, bias, rf, (float*)y, s, g, lds, stream) : launch<2, false>(xf, wf, bias, rf, (float*)y, s, g, lds, stream);

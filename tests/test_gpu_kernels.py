@@ -128,6 +128,47 @@ def test_conv_f32_keeps_non_finite_filters_off_the_padding(B, oracle, H, Wd, C, 
         assert np.all(np.abs(got[i] - want)[finite] <= bound[finite])
 
 
+@pytest.mark.parametrize("H,Wd,C,K,R,stride,pad,n", [
+    (20, 14, 64, 64, 3, 1, 1, 300),       # channel blocks that 32-filter tiles alone would make larger
+    (7, 7, 32, 128, 3, 1, 1, 300), (2, 2, 16, 72, 3, 1, 1, 600), (30, 17, 3, 64, 7, 2, 3, 150), (3, 3, 64, 100, 1, 1, 0, 260),
+    (17, 1, 24, 64, 3, 1, 1, 300),
+])
+def test_conv_f32_bits_do_not_depend_on_the_batch(B, H, Wd, C, K, R, stride, pad, n):
+    """Few images run on tiles of 32 filters, many on tiles of 64, and rows of a tile below a small map are left out: the same
+    image gives the same bits alone and among many."""
+    rng = np.random.default_rng(H + C + K)
+    x = rng.standard_normal((3, H, Wd, C)).astype(np.float32)
+    w = rng.standard_normal((K, R, R, C)).astype(np.float32)
+    bias = rng.standard_normal(K).astype(np.float32)
+    ctx = B.Context(max_requests=1)
+    one, _ = ctx.coe_debug_conv(0, x[:1], w, bias, None, stride, pad, 1)
+    many, _ = ctx.coe_debug_conv(0, x[np.arange(n) % 3], w, bias, None, stride, pad, 1)
+    ctx.close()
+    assert np.array_equal(many[0], one[0]) and np.array_equal(many, many[np.arange(n) % 3])
+
+
+@pytest.mark.parametrize("H,C,K,R,pad,n", [(1, 64, 40, 3, 1, 70), (1, 100, 16, 5, 2, 3), (2, 8, 24, 4, 1, 5)])
+def test_conv_f32_of_one_pixel_on_padding(B, H, C, K, R, pad, n):
+    """An output of one pixel whose window lies on the padding for the most part goes to the plain kernel: one chain of
+    multiply-adds over the window positions inside the image (1 x 1 map, 3 x 3 window, 512 -> 512, 512 images: 276 us, 4813 in tiles)."""
+    rng = np.random.default_rng(C + K)
+    x = rng.standard_normal((n, H, H, C)).astype(np.float32)
+    w = rng.standard_normal((K, R, R, C)).astype(np.float32)
+    bias = rng.standard_normal(K).astype(np.float32)
+    ctx = B.Context(max_requests=1)
+    got, _ = ctx.coe_debug_conv(0, x, w, bias, None, 1, pad, 0)
+    ctx.close()
+    acc = np.zeros((n, K), np.float32)
+    for r in range(R):
+        for t in range(R):
+            if 0 <= r - pad < H and 0 <= t - pad < H:
+                for c in range(C):       # the product of two fp32 numbers is exact in 64 bits
+                    acc = (acc.astype(np.float64) + x[:, r - pad, t - pad, c, None].astype(np.float64) * w[:, r, t, c]).astype(np.float32)
+    assert got.shape == (n, 1, 1, K)
+    # 64-bit sums rounded to fp32 twice: a tie in 2^29 of them may fall differently
+    assert np.mean(got[:, 0, 0] == acc + bias) > 0.999
+
+
 @pytest.mark.parametrize("value", [np.inf, np.nan])
 def test_expert_with_a_non_finite_filter(B, oracle, value):
     """The same through an expert that is registered with such a filter, beside one without."""
