@@ -180,7 +180,8 @@ struct coe_ctx {
     int32_t* h_cnt = nullptr;        // pinned
     int32_t* h_first = nullptr;      // pinned, one entry per request slot: staging of the first experts of a submit
     uint8_t* h_stage = nullptr;      // pinned ring that inputs in pageable host memory go through (copy_pageable), made at need
-    hipEvent_t ev_stage[8] = {};
+    hipEvent_t ev_stage[8] = {};     // recorded after the copy out of each chunk ...
+    bool stage_busy[8] = {};         // ... which may still be on its way
     int32_t last_pending = 0, last_live = 0, last_E = 0;
     std::vector<int32_t> submit_step;   // per request slot: number of the first step that sees the request
     int32_t step_no = 0;
@@ -1338,6 +1339,12 @@ static int copy_pageable(coe_ctx* c, uint8_t* dst, const uint8_t* src, size_t by
             return COE_DONE;
         }
     }
+    // the last chunks of the submit before may still be on their way: a slot belongs to its copy until that has ended
+    for (size_t i = 0; i < kStageSlots; ++i) {
+        if (!c->stage_busy[i]) continue;
+        HIPCHK(c, hipEventSynchronize(c->ev_stage[i]));
+        c->stage_busy[i] = false;
+    }
     const size_t chunks = (bytes + kStageChunk - 1) / kStageChunk;
     std::unique_ptr<std::atomic<bool>[]> filled(new (std::nothrow) std::atomic<bool>[chunks]);
     if (!filled) return COE_DONE;
@@ -1369,10 +1376,12 @@ static int copy_pageable(coe_ctx* c, uint8_t* dst, const uint8_t* src, size_t by
         if (filled[issued].load(std::memory_order_acquire)) {
             err = hipMemcpyAsync(dst + issued * kStageChunk, ring + issued % kStageSlots * kStageChunk, length(issued), hipMemcpyHostToDevice, c->sc);
             if (err == hipSuccess) err = hipEventRecord(c->ev_stage[issued % kStageSlots], c->sc);
+            c->stage_busy[issued % kStageSlots] = err == hipSuccess;
             ++issued;
         } else if (done < issued) {
             const hipError_t q = hipEventQuery(c->ev_stage[done % kStageSlots]);
             if (q == hipSuccess) {
+                c->stage_busy[done % kStageSlots] = false;
                 ++done;
                 free_until.store(done + kStageSlots, std::memory_order_release);
             } else if (q == hipErrorNotReady) {
@@ -1388,7 +1397,8 @@ static int copy_pageable(coe_ctx* c, uint8_t* dst, const uint8_t* src, size_t by
     stop.store(true);
     for (unsigned i = 0; i < started; ++i) threads[i].join();
     if (err != hipSuccess) {
-        (void)hipStreamSynchronize(c->sc);       // the ring stays with the copies that were issued
+        (void)hipStreamSynchronize(c->sc);       // the ring stays with the copies that were issued, of which one has no event
+        std::fill(c->stage_busy, c->stage_busy + kStageSlots, false);
         return fail(c, COE_EDEVICE, hipGetErrorString(err));
     }
     return COE_OK;
@@ -1421,7 +1431,8 @@ int coe_submit(coe_ctx* c, int32_t n, const void* inputs, int on_device, const i
     HIPCHK(c, hipMemsetAsync(c->d_depth + base, 0, (size_t)n * 4, c->sc));
     HIPCHK(c, hipMemsetAsync(c->d_path + base * c->cfg.max_stages, 0xFF, (size_t)n * 4 * c->cfg.max_stages, c->sc));
     HIPCHK(c, hipMemsetAsync(c->d_logits + base * c->max_classes, 0, (size_t)n * 4 * c->max_classes, c->sc));
-    // host inputs are the caller's (possibly pageable) memory and may be freed on return: wait for that copy only
+    // host inputs are the caller's (possibly pageable) memory and may be freed on return: wait for that copy only (the pinned ring
+    // of copy_pageable keeps track of its chunks by itself)
     if (!on_device) HIPCHK(c, hipStreamSynchronize(c->sc));
     std::fill(c->collected.begin() + base, c->collected.begin() + base + n, 0);
     std::fill(c->submit_step.begin() + base, c->submit_step.begin() + base + n, c->step_no);

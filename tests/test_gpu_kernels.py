@@ -446,6 +446,38 @@ def test_pageable_inputs_arrive_whole(B, n):
     assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2][::-1]) and np.array_equal(out[0], out[3])
 
 
+@pytest.mark.parametrize("parts", [(342, 342), (700, 342, 500), (345, 1, 345)])
+def test_submits_in_a_row_through_the_pinned_ring(B, parts):
+    """Submits that follow each other without a step between them share the ring's chunks: every image arrives as it was, also
+    when the caller's memory is written over as soon as a submit returns."""
+    import torch
+    arch = W.tiny_cnn(4, 64)
+    n = sum(parts)
+    x = np.random.default_rng(n).standard_normal((n, 64, 64, 3)).astype(np.float32)
+    dev = torch.from_numpy(x).cuda()
+    out = []
+    for host in (False, True):
+        ctx = B.Context(max_requests=n, max_stages=1, max_batch=256)
+        aid = ctx.coe_register_arch(arch)
+        ctx.coe_register_expert(0, aid, W.make_expert_blob(arch, 7, 0), 1.0)
+        g = W.graph_from_lists([[]])
+        ctx.coe_set_dependency_graph(g.succ_off, g.succ)
+        at = 0
+        for m in parts:
+            if host:
+                mine = x[at:at + m].copy()
+                ctx.coe_submit(m, mine, False)
+                mine[:] = np.nan
+            else:
+                ctx.coe_submit(m, dev[at].data_ptr(), True)
+            at += m
+        while ctx.coe_step()[0] != B.COE_DONE:
+            pass
+        out.append(ctx.coe_collect(n)[1])
+        ctx.close()
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("n,experts,cap", [(30, 6, 0), (300, 9, 0), (60, 8, 5)])
 def test_grouped_transformers_give_the_same_bits(B, n, experts, cap):
     """Small groups of several transformer-shaped experts share launches: same logits, routes and switches, bit for bit, as one
