@@ -431,6 +431,8 @@ int plan_arch(coe_ctx* c, const coe_arch_desc* d, ArchPlan& a)
         const coe_layer& l = L.d;
         coe::k::ConvShape cs{1, L.H, L.W, L.C, L.K, l.r, l.s, l.stride, l.pad, L.P, L.Q, l.act};
         const bool reads_input = l.src == 0 || l.res == 0;
+        for (const size_t at : L.off)
+            if (at > 0x7FFFFFFFull) a.groupable = false;       // a group table holds 31-bit offsets into the weights
         // only the per-group stem and the per-group patches may
         if (reads_input && !(l.op == COE_OP_CONV && (!L.packed || L.patchify) && l.res != 0)) a.groupable = false;
         if (l.op == COE_OP_CONV) {

@@ -510,3 +510,53 @@ def test_grouped_transformers_give_the_same_bits(B, n, experts, cap):
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and a[2:4] == b[2:4]
         assert a[4] == 0
     assert out[0][1][4] >= 2
+
+
+def test_experts_beyond_two_gib_run_group_by_group(B):
+    """Transformer-shaped experts whose last tensors lie more than 2 GiB into their weights, out of reach of a group table's
+    offsets: their small groups run one by one, with the result of a context that groups nothing."""
+    import torch
+    T, D, n_cls, n = 2, 1024, 4, 6
+    p = W._Prog(16, 16, 3, n_scratch=5)
+    p.conv(0, 1, D, 16, 16, 0, W.ACT_NONE)
+    p.raw([W.OP_TOKENS, 1, 2, -1, D, 0, 0, 0, 0, 0, 0, 0]); p.shape[2] = (T, 1, D)
+    p.conv(2, 3, 32768, 1, 1, 0, W.ACT_RELU)
+    p.conv(3, 4, 32704, 1, 1, 0, W.ACT_RELU)
+    p.conv(4, 1, D, 1, 1, 0, W.ACT_NONE)
+    p.raw([W.OP_HEAD_CLS, 1, -1, -1, n_cls, 0, 0, 0, 0, 0, 0, 0])
+    big = W.Arch("wide", W.DT_BF16, 16, 16, 3, n_cls, np.array(p.layers, dtype=np.int32), p.gains)
+    specs, nbytes = W.blob_layout(big)
+    assert specs[-1].offset > 2 ** 31
+    rng = np.random.default_rng(0)
+    blob = np.zeros(nbytes, np.uint8)
+    for sp in specs:                             # every tensor from a few hundred thousand values: its contents do not matter
+        bits = W.f32_to_bf16_bits((rng.standard_normal(300007) * 0.02).astype(np.float32)) if sp.is_param_dtype else \
+            rng.standard_normal(4099).astype(np.float32)
+        raw = bits.view(np.uint8)
+        blob[sp.offset:sp.offset + sp.nbytes] = np.resize(raw, sp.nbytes)
+    root = W.vit(n_cls, 16, 16, 64, 1, 1, 64)
+    x = W.make_inputs(root, 5, range(n))
+    dev = torch.from_numpy(x.view(np.int16)).cuda()
+    g = W.graph_from_lists([[1, 2], [], []])
+    out = []
+    for small in (-1, 0):
+        ctx = B.Context(max_requests=n, max_stages=2, max_batch=64, group_small=small)
+        ids = [ctx.coe_register_arch(root), ctx.coe_register_arch(big)]
+        ctx.coe_register_expert(0, ids[0], W.make_expert_blob(root, 7, 0), 1.0)
+        for e in (1, 2):
+            ctx.coe_register_expert(e, ids[1], blob, 0.5)
+        ctx.coe_set_dependency_graph(g.succ_off, g.succ)
+        for _ in range(2):
+            first = np.array([0, 0, 1, 1, 2, 2], np.int32)             # both wide experts have a group in either step
+            ctx.coe_submit(n, dev.data_ptr(), True, first)
+            grouped = 0
+            while True:
+                rc, st = ctx.coe_step()
+                if rc == B.COE_DONE:
+                    break
+                grouped += st.n_grouped
+            _, logits, path = ctx.coe_collect(n)
+        ctx.close()
+        assert grouped == 0
+        out.append((logits, path))
+    assert np.isfinite(out[0][0]).all() and np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
