@@ -67,8 +67,8 @@ __global__ __launch_bounds__(kPlaceThreads) void regroup_count_kernel(const int3
     extern __shared__ int32_t hist[];
     for (int e = threadIdx.x; e < E; e += kPlaceThreads) hist[e] = 0;
     __syncthreads();
-    const int lo = blockIdx.x * range, hi = min(n, lo + range);
-    for (int i = lo + threadIdx.x; i < hi; i += kPlaceThreads) {
+    const uint32_t lo = blockIdx.x * range, hi = min((uint32_t)n, lo + range);     // unsigned: ranges end up to 2^24 beyond n
+    for (uint32_t i = lo + threadIdx.x; i < hi; i += kPlaceThreads) {
         const int key = cur[i];
         if (key >= 0 && key < E) atomicAdd(&hist[key], 1);
     }
@@ -108,9 +108,9 @@ __global__ __launch_bounds__(kPlaceThreads) void regroup_place_kernel(const int3
     __syncthreads();
 
     const int per_wave = range / kPlaceWaves;          // a multiple of the wavefront size
-    const int lo = block * range + wid * per_wave, hi = min(n, lo + per_wave);
+    const uint32_t lo = (uint32_t)block * range + wid * per_wave, hi = min((uint32_t)n, lo + per_wave);
     int32_t* const mine = wcount + wid * E;
-    for (int i = lo + lane; i < hi; i += kWave) {
+    for (uint32_t i = lo + lane; i < hi; i += kWave) {
         const int key = cur[i];
         if (key >= 0 && key < E) atomicAdd(&mine[key], 1);
     }
@@ -182,8 +182,8 @@ __global__ __launch_bounds__(kPlaceThreads) void regroup_place_kernel(const int3
     // a wavefront places 64 keys a trip: the lanes with the same key find each other by one ballot per key bit, the lowest
     // of them moves the wavefront's position for that key on
     const unsigned long long lt_mask = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-    for (int base = lo; base < hi; base += kWave) {
-        const int i = base + lane;
+    for (uint32_t base = lo; base < hi; base += kWave) {
+        const uint32_t i = base + lane;
         int key = i < hi ? cur[i] : -1;
         const bool live = key >= 0 && key < E;
         unsigned long long peers = __ballot(live);
@@ -676,7 +676,7 @@ hipError_t regroup_index(const int32_t* cur, int32_t n, int32_t E, int32_t* cnt,
     if (n < 0 || E <= 0 || E > kRegroupMaxExperts) return hipErrorInvalidValue;
     const int32_t share = (int32_t)(((long long)n + kPlaceMaxBlocks - 1) / kPlaceMaxBlocks);
     const int32_t range = share <= kPlaceRange ? kPlaceRange : (share + kPlaceThreads - 1) / kPlaceThreads * kPlaceThreads;
-    const int32_t nblocks = n <= range ? 1 : (n + range - 1) / range;
+    const int32_t nblocks = n <= range ? 1 : (int32_t)(((long long)n + range - 1) / range);
     int32_t key_bits = 0;
     while ((1 << key_bits) < E) ++key_bits;
     if (nblocks > 1)
