@@ -1603,7 +1603,8 @@ static int step_body(coe_ctx* c, coe_step_stats& st)
                 if (launched[f] || !small(f) || c->experts[f].arch != x.arch) continue;
                 if (!c->experts[f].buf) continue;              // its switch has not been issued yet
                 // transformer-shaped weights take longer to arrive than a small group to run (170 MB, 3 ms): nothing waits
-                // for another group's copy
+                // for another group's copy.  What counts is whether an expert has run since its weights were loaded: then no
+                // copy can be on its way, and which groups share a launch does not depend on how fast the link is
                 if (a.token_ops && (x.load_pending || c->experts[f].load_pending)) continue;
                 if (rows + c->h_cnt[f] > chunk_rows(c, c->archs[x.arch])) continue;
                 set.push_back({f, off[f], c->h_cnt[f]});
