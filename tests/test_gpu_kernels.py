@@ -200,6 +200,7 @@ def _bf16(rng, *shape, scale=1.0):
     return W.f32_to_bf16_bits((rng.standard_normal(shape) * scale).astype(np.float32)).reshape(shape)
 
 
+@pytest.mark.parametrize("use_res", [True, False])
 @pytest.mark.parametrize("H,Wd,C,K,R,stride,pad,act,few,some,many", [
     (7, 7, 64, 128, 3, 1, 1, 1, 1, 200, 1200),        # slab order: 32 x 32 tiles, 64 x 64 tiles, 256-row tiles
     (9, 11, 32, 64, 3, 1, 1, 0, 3, 300, 1200),        # one channel block (the loop over block pairs ends in its middle)
@@ -217,7 +218,7 @@ def _bf16(rng, *shape, scale=1.0):
     (50, 1, 512, 768, 1, 1, 0, 2, 2, 190, 514),       # 192 x 256 tiles in two turns, three filter tiles; 128 x 256 ones
     (9, 9, 64, 256, 3, 1, 0, 0, 1, 220, 480),         # 3x3 without padding, the same two heights
 ])
-def test_few_tiles_give_the_bits_of_many(B, oracle, H, Wd, C, K, R, stride, pad, act, few, some, many):
+def test_few_tiles_give_the_bits_of_many(B, oracle, H, Wd, C, K, R, stride, pad, act, few, some, many, use_res):
     """Launches with few output tiles run on smaller tiles.  A request's result must not depend on how many requests run
     beside it: the same images alone, among some and among many give the same bits, and those of a few are the oracle's."""
     rng = np.random.default_rng(H * 100 + C + R)
@@ -225,24 +226,63 @@ def test_few_tiles_give_the_bits_of_many(B, oracle, H, Wd, C, K, R, stride, pad,
     w = _bf16(rng, K, R, R, C, scale=np.sqrt(2.0 / (R * R * C)))
     bias = (0.1 * rng.standard_normal(K)).astype(np.float32)
     P = (H + 2 * pad - R) // stride + 1; Q = (Wd + 2 * pad - R) // stride + 1
-    res = _bf16(rng, few + 1, P, Q, K)
+    res = _bf16(rng, few + 1, P, Q, K) if use_res else None
     ctx = B.Context(max_requests=1)
     outs = {}
     for n in (few, some, many):
         if n:
             idx = np.arange(n) % (few + 1)
-            outs[n], _ = ctx.coe_debug_conv(1, x[idx], w, bias, res[idx], stride, pad, act)
+            outs[n], _ = ctx.coe_debug_conv(1, x[idx], w, bias, res[idx] if use_res else None, stride, pad, act)
     ctx.close()
     for n, y in outs.items():
         for r in range(1 if n > few else 0, n // (few + 1)):
             assert np.array_equal(y[r * (few + 1):(r + 1) * (few + 1)], y[:few + 1]), (n, r)
         assert np.array_equal(y[:few], outs[few]), n
-    xf, wf, rf = (W.bf16_bits_to_f32(a).reshape(a.shape) for a in (x, w, res))
+    xf, wf = (W.bf16_bits_to_f32(a).reshape(a.shape) for a in (x, w))
+    rf = W.bf16_bits_to_f32(res).reshape(res.shape) if use_res else [None] * few
     want = np.stack([oracle.conv2d(xf[i], wf, bias, rf[i], stride, pad, act, 1) for i in range(few)])
     got = W.bf16_bits_to_f32(outs[few]).reshape(want.shape)
     # one bf16 ulp where fp32 and fp64 sums round to different sides; 1e-5 absolute where the terms cancel (the fp32 error
     # of a sum of up to 1600 terms of size ~0.05)
     assert np.all(np.abs(got - want) <= np.maximum(np.abs(want) * 2.0 ** -7, 1e-5))
+
+
+def _tiles(n, P, Q, K, side):
+    return -(-n * P * Q // side) * (K // side)
+
+
+@pytest.mark.parametrize("n,H,Wd,C,K,R,stride,pad,use_res,act", [
+    (70, 28, 28, 64, 64, 3, 1, 1, True, 3),       # conv3x3_slab_kernel: 256 x 64 tiles, residual, SiLU
+    (71, 28, 27, 64, 64, 3, 1, 1, False, 1),      # ragged rows
+    (110, 14, 15, 128, 256, 3, 1, 1, False, 1),   # 256 x 128 tiles, two filter tiles
+    (300, 7, 7, 64, 512, 3, 1, 1, True, 0),       # an image is less than a tile
+    (90, 29, 29, 64, 128, 3, 2, 1, False, 1),     # conv_igemm_dma_kernel: stride 2 at an odd size, 128 x 128 tiles
+    (41, 29, 31, 64, 64, 1, 1, 0, True, 1),       # 128 x 64 tiles, ragged
+    (160, 14, 14, 128, 512, 1, 2, 0, False, 2),   # strided rows, GELU
+])
+def test_kernels_of_many_tiles_elementwise(B, oracle, n, H, Wd, C, K, R, stride, pad, use_res, act):
+    """The slab and implicit-GEMM kernels, which launches of few tiles no longer reach: more tiles than conv_ring takes, every output
+    of some images against the oracle (the first, the last and those that straddle tiles)."""
+    rng = np.random.default_rng(n * 10 + K)
+    P = (H + 2 * pad - R) // stride + 1; Q = (Wd + 2 * pad - R) // stride + 1
+    slab = R == 3 and stride == 1
+    assert _tiles(n, P, Q, K, 32) > 512 and _tiles(n, P, Q, K, 64) > (768 if slab else 512)        # kRingTiles32, kRingTiles64(Slab)
+    x = _bf16(rng, n, H, Wd, C)
+    w = _bf16(rng, K, R, R, C, scale=np.sqrt(2.0 / (R * R * C)))
+    bias = (0.1 * rng.standard_normal(K)).astype(np.float32)
+    res = _bf16(rng, n, P, Q, K) if use_res else None
+    ctx = B.Context(max_requests=1)
+    got, cls = ctx.coe_debug_conv(1, x, w, bias, res, stride, pad, act)
+    ctx.close()
+    assert B.KERNEL_CLASS_NAMES[cls] == ("conv_slab" if slab else "conv_mfma")
+    wf = W.bf16_bits_to_f32(w).reshape(w.shape)
+    for i in sorted({0, 1, n // 2, n - 2, n - 1} | set(rng.integers(0, n, 4).tolist())):
+        r = None if res is None else W.bf16_bits_to_f32(res[i]).reshape(res[i].shape)
+        want = oracle.conv2d(W.bf16_bits_to_f32(x[i]).reshape(x[i].shape), wf, bias, r, stride, pad, act, 1)
+        g = W.bf16_bits_to_f32(got[i]).reshape(want.shape)
+        # as in test_few_tiles_give_the_bits_of_many
+        assert np.all(np.abs(g - want) <= np.maximum(np.abs(want) * 2.0 ** -7, 1e-5)), i
+        assert np.mean(g == want) > 0.995
 
 
 @pytest.mark.parametrize("C,pixels", [(64, 200), (64, 6000), (64, 40000), (96, 3000), (512, 33000)])
@@ -510,6 +550,41 @@ def test_grouped_transformers_give_the_same_bits(B, n, experts, cap):
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]) and a[2:4] == b[2:4]
         assert a[4] == 0
     assert out[0][1][4] >= 2
+
+
+@pytest.mark.parametrize("kind,n,experts", [("vit", 1500, 8), ("resnet", 1400, 6), ("vit", 400, 20)])
+def test_large_groups_share_launches_with_the_same_bits(B, kind, n, experts):
+    """Groups of 60 to 300 requests in shared launches of more tiles than conv_ring takes: persistent tiles of token GEMMs whose
+    workgroups go on from one group's rows to the next, slab tiles and strided tiles that start anew in every group."""
+    import torch
+    from oracle import guard as G
+    if kind == "vit":
+        wl = W.config5(n, hw=64, n_experts=experts, cap=0, dim=512, depth=1, heads=8, mlp=1024, calibrated=False)
+        sizes = [(n * 17, k) for k in (512, 1024, 1536)]
+    else:
+        wl = W.config2(n, hw=128, n_experts=experts, width=64, calibrated=False)
+        sizes = [(n * 32 * 32, 64), (n * 16 * 16, 128), (n * 8 * 8, 256)]
+    assert all(rows * k // 4096 > 768 for rows, k in sizes)
+    G.calibrate_workload(wl, n_cal=48)
+    blobs = [wl.blob(e) for e in range(experts)]
+    dev = torch.from_numpy(wl.inputs(range(n)).view(np.int16)).cuda()
+    out = []
+    for small in (-1, 1024):
+        ctx = B.Context(max_requests=n, max_stages=2, max_batch=4096, group_small=small)
+        B.setup_workload(ctx, wl, blobs)
+        for _ in range(2):
+            ctx.coe_submit(n, dev.data_ptr(), True)
+            grouped = 0
+            while True:
+                rc, st = ctx.coe_step()
+                if rc == B.COE_DONE:
+                    break
+                grouped += st.n_grouped
+            _, logits, path = ctx.coe_collect(n)
+        ctx.close()
+        assert (grouped >= experts // 2) == (small > 0)
+        out.append((logits, path))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
 
 def test_experts_beyond_two_gib_run_group_by_group(B):

@@ -448,16 +448,16 @@ def test_error_codes_and_empty_inputs(B):
 # convolution kernels element by element (appended: the full output tensor, not only pooled logits)
 # ---------------------------------------------------------------------------------------------------------------
 @pytest.mark.parametrize("n,H,Wd,C,K,R,stride,pad,use_res,act", [
-    (3, 14, 14, 64, 128, 3, 1, 1, True, 1),       # MFMA, 128-wide tiles, residual
-    (2, 20, 17, 64, 64, 3, 1, 1, False, 1),       # MFMA, 64-wide tiles, ragged rows
+    (3, 14, 14, 64, 128, 3, 1, 1, True, 1),       # MFMA, few tiles in slab order, residual
+    (2, 20, 17, 64, 64, 3, 1, 1, False, 1),       # the same, ragged rows
     (5, 9, 9, 32, 96, 3, 2, 1, True, 0),          # MFMA, 32-channel steps, stride 2, no activation
     (40, 8, 8, 128, 256, 1, 1, 0, False, 2),      # MFMA 1x1 with GELU, 2560 rows
     (2, 33, 30, 3, 64, 7, 2, 3, False, 1),        # stem kernel
     (2, 12, 12, 16, 24, 3, 1, 1, True, 1),        # plain kernel (bf16)
     (21, 57, 57, 64, 256, 1, 1, 0, True, 1),      # large 1x1: 68229 rows (ragged), two filter tiles per row tile, residual
     (11, 57, 57, 32, 512, 1, 1, 0, False, 2),     # one 32-channel step, four filter tiles per row tile, GELU
-    (6, 57, 57, 64, 256, 3, 2, 1, False, 1),      # 3x3 stride 2 at an odd size
-    (3, 28, 28, 64, 64, 3, 1, 1, True, 3),        # SiLU: slab kernel with residual (detector-shaped experts)
+    (6, 57, 57, 64, 256, 3, 2, 1, False, 1),      # 3x3 stride 2 at an odd size, few tiles
+    (3, 28, 28, 64, 64, 3, 1, 1, True, 3),        # SiLU: few tiles in slab order, residual (detector-shaped experts)
     (4, 14, 14, 256, 128, 1, 1, 0, False, 3),     # SiLU: 1x1
     (3, 20, 20, 32, 32, 3, 1, 1, True, 3),        # SiLU: 32 filters (register-staged kernel)
     (2, 40, 40, 3, 32, 6, 2, 2, False, 3),        # SiLU: 6x6 stride-2 stem, 32 filters
