@@ -204,7 +204,10 @@ def run_workload(name, wl, blobs, x, opt, steps, warmup, latency, cache_cap=None
     visits = np.bincount(path[path >= 0].ravel(), minlength=wl.graph.n_experts)
     flops_per_step = 2.0 * float(np.dot(visits, macs_of))
     # the matrix-core convolution classes; the roofline object is for the one that takes the most time
-    mfma_kernels = {"conv_slab": "conv3x3_slab_kernel", "conv_mfma": "conv_igemm_dma_kernel", "attention": "attention_kernel"}
+    # (a class is timed as a whole; conv_mfma's large launches run on the persistent or the implicit-GEMM kernel, as their tiles fill
+    # the chip, its small ones on the ring kernel)
+    mfma_kernels = {"conv_slab": "conv3x3_slab_kernel", "attention": "attention_kernel",
+                    "conv_mfma": "conv_gemm_persistent_kernel / conv_igemm_dma_kernel / conv_igemm_ring_kernel"}
     est_ms = {k: prof[k]["ms"] / prof[k]["launches"] * prof[k]["issued"] for k in mfma_kernels if k in prof}
     roofline = None
     if est_ms:

@@ -2,13 +2,18 @@
 //
 // GEMM view: out[m][k] = sum_{r,s,c} x[n][p*stride-pad+r][q*stride-pad+s][c] * w[k][r][s][c], m = (n,p,q) flattened.
 // NHWC activations make the reduction index contiguous in c, so a reduction step is one (r,s) position and a run
-// of 32 channels.  A workgroup of four wavefronts owns a BM x BN output tile.  Three kernels, picked by conv_mfma():
-//   1. conv3x3_slab_kernel   3x3, stride 1, pad 1, filter count a multiple of 64: the activation rows a tile needs are
-//                            DMA'd into LDS once per 32-channel block and serve all nine window positions;
-//   2. conv_igemm_dma_kernel any other shape with a filter count that is a multiple of 64: both operands DMA'd
-//                            global -> LDS per reduction step;
-//   3. conv_igemm_bf16_kernel (below) the rest: operands staged through registers.
-// Common to all three:
+// of 32 channels.  A workgroup owns a BM x BN output tile.  Five kernels, picked by conv_mfma():
+//   1. conv_igemm_ring_kernel  launches of few output tiles (conv_ring says how few): 32 x 32 tiles of one wavefront or 64 x 64
+//                              tiles of four, loads many reduction steps ahead; same bits as the kernel below that the shape
+//                              otherwise takes;
+//   2. conv3x3_slab_kernel     3x3, stride 1, pad 1, filter count a multiple of 64: the activation rows a tile needs are
+//                              DMA'd into LDS once per 32-channel block and serve all nine window positions;
+//   3. conv_gemm_persistent_kernel  other shapes with a filter count that is a multiple of 256 and a long reduction, in launches whose
+//                              tiles fill the chip well (persistent_height): tiles of up to 256 x 256 by workgroups that stay;
+//   4. conv_igemm_dma_kernel   any other shape with a filter count that is a multiple of 64: both operands DMA'd
+//                              global -> LDS per reduction step;
+//   5. conv_igemm_bf16_kernel  (below) the rest: operands staged through registers.
+// Common to all five:
 //   * Filters are repacked once, when an expert is registered, into matrix-core fragment order (pack_filters_mfma),
 //     so a filter slab is contiguous in memory and in LDS and an operand read is one linear 1 KiB access.
 //   * v_mfma_f32_32x32x16_bf16 is issued with the filter fragment as the first operand, so a lane ends up holding 4
