@@ -27,9 +27,9 @@ PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 # scaled by what the same counters read for the gather kernel's plain copy (profiles/conv3x3_slab_config2_hbm_counters.md).
 # Tied to the kernel source and the launch configuration it was measured on: an edit of that file, another workload,
 # batch cap or grouping threshold make bench.py report null again.
-SLAB_TRAFFIC_BYTES_PER_LAUNCH = 2332.7e6
+SLAB_TRAFFIC_BYTES_PER_LAUNCH = 2331.1e6
 SLAB_TRAFFIC_SOURCE = ("paper_2503_02354_amd/csrc/conv_mfma.hip",
-                       "7752fcdddb0d2eb49fa2ced5bfc67a721b140ad46ce3e1f2c6ebbd121817c217")
+                       "709adda0b0118c12606829e8e5d1b3c08585e1b8c50dac40e8bbf4a82037f420")
 SLAB_TRAFFIC_LAUNCH_CONFIG = ("config2", 0, 4096, 512, 1, "")   # workload, requests, max_batch, group_small, arrivals per step, window
 
 
