@@ -14,6 +14,7 @@
 // up to 78 KB each) keep the matrix cores busy while the other one stages.
 // Measured on 256 requests through two experts of 3->16->32->64 channels, 3x3, 64x64 images (98 GFLOP), the whole pass: 86.6 ms
 // with one thread per output and scalar loads, 1.37 here.
+// Error against 64 bits, 2-norm, plain kernel / here: 3 -> 16 9.54e-8 / 9.56e-8, 32 -> 64 3.02e-7 / 3.02e-7, 256 -> 512 8.32e-7 / 8.30e-7.
 // Small maps: a wavefront whose two tile rows lie below the map has no products to add, and a launch of at most 256 tiles of 64 filters
 // takes tiles of 32.  us, plain kernel / without these two / with them: 2x2 map, 512 -> 512, 3x3, 64 images 559 / 657 / 305,
 // 512 images 7467 / 4833 / 2218; 2x2, 64 -> 64, 3x3, 64 images 40 / 48 / 21; 28x28, 3 -> 64, 3x3, one image 7.8 / 11.4 / 9.1.

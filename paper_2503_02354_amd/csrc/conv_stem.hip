@@ -334,8 +334,9 @@ __global__ __launch_bounds__(kThreads, 4) void conv_smallc_bf16_kernel(const uin
 // (fp32), the horizontal one compares non-negative bf16 as integers.
 // Bound by the matrix cores and the vector instructions between them: 44 of 32 cycles per strip and pooled row beside about
 // 220 of 4 cycles, which the second wavefront of the SIMD overlaps in part.  Groups with filters of their own share a launch.
-// Measured, 224 x 224: 4096 images 2.60 ms with 16 x 16 tiles in LDS (conv_smallc_bf16_kernel), 1.39 here (0.7 for the matrix
-// instructions alone at their full rate, 0.55 for the bytes); 29 images in 15 groups 15 launches of 17 us, now one of 21.
+// Measured, 224 x 224: 4096 images 2.60 ms with 16 x 16 tiles in LDS (conv_smallc_bf16_kernel), 1.42 here (0.7 for the matrix
+// instructions alone at their full rate, 0.6 for the bytes; 1.39 with windows read from an even element on, without the fifth dword);
+// 29 images in 15 groups 15 launches of 17 us, now one of 22.
 // ---------------------------------------------------------------------------------------------------------------
 constexpr int kStripPooled = 15;      // pooled columns per strip: 2 * 15 + 1 conv columns of 32
 constexpr int kStripWaves = 4;

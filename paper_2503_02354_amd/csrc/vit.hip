@@ -144,8 +144,8 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint32_t* __restri
 // accumulator quad and stores 8 bytes at a time.
 // Numerics: scores in fp32, e = exp(s - max), probabilities p = e / sum(e) rounded to bf16 (they are a tensor of their
 // own in storage precision), output = sum_j p_j v_j accumulated in fp32 and rounded to bf16.
-// What bounds it: q, k, v and the output through HBM, 0.47 GB for 389 requests of 197 tokens and 12 heads (98 us at the
-// 4.8 TB/s a large copy reaches); the softmax is about 80 us of vector instructions.  A head of a request is a load of
+// What bounds it: q, k, v and the output through HBM, 0.47 GB for 389 requests of 197 tokens and 12 heads (96 us at the
+// 4.9 TB/s a large copy reaches); the softmax is about 80 us of vector instructions.  A head of a request is a load of
 // 75 KB and a few microseconds of work, so what counts is that loads are always in flight: workgroups of eight wavefronts
 // stay, one per compute unit; K and V of the next unit of work come by DMA into a second buffer, its queries into
 // registers, while every wavefront does one block of 32 queries of this one.  V stays as it is in memory: the transposing

@@ -125,7 +125,7 @@ def test_conv_f32_keeps_non_finite_filters_off_the_padding(B, oracle, H, Wd, C, 
         mag = oracle.conv2d(np.abs(x[i]), wf, np.abs(bias), None, stride, pad, 0, 0)
         # as in test_conv_f32_elementwise
         bound = 1.13 * (R * R * C + 2) * 2.0 ** -24 * mag + 8 * 2.0 ** -24 * np.abs(want) + (1e-6 * mag if act >= 2 else 0)
-        assert np.all(np.abs(got[i] - want)[finite] <= bound[finite])
+        assert np.all(np.abs(got[i][finite] - want[finite]) <= bound[finite])
 
 
 @pytest.mark.parametrize("H,Wd,C,K,R,stride,pad,n", [
