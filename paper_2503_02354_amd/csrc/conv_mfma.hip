@@ -90,14 +90,13 @@ __device__ __forceinline__ float gelu_fast(float x)
 // gelu_erfc.  Compared over all 2^32 arguments: distance at most 10 for x > -12, the same bf16 everywhere, NaN for NaN and for
 // minus infinity.  (Which way single roundings fall moves the logits after twelve transformer layers by 1 %.)  Its time is near
 // that of the fast form alone: chain of 777 transformer requests 91.8 ms with the 128 x 128 tiles and erfcf throughout, 78.6 with
-// today's tiles and erfcf, 74.4 with a fast form that differed in one rounding of 10,000, 76.4 with this (77.4 in groups of four
-// values, 81.1 of sixteen: too many registers).
+// today's tiles and erfcf, 73.9 with a fast form that differed in one rounding of 10,000, 75.1 with this (in groups of eight values
+// on the persistent tiles; of four 2 % slower, of sixteen 7 %: too many registers).
 template <int N> __device__ __forceinline__ void gelu_for_bf16(float (&v)[N])
 {
     constexpr uint32_t kDistance = 10;
-    float x[N];
+    float x[N], lowest = 0.f;
     uint16_t off[N], nearest = 0xFFFF;
-    float lowest = 0.f;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         x[i] = v[i];
@@ -106,7 +105,12 @@ template <int N> __device__ __forceinline__ void gelu_for_bf16(float (&v)[N])
         nearest = min(nearest, off[i]);
         lowest = fminf(lowest, x[i]);
     }
-    if (nearest <= 2 * kDistance || lowest <= -12.f) {
+    if (nearest > 2 * kDistance && lowest > -12.f) return;
+    if constexpr (N <= 4) {                                   // (as few registers as possible)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (off[i] <= 2 * kDistance || x[i] <= -12.f) v[i] = gelu_erfc(x[i]);
+    } else {                                                  // (as little code as possible: one value of a lane at a time)
         uint32_t open = 0;                                    // a bit per value
 #pragma unroll
         for (int i = 0; i < N; ++i) open |= off[i] <= 2 * kDistance || x[i] <= -12.f ? 1u << i : 0u;
@@ -138,13 +142,18 @@ template <int ACT, int N> __device__ __forceinline__ void activate(float (&v)[N]
     }
 }
 // The activation is a launch parameter, but an epilogue that tests it per element compiles into hundreds of
-// branches: dispatch ONCE per wave to a body specialised for the activation.
-template <typename F> __device__ __forceinline__ void with_activation(int act, F&& body)
+// branches: dispatch ONCE per wave to a body specialised for the activation.  GELU's body takes up to 40 registers more than the
+// others and would cost every launch of a kernel a wavefront per SIMD (conv_igemm_dma_kernel<128, 128, 2, 2>: 324 -> 362 us on the
+// stride-2 layers of 4096 images), so it is in kernels of its own, which the launchers choose.
+template <bool GELU, typename F> __device__ __forceinline__ void with_activation(int act, F&& body)
 {
-    if (act == 1) body(std::integral_constant<int, 1>{});
-    else if (act == 2) body(std::integral_constant<int, 2>{});
-    else if (act == 3) body(std::integral_constant<int, 3>{});
-    else body(std::integral_constant<int, 0>{});
+    if constexpr (GELU) {
+        body(std::integral_constant<int, 2>{});
+    } else {
+        if (act == 1) body(std::integral_constant<int, 1>{});
+        else if (act == 3) body(std::integral_constant<int, 3>{});
+        else body(std::integral_constant<int, 0>{});
+    }
 }
 // raw buffer descriptor over [p, p + bytes): offsets at or beyond `bytes` read as zero
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint32_t bytes)
@@ -152,7 +161,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool GELU>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_bf16_kernel(const uint16_t* __restrict__ x,
                                                                     const uint16_t* __restrict__ wp,
                                                                     const float* __restrict__ bias,
@@ -344,7 +353,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_bf16_kernel
     // Epilogue.  With the filter fragment as the first operand, accumulator element v of lane l belongs to pixel l%32
     // and filter 8*(v/4) + 4*(l/32) + v%4 of the 32x32 block: a quad of v is 4 consecutive channels of one pixel.
     const int f_hi = (lane >> 5) * 4;
-    with_activation(s.act, [&](auto act_c) {
+    with_activation<GELU>(s.act, [&](auto act_c) {
     constexpr int ACT = decltype(act_c)::value;
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
@@ -373,10 +382,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_bf16_kernel
     });
 }
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool GELU = false>
 hipError_t launch(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
                   hipStream_t stream)
 {
+    if constexpr (!GELU)
+        if (s.act == 2) return launch<BM, BN, BK, WAVES_M, WAVES_N, true>(x, wp, bias, res, y, s, stream);
     long long M = (long long)s.N * s.P * s.Q;
     int tiles_m = (int)((M + BM - 1) / BM), tiles_n = s.K / BN;
     long long total = (long long)tiles_m * tiles_n;
@@ -385,12 +396,12 @@ hipError_t launch(const void* x, const void* wp, const float* bias, const void* 
     constexpr int kThreads = 64 * WAVES_M * WAVES_N;
     static bool configured = false;
     if (!configured) {   // more than the default 64 KiB of LDS per workgroup needs an explicit opt-in
-        hipError_t e = hipFuncSetAttribute((const void*)conv_igemm_bf16_kernel<BM, BN, BK, WAVES_M, WAVES_N>,
+        hipError_t e = hipFuncSetAttribute((const void*)conv_igemm_bf16_kernel<BM, BN, BK, WAVES_M, WAVES_N, GELU>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    hipLaunchKernelGGL((conv_igemm_bf16_kernel<BM, BN, BK, WAVES_M, WAVES_N>), dim3((unsigned)total), dim3(kThreads), kLdsBytes,
+    hipLaunchKernelGGL((conv_igemm_bf16_kernel<BM, BN, BK, WAVES_M, WAVES_N, GELU>), dim3((unsigned)total), dim3(kThreads), kLdsBytes,
                        stream, (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M,
                        tiles_n);
     return hipGetLastError();
@@ -465,7 +476,7 @@ __device__ __forceinline__ void store_tile_via_lds_act(f32x16 (&acc)[MB][NB], ui
     constexpr int WN = NB * 32, ROW = WN + 8;             // elements; 16 bytes of padding per staged row
     constexpr int CPR = WN / 8;                            // 16-byte chunks per row
     constexpr int T = 32 * CPR / 64;                       // chunks per lane and 32-row block
-    constexpr int kQuads = ACT == 2 ? 2 : 1;               // GELU: eight values share its test
+    constexpr int kQuads = 1;                              // accumulator quads that are finished together
     const int frag_row = lane & 31, f_hi = (lane >> 5) * 4;
     // the residual takes the same road in the other direction: row-contiguous 16-byte loads (all issued up front),
     // staged in LDS, picked up in the accumulator layout
@@ -492,7 +503,7 @@ __device__ __forceinline__ void store_tile_via_lds_act(f32x16 (&acc)[MB][NB], ui
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
 #pragma unroll
-            for (int g = 0; g < 4; g += kQuads) {             // accumulator quads that are finished together
+            for (int g = 0; g < 4; g += kQuads) {
                 float v[4 * kQuads];
 #pragma unroll
                 for (int h = 0; h < kQuads; ++h) {
@@ -524,12 +535,12 @@ __device__ __forceinline__ void store_tile_via_lds_act(f32x16 (&acc)[MB][NB], ui
     }
 }
 
-template <int MB, int NB>
+template <bool GELU, int MB, int NB>
 __device__ __forceinline__ void store_tile_via_lds(f32x16 (&acc)[MB][NB], uint16_t* stage, const float* __restrict__ bias,
                                                    const uint16_t* __restrict__ res, uint16_t* __restrict__ y, int m_wave,
                                                    int n_wave, int M, int K, int act, int lane)
 {
-    with_activation(act, [&](auto a) {
+    with_activation<GELU>(act, [&](auto a) {
         if (res) store_tile_via_lds_act<MB, NB, decltype(a)::value, true>(acc, stage, bias, res, y, m_wave, n_wave, M, K, lane);
         else store_tile_via_lds_act<MB, NB, decltype(a)::value, false>(acc, stage, bias, res, y, m_wave, n_wave, M, K, lane);
     });
@@ -563,7 +574,7 @@ template <int N> __device__ __forceinline__ void wait_before_barrier()
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GELU>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_igemm_dma_kernel(const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ wp_all,
                                                                    const float* __restrict__ bias_all,
@@ -709,14 +720,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_igemm_dma_kern
     }
     wait_before_barrier<0>();
     __builtin_amdgcn_s_barrier();        // every wave is done with the operand stages: LDS is free for the epilogue
-    store_tile_via_lds<MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
+    store_tile_via_lds<GELU, MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
 #endif
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GELU = false>
 hipError_t launch_dma(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
                       hipStream_t stream, const Grouping& grp = Grouping())
 {
+    if constexpr (!GELU)
+        if (s.act == 2) return launch_dma<BM, BN, WAVES_M, WAVES_N, true>(x, wp, bias, res, y, s, stream, grp);
     long long M = (long long)s.N * s.P * s.Q;
     int tiles_n = s.K / BN;
     long long total = count_tiles(M, (long long)s.P * s.Q, BM, tiles_n, grp.table);
@@ -726,12 +739,12 @@ hipError_t launch_dma(const void* x, const void* wp, const float* bias, const vo
     constexpr int kThreads = 64 * WAVES_M * WAVES_N;
     static bool configured = false;
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void*)conv_igemm_dma_kernel<BM, BN, WAVES_M, WAVES_N>,
+        hipError_t e = hipFuncSetAttribute((const void*)conv_igemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, GELU>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    hipLaunchKernelGGL((conv_igemm_dma_kernel<BM, BN, WAVES_M, WAVES_N>), dim3((unsigned)total), dim3(kThreads), kLdsBytes, stream,
+    hipLaunchKernelGGL((conv_igemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, GELU>), dim3((unsigned)total), dim3(kThreads), kLdsBytes, stream,
                        (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M, tiles_n,
                        grp.table, grp.off_w, grp.off_b);
     return hipGetLastError();
@@ -750,7 +763,7 @@ hipError_t launch_dma(const void* x, const void* wp, const float* bias, const vo
 // ---------------------------------------------------------------------------------------------------------------
 constexpr int kSlabMaxW = 56;
 
-template <int BM, int BN, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GELU>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv3x3_slab_kernel(const uint16_t* __restrict__ x,
                                                                     const uint16_t* __restrict__ wp_all,
                                                                     const float* __restrict__ bias_all,
@@ -1044,14 +1057,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv3x3_slab_kernel
     }
     wait_before_barrier<0>();
     __builtin_amdgcn_s_barrier();        // every wave is done with the operand stages: LDS is free for the epilogue
-    store_tile_via_lds<MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
+    store_tile_via_lds<GELU, MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
 #endif
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool GELU = false>
 hipError_t launch_slab(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
                        hipStream_t stream, const Grouping& grp = Grouping())
 {
+    if constexpr (!GELU)
+        if (s.act == 2) return launch_slab<BM, BN, WAVES_M, WAVES_N, true>(x, wp, bias, res, y, s, stream, grp);
     long long M = (long long)s.N * s.P * s.Q;
     int tiles_n = s.K / BN;
     long long total = count_tiles(M, (long long)s.P * s.Q, BM, tiles_n, grp.table);
@@ -1063,12 +1078,12 @@ hipError_t launch_slab(const void* x, const void* wp, const float* bias, const v
     constexpr int kThreads = 64 * WAVES_M * WAVES_N;
     static bool configured = false;
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void*)conv3x3_slab_kernel<BM, BN, WAVES_M, WAVES_N>,
+        hipError_t e = hipFuncSetAttribute((const void*)conv3x3_slab_kernel<BM, BN, WAVES_M, WAVES_N, GELU>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    hipLaunchKernelGGL((conv3x3_slab_kernel<BM, BN, WAVES_M, WAVES_N>), dim3((unsigned)total), dim3(kThreads), kLdsBytes, stream,
+    hipLaunchKernelGGL((conv3x3_slab_kernel<BM, BN, WAVES_M, WAVES_N, GELU>), dim3((unsigned)total), dim3(kThreads), kLdsBytes, stream,
                        (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M, tiles_n,
                        grp.table, grp.off_w, grp.off_b);
     return hipGetLastError();
@@ -1094,7 +1109,7 @@ template <int BEGIN, int END, typename F> __device__ __forceinline__ void static
     }
 }
 
-template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES>
+template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES, bool GELU>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel(const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ wp_all,
                                                                    const float* __restrict__ bias_all,
@@ -1306,14 +1321,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
     }
     wait_before_barrier<0>();
     __builtin_amdgcn_s_barrier();        // every wave is done with the operand stages: LDS is free for the epilogue
-    store_tile_via_lds<MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
+    store_tile_via_lds<GELU, MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
 #endif
 }
 
-template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES>
+template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES, bool GELU = false>
 hipError_t launch_ring(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
                        hipStream_t stream, const Grouping& grp = Grouping())
 {
+    if constexpr (!GELU)
+        if (s.act == 2) return launch_ring<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, true>(x, wp, bias, res, y, s, stream, grp);
     constexpr int BM = 32 * MB * WAVES_M, BN = 32 * NB * WAVES_N;
     long long M = (long long)s.N * s.P * s.Q;
     int tiles_n = s.K / BN;
@@ -1322,10 +1339,10 @@ hipError_t launch_ring(const void* x, const void* wp, const float* bias, const v
     if (total == 0) return hipSuccess;
     constexpr size_t kLdsBytes = STAGES * UN * (size_t)(BM + BN) * 32 * sizeof(uint16_t);
     static_assert(kLdsBytes <= 160 * 1024 && kLdsBytes >= (size_t)WAVES_M * WAVES_N * 32 * (32 * NB + 8) * 2, "operand stages and epilogue rows");
-    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES>,
+    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, GELU>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
     if (configured != hipSuccess) return configured;
-    hipLaunchKernelGGL((conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES>), dim3((unsigned)total), dim3(64 * WAVES_M * WAVES_N),
+    hipLaunchKernelGGL((conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, GELU>), dim3((unsigned)total), dim3(64 * WAVES_M * WAVES_N),
                        kLdsBytes, stream, (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M,
                        tiles_n, grp.table, grp.off_w, grp.off_b);
     return hipGetLastError();
@@ -1358,7 +1375,7 @@ __device__ __forceinline__ void store_tile_counted_act(f32x16 (&acc)[MB][NB], ui
     constexpr int WN = NB * 32, ROW = WN + 8;
     constexpr int CPR = WN / 8;
     constexpr int T = 32 * CPR / 64;
-    constexpr int kQuads = ACT == 2 ? 2 : 1;               // GELU: eight values share its test
+    constexpr int kQuads = ACT == 2 ? 2 : 1;               // accumulator quads that are finished together: GELU shares a test
     const int frag_row = lane & 31, f_hi = (lane >> 5) * 4;
     auto at = [&](int i, int t) -> uint32_t {
         const int idx = lane + 64 * t, mo = m_wave + i * 32 + idx / CPR;
@@ -1385,7 +1402,7 @@ __device__ __forceinline__ void store_tile_counted_act(f32x16 (&acc)[MB][NB], ui
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
 #pragma unroll
-            for (int g = 0; g < 4; g += kQuads) {             // accumulator quads that are finished together
+            for (int g = 0; g < 4; g += kQuads) {
                 float v[4 * kQuads];
 #pragma unroll
                 for (int h = 0; h < kQuads; ++h) {
@@ -1415,7 +1432,7 @@ __device__ __forceinline__ void store_tile_counted_act(f32x16 (&acc)[MB][NB], ui
     }
 }
 
-template <bool ROWS, int MB, int NB, int WAVES_M, int WAVES_N>
+template <bool ROWS, int MB, int NB, int WAVES_M, int WAVES_N, bool GELU>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_gemm_persistent_kernel(const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ wp_all,
                                                                    const float* __restrict__ bias_all,
@@ -1605,7 +1622,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_gemm_persisten
         step(no{}, yes{}, no{}, c0{});
         const TileOrigin o = locate_tile<BM>(tile, tiles_n, PQ, M_all, wp_all, bias_all, gt, off_w, off_b);
         uint16_t* const stage = lds + STAGES * STAGE + wid * (32 * (WN + 8) + 128);
-        with_activation(s.act, [&](auto a) {
+        with_activation<GELU>(s.act, [&](auto a) {
             constexpr int ACT = decltype(a)::value;
             const int m = o.m0 + wm * WM, n = o.tile_n * BN + wn * WN;
             if (res) store_tile_counted_act<MB, NB, ACT, true>(acc, stage, o.bias, r_rsrc, y_rsrc, m, n, o.m_end, s.K, lane);
@@ -1621,10 +1638,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_gemm_persisten
 #endif
 }
 
-template <bool ROWS, int MB, int NB, int WAVES_M, int WAVES_N>
+template <bool ROWS, int MB, int NB, int WAVES_M, int WAVES_N, bool GELU = false>
 hipError_t launch_gemm_persistent(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
                        hipStream_t stream, const Grouping& grp = Grouping())
 {
+    if constexpr (!GELU)
+        if (s.act == 2) return launch_gemm_persistent<ROWS, MB, NB, WAVES_M, WAVES_N, true>(x, wp, bias, res, y, s, stream, grp);
     constexpr int BM = 32 * MB * WAVES_M, BN = 32 * NB * WAVES_N;
     long long M = (long long)s.N * s.P * s.Q;
     int tiles_n = s.K / BN;
@@ -1633,11 +1652,11 @@ hipError_t launch_gemm_persistent(const void* x, const void* wp, const float* bi
     if (total == 0) return hipSuccess;
     constexpr int NW = WAVES_M * WAVES_N, kRowsLds = (BM / 16 + NW - 1) / NW * NW * 16;
     constexpr size_t kLdsBytes = (3 * (size_t)(kRowsLds + BN) * 32 + WAVES_M * WAVES_N * (32 * (32 * NB + 8) + 128)) * sizeof(uint16_t);
-    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N>,
+    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N, GELU>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
     if (configured != hipSuccess) return configured;
     const unsigned grid = (unsigned)(total < 256 ? total : 256);
-    hipLaunchKernelGGL((conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N>), dim3(grid), dim3(64 * WAVES_M * WAVES_N),
+    hipLaunchKernelGGL((conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N, GELU>), dim3(grid), dim3(64 * WAVES_M * WAVES_N),
                        kLdsBytes, stream, (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M,
                        tiles_n, (int)total, grp.table, grp.off_w, grp.off_b);
     return hipGetLastError();
