@@ -1097,7 +1097,10 @@ hipError_t launch_slab(const void* x, const void* wp, const float* bias, const v
 // the loads run further ahead.  Same operands, same instruction and same order of accumulation as the kernel that the
 // shape otherwise takes (slab_order: channel blocks outside, window positions inside), hence the same bits.
 //   * STAGES stages of UN 32-channel steps each in LDS, all but two of them in flight; one barrier per stage.
-//   * operands of a stage are read into registers while the stage before it is multiplied.
+//   * operands of a stage are read into registers while the stage before it is multiplied, and the loads of a later one issued,
+//     each between two products: a wave issues in order, and what stands in front of the products delays them.  us, reads, then
+//     loads, then products / this order: 3072 -> 768, 197 rows 11.3 / 9.1, 985 rows 16.0 / 13.9; 3x3 stride 2, 256 -> 512 on 14 x 14,
+//     1 image 9.9 / 8.1, 29 images 13.4 / 11.2; 3x3 stride 1, 512 -> 512 on 7 x 7, 1 image 10.1 / 9.4, 29 images 14.1 / 13.2.
 //   * row tiles run fastest: the workgroups of one XCD take all rows of a few filter tiles, so filters - most of the
 //     bytes here - come from memory once and not once per XCD.
 // ---------------------------------------------------------------------------------------------------------------
@@ -1205,20 +1208,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
     uint32_t f_c = 0, f_w = 0, r_pos = 0, t_pos = 0;
     const uint32_t c_end = (uint32_t)s.C * 2, tap_w = (uint32_t)cblocks * (KS * FRAG * 2);
     // part (slab order): which UN of the nine positions
-    auto issue = [&](auto part_c, int stage) __attribute__((always_inline)) {
+    auto load_one = [&](auto part_c, auto k_c, int stage) __attribute__((always_inline)) {
+        constexpr int part = decltype(part_c)::value, u = decltype(k_c)::value / (A_PER_WAVE + B_PER_WAVE), j = decltype(k_c)::value % (A_PER_WAVE + B_PER_WAVE);
+        uint16_t* const st = lds + stage * STAGE + u * STEP;
+        if constexpr (j < A_PER_WAVE)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void*)(st + (wid * A_PER_WAVE + j) * FRAG), 16,
+                                                     a_at[j][SLAB_ORDER ? part * UN + u : 0], SLAB_ORDER ? f_c : f_c + u * (BK * 2), 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void*)(st + (FA + wid * B_PER_WAVE + j - A_PER_WAVE) * FRAG), 16, b_off[j - A_PER_WAVE],
+                                                     SLAB_ORDER ? f_w + (part * UN + u) * tap_w : f_w + u * (KS * FRAG * 2), 0, 0);
+    };
+    auto advance = [&](auto part_c) __attribute__((always_inline)) {
         constexpr int part = decltype(part_c)::value;
-        uint16_t* const st = lds + stage * STAGE;
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-#pragma unroll
-            for (int j = 0; j < A_PER_WAVE; ++j)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void*)(st + u * STEP + (wid * A_PER_WAVE + j) * FRAG), 16,
-                                                         a_at[j][SLAB_ORDER ? part * UN + u : 0], SLAB_ORDER ? f_c : f_c + u * (BK * 2), 0, 0);
-#pragma unroll
-            for (int j = 0; j < B_PER_WAVE; ++j)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void*)(st + u * STEP + (FA + wid * B_PER_WAVE + j) * FRAG), 16, b_off[j],
-                                                         SLAB_ORDER ? f_w + (part * UN + u) * tap_w : f_w + u * (KS * FRAG * 2), 0, 0);
-        }
         // past the last stage the position stays put: what is fetched there is never used
         if (SLAB_ORDER) {
             if (part == kParts - 1 && f_c + BK * 2 < c_end) { f_c += BK * 2; f_w += KS * FRAG * 2; }
@@ -1249,41 +1250,29 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
     const int rd_row = lane & 31;
     const int rd0 = (rd_row >> 4) * FRAG + ((rd_row & 15) * 4 + ((lane >> 5) ^ swz(rd_row & 15))) * 8;
     bf16x8 af[2][UN][KS][MB], bfr[2][UN][KS][NB];             // [stage parity]
-    auto read = [&](auto set_c, int stage) __attribute__((always_inline)) {
-        constexpr int set = decltype(set_c)::value;
-#pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const uint16_t* a_lds = lds + stage * STAGE + u * STEP + (wm * MB * 2) * FRAG;
-            const uint16_t* b_lds = lds + stage * STAGE + u * STEP + (FA + wn * NB * KS) * FRAG + lane * 8;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-                for (int i = 0; i < MB; ++i) af[set][u][ks][i] = *(const bf16x8*)(a_lds + i * 2 * FRAG + (rd0 ^ (ks * 16)));
-#pragma unroll
-                for (int j = 0; j < NB; ++j) bfr[set][u][ks][j] = *(const bf16x8*)(b_lds + (j * KS + ks) * FRAG);
-            }
-        }
+    constexpr int kReads = UN * KS * (MB + NB), kMfma = UN * KS * MB * NB;
+    auto read_one = [&](auto set_c, auto k_c, int stage) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_c)::value, k = decltype(k_c)::value, u = k / (KS * (MB + NB)), ks = k / (MB + NB) % KS, i = k % (MB + NB);
+        const uint16_t* const st = lds + stage * STAGE + u * STEP;
+        if constexpr (i < MB) af[set][u][ks][i] = *(const bf16x8*)(st + (wm * MB * 2) * FRAG + i * 2 * FRAG + (rd0 ^ (ks * 16)));
+        else bfr[set][u][ks][i - MB] = *(const bf16x8*)(st + (FA + wn * NB * KS) * FRAG + lane * 8 + ((i - MB) * KS + ks) * FRAG);
     };
-    auto multiply = [&](auto set_c, int u) __attribute__((always_inline)) {
-        constexpr int set = decltype(set_c)::value;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int i = 0; i < MB; ++i)
-#pragma unroll
-                for (int j = 0; j < NB; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][u][ks][j], af[set][u][ks][i], acc[i][j], 0, 0, 0);
+    auto multiply_one = [&](auto set_c, auto k_c) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_c)::value, k = decltype(k_c)::value, u = k / (KS * MB * NB), ks = k / (MB * NB) % KS, i = k / NB % MB, j = k % NB;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][u][ks][j], af[set][u][ks][i], acc[i][j], 0, 0, 0);
     };
 
     typedef std::integral_constant<int, 0> c0;
     typedef std::integral_constant<int, 1> c1;
     // stages are fetched in order; in slab order stage k holds part k % kParts of channel block k / kParts
     static_for<0, STAGES - 1>([&](auto k) __attribute__((always_inline)) {
-        issue(std::integral_constant<int, decltype(k)::value % kParts>{}, decltype(k)::value);
+        typedef std::integral_constant<int, decltype(k)::value % kParts> part;
+        static_for<0, LOADS>([&](auto l) __attribute__((always_inline)) { load_one(part{}, l, decltype(k)::value); });
+        advance(part{});
     });
     wait_before_barrier<(STAGES - 2) * LOADS>();
     __builtin_amdgcn_s_barrier();
-    read(c0{}, 0);
+    static_for<0, kReads>([&](auto k) __attribute__((always_inline)) { read_one(c0{}, k, 0); });
     // body of stage i: the loads of stage i + 1 have landed (its successors may be in flight) | barrier | stage i + STAGES - 1
     // goes where stage i - 1 was: every wave has its operands in registers since before this barrier | operands of stage
     // i + 1 | products of stage i.  Past the end stale stages are read into registers that nothing uses.
@@ -1292,10 +1281,17 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
         constexpr int part = decltype(part_c)::value;
         wait_before_barrier<(STAGES - 3) * LOADS>();
         __builtin_amdgcn_s_barrier();
-        read(nxt_c, next);
-        issue(std::integral_constant<int, (part + STAGES - 1) % kParts>{}, fill);
-#pragma unroll
-        for (int u = 0; u < UN; ++u) multiply(cur_c, u);
+        typedef std::integral_constant<int, (part + STAGES - 1) % kParts> fill_part;
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<0, kMfma>([&](auto m_c) __attribute__((always_inline)) {
+            constexpr int m = decltype(m_c)::value;
+            multiply_one(cur_c, m_c);
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<kReads * m / kMfma, kReads * (m + 1) / kMfma>([&](auto k) __attribute__((always_inline)) { read_one(nxt_c, k, next); });
+            static_for<LOADS * m / kMfma, LOADS * (m + 1) / kMfma>([&](auto l) __attribute__((always_inline)) { load_one(fill_part{}, l, fill); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        advance(fill_part{});
         next = next == STAGES - 1 ? 0 : next + 1;
         fill = fill == STAGES - 1 ? 0 : fill + 1;
     };
