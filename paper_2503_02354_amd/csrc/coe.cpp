@@ -177,7 +177,9 @@ struct coe_ctx {
 
     // regroup
     int32_t *d_cnt = nullptr, *d_off = nullptr, *d_perm = nullptr, *d_inv = nullptr, *d_blockhist = nullptr;
-    int32_t* h_cnt = nullptr;        // pinned
+    int32_t* h_cnt = nullptr;        // pinned: the regroup kernel writes the counts (and the oldest request of every group) here
+    uint32_t* h_out = nullptr;       // pinned: coe_collect's results arrive here, if they fit
+    size_t out_words = 0;
     int32_t* h_first = nullptr;      // pinned, one entry per request slot: staging of the first experts of a submit
     uint8_t* h_stage = nullptr;      // pinned ring that inputs in pageable host memory go through (copy_pageable), made at need
     hipEvent_t ev_stage[8] = {};     // recorded after the copy out of each chunk ...
@@ -185,6 +187,11 @@ struct coe_ctx {
     int32_t last_pending = 0, last_live = 0, last_E = 0;
     std::vector<int32_t> submit_step;   // per request slot: number of the first step that sees the request
     int32_t step_no = 0;
+    // The counts of the queued groups, and their oldest requests, while the host knows them: nothing has run since the store was empty
+    bool known = false;
+    std::vector<int32_t> known_cnt, known_head;
+    hipEvent_t ev_regrouped = nullptr;  // recorded after the regroup of a step that did not wait for its counts
+    bool regroup_pending = false;
 
     // executors: lanes[0] runs on the compute stream; further lanes (cfg.executors > 1) have a stream and an activation
     // workspace of their own, so that launch sequences of different groups overlap on the device
@@ -457,6 +464,9 @@ hipError_t dev_malloc(coe_ctx* c, void** p, size_t bytes)
     return hipMalloc(p, bytes);
 }
 
+// Pinned memory for the results of a collect; what does not fit (more than a hundred thousand requests) goes by copies.
+constexpr size_t kCollectPinned = (size_t)16 << 20;
+
 int ensure_store(coe_ctx* c)
 {
     if (c->archs.empty()) return fail(c, COE_ESTATE, "no architecture registered");
@@ -471,6 +481,15 @@ int ensure_store(coe_ctx* c)
         if (c->d_logits) HIPCHK(c, hipFree(c->d_logits));
         HIPCHK(c, dev_malloc(c, (void**)&c->d_logits, nreq * c->max_classes * sizeof(float)));
         c->logits_alloc_classes = c->max_classes;
+        // results of a collect: next expert, path and logits of every request
+        const size_t words = nreq * (1 + (size_t)c->cfg.max_stages + (size_t)c->max_classes);
+        if (c->h_out) HIPCHK(c, hipHostFree(c->h_out));
+        c->h_out = nullptr;
+        c->out_words = 0;
+        if (words * 4 <= kCollectPinned) {
+            HIPCHK(c, hipHostMalloc((void**)&c->h_out, words * 4, hipHostMallocDefault));
+            c->out_words = words;
+        }
     }
     return COE_OK;
 }
@@ -1081,6 +1100,7 @@ int coe_create(const coe_config* cfg, coe_ctx** out)
             hipEventCreateWithFlags(&c->lanes[l].done, hipEventDisableTiming) != hipSuccess)
             return bail(COE_EDEVICE);
     if (hipEventCreateWithFlags(&c->ev_ready, hipEventDisableTiming) != hipSuccess) return bail(COE_EDEVICE);
+    if (hipEventCreateWithFlags(&c->ev_regrouped, hipEventDisableTiming) != hipSuccess) return bail(COE_EDEVICE);
     size_t nreq = (size_t)cfg->max_requests;
     size_t nblocks = (nreq + coe::k::kRegroupTile - 1) / coe::k::kRegroupTile;
     bool ok = hipMalloc((void**)&c->d_cur, nreq * 4) == hipSuccess && hipMalloc((void**)&c->d_depth, nreq * 4) == hipSuccess &&
@@ -1140,7 +1160,9 @@ void coe_destroy(coe_ctx* c)
         if (l > 0 && ln.s) hipStreamDestroy(ln.s);
     }
     if (c->ev_ready) hipEventDestroy(c->ev_ready);
+    if (c->ev_regrouped) hipEventDestroy(c->ev_regrouped);
     if (c->h_cnt) hipHostFree(c->h_cnt);
+    if (c->h_out) hipHostFree(c->h_out);
     if (c->h_first) hipHostFree(c->h_first);
     if (c->h_stage) hipHostFree(c->h_stage);
     for (hipEvent_t e : c->ev_stage)
@@ -1406,6 +1428,27 @@ static int copy_pageable(coe_ctx* c, uint8_t* dst, const uint8_t* src, size_t by
     return COE_OK;
 }
 
+// Images that the launch of a submit moves itself: up to 16 MB (53 of 224 x 224) the copy's own launch costs more than its kernel gains.
+constexpr size_t kSubmitInLaunch = (size_t)16 << 20;
+
+// Images that a kernel on this device may read: `bytes` inside one allocation of its own memory, from a 16-byte boundary on.  Anything
+// else that the runtime's copy takes (memory of another device, of the host, managed) is left to it.
+static bool readable_in_launch(const void* p, size_t bytes)
+{
+    if (bytes > kSubmitInLaunch || bytes % 16 || ((uintptr_t)p & 15)) return false;
+    hipPointerAttribute_t attr{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&attr, p) != hipSuccess || attr.type != hipMemoryTypeDevice || attr.device != dev ||
+        attr.isManaged || hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)const_cast<void*>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const size_t at = (size_t)((const char*)p - (const char*)base);
+    return at <= size && bytes <= size - at;
+}
+
 int coe_submit(coe_ctx* c, int32_t n, const void* inputs, int on_device, const int32_t* first, int64_t* first_id)
 {
     if (!c || n < 0 || (n > 0 && !inputs)) return fail(c, COE_EINVAL, "bad argument");
@@ -1422,22 +1465,33 @@ int coe_submit(coe_ctx* c, int32_t n, const void* inputs, int on_device, const i
     size_t base = (size_t)c->n_live;
     rc = on_device ? COE_DONE : copy_pageable(c, (uint8_t*)c->d_inputs + base * ib, (const uint8_t*)inputs, (size_t)n * ib);
     if (rc != COE_OK && rc != COE_DONE) return rc;
-    if (rc == COE_DONE)
-        HIPCHK(c, hipMemcpyAsync((uint8_t*)c->d_inputs + base * ib, inputs, (size_t)n * ib,
-                                 on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->sc));
+    // images of a small submit from device memory move in the launch that sets the store up, larger ones and those from the host by a copy
+    uint8_t* const dst = (uint8_t*)c->d_inputs + base * ib;
+    const size_t bytes = (size_t)n * ib;
+    const bool in_launch = rc == COE_DONE && on_device && ((uintptr_t)dst & 15) == 0 && readable_in_launch(inputs, bytes);
+    if (rc == COE_DONE && !in_launch)
+        HIPCHK(c, hipMemcpyAsync(dst, inputs, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->sc));
     // the first experts travel through pinned staging, one entry per request slot (a slot is reused only after the store
     // has drained, which synchronises), so the call returns without waiting for the stream
     if (first) std::copy(first, first + n, c->h_first + base);
-    else std::fill(c->h_first + base, c->h_first + base + n, 0);
-    HIPCHK(c, hipMemcpyAsync(c->d_cur + base, c->h_first + base, (size_t)n * 4, hipMemcpyHostToDevice, c->sc));
-    HIPCHK(c, hipMemsetAsync(c->d_depth + base, 0, (size_t)n * 4, c->sc));
-    HIPCHK(c, hipMemsetAsync(c->d_path + base * c->cfg.max_stages, 0xFF, (size_t)n * 4 * c->cfg.max_stages, c->sc));
-    HIPCHK(c, hipMemsetAsync(c->d_logits + base * c->max_classes, 0, (size_t)n * 4 * c->max_classes, c->sc));
+    HIPCHK(c, coe::k::submit_store(in_launch ? inputs : nullptr, in_launch ? dst : nullptr, in_launch ? bytes : 0, first ? c->h_first + base : nullptr,
+                                   c->d_cur + base, c->d_depth + base, (size_t)n, c->d_path + base * c->cfg.max_stages,
+                                   (size_t)n * c->cfg.max_stages, c->d_logits + base * c->max_classes, (size_t)n * c->max_classes, c->sc));
     // host inputs are the caller's (possibly pageable) memory and may be freed on return: wait for that copy only (the pinned ring
     // of copy_pageable keeps track of its chunks by itself)
     if (!on_device) HIPCHK(c, hipStreamSynchronize(c->sc));
     std::fill(c->collected.begin() + base, c->collected.begin() + base + n, 0);
     std::fill(c->submit_step.begin() + base, c->submit_step.begin() + base + n, c->step_no);
+    if (base == 0) {
+        c->known = true;
+        c->known_cnt.assign(c->E, 0);
+        c->known_head.assign(c->E, -1);
+    }
+    if (c->known)
+        for (int32_t i = 0; i < n; ++i) {
+            const int32_t e = first ? first[i] : 0;
+            if (c->known_cnt[e]++ == 0) c->known_head[e] = (int32_t)base + i;
+        }
     c->n_live += n;
     return COE_OK;
 }
@@ -1456,17 +1510,29 @@ static int step_body(coe_ctx* c, coe_step_stats& st)
     {
         Span sp(c, COE_K_REGROUP_INDEX, (double)c->n_live * 16.0, c->sc);
         HIPCHK(c, coe::k::regroup_index(c->d_cur, c->n_live, E, c->d_cnt, c->d_off, c->d_perm, c->d_inv, c->d_blockhist,
-                                        arranging ? c->d_cnt + E : nullptr, c->sc));
+                                        arranging ? c->d_cnt + E : nullptr, c->known ? nullptr : c->h_cnt, c->sc));
     }
-    HIPCHK(c, hipMemcpyAsync(c->h_cnt, c->d_cnt, (size_t)E * 4 * (arranging ? 2 : 1), hipMemcpyDeviceToHost, c->sc));
-    HIPCHK(c, hipStreamSynchronize(c->sc));
+    // counts that the host knows already (nothing has run yet) are not waited for: the launches of this step follow at once, and
+    // the step waits for the regroup, and with it for the submits before it, when it has enqueued them
+    std::vector<int32_t> cnt, head;
+    if (c->known) {
+        HIPCHK(c, hipEventRecord(c->ev_regrouped, c->sc));
+        c->regroup_pending = true;
+        cnt = c->known_cnt;
+        head = c->known_head;
+        c->known = false;
+    } else {
+        HIPCHK(c, hipStreamSynchronize(c->sc));
+        cnt.assign(c->h_cnt, c->h_cnt + E);
+        if (arranging) head.assign(c->h_cnt + E, c->h_cnt + 2 * E);
+    }
     auto t0 = std::chrono::steady_clock::now();
     std::vector<int32_t> off(E + 1, 0);
     std::vector<uint8_t> has_group(E, 0);
     int32_t n_groups_queued = 0;
     for (int32_t e = 0; e < E; ++e) {
-        off[e + 1] = off[e] + c->h_cnt[e];
-        has_group[e] = c->h_cnt[e] > 0;
+        off[e + 1] = off[e] + cnt[e];
+        has_group[e] = cnt[e] > 0;
         n_groups_queued += has_group[e];
     }
     const int32_t n_pending = off[E];
@@ -1483,14 +1549,14 @@ static int step_body(coe_ctx* c, coe_step_stats& st)
             const ArchPlan& a = c->archs[c->experts[e].arch];
             min_res[e] = a.arr_min_res; min_miss[e] = a.arr_min_miss; wait[e] = a.arr_wait;
             resident[e] = c->policy->resident(e);
-            if (has_group[e]) age[e] = step_no - c->submit_step[c->h_cnt[E + e]];
+            if (has_group[e]) age[e] = step_no - c->submit_step[head[e]];
         }
-        coe_arrange_defer(E, c->h_cnt, age.data(), resident.data(), min_res.data(), min_miss.data(), wait.data(), defer.data());
+        coe_arrange_defer(E, cnt.data(), age.data(), resident.data(), min_res.data(), min_miss.data(), wait.data(), defer.data());
         for (int32_t e = 0; e < E; ++e)
             if (defer[e]) {
                 has_group[e] = 0;
                 ++st.n_deferred_groups;
-                st.n_deferred_requests += c->h_cnt[e];
+                st.n_deferred_requests += cnt[e];
             }
     }
 
@@ -1574,12 +1640,12 @@ static int step_body(coe_ctx* c, coe_step_stats& st)
     };
     auto group_cost = [&](int32_t e) {
         const ArchPlan& a = c->archs[c->experts[e].arch];
-        return a.lat_k_ns * (int64_t)c->h_cnt[e] + (was_missing[e] ? a.lat_load_ns : 0);
+        return a.lat_k_ns * (int64_t)cnt[e] + (was_missing[e] ? a.lat_load_ns : 0);
     };
     const int32_t group_small = c->cfg.group_small == 0 ? 64 : c->cfg.group_small;
     auto small = [&](int32_t e) {
         const ArchPlan& a = c->archs[c->experts[e].arch];
-        return group_small > 0 && c->h_cnt[e] <= group_small && c->h_cnt[e] <= chunk_rows(c, a) && a.groupable;
+        return group_small > 0 && cnt[e] <= group_small && cnt[e] <= chunk_rows(c, a) && a.groupable;
     };
     for (size_t i = 0; i < order.size(); ++i) {
         const int32_t e = order[i];
@@ -1596,8 +1662,8 @@ static int step_body(coe_ctx* c, coe_step_stats& st)
         std::vector<SetMember> set;
         if (small(e)) {
             const ArchPlan& a = c->archs[x.arch];
-            set.push_back({e, off[e], c->h_cnt[e]});
-            int32_t rows = c->h_cnt[e];
+            set.push_back({e, off[e], cnt[e]});
+            int32_t rows = cnt[e];
             for (size_t j = i + 1; j < order.size() && (int32_t)set.size() < coe::k::kMaxGroups; ++j) {
                 const int32_t f = order[j];
                 if (launched[f] || !small(f) || c->experts[f].arch != x.arch) continue;
@@ -1606,9 +1672,9 @@ static int step_body(coe_ctx* c, coe_step_stats& st)
                 // for another group's copy.  What counts is whether an expert has run since its weights were loaded: then no
                 // copy can be on its way, and which groups share a launch does not depend on how fast the link is
                 if (a.token_ops && (x.load_pending || c->experts[f].load_pending)) continue;
-                if (rows + c->h_cnt[f] > chunk_rows(c, c->archs[x.arch])) continue;
-                set.push_back({f, off[f], c->h_cnt[f]});
-                rows += c->h_cnt[f];
+                if (rows + cnt[f] > chunk_rows(c, c->archs[x.arch])) continue;
+                set.push_back({f, off[f], cnt[f]});
+                rows += cnt[f];
             }
         }
         Lane* lane = nullptr;
@@ -1643,8 +1709,8 @@ static int step_body(coe_ctx* c, coe_step_stats& st)
         const int32_t n_route = c->succ_off[e + 1] - c->succ_off[e];
         // request splitting: as few launch sequences as the cap allows, of equal size (no short last one)
         const int32_t cap_rows = chunk_rows(c, c->archs[x.arch]);
-        const int32_t n_seq = (c->h_cnt[e] + cap_rows - 1) / cap_rows;
-        const int32_t chunk = (c->h_cnt[e] + n_seq - 1) / n_seq;
+        const int32_t n_seq = (cnt[e] + cap_rows - 1) / cap_rows;
+        const int32_t chunk = (cnt[e] + n_seq - 1) / n_seq;
         rc = take_lane(e, group_cost(e) + c->archs[x.arch].lat_b_ns * n_seq, &lane);   // a group stays on one executor
         if (rc) return rc;
         if (x.load_pending) {
@@ -1679,6 +1745,11 @@ int coe_step(coe_ctx* c, coe_step_stats* stats)
     const int64_t allocs_before = c->device_allocs;
     for (Lane& ln : c->lanes) ln.used = false;
     int rc = step_body(c, st);
+    if (c->regroup_pending) {
+        c->regroup_pending = false;
+        const hipError_t e = hipEventSynchronize(c->ev_regrouped);
+        if (e != hipSuccess && rc >= 0) rc = fail(c, COE_EDEVICE, std::string("waiting for the regroup: ") + hipGetErrorString(e));
+    }
     // the step is complete on the compute stream once every executor is - also when the step ended in an error after some
     // executors had been given work
     for (size_t l = 1; l < c->lanes.size(); ++l) {
@@ -1787,19 +1858,30 @@ int coe_collect(coe_ctx* c, int32_t cap, int64_t* ids, float* logits, int32_t* p
     if (!c || cap < 0 || !n_out) return fail(c, COE_EINVAL, "bad argument");
     *n_out = 0;
     if (c->n_live == 0) return COE_OK;
-    HIPCHK(c, hipStreamSynchronize(c->sc));
     const size_t n = (size_t)c->n_live, ms = (size_t)c->cfg.max_stages, mc = (size_t)c->max_classes;
-    std::vector<int32_t> cur(n), hpath(path ? n * ms : 0);
-    std::vector<float> hlog(logits ? n * mc : 0);
-    HIPCHK(c, hipMemcpy(cur.data(), c->d_cur, n * 4, hipMemcpyDeviceToHost));
-    if (path) HIPCHK(c, hipMemcpy(hpath.data(), c->d_path, n * ms * 4, hipMemcpyDeviceToHost));
-    if (logits) HIPCHK(c, hipMemcpy(hlog.data(), c->d_logits, n * mc * 4, hipMemcpyDeviceToHost));
+    const size_t path_words = path ? n * ms : 0, logit_words = logits ? n * mc : 0;
+    std::vector<int32_t> own;                // results that do not fit the pinned memory
+    const int32_t* cur = nullptr;
+    if (n + path_words + logit_words <= c->out_words) {
+        HIPCHK(c, coe::k::collect_words(c->d_cur, n, c->d_path, path_words, c->d_logits, logit_words, c->h_out, c->sc));
+        HIPCHK(c, hipStreamSynchronize(c->sc));
+        cur = (const int32_t*)c->h_out;
+    } else {
+        HIPCHK(c, hipStreamSynchronize(c->sc));
+        own.resize(n + path_words + logit_words);
+        HIPCHK(c, hipMemcpy(own.data(), c->d_cur, n * 4, hipMemcpyDeviceToHost));
+        if (path) HIPCHK(c, hipMemcpy(own.data() + n, c->d_path, path_words * 4, hipMemcpyDeviceToHost));
+        if (logits) HIPCHK(c, hipMemcpy(own.data() + n + path_words, c->d_logits, logit_words * 4, hipMemcpyDeviceToHost));
+        cur = own.data();
+    }
+    const int32_t* const hpath = cur + n;
+    const float* const hlog = (const float*)(hpath + path_words);
     int32_t m = 0;
     for (size_t i = 0; i < n && m < cap; ++i) {
         if (c->collected[i] || cur[i] >= 0) continue;
         if (ids) ids[m] = c->id_base + (int64_t)i;
-        if (logits) std::memcpy(logits + (size_t)m * mc, hlog.data() + i * mc, mc * 4);
-        if (path) std::memcpy(path + (size_t)m * ms, hpath.data() + i * ms, ms * 4);
+        if (logits) std::memcpy(logits + (size_t)m * mc, hlog + i * mc, mc * 4);
+        if (path) std::memcpy(path + (size_t)m * ms, hpath + i * ms, ms * 4);
         c->collected[i] = 1;
         ++c->n_collected;
         ++m;
@@ -1931,7 +2013,7 @@ int coe_debug_regroup(coe_ctx* c, int32_t n, const int32_t* cur, int32_t E, int3
     if (n > c->cfg.max_requests) return fail(c, COE_ERANGE, "more keys than max_requests");
     if (c->n_live > 0) return fail(c, COE_ESTATE, "requests are live");
     if (n) HIPCHK(c, hipMemcpy(c->d_cur, cur, (size_t)n * 4, hipMemcpyHostToDevice));
-    HIPCHK(c, coe::k::regroup_index(c->d_cur, n, E, c->d_cnt, c->d_off, c->d_perm, c->d_inv, c->d_blockhist, nullptr, c->sc));
+    HIPCHK(c, coe::k::regroup_index(c->d_cur, n, E, c->d_cnt, c->d_off, c->d_perm, c->d_inv, c->d_blockhist, nullptr, nullptr, c->sc));
     HIPCHK(c, hipStreamSynchronize(c->sc));
     std::vector<int32_t> hoff(E + 1);
     HIPCHK(c, hipMemcpy(hoff.data(), c->d_off, ((size_t)E + 1) * 4, hipMemcpyDeviceToHost));

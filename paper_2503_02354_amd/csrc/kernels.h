@@ -29,9 +29,10 @@ struct RouteArgs {
 // Request arranging, index part: per-expert histogram, prefix scan, stable scatter of request indices.
 // cur[n]: expert id in [0,E) = pending, anything else = not pending.  cnt[E], off[E+1], perm[<=n], inv[n].
 // blockhist: scratch of ceil(n/kRegroupTile)*E int32.  heads, if not null: heads[e] = perm[off[e]] (the oldest queued
-// request of expert e: the regroup is stable) or -1 for an empty group.
+// request of expert e: the regroup is stable) or -1 for an empty group.  host, if not null: pinned host memory that receives
+// cnt[E] and, with heads, heads[E] behind it.
 hipError_t regroup_index(const int32_t* cur, int32_t n, int32_t E, int32_t* cnt, int32_t* off, int32_t* perm,
-                         int32_t* inv, int32_t* blockhist, int32_t* heads, hipStream_t stream);
+                         int32_t* inv, int32_t* blockhist, int32_t* heads, int32_t* host, hipStream_t stream);
 
 // The same with the histogram scratch in a static device array of kRegroupStaticInts int32 (no allocation anywhere on the
 // path): hipErrorInvalidValue when ceil(n / kRegroupTile) * E exceeds it.  Runs on the current device; calls on one device
@@ -39,6 +40,14 @@ hipError_t regroup_index(const int32_t* cur, int32_t n, int32_t E, int32_t* cnt,
 constexpr int kRegroupStaticInts = 1 << 20;
 hipError_t regroup_index_static(const int32_t* cur, int32_t n, int32_t E, int32_t* cnt, int32_t* off, int32_t* perm,
                                 int32_t* inv, hipStream_t stream);
+
+// The store's side of a submit in one launch: `bytes` of images from src to dst (both 16-byte aligned, bytes a multiple of 16; 0: the
+// images travel by another copy), n entries of cur (first[i], which may lie in pinned host memory, or 0) and depth (0), the path
+// words (-1) and the logits (0).
+hipError_t submit_store(const void* src, void* dst, size_t bytes, const int32_t* first, int32_t* cur, int32_t* depth, size_t n,
+                        int32_t* path, size_t path_words, float* logits, size_t logit_words, hipStream_t stream);
+// na + nb + nc 4-byte words of three arrays one behind the other into pinned host memory.
+hipError_t collect_words(const void* a, size_t na, const void* b, size_t nb, const void* c, size_t nc, void* out, hipStream_t stream);
 
 // Request arranging, activation part: dst row i = src row perm[i]; rows of row_bytes (multiple of 4) bytes.
 hipError_t gather_rows(const void* src, const int32_t* perm, int32_t n_rows, size_t row_bytes, void* dst,

@@ -518,6 +518,48 @@ def test_submits_in_a_row_through_the_pinned_ring(B, parts):
     assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1])
 
 
+@pytest.mark.parametrize("n,hw,shift", [(1, 16, 0), (1, 5, 0), (9, 16, 4), (130, 5, 0), (130, 16, 0), (5463, 16, 0), (200, 64, 16)])
+def test_device_inputs_and_known_counts(B, n, hw, shift):
+    """Submits from device memory that move in the launch which sets the store up (a multiple of 16 bytes from a 16-byte boundary on, at
+    most 16 MB) and those that do not (5 x 5 images, a shifted start, 16.8 MB) give the bits of host inputs.  A step regroups by the
+    counts the host knows (two submits into an empty store) as by those it reads back (a submit beside requests that have run), and a
+    store that was collected starts over."""
+    import torch
+    arch, E = W.tiny_cnn(4, hw), 3
+    rng = np.random.default_rng(n + hw)
+    x = rng.standard_normal((n, hw, hw, 3)).astype(np.float32)
+    first = rng.integers(0, E, n).astype(np.int32)
+    raw = torch.zeros(x.size + 8, dtype=torch.float32, device="cuda")
+    raw[shift // 4:shift // 4 + x.size] = torch.from_numpy(x.reshape(-1)).cuda()
+    torch.cuda.synchronize()
+    at = lambda i: raw.data_ptr() + shift + i * hw * hw * 3 * 4
+    out, cut = [], max(1, n // 3)
+    for on_device in (False, True):
+        ctx = B.Context(max_requests=2 * n, max_stages=1, max_batch=256)
+        aid = ctx.coe_register_arch(arch)
+        for e in range(E):
+            ctx.coe_register_expert(e, aid, W.make_expert_blob(arch, 7, e), 1.0 / E)
+        g = W.graph_from_lists([[]] * E)
+        ctx.coe_set_dependency_graph(g.succ_off, g.succ)
+        for _ in range(2):
+            for a, b in ((0, cut), (cut, n)):
+                if b > a:
+                    ctx.coe_submit(b - a, at(a) if on_device else x[a:b], on_device, first[a:b])
+            assert ctx.coe_step()[0] == B.COE_OK
+            r = ctx.coe_debug_last_regroup(2 * n)
+            assert np.array_equal(r["cnt"], np.bincount(first, minlength=E)) and np.array_equal(r["perm"], np.argsort(first, kind="stable"))
+            ctx.coe_submit(n, at(0) if on_device else x, on_device, first[::-1].copy())
+            assert ctx.coe_step()[0] == B.COE_OK
+            r = ctx.coe_debug_last_regroup(2 * n)
+            assert np.array_equal(r["cnt"], np.bincount(first, minlength=E)) and np.array_equal(r["perm"], n + np.argsort(first[::-1], kind="stable"))
+            assert ctx.coe_step()[0] == B.COE_DONE
+            ids, logits, path = ctx.coe_collect(2 * n)
+            assert np.array_equal(path[:, 0], np.concatenate([first, first[::-1]])) and len(ids) == 2 * n
+            out.append(logits)
+        ctx.close()
+    assert np.isfinite(out[0]).all() and all(np.array_equal(out[0], o) for o in out[1:])
+
+
 @pytest.mark.parametrize("n,experts,cap", [(30, 6, 0), (300, 9, 0), (60, 8, 5)])
 def test_grouped_transformers_give_the_same_bits(B, n, experts, cap):
     """Small groups of several transformer-shaped experts share launches: same logits, routes and switches, bit for bit, as one
