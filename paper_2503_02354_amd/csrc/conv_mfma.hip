@@ -34,6 +34,7 @@
 
 #include <type_traits>
 
+#include "activation.h"
 #include "kernels.h"
 
 namespace coe {
@@ -129,13 +130,14 @@ template <int N> __device__ __forceinline__ void gelu_for_bf16(float (&v)[N])
 __device__ __forceinline__ float act_fn(float v, int act)
 {
     if (act == 1) return v > 0.f ? v : 0.f;
-    if (act == 3) return v / (1.f + expf(-v));
     return v;
 }
 template <int ACT, int N> __device__ __forceinline__ void activate(float (&v)[N])
 {
     if (ACT == 2) {
         gelu_for_bf16(v);
+    } else if (ACT == 3) {
+        silu_for_bf16(v);
     } else {
 #pragma unroll
         for (int i = 0; i < N; ++i) v[i] = act_fn(v[i], ACT);

@@ -18,6 +18,7 @@
 
 #include <type_traits>
 
+#include "activation.h"
 #include "kernels.h"
 
 namespace coe {
@@ -52,7 +53,6 @@ __device__ __forceinline__ float act_fn(float v, int act)
 {
     if (act == 1) return v > 0.f ? v : 0.f;
     if (act == 2) return 0.5f * v * erfcf(-v * 0.70710678118654752440f);
-    if (act == 3) return v / (1.f + expf(-v));
     return v;
 }
 template <typename F> __device__ __forceinline__ void with_activation(int act, F&& body)
@@ -246,8 +246,16 @@ __global__ __launch_bounds__(kThreads, 4) void conv_smallc_bf16_kernel(const uin
                     const int ch = jn * 32 + 8 * gq + half * 4;
                     const float4 bv = *(const float4*)(bias + ch);
                     uint2 o;
-                    o.x = pack_bf16(act_fn(acc[i][jn][4 * gq + 0] + bv.x, ACT), act_fn(acc[i][jn][4 * gq + 1] + bv.y, ACT));
-                    o.y = pack_bf16(act_fn(acc[i][jn][4 * gq + 2] + bv.z, ACT), act_fn(acc[i][jn][4 * gq + 3] + bv.w, ACT));
+                    float v[4] = {acc[i][jn][4 * gq + 0] + bv.x, acc[i][jn][4 * gq + 1] + bv.y, acc[i][jn][4 * gq + 2] + bv.z,
+                                  acc[i][jn][4 * gq + 3] + bv.w};
+                    if constexpr (ACT == 3) {
+                        silu_for_bf16(v);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = act_fn(v[e], ACT);
+                    }
+                    o.x = pack_bf16(v[0], v[1]);
+                    o.y = pack_bf16(v[2], v[3]);
                     if (POOL) {
                         // outside the conv output: -inf (or 0 after ReLU, see the pool below) never wins the max
                         if (!inside) o = ACT == 1 ? make_uint2(0u, 0u) : make_uint2(0xFF80FF80u, 0xFF80FF80u);

@@ -307,6 +307,83 @@ def test_gelu_rounds_like_the_fp32_path(B, C, pixels):
     assert int(np.sum((got != want) & ~nan)) == 0
 
 
+@pytest.mark.parametrize("C,K,pixels", [(64, 64, 200), (64, 64, 6000), (64, 64, 40000), (96, 96, 3000), (512, 512, 33000), (4, 32, 5000)])
+def test_silu_rounds_like_the_fp32_path(B, C, K, pixels):
+    """SiLU in the bf16 epilogues (the kernels of the GELU test, then the one for few input channels) gives the rounded value of the plain
+    formula, which fp32 experts evaluate, bit for bit: an identity convolution, so that the value before the activation is one fp32 sum of
+    a bf16 number and a bias on both paths."""
+    rng = np.random.default_rng(C + pixels)
+    scale = np.exp(rng.uniform(np.log(1e-3), np.log(12.0), (1, pixels, 1, C)))
+    x = W.f32_to_bf16_bits((rng.standard_normal((1, pixels, 1, C)) * scale).astype(np.float32)).reshape(1, pixels, 1, C)
+    bias = rng.standard_normal(K).astype(np.float32)
+    bias[:12] = [-np.inf, np.inf, np.nan, -9.9, 10.1, -30.0, 80.0, 1e30, -1e30, 0.0, -87.5, -89.0]
+    eye = np.eye(K, C, dtype=np.float32).reshape(K, 1, 1, C)
+    ctx = B.Context(max_requests=1)
+    got, _ = ctx.coe_debug_conv(1, x, W.f32_to_bf16_bits(eye).reshape(eye.shape), bias, None, 1, 0, W.ACT_SILU)
+    plain, _ = ctx.coe_debug_conv(0, W.bf16_bits_to_f32(x).reshape(x.shape), eye, bias, None, 1, 0, W.ACT_SILU)
+    ctx.close()
+    same, nan = got == W.f32_to_bf16_bits(plain).reshape(got.shape), np.isnan(plain)
+    assert np.all(same | nan) and np.isnan(W.bf16_bits_to_f32(got[nan])).all() and nan[..., 2].all()
+
+
+@pytest.mark.parametrize("H,Wd,C,R,pad", [(14, 14, 256, 5, 2), (7, 9, 64, 5, 2), (22, 23, 32, 5, 2), (20, 20, 96, 5, 2), (13, 13, 64, 7, 3),
+                                          (9, 9, 64, 5, 1), (5, 5, 32, 5, 0), (60, 60, 64, 5, 2), (14, 14, 64, 3, 1), (6, 6, 40, 5, 2)])
+def test_pools_with_stride_one(B, H, Wd, C, R, pad):
+    """Stride-1 pools in LDS (eight and four chunks of channels, windows larger than the rest of the map) and those that stay on the kernel
+    for all pools (a map that does not fit, small windows, odd channel counts): the maximum of the window's numbers, minus infinity
+    where there is none."""
+    n = 3
+    p = W._Prog(H, Wd, C); p.maxpool(0, 1, R, 1, pad); p.head(1, 4)
+    arch = W.Arch("pool", W.DT_BF16, H, Wd, C, 4, np.array(p.layers, dtype=np.int32), p.gains)
+    rng = np.random.default_rng(H * C + R)
+    x = W.bf16_bits_to_f32(_bf16(rng, n, H, Wd, C)).reshape(n, H, Wd, C).copy()
+    x[rng.random(x.shape) < 0.2] = -np.inf
+    x[rng.random(x.shape) < 0.1] = np.nan
+    x[rng.random(x.shape) < 0.1] = -3.3895e38
+    x[0, :, :, 0], x[1, :, :, 1], x[2, :, :, 2] = np.nan, -np.inf, np.inf
+    bits = W.f32_to_bf16_bits(x).reshape(x.shape)
+    x = W.bf16_bits_to_f32(bits).reshape(x.shape)
+    ctx = B.Context(max_requests=n, max_batch=n)
+    aid = ctx.coe_register_arch(arch)
+    ctx.coe_register_expert(0, aid, W.make_expert_blob(arch, 7, 0), 1.0)
+    import torch
+    dev = torch.from_numpy(bits.view(np.int16)).cuda()
+    P, Q = H + 2 * pad - R + 1, Wd + 2 * pad - R + 1
+    got = ctx.coe_debug_layer_output(0, n, dev.data_ptr(), 0, (n, P, Q, C), np.uint16)
+    ctx.close()
+    padded = np.full((n, H + 2 * pad, Wd + 2 * pad, C), -np.inf, np.float32)
+    padded[:, pad:pad + H, pad:pad + Wd] = x
+    want = np.full((n, P, Q, C), -np.inf, np.float32)
+    for r in range(R):
+        for s in range(R):
+            want = np.fmax(want, padded[:, r:r + P, s:s + Q])
+    assert np.array_equal(W.bf16_bits_to_f32(got).reshape(want.shape), want)
+
+
+@pytest.mark.parametrize("n,H,Wd,C,K,R,stride,pad,act", [
+    (3, 45, 50, 3, 64, 6, 2, 2, 3),      # reduction unrolled, outputs through LDS, ragged tiles
+    (2, 16, 16, 3, 64, 6, 2, 2, 1),      # less than a tile
+    (2, 33, 30, 4, 32, 3, 1, 1, 2),      # 32 filters through LDS
+    (2, 20, 20, 4, 64, 9, 1, 4, 0),      # filters and patch leave no room: stores out of the accumulators
+])
+def test_few_channels_without_pool(B, oracle, n, H, Wd, C, K, R, stride, pad, act):
+    """The kernel for few input channels without the fused pool, every output against the oracle."""
+    rng = np.random.default_rng(H + K + R)
+    x = _bf16(rng, n, H, Wd, C)
+    w = _bf16(rng, K, R, R, C, scale=np.sqrt(2.0 / (R * R * C)))
+    bias = (0.1 * rng.standard_normal(K)).astype(np.float32)
+    ctx = B.Context(max_requests=1)
+    got, cls = ctx.coe_debug_conv(1, x, w, bias, None, stride, pad, act)
+    ctx.close()
+    assert B.KERNEL_CLASS_NAMES[cls] == "conv_stem"
+    xf, wf = (W.bf16_bits_to_f32(a).reshape(a.shape) for a in (x, w))
+    want = np.stack([oracle.conv2d(xf[i], wf, bias, None, stride, pad, act, 1) for i in range(n)])
+    g = W.bf16_bits_to_f32(got).reshape(want.shape)
+    # as in test_few_tiles_give_the_bits_of_many
+    assert np.all(np.abs(g - want) <= np.maximum(np.abs(want) * 2.0 ** -7, 1e-5))
+    assert np.mean(g == want) > 0.995
+
+
 @pytest.mark.parametrize("T,heads,n", [(17, 12, 5), (31, 3, 1), (33, 2, 3), (65, 12, 2), (97, 1, 5), (129, 3, 2), (160, 2, 1), (192, 1, 3),
                                        (193, 3, 2), (197, 12, 29)])
 def test_attention_block_counts(B, oracle, T, heads, n):
