@@ -40,6 +40,7 @@ struct LayerPlan {
     bool packed = false;    // conv filters are stored in matrix-core fragment order (device and pinned copies)
     bool fuse_pool = false; // conv: the max pool that follows runs inside the conv kernel, which writes the pool's dst
     bool fused_away = false;// pool: done by the preceding conv kernel
+    bool pairs = false;     // matrix-core conv independent of the next layer, another one: they share a launch where few tiles are to do
     bool patchify = false;  // conv with stride == window and no padding: patches are gathered into GEMM rows, then a 1x1 conv
 };
 
@@ -405,6 +406,15 @@ int plan_arch(coe_ctx* c, const coe_arch_desc* d, ArchPlan& a)
         if (read_later) continue;
         cv.fuse_pool = true;
         pl.fused_away = true;
+    }
+    // neighbouring convs on the matrix cores of which neither reads or overwrites what the other writes (a projection beside the
+    // first conv of its block, the two branches of a cross-stage block)
+    for (size_t i = 0; i + 1 < a.layers.size(); ++i) {
+        LayerPlan& u = a.layers[i];
+        const LayerPlan& v = a.layers[i + 1];
+        const bool convs = u.d.op == COE_OP_CONV && v.d.op == COE_OP_CONV && u.packed && v.packed && !u.patchify && !v.patchify;
+        const bool apart = u.d.dst != v.d.src && u.d.dst != v.d.res && u.d.dst != v.d.dst && v.d.dst != u.d.src && v.d.dst != u.d.res;
+        u.pairs = convs && apart && !(i > 0 && a.layers[i - 1].pairs);
     }
     // activation buffers per request: what the launched kernels write (a conv fused with its pool writes the pool's output)
     for (const LayerPlan& L : a.layers) {
@@ -774,6 +784,20 @@ int issue_load(coe_ctx* c, const coe::Switch& sw, coe_step_stats* st, coe_step_s
     return COE_OK;
 }
 
+coe::k::ConvShape conv_shape(const LayerPlan& L, int32_t n)
+{
+    return {n, L.H, L.W, L.C, L.K, L.d.r, L.d.s, L.d.stride, L.d.pad, L.P, L.Q, L.d.act};
+}
+// done: both convolutions have been launched
+int run_pair(coe_ctx* c, Lane& ln, const coe::k::ConvCall& a, const coe::k::ConvCall& b, double flops, const coe::k::GroupTable* groups, bool& done)
+{
+    if (!coe::k::conv_mfma_pairable(a.s, b.s, groups)) return COE_OK;
+    Span sp(c, COE_K_CONV_MFMA, flops, ln.s);
+    HIPCHK(c, coe::k::conv_mfma_pair(a, b, groups, ln.s));
+    done = true;
+    return COE_OK;
+}
+
 // ---- one expert over one batch ---------------------------------------------------------------------------------------
 // rows: the batch is rows[0..n) of the array at `input` (only for architectures whose first kernel follows a row table)
 int run_expert(coe_ctx* c, Lane& ln, const Expert& x, const void* weights, const void* input, int32_t n,
@@ -783,9 +807,19 @@ int run_expert(coe_ctx* c, Lane& ln, const Expert& x, const void* weights, const
     const ArchPlan& a = c->archs[x.arch];
     const uint8_t* wb = (const uint8_t*)weights;
     auto buf = [&](int id) -> void* { return id == 0 ? const_cast<void*>(input) : ln.d_buf[id]; };
+    bool done = false;                  // by the launch of the layer before
     for (const LayerPlan& L : a.layers) {
         const coe_layer& l = L.d;
         if (last_layer >= 0 && ++li > last_layer) break;
+        if (done) { done = false; continue; }
+        if (L.pairs && last_layer < 0) {
+            auto call = [&](const LayerPlan& v) {
+                return coe::k::ConvCall{buf(v.d.src), wb + v.off[0], (const float*)(wb + v.off[1]), v.d.res >= 0 ? buf(v.d.res) : nullptr,
+                                        buf(v.d.dst), conv_shape(v, n), 0, 0};
+            };
+            if (int rc = run_pair(c, ln, call(L), call(*(&L + 1)), 2.0 * (L.macs + (&L + 1)->macs) * n, nullptr, done)) return rc;
+            if (done) continue;
+        }
         switch (l.op) {
         case COE_OP_CONV: {
             coe::k::ConvShape s{n, L.H, L.W, L.C, L.K, l.r, l.s, l.stride, l.pad, L.P, L.Q, l.act};
@@ -911,8 +945,19 @@ int run_group_set(coe_ctx* c, Lane& ln, const std::vector<SetMember>& set, const
     }
     gt.first_row[set.size()] = n;
     auto buf = [&](int id) -> uint8_t* { return (uint8_t*)ln.d_buf[id]; };
+    bool done = false;                  // by the launch of the layer before
     for (const LayerPlan& L : a.layers) {
         const coe_layer& l = L.d;
+        if (done) { done = false; continue; }
+        if (L.pairs) {
+            if (l.src == 0 || (&L + 1)->d.src == 0) return fail(c, COE_ESTATE, "internal: grouped matrix-core conv on the raw input");
+            auto call = [&](const LayerPlan& v) {
+                return coe::k::ConvCall{buf(v.d.src), nullptr, nullptr, v.d.res >= 0 ? buf(v.d.res) : nullptr, buf(v.d.dst), conv_shape(v, n),
+                                        v.off[0], v.off[1]};
+            };
+            if (int rc = run_pair(c, ln, call(L), call(*(&L + 1)), 2.0 * (L.macs + (&L + 1)->macs) * n, &gt, done)) return rc;
+            if (done) continue;
+        }
         switch (l.op) {
         case COE_OP_CONV: {
             coe::k::ConvShape s{n, L.H, L.W, L.C, L.K, l.r, l.s, l.stride, l.pad, L.P, L.Q, l.act};

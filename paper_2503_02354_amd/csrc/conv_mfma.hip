@@ -1114,13 +1114,24 @@ template <int BEGIN, int END, typename F> __device__ __forceinline__ void static
     }
 }
 
-template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES, bool GELU>
+// The other convolution of a launch that does two (PAIR): its tiles follow the first one's
+struct RingSecond {
+    ConvShape s;
+    int32_t M, tiles_n;
+    uint32_t off_w, off_b;
+    uint32_t first_tiles;      // tiles of the first convolution
+};
+
+template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES, bool GELU, bool PAIR>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel(const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ wp_all,
                                                                    const float* __restrict__ bias_all,
                                                                    const uint16_t* __restrict__ res,
                                                                    uint16_t* __restrict__ y, ConvShape s, int M,
-                                                                   int tiles_n, GroupTable gt, uint32_t off_w, uint32_t off_b)
+                                                                   int tiles_n, GroupTable gt, uint32_t off_w, uint32_t off_b,
+                                                                   const uint16_t* __restrict__ x2, const uint16_t* __restrict__ wp2,
+                                                                   const float* __restrict__ bias2, const uint16_t* __restrict__ res2,
+                                                                   uint16_t* __restrict__ y2, RingSecond second)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BK = 32, KS = 2;
@@ -1139,6 +1150,26 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
     int tile;
     {
         int L = blockIdx.x, total = gridDim.x;
+        if (PAIR) {
+            const int first = (int)second.first_tiles;
+            const bool is_second = L >= first;
+            L = is_second ? L - first : L;
+            total = is_second ? total - first : first;
+            x = is_second ? x2 : x;
+            wp_all = is_second ? wp2 : wp_all;
+            bias_all = is_second ? bias2 : bias_all;
+            res = is_second ? res2 : res;
+            y = is_second ? y2 : y;
+            // (member by member: a choice between the two structures would go through scratch memory)
+            auto pick = [&](int32_t& a, int32_t b) { a = is_second ? b : a; };
+            pick(s.N, second.s.N); pick(s.H, second.s.H); pick(s.W, second.s.W); pick(s.C, second.s.C);
+            pick(s.K, second.s.K); pick(s.R, second.s.R); pick(s.S, second.s.S); pick(s.stride, second.s.stride);
+            pick(s.pad, second.s.pad); pick(s.P, second.s.P); pick(s.Q, second.s.Q); pick(s.act, second.s.act);
+            M = is_second ? second.M : M;
+            tiles_n = is_second ? second.tiles_n : tiles_n;
+            off_w = is_second ? second.off_w : off_w;
+            off_b = is_second ? second.off_b : off_b;
+        }
         int xcd = L % kXcds, slot = L / kXcds;
         int base = total / kXcds, rem = total % kXcds;
         tile = xcd * base + (xcd < rem ? xcd : rem) + slot;
@@ -1323,26 +1354,43 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
 #endif
 }
 
-template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES, bool GELU = false>
-hipError_t launch_ring(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
-                       hipStream_t stream, const Grouping& grp = Grouping())
+struct ConvArgs {
+    const void *x, *wp;
+    const float* bias;
+    const void* res;
+    void* y;
+    ConvShape s;
+    Grouping grp;
+};
+
+// b != nullptr: a second convolution, over the same groups, in the same launch
+template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES, bool GELU = false, bool PAIR = false>
+hipError_t launch_ring(const ConvArgs& a, hipStream_t stream, const ConvArgs* b = nullptr)
 {
-    if constexpr (!GELU)
-        if (s.act == 2) return launch_ring<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, true>(x, wp, bias, res, y, s, stream, grp);
+    if constexpr (!GELU && !PAIR)
+        if (a.s.act == 2) return launch_ring<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, true>(a, stream);
+    if constexpr (!GELU && !PAIR && !SLAB_ORDER)
+        if (b) return launch_ring<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, false, true>(a, stream, b);
     constexpr int BM = 32 * MB * WAVES_M, BN = 32 * NB * WAVES_N;
-    long long M = (long long)s.N * s.P * s.Q;
-    int tiles_n = s.K / BN;
-    long long total = count_tiles(M, (long long)s.P * s.Q, BM, tiles_n, grp.table);
+    const long long M = (long long)a.s.N * a.s.P * a.s.Q;
+    long long total = count_tiles(M, (long long)a.s.P * a.s.Q, BM, a.s.K / BN, a.grp.table);
+    RingSecond second{};
+    if (PAIR) {
+        const long long M2 = (long long)b->s.N * b->s.P * b->s.Q;
+        second = {b->s, (int32_t)M2, b->s.K / BN, b->grp.off_w, b->grp.off_b, (uint32_t)total};
+        total += count_tiles(M2, (long long)b->s.P * b->s.Q, BM, b->s.K / BN, b->grp.table);
+    }
     if (total > 0x7FFFFFFFll) return hipErrorInvalidValue;
     if (total == 0) return hipSuccess;
     constexpr size_t kLdsBytes = STAGES * UN * (size_t)(BM + BN) * 32 * sizeof(uint16_t);
     static_assert(kLdsBytes <= 160 * 1024 && kLdsBytes >= (size_t)WAVES_M * WAVES_N * 32 * (32 * NB + 8) * 2, "operand stages and epilogue rows");
-    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, GELU>,
+    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, GELU, PAIR>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
     if (configured != hipSuccess) return configured;
-    hipLaunchKernelGGL((conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, GELU>), dim3((unsigned)total), dim3(64 * WAVES_M * WAVES_N),
-                       kLdsBytes, stream, (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M,
-                       tiles_n, grp.table, grp.off_w, grp.off_b);
+    hipLaunchKernelGGL((conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, GELU, PAIR>), dim3((unsigned)total), dim3(64 * WAVES_M * WAVES_N),
+                       kLdsBytes, stream, (const uint16_t*)a.x, (const uint16_t*)a.wp, a.bias, (const uint16_t*)a.res, (uint16_t*)a.y, a.s, (int)M,
+                       a.s.K / BN, a.grp.table, a.grp.off_w, a.grp.off_b, b ? (const uint16_t*)b->x : nullptr, b ? (const uint16_t*)b->wp : nullptr,
+                       b ? b->bias : nullptr, b ? (const uint16_t*)b->res : nullptr, b ? (uint16_t*)b->y : nullptr, second);
     return hipGetLastError();
 }
 
@@ -1725,29 +1773,45 @@ hipError_t conv_gemm(const void* x, const void* wp, const float* bias, const voi
     return launch_dma<128, 64, 2, 2>(x, wp, bias, res, y, s, stream, grp);
 }
 
-// hipErrorNotSupported: not a launch for these tiles
-hipError_t conv_ring(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
-                     hipStream_t stream, const Grouping& grp = Grouping())
+// The tiles of a launch with few of them; none: not a launch for these tiles
+enum class Ring { none, slab32, deep32, shallow32, slab64_3, slab64_1, tile64 };
+Ring ring_tiles(const ConvShape& s, const GroupTable& gt)
 {
     const bool slab = conv_mfma_uses_slab(s);
     const int cblocks = s.C / 32;
-    if (!slab && cblocks % 2) return hipErrorNotSupported;       // a stage holds channel blocks of one window position
+    if (!slab && cblocks % 2) return Ring::none;                 // a stage holds channel blocks of one window position
     const long long M = (long long)s.N * s.P * s.Q, PQ = (long long)s.P * s.Q;
-    if (count_tiles(M, PQ, 32, s.K / 32, grp.table) <= kRingTiles32) {
-        if (slab) return launch_ring<true, 1, 1, 1, 1, 3, 6>(x, wp, bias, res, y, s, stream, grp);
-        if (cblocks % 4 == 0) return launch_ring<false, 1, 1, 1, 1, 4, 4>(x, wp, bias, res, y, s, stream, grp);
-        return launch_ring<false, 1, 1, 1, 1, 2, 6>(x, wp, bias, res, y, s, stream, grp);
-    }
-    const long long tiles64 = count_tiles(M, PQ, 64, s.K / 64, grp.table);
+    if (count_tiles(M, PQ, 32, s.K / 32, gt) <= kRingTiles32)
+        return slab ? Ring::slab32 : cblocks % 4 == 0 ? Ring::deep32 : Ring::shallow32;
+    const long long tiles64 = count_tiles(M, PQ, 64, s.K / 64, gt);
     if (s.K % 64 == 0 && tiles64 <= (slab ? kRingTiles64Slab : kRingTiles64)) {
         // 3x3: one workgroup per compute unit has its LDS to itself, with more tiles than that two share it.  Nine steps in
         // three stages (72 KB) were too shallow for filters that come from memory: 512 -> 512 over 29 images of 15 groups
         // took 42 us, with five stages or nine single-step ones in flight 22.
-        if (slab && tiles64 <= 256) return launch_ring<true, 1, 1, 2, 2, 3, 5>(x, wp, bias, res, y, s, stream, grp);
-        if (slab) return launch_ring<true, 1, 1, 2, 2, 1, 10>(x, wp, bias, res, y, s, stream, grp);
-        return launch_ring<false, 1, 1, 2, 2, 2, 5>(x, wp, bias, res, y, s, stream, grp);
+        return !slab ? Ring::tile64 : tiles64 <= 256 ? Ring::slab64_3 : Ring::slab64_1;
+    }
+    return Ring::none;
+}
+// hipErrorNotSupported: not a launch for these tiles
+hipError_t conv_ring(const ConvArgs& a, hipStream_t stream, const ConvArgs* b = nullptr)
+{
+    switch (ring_tiles(a.s, a.grp.table)) {
+    case Ring::slab32: return launch_ring<true, 1, 1, 1, 1, 3, 6>(a, stream);
+    case Ring::deep32: return launch_ring<false, 1, 1, 1, 1, 4, 4>(a, stream, b);
+    case Ring::shallow32: return launch_ring<false, 1, 1, 1, 1, 2, 6>(a, stream, b);
+    case Ring::slab64_3: return launch_ring<true, 1, 1, 2, 2, 3, 5>(a, stream);
+    case Ring::slab64_1: return launch_ring<true, 1, 1, 2, 2, 1, 10>(a, stream);
+    case Ring::tile64: return launch_ring<false, 1, 1, 2, 2, 2, 5>(a, stream, b);
+    case Ring::none: break;
     }
     return hipErrorNotSupported;
+}
+
+// 31-bit byte offsets inside the kernels (buffer offsets; bit 31 marks "out of range")
+bool offsets_fit(const ConvShape& s)
+{
+    return (long long)s.N * s.H * s.W * s.C * 2 < 0x7FFFFFFFll && (long long)s.K * s.R * s.S * s.C * 2 < 0x7FFFFFFFll &&
+           (long long)s.N * s.P * s.Q < 0x7FFFFFFFll - 256;
 }
 
 template <int BK>
@@ -1785,11 +1849,8 @@ hipError_t conv_mfma(const void* x, const void* wp, const float* bias, const voi
     if (!conv_mfma_supported(s)) return hipErrorInvalidValue;
     long long M = (long long)s.N * s.P * s.Q;
     if (M <= 0) return hipSuccess;
-    // 31-bit byte offsets inside the kernel (buffer offsets; bit 31 marks "out of range")
-    if ((long long)s.N * s.H * s.W * s.C * 2 >= 0x7FFFFFFFll || (long long)s.K * s.R * s.S * s.C * 2 >= 0x7FFFFFFFll ||
-        M >= 0x7FFFFFFFll - 256)
-        return hipErrorInvalidValue;
-    const hipError_t ring = conv_ring(x, wp, bias, res, y, s, stream);
+    if (!offsets_fit(s)) return hipErrorInvalidValue;
+    const hipError_t ring = conv_ring(ConvArgs{x, wp, bias, res, y, s, Grouping()}, stream);
     if (ring != hipErrorNotSupported) return ring;
     // 32-channel steps everywhere: measured equal or better than 64-channel steps on every ResNet layer shape
     if (conv_mfma_uses_slab(s)) {
@@ -1807,24 +1868,25 @@ bool conv_mfma_groupable(const ConvShape& s)
     return conv_mfma_supported(s) && s.K % 64 == 0;
 }
 
-hipError_t conv_mfma_grouped(const void* x, const GroupTable& groups, size_t off_w, size_t off_b, const void* res, void* y,
-                             const ConvShape& s, hipStream_t stream)
+static bool valid_groups(const GroupTable& groups, size_t off_w, size_t off_b, const ConvShape& s)
 {
     if (!conv_mfma_groupable(s) || groups.n <= 0 || groups.n > kMaxGroups || groups.first_row[0] != 0 ||
         groups.first_row[groups.n] != s.N || off_w > 0x7FFFFFFFull || off_b > 0x7FFFFFFFull)
-        return hipErrorInvalidValue;
+        return false;
     for (int g = 0; g < groups.n; ++g)
-        if (groups.first_row[g + 1] < groups.first_row[g] || !groups.weights[g]) return hipErrorInvalidValue;
+        if (groups.first_row[g + 1] < groups.first_row[g] || !groups.weights[g]) return false;
+    return true;
+}
+
+hipError_t conv_mfma_grouped(const void* x, const GroupTable& groups, size_t off_w, size_t off_b, const void* res, void* y,
+                             const ConvShape& s, hipStream_t stream)
+{
+    if (!valid_groups(groups, off_w, off_b, s)) return hipErrorInvalidValue;
     long long M = (long long)s.N * s.P * s.Q;
     if (M <= 0) return hipSuccess;
-    if ((long long)s.N * s.H * s.W * s.C * 2 >= 0x7FFFFFFFll || (long long)s.K * s.R * s.S * s.C * 2 >= 0x7FFFFFFFll ||
-        M >= 0x7FFFFFFFll - 256)
-        return hipErrorInvalidValue;
-    Grouping grp;
-    grp.table = groups;
-    grp.off_w = (uint32_t)off_w;
-    grp.off_b = (uint32_t)off_b;
-    const hipError_t ring = conv_ring(x, nullptr, nullptr, res, y, s, stream, grp);
+    if (!offsets_fit(s)) return hipErrorInvalidValue;
+    const Grouping grp{groups, (uint32_t)off_w, (uint32_t)off_b};
+    const hipError_t ring = conv_ring(ConvArgs{x, nullptr, nullptr, res, y, s, grp}, stream);
     if (ring != hipErrorNotSupported) return ring;
     // every group starts a fresh row of tiles: 128-row tiles waste fewer rows past the end of a small group, 256-row
     // tiles (twice the accumulator rows per wave and operand read) are the faster ones where that waste stays small
@@ -1838,6 +1900,31 @@ hipError_t conv_mfma_grouped(const void* x, const GroupTable& groups, size_t off
                     : launch_slab<128, 64, 4, 1>(x, nullptr, nullptr, res, y, s, stream, grp);
     }
     return conv_gemm(x, nullptr, nullptr, res, y, s, stream, grp);
+}
+
+// Two launches of few tiles each leave most of the chip idle, and the second waits for the first for nothing: a launch with the
+// tiles of both takes the time of the longer one.  The tiles are those that each would take by itself, so the bits are the same.
+// Launches that fill the chip gain nothing by sharing it, and pairs whose tiles differ would need a kernel per combination: these
+// stay apart.  Passes with a launch for each / with shared ones, us: one ResNet-18 request (three pairs per expert) 324 / 308, 29 requests
+// 755 / 735.
+bool conv_mfma_pairable(const ConvShape& a, const ConvShape& b, const GroupTable* groups)
+{
+    const GroupTable none{};
+    for (const ConvShape* s : {&a, &b})
+        if (!conv_mfma_supported(*s) || (long long)s->N * s->P * s->Q <= 0 || !offsets_fit(*s) || s->act == 2 || conv_mfma_uses_slab(*s))
+            return false;
+    const Ring tiles = ring_tiles(a, groups ? *groups : none);
+    return tiles != Ring::none && tiles == ring_tiles(b, groups ? *groups : none);
+}
+
+hipError_t conv_mfma_pair(const ConvCall& a, const ConvCall& b, const GroupTable* groups, hipStream_t stream)
+{
+    if (!conv_mfma_pairable(a.s, b.s, groups)) return hipErrorInvalidValue;
+    if (groups && (!valid_groups(*groups, a.off_w, a.off_b, a.s) || !valid_groups(*groups, b.off_w, b.off_b, b.s))) return hipErrorInvalidValue;
+    const GroupTable& gt = groups ? *groups : GroupTable{};
+    const ConvArgs a1{a.x, a.wp, a.bias, a.res, a.y, a.s, Grouping{gt, (uint32_t)a.off_w, (uint32_t)a.off_b}};
+    const ConvArgs b1{b.x, b.wp, b.bias, b.res, b.y, b.s, Grouping{gt, (uint32_t)b.off_w, (uint32_t)b.off_b}};
+    return conv_ring(a1, stream, &b1);
 }
 
 }  // namespace k

@@ -101,6 +101,19 @@ hipError_t conv_mfma(const void* x, const void* w, const float* bias, const void
 bool conv_mfma_groupable(const ConvShape& s);
 hipError_t conv_mfma_grouped(const void* x, const GroupTable& groups, size_t off_w, size_t off_b, const void* res, void* y,
                              const ConvShape& s, hipStream_t stream);
+// Two convolutions that do not read or write each other's outputs in one launch, with the bits of two.  groups == nullptr: wp and bias
+// are the filters, else the offsets off_w and off_b as in the grouped form.  conv_mfma_pairable: both are launches of few tiles, of
+// one kind; every other pair is called one by one.
+struct ConvCall {
+    const void *x, *wp;
+    const float* bias;
+    const void* res;
+    void* y;
+    ConvShape s;
+    size_t off_w, off_b;
+};
+bool conv_mfma_pairable(const ConvShape& a, const ConvShape& b, const GroupTable* groups);
+hipError_t conv_mfma_pair(const ConvCall& a, const ConvCall& b, const GroupTable* groups, hipStream_t stream);
 
 // bf16 convolution with few input channels (C not a multiple of 32, e.g. the C=3 stem) on the matrix cores.
 // Requires K in {32, 64}, stride*C even, no residual.  fused_pool: the 3x3 / stride 2 / pad 1 max pool that follows is

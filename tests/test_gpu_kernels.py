@@ -637,6 +637,56 @@ def test_device_inputs_and_known_counts(B, n, hw, shift):
     assert np.isfinite(out[0]).all() and all(np.array_equal(out[0], o) for o in out[1:])
 
 
+@pytest.mark.parametrize("C,hw,n", [(64, 16, 1), (64, 16, 33), (128, 16, 7), (128, 16, 200), (128, 20, 150), (96, 16, 5)])
+def test_independent_convolutions_share_a_launch_with_the_same_bits(B, C, hw, n):
+    """Neighbouring convolutions that do not depend on each other run in one launch where both have few tiles (32 x 32 tiles with two or
+    four channel blocks to a stage, 64 x 64 tiles), alone and in groups: the bits of a batch of 700, whose launches are apart.  96
+    channels have no such tiles.  Neighbours that read or overwrite each other's outputs stay in order."""
+    import torch
+    K, many, E = 128, 700, 3
+    p = W._Prog(hw, hw, 3, n_scratch=7)
+    p.conv(0, 1, 64, 3, 1, 1, W.ACT_RELU)
+    p.conv(1, 2, C, 1, 1, 0, W.ACT_RELU)
+    p.conv(2, 3, K, 3, 2, 1, W.ACT_RELU)                 # a strided convolution and the projection beside it
+    p.conv(2, 4, K, 1, 2, 0, W.ACT_NONE)
+    p.conv(3, 5, K, 3, 1, 1, W.ACT_RELU, res=4, gain=0.5)
+    p.conv(5, 1, K // 2, 1, 1, 0, W.ACT_SILU)            # two branches
+    p.conv(5, 2, K // 2, 1, 1, 0, W.ACT_SILU)
+    p.conv(1, 3, K, 1, 1, 0, W.ACT_NONE)                 # the second reads the first as its residual
+    p.conv(2, 4, K, 1, 1, 0, W.ACT_RELU, res=3)
+    p.conv(4, 6, 2 * K, 1, 2, 0, W.ACT_NONE)             # unlike shapes
+    p.conv(4, 7, K // 2, 1, 1, 0, W.ACT_RELU)
+    p.conv(7, 1, K, 1, 1, 0, W.ACT_RELU)                 # the second overwrites what the first reads
+    p.conv(4, 7, K // 2, 1, 1, 0, W.ACT_RELU)
+    p.conv(7, 2, K, 1, 1, 0, W.ACT_RELU, res=1)
+    p.conv(2, 3, 2 * K, 3, 2, 1, W.ACT_RELU, res=6, gain=0.5)
+    p.head(3, 6)
+    arch = W.Arch("pairs", W.DT_BF16, hw, hw, 3, 6, np.array(p.layers, dtype=np.int32), p.gains)
+    blobs = [W.make_expert_blob(arch, 11, e) for e in range(E)]
+    x = torch.randn((many, hw, hw, 3), generator=torch.Generator().manual_seed(C + hw)).bfloat16().cuda()
+    first = np.random.default_rng(n).integers(0, E, n).astype(np.int32)
+    got = {}
+    for small in (-1, 64):
+        ctx = B.Context(max_requests=many, max_stages=1, max_batch=many, group_small=small)
+        aid = ctx.coe_register_arch(arch)
+        for e, blob in enumerate(blobs):
+            ctx.coe_register_expert(e, aid, blob, 1.0 / E)
+        g = W.graph_from_lists([[]] * E)
+        ctx.coe_set_dependency_graph(g.succ_off, g.succ)
+        ctx.coe_submit(n, x.data_ptr(), True, first)
+        while ctx.coe_step()[0] != B.COE_DONE:
+            pass
+        got[small] = ctx.coe_collect(n)[1]
+        if small < 0:
+            want = np.stack([ctx.coe_debug_forward(e, many, x.data_ptr()) for e in range(E)])
+            few = np.stack([ctx.coe_debug_forward(e, n, x.data_ptr()) for e in range(E)])
+        ctx.close()
+    assert np.isfinite(want).all() and want.std() > 0
+    assert np.array_equal(few, want[:, :n])
+    for logits in got.values():
+        assert np.array_equal(logits, want[first, np.arange(n)])
+
+
 @pytest.mark.parametrize("n,experts,cap", [(30, 6, 0), (300, 9, 0), (60, 8, 5)])
 def test_grouped_transformers_give_the_same_bits(B, n, experts, cap):
     """Small groups of several transformer-shaped experts share launches: same logits, routes and switches, bit for bit, as one
