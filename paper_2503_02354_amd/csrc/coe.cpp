@@ -26,7 +26,8 @@
 
 namespace {
 
-constexpr int kMaxBufs = 8;
+constexpr int kMaxBufs = 8;             // that a description may name
+constexpr int kPlanBufs = 12;           // that a plan may use
 constexpr size_t kBlobAlign = 256;
 
 size_t align_up(size_t x, size_t a = kBlobAlign) { return (x + a - 1) / a * a; }
@@ -41,6 +42,10 @@ struct LayerPlan {
     bool fuse_pool = false; // conv: the max pool that follows runs inside the conv kernel, which writes the pool's dst
     bool fused_away = false;// pool: done by the preceding conv kernel
     bool pairs = false;     // matrix-core conv independent of the next layer, another one: they share a launch where few tiles are to do
+    // the buffers the launches of a pass use: the description's, except where a plan keeps maps longer (plan_sources)
+    int32_t src = -1, dst = -1, res = -1;
+    int32_t n_sources = 0;              // conv: of a concatenation that is never made, whose maps it reads from source[]
+    int32_t source[coe::k::kMaxSources] = {0};
     bool patchify = false;  // conv with stride == window and no padding: patches are gathered into GEMM rows, then a 1x1 conv
 };
 
@@ -48,7 +53,7 @@ struct ArchPlan {
     int32_t dtype, in_h, in_w, in_c, n_classes;
     std::vector<LayerPlan> layers;
     size_t blob_bytes = 0;
-    size_t buf_elems[kMaxBufs] = {0};   // per request
+    size_t buf_elems[kPlanBufs] = {0};   // per request
     size_t patch_elems = 0;             // per request: rows of the largest patch-gathered conv
     bool groupable = false;             // every layer can run several experts' small groups in one launch
     bool token_ops = false;             // transformer-shaped
@@ -120,8 +125,8 @@ constexpr int kMaxLanes = 3;          // with the copy stream: four hardware que
 
 struct Lane {
     hipStream_t s = nullptr;
-    void* d_buf[kMaxBufs] = {nullptr};
-    size_t buf_bytes[kMaxBufs] = {0};
+    void* d_buf[kPlanBufs] = {nullptr};
+    size_t buf_bytes[kPlanBufs] = {0};
     void* d_patch = nullptr;         // GEMM rows of patch-gathered convolutions
     size_t patch_bytes = 0;
     hipEvent_t done = nullptr;       // recorded after the lane's last launch of a step
@@ -258,6 +263,94 @@ struct Span {
     }
 };
 
+// Concatenations that only 1x1 convolutions read are not made: these read the concatenated maps where they lie, in the same
+// order.  The maps then live until those convolutions have run, so every map gets a buffer anew: the description's own if it is free
+// at that point, else the one that grows least.  Nothing changes where no concatenation goes or the buffers do not suffice.
+void plan_sources(ArchPlan& a)
+{
+    const int n = (int)a.layers.size();
+    // map i is what layer i writes, map n the input
+    std::vector<int> in(n, -1), in2(n, -1);
+    int holds[kMaxBufs];
+    for (int& h : holds) h = n;
+    for (int i = 0; i < n; ++i) {
+        const coe_layer& l = a.layers[i].d;
+        in[i] = holds[l.src];
+        if (l.res >= 0) in2[i] = holds[l.res];
+        if (l.dst >= 0) holds[l.dst] = i;
+    }
+    std::vector<std::vector<int>> parts(n + 1);       // the maps that a concatenation is made of, in order
+    for (int i = 0; i < n; ++i)
+        if (a.layers[i].d.op == COE_OP_CONCAT)
+            for (int v : {in[i], in2[i]}) {
+                if (parts[v].empty()) parts[i].push_back(v);
+                else parts[i].insert(parts[i].end(), parts[v].begin(), parts[v].end());
+            }
+    auto channels = [&](int v) { return v == n ? a.in_c : a.layers[v].K; };
+    std::vector<uint8_t> reads_parts(n, 0), made(n, 0);
+    for (int i = 0; i < n; ++i) {
+        const LayerPlan& L = a.layers[i];
+        if (L.d.op != COE_OP_CONV || !L.packed || L.patchify || parts[in[i]].empty()) continue;
+        const std::vector<int>& from = parts[in[i]];
+        const coe::k::ConvShape one{1, L.H, L.W, channels(from[0]), L.K, L.d.r, L.d.s, L.d.stride, L.d.pad, L.P, L.Q, L.d.act};
+        reads_parts[i] = coe::k::conv_mfma_sources_supported(one, (int32_t)from.size());
+        for (int v : from) reads_parts[i] = reads_parts[i] && v != n && channels(v) == channels(from[0]);
+    }
+    bool any = false;
+    for (int i = n - 1; i >= 0; --i) {                // (readers come after what they read)
+        if (a.layers[i].d.op != COE_OP_CONCAT) continue;
+        for (int j = i + 1; j < n; ++j) {
+            if (in[j] == i && !(reads_parts[j] || (a.layers[j].d.op == COE_OP_CONCAT && !made[j]))) made[i] = 1;
+            if (in2[j] == i && !(a.layers[j].d.op == COE_OP_CONCAT && !made[j])) made[i] = 1;
+        }
+        any = any || !made[i];
+    }
+    if (!any) return;
+    // who reads which map last; a convolution fused with its pool writes the pool's map
+    std::vector<std::vector<int>> reads(n);
+    std::vector<int> last(n + 1, -1);
+    for (int i = 0; i < n; ++i) {
+        const LayerPlan& L = a.layers[i];
+        if (L.fused_away || (L.d.op == COE_OP_CONCAT && !made[i])) continue;
+        if (reads_parts[i]) reads[i] = parts[in[i]];
+        else reads[i].push_back(in[i]);
+        if (in2[i] >= 0) reads[i].push_back(in2[i]);
+        for (int v : reads[i]) last[v] = i;
+    }
+    std::vector<int> at(n + 1, -1), owner(kPlanBufs, -1);
+    std::vector<size_t> size(a.buf_elems, a.buf_elems + kPlanBufs);
+    at[n] = 0;
+    for (int i = 0; i < n; ++i) {
+        const LayerPlan& L = a.layers[i];
+        if (L.d.dst < 0 || L.fused_away || (L.d.op == COE_OP_CONCAT && !made[i])) continue;
+        const int v = L.fuse_pool ? i + 1 : i;
+        const LayerPlan& out = a.layers[v];
+        const size_t need = (size_t)out.P * out.Q * out.K;
+        auto is_free = [&](int b) { return owner[b] < 0 || last[owner[b]] < i; };      // what layer i reads stays until it has run
+        int pick = is_free(out.d.dst) ? out.d.dst : -1;
+        for (int b = 1; b < kPlanBufs && pick != out.d.dst; ++b) {
+            auto grows = [&](int k) { return need > size[k] ? need - size[k] : 0; };
+            if (is_free(b) && (pick < 0 || grows(b) < grows(pick))) pick = b;
+        }
+        if (pick < 0) return;
+        owner[pick] = v;
+        at[v] = pick;
+        size[pick] = std::max(size[pick], need);
+    }
+    for (int i = 0; i < n; ++i) {
+        LayerPlan& L = a.layers[i];
+        if (L.d.op == COE_OP_CONCAT && !made[i]) { L.fused_away = true; continue; }
+        if (L.fused_away) { L.dst = at[i]; continue; }
+        L.src = reads_parts[i] ? -1 : at[in[i]];
+        if (in2[i] >= 0) L.res = at[in2[i]];
+        if (L.d.dst >= 0) L.dst = at[L.fuse_pool ? i + 1 : i];
+        if (reads_parts[i]) {
+            for (int v : parts[in[i]]) L.source[L.n_sources++] = at[v];
+        }
+    }
+    std::copy(size.begin(), size.end(), a.buf_elems);
+}
+
 // ---- architecture planning -----------------------------------------------------------------------------------------
 int plan_arch(coe_ctx* c, const coe_arch_desc* d, ArchPlan& a)
 {
@@ -278,6 +371,7 @@ int plan_arch(coe_ctx* c, const coe_arch_desc* d, ArchPlan& a)
     for (int32_t i = 0; i < d->n_layers; ++i) {
         LayerPlan L{};
         L.d = d->layers[i];
+        L.src = L.d.src; L.dst = L.d.dst; L.res = L.d.res;
         const coe_layer& l = L.d;
         if (l.src < 0 || l.src >= kMaxBufs || !shp[l.src].set) return fail(c, COE_EINVAL, "arch: layer reads an unset buffer");
         L.H = shp[l.src].h; L.W = shp[l.src].w; L.C = shp[l.src].c;
@@ -407,25 +501,27 @@ int plan_arch(coe_ctx* c, const coe_arch_desc* d, ArchPlan& a)
         cv.fuse_pool = true;
         pl.fused_away = true;
     }
-    // neighbouring convs on the matrix cores of which neither reads or overwrites what the other writes (a projection beside the
-    // first conv of its block, the two branches of a cross-stage block)
-    for (size_t i = 0; i + 1 < a.layers.size(); ++i) {
-        LayerPlan& u = a.layers[i];
-        const LayerPlan& v = a.layers[i + 1];
-        const bool convs = u.d.op == COE_OP_CONV && v.d.op == COE_OP_CONV && u.packed && v.packed && !u.patchify && !v.patchify;
-        const bool apart = u.d.dst != v.d.src && u.d.dst != v.d.res && u.d.dst != v.d.dst && v.d.dst != u.d.src && v.d.dst != u.d.res;
-        u.pairs = convs && apart && !(i > 0 && a.layers[i - 1].pairs);
-    }
     // activation buffers per request: what the launched kernels write (a conv fused with its pool writes the pool's output)
     for (const LayerPlan& L : a.layers) {
         const int op = L.d.op;
         if (op == COE_OP_HEAD || op == COE_OP_HEAD_CLS || op == COE_OP_HEAD_DET || L.fuse_pool) continue;
         a.buf_elems[L.d.dst] = std::max(a.buf_elems[L.d.dst], (size_t)L.P * L.Q * L.K);
     }
+    if (a.dtype == COE_DT_BF16) plan_sources(a);
+    // neighbouring convs on the matrix cores of which neither reads or overwrites what the other writes (a projection beside the
+    // first conv of its block, the two branches of a cross-stage block)
+    for (size_t i = 0; i + 1 < a.layers.size(); ++i) {
+        LayerPlan& u = a.layers[i];
+        const LayerPlan& v = a.layers[i + 1];
+        const bool convs = u.d.op == COE_OP_CONV && v.d.op == COE_OP_CONV && u.packed && v.packed && !u.patchify && !v.patchify &&
+                           !u.n_sources && !v.n_sources;
+        const bool apart = u.dst != v.src && u.dst != v.res && u.dst != v.dst && v.dst != u.src && v.dst != u.res;
+        u.pairs = convs && apart && !(i > 0 && a.layers[i - 1].pairs);
+    }
     a.blob_bytes = align_up(off);
     {
         size_t widest = a.in_bytes();
-        for (int b = 1; b < kMaxBufs; ++b) widest = std::max(widest, a.buf_elems[b] * a.elem());
+        for (int b = 1; b < kPlanBufs; ++b) widest = std::max(widest, a.buf_elems[b] * a.elem());
         widest = std::max(widest, a.patch_elems * a.elem());
         a.row_cap = (int32_t)std::min<size_t>((size_t)INT32_MAX, (size_t)0x7FFFFFFE / widest);
         if (a.row_cap < 1) return fail(c, COE_EINVAL, "arch: one request's largest tensor exceeds 2 GiB");
@@ -511,7 +607,7 @@ int32_t chunk_rows(const coe_ctx* c, const ArchPlan& a) { return std::min(c->cfg
 int ensure_workspace(coe_ctx* c)
 {
     for (Lane& ln : c->lanes) {
-        for (int b = 1; b < kMaxBufs; ++b) {
+        for (int b = 1; b < kPlanBufs; ++b) {
             size_t need = 0;
             for (const ArchPlan& a : c->archs) need = std::max(need, a.buf_elems[b] * a.elem() * (size_t)chunk_rows(c, a));
             if (need > ln.buf_bytes[b]) {
@@ -812,10 +908,13 @@ int run_expert(coe_ctx* c, Lane& ln, const Expert& x, const void* weights, const
         const coe_layer& l = L.d;
         if (last_layer >= 0 && ++li > last_layer) break;
         if (done) { done = false; continue; }
+        // up to one layer: as the description has it, every map made in its own buffer
+        const bool plain = last_layer >= 0;
+        const int32_t src = plain ? l.src : L.src, dst = plain ? l.dst : L.dst, rsd = plain ? l.res : L.res;
         if (L.pairs && last_layer < 0) {
             auto call = [&](const LayerPlan& v) {
-                return coe::k::ConvCall{buf(v.d.src), wb + v.off[0], (const float*)(wb + v.off[1]), v.d.res >= 0 ? buf(v.d.res) : nullptr,
-                                        buf(v.d.dst), conv_shape(v, n), 0, 0};
+                return coe::k::ConvCall{buf(v.src), wb + v.off[0], (const float*)(wb + v.off[1]), v.res >= 0 ? buf(v.res) : nullptr,
+                                        buf(v.dst), conv_shape(v, n), 0, 0};
             };
             if (int rc = run_pair(c, ln, call(L), call(*(&L + 1)), 2.0 * (L.macs + (&L + 1)->macs) * n, nullptr, done)) return rc;
             if (done) continue;
@@ -823,32 +922,38 @@ int run_expert(coe_ctx* c, Lane& ln, const Expert& x, const void* weights, const
         switch (l.op) {
         case COE_OP_CONV: {
             coe::k::ConvShape s{n, L.H, L.W, L.C, L.K, l.r, l.s, l.stride, l.pad, L.P, L.Q, l.act};
-            const void* res = l.res >= 0 ? buf(l.res) : nullptr;
+            const void* res = rsd >= 0 ? buf(rsd) : nullptr;
             double flops = 2.0 * L.macs * n;
             if (L.patchify) {
                 {
                     double bytes = 2.0 * n * (double)L.H * L.W * L.C * a.elem();
                     Span sp(c, COE_K_TOKEN_OPS, bytes, ln.s);
-                    HIPCHK(c, coe::k::patchify(buf(l.src), ln.d_patch, n, L.H, L.W, L.C, l.r, l.s, ln.s));
+                    HIPCHK(c, coe::k::patchify(buf(src), ln.d_patch, n, L.H, L.W, L.C, l.r, l.s, ln.s));
                 }
                 coe::k::ConvShape g{n, L.P, L.Q, l.r * l.s * L.C, L.K, 1, 1, 1, 0, L.P, L.Q, l.act};
                 Span sp(c, COE_K_CONV_MFMA, flops, ln.s);
-                HIPCHK(c, coe::k::conv_mfma(ln.d_patch, wb + L.off[0], (const float*)(wb + L.off[1]), nullptr, buf(l.dst), g, ln.s));
+                HIPCHK(c, coe::k::conv_mfma(ln.d_patch, wb + L.off[0], (const float*)(wb + L.off[1]), nullptr, buf(dst), g, ln.s));
+            } else if (L.n_sources && !plain) {
+                const void* from[coe::k::kMaxSources];
+                for (int i = 0; i < L.n_sources; ++i) from[i] = buf(L.source[i]);
+                s.C = L.C / L.n_sources;
+                Span sp(c, COE_K_CONV_MFMA, flops, ln.s);
+                HIPCHK(c, coe::k::conv_mfma_sources(from, L.n_sources, wb + L.off[0], (const float*)(wb + L.off[1]), res, buf(dst), s, ln.s));
             } else if (L.packed) {
                 Span sp(c, coe::k::conv_mfma_uses_slab(s) ? COE_K_CONV_SLAB : COE_K_CONV_MFMA, flops, ln.s);
-                HIPCHK(c, coe::k::conv_mfma(buf(l.src), wb + L.off[0], (const float*)(wb + L.off[1]), res, buf(l.dst), s, ln.s));
+                HIPCHK(c, coe::k::conv_mfma(buf(src), wb + L.off[0], (const float*)(wb + L.off[1]), res, buf(dst), s, ln.s));
             } else if (L.fuse_pool) {
                 const LayerPlan& pool = *(&L + 1);
                 Span sp(c, COE_K_CONV_STEM, flops, ln.s);
-                HIPCHK(c, coe::k::conv_smallc(buf(l.src), wb + L.off[0], (const float*)(wb + L.off[1]), buf(pool.d.dst), s, true, ln.s,
-                                              l.src == 0 ? rows : nullptr));
+                HIPCHK(c, coe::k::conv_smallc(buf(src), wb + L.off[0], (const float*)(wb + L.off[1]), buf(plain ? pool.d.dst : pool.dst), s, true, ln.s,
+                                              src == 0 ? rows : nullptr));
             } else if (a.dtype == COE_DT_BF16 && coe::k::conv_smallc_supported(s, res != nullptr, false)) {
                 Span sp(c, COE_K_CONV_STEM, flops, ln.s);
-                HIPCHK(c, coe::k::conv_smallc(buf(l.src), wb + L.off[0], (const float*)(wb + L.off[1]), buf(l.dst), s, false, ln.s,
-                                              l.src == 0 ? rows : nullptr));
+                HIPCHK(c, coe::k::conv_smallc(buf(src), wb + L.off[0], (const float*)(wb + L.off[1]), buf(dst), s, false, ln.s,
+                                              src == 0 ? rows : nullptr));
             } else {
                 Span sp(c, COE_K_CONV_DIRECT, flops, ln.s);
-                HIPCHK(c, coe::k::conv_direct(a.dtype, buf(l.src), wb + L.off[0], (const float*)(wb + L.off[1]), res, buf(l.dst), s,
+                HIPCHK(c, coe::k::conv_direct(a.dtype, buf(src), wb + L.off[0], (const float*)(wb + L.off[1]), res, buf(dst), s,
                                               x.finite_filters, ln.s));
             }
             break;
@@ -857,57 +962,58 @@ int run_expert(coe_ctx* c, Lane& ln, const Expert& x, const void* weights, const
             if (L.fused_away) break;
             double bytes = (double)n * ((double)L.H * L.W * L.C + (double)L.P * L.Q * L.K) * a.elem();
             Span sp(c, COE_K_POOL, bytes, ln.s);
-            HIPCHK(c, coe::k::maxpool(a.dtype, buf(l.src), buf(l.dst), n, L.H, L.W, L.C, l.r, l.s, l.stride, l.pad, L.P, L.Q, ln.s));
+            HIPCHK(c, coe::k::maxpool(a.dtype, buf(src), buf(dst), n, L.H, L.W, L.C, l.r, l.s, l.stride, l.pad, L.P, L.Q, ln.s));
             break;
         }
         case COE_OP_HEAD: {
             double bytes = (double)n * L.H * L.W * L.C * a.elem();
             Span sp(c, COE_K_HEAD, bytes, ln.s);
-            HIPCHK(c, coe::k::head_gap_fc(a.dtype, buf(l.src), wb + L.off[0], (const float*)(wb + L.off[1]), n, L.H * L.W, L.C, L.K,
+            HIPCHK(c, coe::k::head_gap_fc(a.dtype, buf(src), wb + L.off[0], (const float*)(wb + L.off[1]), n, L.H * L.W, L.C, L.K,
                                           route, ln.s));
             break;
         }
         case COE_OP_TOKENS: {
             double bytes = (double)n * ((double)L.H * L.W + L.P) * L.C * a.elem();
             Span sp(c, COE_K_TOKEN_OPS, bytes, ln.s);
-            HIPCHK(c, coe::k::tokens(buf(l.src), wb + L.off[0], wb + L.off[1], buf(l.dst), n, L.P, L.C, ln.s));
+            HIPCHK(c, coe::k::tokens(buf(src), wb + L.off[0], wb + L.off[1], buf(dst), n, L.P, L.C, ln.s));
             break;
         }
         case COE_OP_LAYERNORM: {
             double bytes = 2.0 * n * (double)L.H * L.W * L.C * a.elem();
             Span sp(c, COE_K_TOKEN_OPS, bytes, ln.s);
-            HIPCHK(c, coe::k::layernorm(buf(l.src), (const float*)(wb + L.off[0]), (const float*)(wb + L.off[1]), buf(l.dst),
+            HIPCHK(c, coe::k::layernorm(buf(src), (const float*)(wb + L.off[0]), (const float*)(wb + L.off[1]), buf(dst),
                                         (int64_t)n * L.H * L.W, L.C, ln.s));
             break;
         }
         case COE_OP_ATTENTION: {
             Span sp(c, COE_K_ATTENTION, 2.0 * L.macs * n, ln.s);
-            HIPCHK(c, coe::k::attention(buf(l.src), buf(l.dst), n, L.H * L.W, L.K, l.aux0, ln.s));
+            HIPCHK(c, coe::k::attention(buf(src), buf(dst), n, L.H * L.W, L.K, l.aux0, ln.s));
             break;
         }
         case COE_OP_CONCAT: {
+            if (L.fused_away && !plain) break;
             const int32_t cb = L.K - L.C;
             double bytes = 2.0 * n * (double)L.H * L.W * L.K * a.elem();
             Span sp(c, COE_K_TOKEN_OPS, bytes, ln.s);
-            HIPCHK(c, coe::k::concat_channels(buf(l.src), buf(l.res), buf(l.dst), (int64_t)n * L.H * L.W, L.C, cb, ln.s));
+            HIPCHK(c, coe::k::concat_channels(buf(src), buf(rsd), buf(dst), (int64_t)n * L.H * L.W, L.C, cb, ln.s));
             break;
         }
         case COE_OP_UPSAMPLE: {
             double bytes = 5.0 * n * (double)L.H * L.W * L.C * a.elem();
             Span sp(c, COE_K_TOKEN_OPS, bytes, ln.s);
-            HIPCHK(c, coe::k::upsample2(buf(l.src), buf(l.dst), n, L.H, L.W, L.C, ln.s));
+            HIPCHK(c, coe::k::upsample2(buf(src), buf(dst), n, L.H, L.W, L.C, ln.s));
             break;
         }
         case COE_OP_HEAD_DET: {
             double bytes = (double)n * ((double)L.H * L.W + L.P) * L.C * a.elem();
             Span sp(c, COE_K_HEAD, bytes, ln.s);
-            HIPCHK(c, coe::k::head_det(buf(l.src), L.H * L.W, l.res >= 0 ? buf(l.res) : nullptr, L.P, n, l.aux0, L.K, route, ln.s));
+            HIPCHK(c, coe::k::head_det(buf(src), L.H * L.W, rsd >= 0 ? buf(rsd) : nullptr, L.P, n, l.aux0, L.K, route, ln.s));
             break;
         }
         case COE_OP_HEAD_CLS: {
             double bytes = (double)n * L.C * a.elem();
             Span sp(c, COE_K_HEAD, bytes, ln.s);
-            HIPCHK(c, coe::k::head_cls(buf(l.src), (const float*)(wb + L.off[0]), (const float*)(wb + L.off[1]), wb + L.off[2],
+            HIPCHK(c, coe::k::head_cls(buf(src), (const float*)(wb + L.off[0]), (const float*)(wb + L.off[1]), wb + L.off[2],
                                        (const float*)(wb + L.off[3]), n, L.H * L.W, L.C, L.K, route, ln.s));
             break;
         }
@@ -1199,7 +1305,7 @@ void coe_destroy(coe_ctx* c)
     for (void* p : ptrs) if (p) hipFree(p);
     for (size_t l = 0; l < c->lanes.size(); ++l) {
         Lane& ln = c->lanes[l];
-        for (int b = 1; b < kMaxBufs; ++b) if (ln.d_buf[b]) hipFree(ln.d_buf[b]);
+        for (int b = 1; b < kPlanBufs; ++b) if (ln.d_buf[b]) hipFree(ln.d_buf[b]);
         if (ln.d_patch) hipFree(ln.d_patch);
         if (ln.done) hipEventDestroy(ln.done);
         if (l > 0 && ln.s) hipStreamDestroy(ln.s);
@@ -2030,7 +2136,7 @@ int coe_debug_layer_output(coe_ctx* c, int32_t e, int32_t n, const void* dev_in,
     if (n > chunk_rows(c, a)) return fail(c, COE_ERANGE, "more inputs than one launch sequence takes");
     if (layer < 0 || layer >= (int32_t)a.layers.size() - 1) return fail(c, COE_EINVAL, "layer index out of range (heads have no output tensor)");
     const LayerPlan& L = a.layers[layer];
-    if (L.fuse_pool || L.fused_away) return fail(c, COE_EINVAL, "layer is fused with its neighbour");
+    if (L.fuse_pool || (L.fused_away && L.d.op == COE_OP_MAXPOOL)) return fail(c, COE_EINVAL, "layer is fused with its neighbour");
     const size_t bytes = (size_t)n * L.P * L.Q * L.K * a.elem();
     if (out_bytes != bytes) return fail(c, COE_EINVAL, "output size does not match the layer");
     if (c->host_cap > 0) return fail(c, COE_ESTATE, "not available with a host tier");

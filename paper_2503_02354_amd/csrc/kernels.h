@@ -101,6 +101,13 @@ hipError_t conv_mfma(const void* x, const void* w, const float* bias, const void
 bool conv_mfma_groupable(const ConvShape& s);
 hipError_t conv_mfma_grouped(const void* x, const GroupTable& groups, size_t off_w, size_t off_b, const void* res, void* y,
                              const ConvShape& s, hipStream_t stream);
+// 1x1 convolution of the concatenation of n_sources maps of one shape, which it reads where they lie; `one` is the shape with the
+// channels of a single map.  The bits of conv_mfma on the concatenated map.  y overlaps none of them.
+constexpr int kMaxSources = 4;
+bool conv_mfma_sources_supported(const ConvShape& one, int32_t n_sources);
+hipError_t conv_mfma_sources(const void* const* x, int32_t n_sources, const void* wp, const float* bias, const void* res, void* y,
+                             const ConvShape& one, hipStream_t stream);
+
 // Two convolutions that do not read or write each other's outputs in one launch, with the bits of two.  groups == nullptr: wp and bias
 // are the filters, else the offsets off_w and off_b as in the grouped form.  conv_mfma_pairable: both are launches of few tiles, of
 // one kind; every other pair is called one by one.

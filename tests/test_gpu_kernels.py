@@ -687,6 +687,59 @@ def test_independent_convolutions_share_a_launch_with_the_same_bits(B, C, hw, n)
         assert np.array_equal(logits, want[first, np.arange(n)])
 
 
+@pytest.mark.parametrize("c,K,hw,n", [(32, 64, 8, 3), (32, 128, 8, 900), (64, 64, 8, 1), (64, 256, 7, 40), (64, 64, 12, 300), (128, 128, 8, 2), (128, 256, 9, 700),
+                                      (256, 512, 14, 128), (48, 64, 8, 5), (64, 96, 8, 5)])
+def test_concatenations_read_in_place(B, c, K, hw, n):
+    """A 1x1 convolution over a concatenation reads the concatenated maps themselves: two, four (chained), three, with residual, beside
+    readers that need the concatenated map, and over the parts of unequal size that it leaves alone.  Same bits as with a 1x1 pool in between,
+    which makes the map.  Sizes: few tiles (32 x 32 of two and four channel blocks to a stage, 64 x 64), 128-row tiles of 64 and 128 filters,
+    persistent tiles; 48 channels and 96 filters keep the concatenation."""
+    import torch
+    def build(direct):
+        p = W._Prog(hw, hw, 3, n_scratch=7)
+        def fuse(src, dst, spare, k, act, res=-1):
+            if direct:
+                p.conv(src, dst, k, 1, 1, 0, act, res=res)
+            else:
+                p.maxpool(src, spare, 1, 1, 0)
+                p.conv(spare, dst, k, 1, 1, 0, act, res=res)
+        p.conv(0, 1, 64, 3, 1, 1, W.ACT_RELU)
+        p.conv(1, 2, c, 1, 1, 0, W.ACT_SILU)
+        p.conv(1, 3, c, 1, 1, 0, W.ACT_RELU)
+        p.concat(2, 3, 1)
+        fuse(1, 7, 5, K, W.ACT_RELU)                        # two maps; 7 stays
+        p.maxpool(2, 4, 3, 1, 1)
+        p.concat(1, 4, 5)
+        fuse(5, 6, 3, K, W.ACT_NONE, res=7)                 # three maps, residual
+        p.conv(6, 7, c, 1, 1, 0, W.ACT_RELU)
+        p.concat(5, 7, 1)
+        fuse(1, 6, 3, K, W.ACT_SILU)                        # four maps, the first two kept from the start
+        p.concat(7, 6, 2)
+        fuse(2, 5, 3, 64, W.ACT_RELU)                       # parts of unequal size where K is not c
+        p.concat(5, 5, 3)
+        p.maxpool(3, 4, 3, 1, 1)                         # a reader that needs the map, and one that does not
+        fuse(3, 6, 1, 128, W.ACT_NONE, res=4)
+        p.head(6, 5)
+        return W.Arch("cat", W.DT_BF16, hw, hw, 3, 5, np.array(p.layers, dtype=np.int32), p.gains)
+    archs = [build(True), build(False)]
+    blob = W.make_expert_blob(archs[0], 5, 0)
+    x = torch.randn((n, hw, hw, 3), generator=torch.Generator().manual_seed(c + K)).bfloat16().cuda()
+    out = []
+    for arch in archs:
+        assert W.blob_layout(arch)[1] == blob.nbytes
+        ctx = B.Context(max_requests=n, max_stages=1, max_batch=n)
+        ctx.coe_register_expert(0, ctx.coe_register_arch(arch), blob, 1.0)
+        g = W.graph_from_lists([[]])
+        ctx.coe_set_dependency_graph(g.succ_off, g.succ)
+        out.append(ctx.coe_debug_forward(0, n, x.data_ptr()))
+        if arch is archs[0]:                             # layer by layer every map is made
+            at = [i for i, l in enumerate(arch.layers) if l[0] == W.OP_CONCAT]
+            maps = [ctx.coe_debug_layer_output(0, n, x.data_ptr(), i, (n, hw, hw, w), np.uint16) for i, w in ((at[0], 2 * c), (at[0] - 2, c), (at[0] - 1, c))]
+            assert np.array_equal(maps[0], np.concatenate(maps[1:], -1))
+        ctx.close()
+    assert np.isfinite(out[0]).all() and out[0].std() > 0 and np.array_equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("n,experts,cap", [(30, 6, 0), (300, 9, 0), (60, 8, 5)])
 def test_grouped_transformers_give_the_same_bits(B, n, experts, cap):
     """Small groups of several transformer-shaped experts share launches: same logits, routes and switches, bit for bit, as one
