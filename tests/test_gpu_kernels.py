@@ -538,6 +538,36 @@ def test_fp32_head_pooling(B, H, Wd, C):
     assert np.all(np.abs(logits[:, :5] - want) <= bound)
 
 
+@pytest.mark.parametrize("H,Wd,C,n_cls", [(7, 7, 512, 16), (7, 7, 2048, 65), (1, 1, 64, 1), (8, 16, 64, 5), (43, 3, 64, 17), (4, 4, 2048, 4), (1, 17, 2048, 3),
+                                          (33, 31, 512, 9), (5, 5, 96, 6), (65, 1, 512, 2)])
+def test_bf16_head_pooling(B, H, Wd, C, n_cls):
+    """Average pool and classifier of bf16 experts: sixteen positions in flight per thread, one less and one more, one position group
+    (2048 channels), more classes than one round of the wavefronts takes, and a channel count that keeps the plain loads (96)."""
+    import torch
+    n = 3
+    p = W._Prog(H, Wd, C)
+    p.head(0, n_cls)
+    arch = W.Arch("head", W.DT_BF16, H, Wd, C, n_cls, np.array(p.layers, dtype=np.int32), p.gains)
+    blob = W.make_expert_blob(arch, 7, 0)
+    x = torch.randn((n, H, Wd, C), generator=torch.Generator().manual_seed(H * 7 + C)).bfloat16().cuda()
+    ctx = B.Context(max_requests=n, max_stages=1, max_batch=n)
+    aid = ctx.coe_register_arch(arch)
+    ctx.coe_register_expert(0, aid, blob, 1.0)
+    g = W.graph_from_lists([[]])
+    ctx.coe_set_dependency_graph(g.succ_off, g.succ)
+    ctx.coe_submit(n, x.data_ptr(), True)
+    while ctx.coe_step()[0] != B.COE_DONE:
+        pass
+    _, logits, path = ctx.coe_collect(n)
+    ctx.close()
+    xd = x.cpu().double().numpy()
+    w, b = W.blob_tensor(arch, blob, 0, "w").astype(np.float64).reshape(n_cls, C), W.blob_tensor(arch, blob, 0, "b").astype(np.float64)
+    want = xd.mean((1, 2)) @ w.T + b
+    # first order: HW - 1 additions, a division, C products and additions, each 2^-24 of the absolute terms
+    bound = (H * Wd + 2 * C + 4) * 2.0 ** -24 * (np.abs(xd).mean((1, 2)) @ np.abs(w).T + np.abs(b))
+    assert np.all(np.abs(logits[:, :n_cls] - want) <= bound) and np.all(path[:, 0] == 0)
+
+
 @pytest.mark.parametrize("n", [341, 342, 700])
 def test_pageable_inputs_arrive_whole(B, n):
     """Inputs from pageable memory (below 16 MB by the runtime's copy, from there through the pinned ring: eight chunks and a
