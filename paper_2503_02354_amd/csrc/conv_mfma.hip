@@ -3,8 +3,8 @@
 // GEMM view: out[m][k] = sum_{r,s,c} x[n][p*stride-pad+r][q*stride-pad+s][c] * w[k][r][s][c], m = (n,p,q) flattened.
 // NHWC activations make the reduction index contiguous in c, so a reduction step is one (r,s) position and a run
 // of 32 channels.  A workgroup owns a BM x BN output tile.  Five kernels, picked by conv_mfma():
-//   1. conv_igemm_ring_kernel  launches of few output tiles (conv_ring says how few): 32 x 32 tiles of one wavefront or 64 x 64
-//                              tiles of four, loads many reduction steps ahead; same bits as the kernel below that the shape
+//   1. conv_igemm_ring_kernel  launches of few output tiles (conv_ring says how few): 32 x 32 or 64 x 64 tiles of four
+//                              wavefronts, loads many reduction steps ahead; same bits as the kernel below that the shape
 //                              otherwise takes;
 //   2. conv3x3_slab_kernel     3x3, stride 1, pad 1, filter count a multiple of 64: the activation rows a tile needs are
 //                              DMA'd into LDS once per 32-channel block and serve all nine window positions;
@@ -16,7 +16,7 @@
 // Common to all five:
 //   * Filters are repacked once, when an expert is registered, into matrix-core fragment order (pack_filters_mfma),
 //     so a filter slab is contiguous in memory and in LDS and an operand read is one linear 1 KiB access.
-//   * v_mfma_f32_32x32x16_bf16 is issued with the filter fragment as the first operand, so a lane ends up holding 4
+//   * v_mfma_f32_32x32x16_bf16 (16x16x32 in the smallest tiles) is issued with the filter fragment as the first operand, so a lane ends up holding 4
 //     consecutive output channels of one pixel per accumulator quad.
 //   * Epilogue in fp32: + bias (+ residual), activation, one round-to-nearest-even to bf16 (v_cvt_pk_bf16_f32).
 //   * Zero padding of the convolution and rows past the end of a tile come from buffer loads whose out-of-range
@@ -46,6 +46,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kPad = 8;              // elements of padding per LDS activation row (16 bytes)
@@ -1117,13 +1118,19 @@ hipError_t launch_slab(const void* x, const void* wp, const float* bias, const v
 // pixels of one 7 x 7 image are four 256 x 128 tiles) and each of their few workgroups walks the whole reduction with
 // its loads only two short steps ahead.  Splitting the reduction would change the order of the sums, and with it the
 // bits of a request's result with the number of requests that happen to run beside it; so the tile shrinks instead and
-// the loads run further ahead.  Same operands, same instruction and same order of accumulation as the kernel that the
+// the loads run further ahead.  Same operands and same order of accumulation as the kernel that the
 // shape otherwise takes (slab_order: channel blocks outside, window positions inside), hence the same bits.
 //   * STAGES stages of UN 32-channel steps each in LDS, all but two of them in flight; one barrier per stage.
 //   * operands of a stage are read into registers while the stage before it is multiplied, and the loads of a later one issued,
 //     each between two products: a wave issues in order, and what stands in front of the products delays them.  us, reads, then
 //     loads, then products / this order: 3072 -> 768, 197 rows 11.3 / 9.1, 985 rows 16.0 / 13.9; 3x3 stride 2, 256 -> 512 on 14 x 14,
 //     1 image 9.9 / 8.1, 29 images 13.4 / 11.2; 3x3 stride 1, 512 -> 512 on 7 x 7, 1 image 10.1 / 9.4, 29 images 14.1 / 13.2.
+//   * 32 x 32 tiles are four wavefronts of 16 x 16 (T = 16): a product of 16 x 16 x 32 sums in the order of two of 32 x 32 x 16 one after the
+//     other (no bit of 150,000 sums over 32 to 512 elements differs) and the chain of them, which bounds a tile of one wavefront (144
+//     steps of 64 cycles where 512 channels go into a 3x3 window), takes a quarter of the time; a step's four loads are one per
+//     wavefront, so more of them are in flight; bias and residual are fetched first and 8-byte stores leave straight from the
+//     accumulators.  us per launch, one image, a tile of one wavefront / of four: 3x3 512 -> 512 on 7 x 7 9.3 / 8.1, 256 -> 256 on
+//     14 x 14 7.2 / 6.3, 128 -> 128 on 28 x 28 5.6 / 5.2, 64 -> 64 on 56 x 56 4.9 / 4.5; one ResNet-18 request 297 / 268.
 //   * row tiles run fastest: the workgroups of one XCD take all rows of a few filter tiles, so filters - most of the
 //     bytes here - come from memory once and not once per XCD.
 // ---------------------------------------------------------------------------------------------------------------
@@ -1135,6 +1142,8 @@ template <int BEGIN, int END, typename F> __device__ __forceinline__ void static
     }
 }
 
+constexpr int kRingWaves = 4;
+
 // The other convolution of a launch that does two (PAIR): its tiles follow the first one's
 struct RingSecond {
     ConvShape s;
@@ -1143,8 +1152,8 @@ struct RingSecond {
     uint32_t first_tiles;      // tiles of the first convolution
 };
 
-template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES, bool GELU, bool PAIR, bool SOURCES>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel(const uint16_t* __restrict__ x,
+template <bool SLAB_ORDER, int T, int UN, int STAGES, bool GELU, bool PAIR, bool SOURCES>
+__global__ __launch_bounds__(64 * kRingWaves) void conv_igemm_ring_kernel(const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ wp_all,
                                                                    const float* __restrict__ bias_all,
                                                                    const uint16_t* __restrict__ res,
@@ -1156,12 +1165,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BK = 32, KS = 2;
-    constexpr int NW = WAVES_M * WAVES_N;
-    constexpr int WM = 32 * MB, WN = 32 * NB, BM = WM * WAVES_M, BN = WN * WAVES_N;
+    constexpr bool QUARTERS = T == 16;
+    constexpr int BM = 2 * T, BN = 2 * T;                     // waves 2 x 2, T x T accumulators each
     constexpr int FA = BM / 16, FB = BN / 32 * KS;            // 1 KiB blocks per step
-    static_assert(FA % NW == 0 && FB % NW == 0, "every wave issues the same number of loads");
-    constexpr int A_PER_WAVE = FA / NW, B_PER_WAVE = FB / NW;
-    constexpr int LOADS = UN * (A_PER_WAVE + B_PER_WAVE);     // of a wave and stage
+    // every wave issues the same number of loads: of a step's 4 KiB in quarters one block each (two waves pixel rows, two filters)
+    static_assert(QUARTERS ? FA + FB == kRingWaves : FA == kRingWaves && FB == kRingWaves, "blocks of a step");
+    constexpr int PER_STEP = QUARTERS ? 1 : 2;
+    constexpr int LOADS = UN * PER_STEP;                      // of a wave and stage
     constexpr int FRAG = 512;                                 // elements per 1 KiB block
     constexpr int STEP = (FA + FB) * FRAG, STAGE = UN * STEP;
     static_assert(STAGES >= 3 && (STAGES - 2) * LOADS <= 63, "what is in flight at a wait fits its counter");
@@ -1213,7 +1223,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
     }
     const int m0 = m_first + (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
     const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wid / WAVES_N, wn = wid % WAVES_N;
+    const int wm = wid / 2, wn = wid % 2;
 
     const int cblocks = s.C / BK;
     const int RS = s.R * s.S;
@@ -1229,48 +1239,49 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
     constexpr int kPos = SLAB_ORDER ? 9 : 1;
     constexpr int kParts = SLAB_ORDER ? 9 / UN : 1;           // stages per channel block (slab order)
     static_assert(!SLAB_ORDER || 9 % UN == 0, "whole stages per channel block");
-    uint32_t a_at[A_PER_WAVE][kPos];
-    int32_t a_off[A_PER_WAVE], a_ih[A_PER_WAVE], a_iw[A_PER_WAVE];
-    auto place = [&](int j, int rr, int tt) __attribute__((always_inline)) -> uint32_t {
-        const bool in = (unsigned)(a_ih[j] + rr) < (unsigned)s.H && (unsigned)(a_iw[j] + tt) < (unsigned)s.W;
-        return in ? (uint32_t)(a_off[j] + (rr * s.W + tt) * s.C * 2) : kOutOfRange;
+    uint32_t a_at[kPos];
+    int32_t a_off, a_ih, a_iw;
+    auto place = [&](int rr, int tt) __attribute__((always_inline)) -> uint32_t {
+        const bool in = (unsigned)(a_ih + rr) < (unsigned)s.H && (unsigned)(a_iw + tt) < (unsigned)s.W;
+        return in ? (uint32_t)(a_off + (rr * s.W + tt) * s.C * 2) : kOutOfRange;
     };
+    const bool rows = !QUARTERS || wid < FA;                  // this wave fetches pixel rows
     {
         const int chunk = (lane & 3) ^ swz(lane >> 2);
+        const int m = m0 + wid * 16 + (lane >> 2);
+        const bool ok = m < M && rows;
+        const int mm = ok ? m : 0;
+        const int n = mm / PQ, pq = mm % PQ;
+        const int p = pq / s.Q, q = pq % s.Q;
+        a_ih = ok ? p * s.stride - s.pad : -0x10000;          // a row past the end: no position is inside
+        a_iw = q * s.stride - s.pad;
+        a_off = ((n * s.H + p * s.stride - s.pad) * s.W + a_iw) * s.C * 2 + chunk * 16;
 #pragma unroll
-        for (int j = 0; j < A_PER_WAVE; ++j) {
-            const int m = m0 + (wid * A_PER_WAVE + j) * 16 + (lane >> 2);
-            const bool ok = m < M;
-            const int mm = ok ? m : 0;
-            const int n = mm / PQ, pq = mm % PQ;
-            const int p = pq / s.Q, q = pq % s.Q;
-            a_ih[j] = ok ? p * s.stride - s.pad : -0x10000;    // a row past the end: no position is inside
-            a_iw[j] = q * s.stride - s.pad;
-            a_off[j] = ((n * s.H + p * s.stride - s.pad) * s.W + a_iw[j]) * s.C * 2 + chunk * 16;
-#pragma unroll
-            for (int k = 0; k < kPos; ++k) a_at[j][k] = place(j, k / 3, k % 3);
-        }
+        for (int i = 0; i < kPos; ++i) a_at[i] = place(i / 3, i % 3);
     }
-    uint32_t b_off[B_PER_WAVE];
+    const int fb = QUARTERS ? (rows ? 0 : wid - FA) : wid;    // filter fragment of this wave
+    const uint32_t b_off = (uint32_t)((((n0 / 32 + fb / KS) * ks16_total + fb % KS) * FRAG + lane * 8) * 2);
+    // in quarters a wave has one kind of load: descriptor and lane offsets are picked once, the scalar offset per load
+    __amdgpu_buffer_rsrc_t own_rsrc = rows ? x_rsrc : w_rsrc;
+    if (!rows)
 #pragma unroll
-    for (int j = 0; j < B_PER_WAVE; ++j) {
-        int fb = wid * B_PER_WAVE + j;
-        b_off[j] = (uint32_t)((((n0 / 32 + fb / KS) * ks16_total + fb % KS) * FRAG + lane * 8) * 2);
-    }
+        for (int i = 0; i < kPos; ++i) a_at[i] = b_off;
 
     // the stage that is fetched next: scalar offsets of its first channel block in a row and of its first filter fragment
     uint32_t f_c = 0, f_w = 0, r_pos = 0, t_pos = 0;
     const uint32_t c_end = (uint32_t)s.C * 2, tap_w = (uint32_t)cblocks * (KS * FRAG * 2);
     // part (slab order): which UN of the nine positions
     auto load_one = [&](auto part_c, auto k_c, int stage) __attribute__((always_inline)) {
-        constexpr int part = decltype(part_c)::value, u = decltype(k_c)::value / (A_PER_WAVE + B_PER_WAVE), j = decltype(k_c)::value % (A_PER_WAVE + B_PER_WAVE);
+        constexpr int part = decltype(part_c)::value, u = decltype(k_c)::value / PER_STEP, j = decltype(k_c)::value % PER_STEP;
         uint16_t* const st = lds + stage * STAGE + u * STEP;
-        if constexpr (j < A_PER_WAVE)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void*)(st + (wid * A_PER_WAVE + j) * FRAG), 16,
-                                                     a_at[j][SLAB_ORDER ? part * UN + u : 0], SLAB_ORDER ? f_c : f_c + u * (BK * 2), 0, 0);
+        const uint32_t at = a_at[SLAB_ORDER ? part * UN + u : 0];
+        const uint32_t c_at = SLAB_ORDER ? f_c : f_c + u * (BK * 2), w_at = SLAB_ORDER ? f_w + (part * UN + u) * tap_w : f_w + u * (KS * FRAG * 2);
+        if constexpr (QUARTERS)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(own_rsrc, (lds_void*)(st + wid * FRAG), 16, at, rows ? c_at : w_at, 0, 0);
+        else if constexpr (j == 0)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void*)(st + wid * FRAG), 16, at, c_at, 0, 0);
         else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void*)(st + (FA + wid * B_PER_WAVE + j - A_PER_WAVE) * FRAG), 16, b_off[j - A_PER_WAVE],
-                                                     SLAB_ORDER ? f_w + (part * UN + u) * tap_w : f_w + u * (KS * FRAG * 2), 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void*)(st + (FA + wid) * FRAG), 16, b_off, w_at, 0, 0);
     };
     auto advance = [&](auto part_c) __attribute__((always_inline)) {
         constexpr int part = decltype(part_c)::value;
@@ -1289,36 +1300,45 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
                 f_w += UN * KS * FRAG * 2;
                 if (SOURCES) {
                     x_rsrc = make_rsrc(source_at(x, from, (int)r_pos), (uint32_t)s.N * (uint32_t)(s.H * s.W * s.C) * 2u);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < A_PER_WAVE; ++j) a_at[j][0] = place(j, r_pos, t_pos);
+                    own_rsrc = rows ? x_rsrc : w_rsrc;
+                } else if (rows) {
+                    a_at[0] = place(r_pos, t_pos);
                 }
             }
         }
     };
 
-    f32x16 acc[MB][NB];
+    // Operands.  In quarters a product takes a whole step: lane l holds pixel row (and filter) l % 16 and the 8 channels l / 16 of 32.
+    constexpr int PRODUCTS = QUARTERS ? 1 : KS;               // of a step
+    std::conditional_t<QUARTERS, f32x4, f32x16> acc;
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
+    for (int v = 0; v < (QUARTERS ? 4 : 16); ++v) acc[v] = 0.f;
+    const int l16 = lane & 15, g16 = lane >> 4;
     const int rd_row = lane & 31;
-    const int rd0 = (rd_row >> 4) * FRAG + ((rd_row & 15) * 4 + ((lane >> 5) ^ swz(rd_row & 15))) * 8;
-    bf16x8 af[2][UN][KS][MB], bfr[2][UN][KS][NB];             // [stage parity]
-    constexpr int kReads = UN * KS * (MB + NB), kMfma = UN * KS * MB * NB;
+    const int rd_a = QUARTERS ? wm * FRAG + (l16 * 4 + (g16 ^ swz(l16))) * 8
+                              : (wm * 2 + (rd_row >> 4)) * FRAG + ((rd_row & 15) * 4 + ((lane >> 5) ^ swz(rd_row & 15))) * 8;
+    const int rd_b = QUARTERS ? (FA + (g16 >> 1)) * FRAG + ((g16 & 1) * 32 + wn * 16 + l16) * 8 : (FA + wn * KS) * FRAG + lane * 8;
+    bf16x8 af[2][UN][PRODUCTS], bfr[2][UN][PRODUCTS];         // [stage parity]
+    constexpr int kReads = UN * PRODUCTS * 2, kMfma = UN * PRODUCTS;
     auto read_one = [&](auto set_c, auto k_c, int stage) __attribute__((always_inline)) {
-        constexpr int set = decltype(set_c)::value, k = decltype(k_c)::value, u = k / (KS * (MB + NB)), ks = k / (MB + NB) % KS, i = k % (MB + NB);
+        constexpr int set = decltype(set_c)::value, k = decltype(k_c)::value, u = k / (PRODUCTS * 2), ks = k / 2 % PRODUCTS;
         const uint16_t* const st = lds + stage * STAGE + u * STEP;
-        if constexpr (i < MB) af[set][u][ks][i] = *(const bf16x8*)(st + (wm * MB * 2) * FRAG + i * 2 * FRAG + (rd0 ^ (ks * 16)));
-        else bfr[set][u][ks][i - MB] = *(const bf16x8*)(st + (FA + wn * NB * KS) * FRAG + lane * 8 + ((i - MB) * KS + ks) * FRAG);
+        if constexpr (k % 2 == 0) af[set][u][ks] = *(const bf16x8*)(st + (rd_a ^ (ks * 16)));
+        else bfr[set][u][ks] = *(const bf16x8*)(st + rd_b + ks * FRAG);
     };
     auto multiply_one = [&](auto set_c, auto k_c) __attribute__((always_inline)) {
-        constexpr int set = decltype(set_c)::value, k = decltype(k_c)::value, u = k / (KS * MB * NB), ks = k / (MB * NB) % KS, i = k / NB % MB, j = k % NB;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][u][ks][j], af[set][u][ks][i], acc[i][j], 0, 0, 0);
+        constexpr int set = decltype(set_c)::value, k = decltype(k_c)::value, u = k / PRODUCTS, ks = k % PRODUCTS;
+        if constexpr (QUARTERS) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[set][u][ks], af[set][u][ks], acc, 0, 0, 0);
+        else acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[set][u][ks], af[set][u][ks], acc, 0, 0, 0);
     };
+    // in quarters the bias and the residual are fetched before everything else
+    const int q_px = m0 + wm * 16 + l16, q_f = n0 + wn * 16 + g16 * 4;
+    float4 q_bias = make_float4(0.f, 0.f, 0.f, 0.f);
+    uint2 q_res = make_uint2(0u, 0u);
+    if constexpr (QUARTERS) {
+        q_bias = *(const float4*)(bias + q_f);
+        if (res && q_px < M) q_res = *(const uint2*)(res + (size_t)q_px * s.K + q_f);
+    }
 
     typedef std::integral_constant<int, 0> c0;
     typedef std::integral_constant<int, 1> c1;
@@ -1374,8 +1394,21 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_ring_kernel
         }
     }
     wait_before_barrier<0>();
-    __builtin_amdgcn_s_barrier();        // every wave is done with the operand stages: LDS is free for the epilogue
-    store_tile_via_lds<GELU, MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
+    if constexpr (QUARTERS) {
+        with_activation<GELU>(s.act, [&](auto a) {
+            float v[4] = {acc[0] + q_bias.x, acc[1] + q_bias.y, acc[2] + q_bias.z, acc[3] + q_bias.w};
+            if (res) {
+                v[0] += bf16_to_f32(q_res.x & 0xFFFFu); v[1] += bf16_to_f32(q_res.x >> 16);
+                v[2] += bf16_to_f32(q_res.y & 0xFFFFu); v[3] += bf16_to_f32(q_res.y >> 16);
+            }
+            activate<decltype(a)::value>(v);
+            if (q_px < M) *(uint2*)(y + (size_t)q_px * s.K + q_f) = make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+        });
+    } else {
+        __builtin_amdgcn_s_barrier();    // every wave is done with the operand stages: LDS is free for the epilogue
+        f32x16 (&tile_acc)[1][1] = reinterpret_cast<f32x16 (&)[1][1]>(acc);
+        store_tile_via_lds<GELU, 1, 1>(tile_acc, lds + wid * (32 * (T + 8)), bias, res, y, m0 + wm * T, n0 + wn * T, M, s.K, s.act, lane);
+    }
 #endif
 }
 
@@ -1390,16 +1423,16 @@ struct ConvArgs {
 };
 
 // b != nullptr: a second convolution, over the same groups, in the same launch
-template <bool SLAB_ORDER, int MB, int NB, int WAVES_M, int WAVES_N, int UN, int STAGES, bool GELU = false, bool PAIR = false, bool SOURCES = false>
+template <bool SLAB_ORDER, int T, int UN, int STAGES, bool GELU = false, bool PAIR = false, bool SOURCES = false>
 hipError_t launch_ring(const ConvArgs& a, hipStream_t stream, const ConvArgs* b = nullptr)
 {
     if constexpr (!GELU && !PAIR && !SOURCES && !SLAB_ORDER)
-        if (a.from) return launch_ring<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, false, false, true>(a, stream);
+        if (a.from) return launch_ring<SLAB_ORDER, T, UN, STAGES, false, false, true>(a, stream);
     if constexpr (!GELU && !PAIR && !SOURCES)
-        if (a.s.act == 2) return launch_ring<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, true>(a, stream);
+        if (a.s.act == 2) return launch_ring<SLAB_ORDER, T, UN, STAGES, true>(a, stream);
     if constexpr (!GELU && !PAIR && !SOURCES && !SLAB_ORDER)
-        if (b) return launch_ring<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, false, true>(a, stream, b);
-    constexpr int BM = 32 * MB * WAVES_M, BN = 32 * NB * WAVES_N;
+        if (b) return launch_ring<SLAB_ORDER, T, UN, STAGES, false, true>(a, stream, b);
+    constexpr int BM = 2 * T, BN = 2 * T;
     const long long M = (long long)a.s.N * a.s.P * a.s.Q;
     long long total = count_tiles(M, (long long)a.s.P * a.s.Q, BM, a.s.K / BN, a.grp.table);
     RingSecond second{};
@@ -1411,11 +1444,11 @@ hipError_t launch_ring(const ConvArgs& a, hipStream_t stream, const ConvArgs* b 
     if (total > 0x7FFFFFFFll) return hipErrorInvalidValue;
     if (total == 0) return hipSuccess;
     constexpr size_t kLdsBytes = STAGES * UN * (size_t)(BM + BN) * 32 * sizeof(uint16_t);
-    static_assert(kLdsBytes <= 160 * 1024 && kLdsBytes >= (size_t)WAVES_M * WAVES_N * 32 * (32 * NB + 8) * 2, "operand stages and epilogue rows");
-    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, GELU, PAIR, SOURCES>,
+    static_assert(kLdsBytes <= 160 * 1024 && kLdsBytes >= (T == 16 ? 0 : (size_t)kRingWaves * 32 * (T + 8) * 2), "operand stages and epilogue rows");
+    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_igemm_ring_kernel<SLAB_ORDER, T, UN, STAGES, GELU, PAIR, SOURCES>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
     if (configured != hipSuccess) return configured;
-    hipLaunchKernelGGL((conv_igemm_ring_kernel<SLAB_ORDER, MB, NB, WAVES_M, WAVES_N, UN, STAGES, GELU, PAIR, SOURCES>), dim3((unsigned)total), dim3(64 * WAVES_M * WAVES_N),
+    hipLaunchKernelGGL((conv_igemm_ring_kernel<SLAB_ORDER, T, UN, STAGES, GELU, PAIR, SOURCES>), dim3((unsigned)total), dim3(64 * kRingWaves),
                        kLdsBytes, stream, (const uint16_t*)a.x, (const uint16_t*)a.wp, a.bias, (const uint16_t*)a.res, (uint16_t*)a.y, a.s, (int)M,
                        a.s.K / BN, a.grp.table, a.grp.off_w, a.grp.off_b, b ? (const uint16_t*)b->x : nullptr, b ? (const uint16_t*)b->wp : nullptr,
                        b ? b->bias : nullptr, b ? (const uint16_t*)b->res : nullptr, b ? (uint16_t*)b->y : nullptr, second, a.from ? *a.from : Sources{});
@@ -1760,8 +1793,8 @@ namespace {
 //   64 -> 64, 3x3, 56 x 56:   1 image 10 / 6 / 7,    30 images 16 / 36 / 27
 //   3072 -> 768, 1x1, 197 positions: 1 image 34 / 14 / 17,  5 images 35 / 26 / 18
 //   768 -> 2304, 1x1, 197 positions: 1 image 13 / 8 / 9,    5 images 14 / 20 / 15
-// A single wavefront per 32 x 32 tile is ahead while the chip holds all tiles at once at two per compute unit; 64 x 64
-// tiles, which share operands between four wavefronts, while there are about two of them (three: 3x3) per compute unit.
+// (32 x 32 tiles of one wavefront, as they were then.)  These are ahead while the chip holds all tiles at once at two per compute
+// unit; 64 x 64 tiles, which share operands between four wavefronts, while there are about two of them (three: 3x3) per compute unit.
 constexpr long long kRingTiles32 = 512, kRingTiles64 = 512, kRingTiles64Slab = 768;
 
 // Which tiles a long GEMM-like launch takes: height / 64 of conv_gemm_persistent_kernel's tiles, or 0 for the 128 x 128 tiles of
@@ -1809,15 +1842,18 @@ hipError_t conv_gemm(const void* x, const void* wp, const float* bias, const voi
 }
 
 // The tiles of a launch with few of them; none: not a launch for these tiles
-enum class Ring { none, slab32, deep32, shallow32, slab64_3, slab64_1, tile64 };
+enum class Ring { none, slab32_9, slab32_3, deep32_9, deep32_4, shallow32, slab64_3, slab64_1, tile64 };
 Ring ring_tiles(const ConvShape& s, const GroupTable& gt)
 {
     const bool slab = conv_mfma_uses_slab(s);
     const int cblocks = s.C / 32;
     if (!slab && cblocks % 2) return Ring::none;                 // a stage holds channel blocks of one window position
     const long long M = (long long)s.N * s.P * s.Q, PQ = (long long)s.P * s.Q;
-    if (count_tiles(M, PQ, 32, s.K / 32, gt) <= kRingTiles32)
-        return slab ? Ring::slab32 : cblocks % 4 == 0 ? Ring::deep32 : Ring::shallow32;
+    const long long tiles32 = count_tiles(M, PQ, 32, s.K / 32, gt);
+    if (tiles32 <= kRingTiles32) {                               // one workgroup per compute unit, or two that share its LDS
+        if (slab) return tiles32 <= 256 ? Ring::slab32_9 : Ring::slab32_3;
+        return cblocks % 4 ? Ring::shallow32 : tiles32 <= 256 ? Ring::deep32_9 : Ring::deep32_4;
+    }
     const long long tiles64 = count_tiles(M, PQ, 64, s.K / 64, gt);
     if (s.K % 64 == 0 && tiles64 <= (slab ? kRingTiles64Slab : kRingTiles64)) {
         // 3x3: one workgroup per compute unit has its LDS to itself, with more tiles than that two share it.  Nine steps in
@@ -1831,12 +1867,14 @@ Ring ring_tiles(const ConvShape& s, const GroupTable& gt)
 hipError_t conv_ring(const ConvArgs& a, hipStream_t stream, const ConvArgs* b = nullptr)
 {
     switch (ring_tiles(a.s, a.grp.table)) {
-    case Ring::slab32: return launch_ring<true, 1, 1, 1, 1, 3, 6>(a, stream);
-    case Ring::deep32: return launch_ring<false, 1, 1, 1, 1, 4, 4>(a, stream, b);
-    case Ring::shallow32: return launch_ring<false, 1, 1, 1, 1, 2, 6>(a, stream, b);
-    case Ring::slab64_3: return launch_ring<true, 1, 1, 2, 2, 3, 5>(a, stream);
-    case Ring::slab64_1: return launch_ring<true, 1, 1, 2, 2, 1, 10>(a, stream);
-    case Ring::tile64: return launch_ring<false, 1, 1, 2, 2, 2, 5>(a, stream, b);
+    case Ring::slab32_9: return launch_ring<true, 16, 9, 4>(a, stream);
+    case Ring::slab32_3: return launch_ring<true, 16, 3, 6>(a, stream);
+    case Ring::deep32_9: return launch_ring<false, 16, 4, 9>(a, stream, b);
+    case Ring::deep32_4: return launch_ring<false, 16, 4, 4>(a, stream, b);
+    case Ring::shallow32: return launch_ring<false, 16, 2, 9>(a, stream, b);
+    case Ring::slab64_3: return launch_ring<true, 32, 3, 5>(a, stream);
+    case Ring::slab64_1: return launch_ring<true, 32, 1, 10>(a, stream);
+    case Ring::tile64: return launch_ring<false, 32, 2, 5>(a, stream, b);
     case Ring::none: break;
     }
     return hipErrorNotSupported;
