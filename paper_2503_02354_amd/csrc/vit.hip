@@ -27,10 +27,24 @@ __device__ __forceinline__ float scaled(float a, float b)
 #pragma clang fp contract(off)
     return a * b;
 }
+template <int CTRL> __device__ __forceinline__ float dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
+}
+// v + the value of lane ^ 32, then ^ 16, 8, 4, 2 and 1, as a loop of __shfl_xor would have it
 __device__ __forceinline__ float wave_sum(float v)
 {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int kRor8 = 0x128, kMirror8 = 0x141, kXor3 = 0x1B, kXor2 = 0x4E, kXor1 = 0xB1;    // row rotate, half-row mirror, quad permutations
+    auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
+    auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(rows[0]) + __uint_as_float(rows[1]);
+    v += dpp<kRor8>(v);
+    v += dpp<kXor3>(dpp<kMirror8>(v));                        // 7 - i, then ^ 3: ^ 4
+    v += dpp<kXor2>(v);
+    v += dpp<kXor1>(v);
+#endif
     return v;
 }
 
@@ -89,8 +103,12 @@ __global__ __launch_bounds__(256) void tokens_kernel(const uint4* __restrict__ x
 }
 
 // ---- layer norm over channels, one wavefront per token, the token held in registers ---------------------------------
+// A launch of a few requests is a chain of latencies: the token, two sums over the wavefront, scale and shift.  Scale and shift are
+// on their way from the start, up to 1024 channels (beyond, their registers would cost long launches half the wavefronts), and
+// the sums exchange lanes by register operations instead of through LDS, in the same order.  us per launch, 985 tokens of 768 channels:
+// 5.5 / 4.3 (6.3 / 4.6 with a group table); five requests, 48 launches, 1975 / 1877.
 constexpr int kLnMaxPairs = 16;     // D <= 64 lanes * 2 * 16 = 2048
-template <bool GROUPED>
+template <bool GROUPED, int PAIRS>
 __global__ __launch_bounds__(256) void layernorm_kernel(const uint32_t* __restrict__ x, const float* __restrict__ gamma,
                                                         const float* __restrict__ beta, uint32_t* __restrict__ y, int rows,
                                                         int D2 /* pairs per token */, GroupTable gt, int tokens_per_image,
@@ -104,34 +122,47 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint32_t* __restri
     }
     int lane = threadIdx.x & 63;
     const uint32_t* xp = x + (size_t)row * D2;
-    float v[2 * kLnMaxPairs];
+    float v[2 * PAIRS];
+    uint32_t w[PAIRS];
+    constexpr bool kAhead = PAIRS <= 8;
+    float2 g[PAIRS], b[PAIRS];
+    auto scale_shift = [&](int j) {
+        const int c = lane + 64 * j;
+        g[j] = c < D2 ? *(const float2*)(gamma + 2 * c) : make_float2(0.f, 0.f);
+        b[j] = c < D2 ? *(const float2*)(beta + 2 * c) : make_float2(0.f, 0.f);
+    };
     float sum = 0.f;
 #pragma unroll
-    for (int j = 0; j < kLnMaxPairs; ++j) {
-        int c = lane + 64 * j;
-        uint32_t w = c < D2 ? xp[c] : 0u;
-        v[2 * j] = bf16_lo(w);
-        v[2 * j + 1] = bf16_hi(w);
+    for (int j = 0; j < PAIRS; ++j) {
+        const int c = lane + 64 * j;
+        w[j] = c < D2 ? xp[c] : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j)
+        if (kAhead) scale_shift(j);
+#pragma unroll
+    for (int j = 0; j < PAIRS; ++j) {
+        v[2 * j] = bf16_lo(w[j]);
+        v[2 * j + 1] = bf16_hi(w[j]);
         sum += v[2 * j] + v[2 * j + 1];
     }
     const float inv_d = 1.f / (float)(2 * D2);
     const float mean = wave_sum(sum) * inv_d;
     float sq = 0.f;
 #pragma unroll
-    for (int j = 0; j < kLnMaxPairs; ++j) {
+    for (int j = 0; j < PAIRS; ++j) {
         if (lane + 64 * j < D2) {
-            float a = v[2 * j] - mean, b = v[2 * j + 1] - mean;
-            sq += a * a + b * b;
+            float p = v[2 * j] - mean, q = v[2 * j + 1] - mean;
+            sq += p * p + q * q;
         }
     }
     const float rstd = rsqrtf(wave_sum(sq) * inv_d + 1e-6f);
 #pragma unroll
-    for (int j = 0; j < kLnMaxPairs; ++j) {
-        int c = lane + 64 * j;
-        if (c < D2) {
-            float2 g = *(const float2*)(gamma + 2 * c), b = *(const float2*)(beta + 2 * c);
-            y[(size_t)row * D2 + c] = pack_bf16((v[2 * j] - mean) * rstd * g.x + b.x, (v[2 * j + 1] - mean) * rstd * g.y + b.y);
-        }
+    for (int j = 0; j < PAIRS; ++j) {
+        const int c = lane + 64 * j;
+        if (!kAhead) scale_shift(j);
+        if (c < D2)
+            y[(size_t)row * D2 + c] = pack_bf16((v[2 * j] - mean) * rstd * g[j].x + b[j].x, (v[2 * j + 1] - mean) * rstd * g[j].y + b[j].y);
     }
 }
 
@@ -372,8 +403,14 @@ hipError_t launch_layernorm(const void* x, const float* gamma, const float* beta
     if (rows == 0) return hipSuccess;
     int64_t blocks = (rows + 3) / 4;
     if (blocks > 0x7FFFFFFFll) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(layernorm_kernel<GROUPED>, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint32_t*)x, gamma, beta,
-                       (uint32_t*)y, (int)rows, D / 2, gt, tokens_per_image, off_gamma, off_beta);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint32_t*)x, gamma, beta, (uint32_t*)y, (int)rows, D / 2,
+                           gt, tokens_per_image, off_gamma, off_beta);
+    };
+    if (D <= 128 * 4) launch(layernorm_kernel<GROUPED, 4>);
+    else if (D <= 128 * 6) launch(layernorm_kernel<GROUPED, 6>);
+    else if (D <= 128 * 8) launch(layernorm_kernel<GROUPED, 8>);
+    else launch(layernorm_kernel<GROUPED, kLnMaxPairs>);
     return hipGetLastError();
 }
 

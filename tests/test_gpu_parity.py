@@ -544,6 +544,12 @@ def test_layernorm_elementwise(B, oracle, T, D, n):
     assert np.mean(g == want) > 0.995
 
 
+@pytest.mark.parametrize("T,D,n", [(3, 2, 1), (4, 128, 2), (9, 512, 3), (5, 514, 1), (7, 770, 2), (6, 1024, 1), (5, 1026, 2), (3, 2046, 1)])
+def test_layernorm_widths(B, oracle, T, D, n):
+    """One pair of channels, full and partly filled registers, and the widths at which another kernel takes over (512, 768, 1024)."""
+    test_layernorm_elementwise(B, oracle, T, D, n)
+
+
 def test_tokens_elementwise(B, oracle):
     T0, D, n = 49, 72, 3
     arch = _token_op_arch(T0, D, [W.OP_TOKENS, D, 0, 0, 0, 0, 0, 0, 0], D)
