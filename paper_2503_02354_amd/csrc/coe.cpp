@@ -42,7 +42,8 @@ struct LayerPlan {
     bool fuse_pool = false; // conv: the max pool that follows runs inside the conv kernel, which writes the pool's dst
     bool fused_away = false;// pool: done by the preceding conv kernel
     bool pairs = false;     // matrix-core conv independent of the next layer, another one: they share a launch where few tiles are to do
-    // the buffers the launches of a pass use: the description's, except where a plan keeps maps longer (plan_sources)
+    // the buffers the launches of a pass use: the description's, except where a plan keeps maps longer (plan_sources).  -1 where the
+    // operation has none, whatever the description says there
     int32_t src = -1, dst = -1, res = -1;
     int32_t n_sources = 0;              // conv: of a concatenation that is never made, whose maps it reads from source[]
     int32_t source[coe::k::kMaxSources] = {0};
@@ -274,10 +275,10 @@ void plan_sources(ArchPlan& a)
     int holds[kMaxBufs];
     for (int& h : holds) h = n;
     for (int i = 0; i < n; ++i) {
-        const coe_layer& l = a.layers[i].d;
-        in[i] = holds[l.src];
-        if (l.res >= 0) in2[i] = holds[l.res];
-        if (l.dst >= 0) holds[l.dst] = i;
+        const LayerPlan& L = a.layers[i];
+        in[i] = holds[L.src];
+        if (L.res >= 0) in2[i] = holds[L.res];
+        if (L.dst >= 0) holds[L.dst] = i;
     }
     std::vector<std::vector<int>> parts(n + 1);       // the maps that a concatenation is made of, in order
     for (int i = 0; i < n; ++i)
@@ -322,7 +323,7 @@ void plan_sources(ArchPlan& a)
     at[n] = 0;
     for (int i = 0; i < n; ++i) {
         const LayerPlan& L = a.layers[i];
-        if (L.d.dst < 0 || L.fused_away || (L.d.op == COE_OP_CONCAT && !made[i])) continue;
+        if (L.dst < 0 || L.fused_away || (L.d.op == COE_OP_CONCAT && !made[i])) continue;
         const int v = L.fuse_pool ? i + 1 : i;
         const LayerPlan& out = a.layers[v];
         const size_t need = (size_t)out.P * out.Q * out.K;
@@ -343,7 +344,7 @@ void plan_sources(ArchPlan& a)
         if (L.fused_away) { L.dst = at[i]; continue; }
         L.src = reads_parts[i] ? -1 : at[in[i]];
         if (in2[i] >= 0) L.res = at[in2[i]];
-        if (L.d.dst >= 0) L.dst = at[L.fuse_pool ? i + 1 : i];
+        if (L.dst >= 0) L.dst = at[L.fuse_pool ? i + 1 : i];
         if (reads_parts[i]) {
             for (int v : parts[in[i]]) L.source[L.n_sources++] = at[v];
         }
@@ -371,7 +372,6 @@ int plan_arch(coe_ctx* c, const coe_arch_desc* d, ArchPlan& a)
     for (int32_t i = 0; i < d->n_layers; ++i) {
         LayerPlan L{};
         L.d = d->layers[i];
-        L.src = L.d.src; L.dst = L.d.dst; L.res = L.d.res;
         const coe_layer& l = L.d;
         if (l.src < 0 || l.src >= kMaxBufs || !shp[l.src].set) return fail(c, COE_EINVAL, "arch: layer reads an unset buffer");
         L.H = shp[l.src].h; L.W = shp[l.src].w; L.C = shp[l.src].c;
@@ -379,6 +379,9 @@ int plan_arch(coe_ctx* c, const coe_arch_desc* d, ArchPlan& a)
         if (!is_head && (l.dst <= 0 || l.dst >= kMaxBufs || l.dst == l.src))
             return fail(c, COE_EINVAL, "arch: bad destination buffer");
         if (is_head && i != d->n_layers - 1) return fail(c, COE_EINVAL, "arch: head must be the last layer");
+        L.src = l.src;
+        L.dst = is_head ? -1 : l.dst;
+        L.res = l.op == COE_OP_CONV || l.op == COE_OP_CONCAT || l.op == COE_OP_HEAD_DET ? l.res : -1;
         switch (l.op) {
         case COE_OP_CONV:
         case COE_OP_MAXPOOL: {

@@ -770,6 +770,30 @@ def test_concatenations_read_in_place(B, c, K, hw, n):
     assert np.isfinite(out[0]).all() and out[0].std() > 0 and np.array_equal(out[0], out[1])
 
 
+@pytest.mark.parametrize("dst,res", [(8, -1), (99, -1), (-1, 40), (5, 3)])
+def test_buffers_that_an_operation_does_not_have_change_nothing(B, dst, res):
+    """The destination of a head and the residual of a pool or an upsampling may hold anything: same logits as with -1."""
+    import torch
+    arch = W.detector(27, 64)
+    blob, n = W.make_expert_blob(arch, 5, 0), 3
+    x = torch.randn((n, 64, 64, 3), generator=torch.Generator().manual_seed(1)).bfloat16().cuda()
+    layers = arch.layers.copy()
+    for l in layers:
+        if l[0] == W.OP_HEAD_DET:
+            l[2] = dst
+        if l[0] in (W.OP_MAXPOOL, W.OP_UPSAMPLE):
+            l[3] = res
+    out = []
+    for a in (arch, W.Arch("stray", arch.dtype, 64, 64, 3, 27, layers, arch.gains)):
+        ctx = B.Context(max_requests=n, max_stages=1, max_batch=n)
+        ctx.coe_register_expert(0, ctx.coe_register_arch(a), blob, 1.0)
+        g = W.graph_from_lists([[]])
+        ctx.coe_set_dependency_graph(g.succ_off, g.succ)
+        out.append(ctx.coe_debug_forward(0, n, x.data_ptr()))
+        ctx.close()
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("n,experts,cap", [(30, 6, 0), (300, 9, 0), (60, 8, 5)])
 def test_grouped_transformers_give_the_same_bits(B, n, experts, cap):
     """Small groups of several transformer-shaped experts share launches: same logits, routes and switches, bit for bit, as one

@@ -2,6 +2,7 @@
 import ctypes as C
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -355,3 +356,48 @@ def test_usage_probabilities_from_sample_paths(B, oracle):
     for bad in (np.array([[7]], np.int32), np.array([[-2]], np.int32)):
         with pytest.raises(B.CoEError):
             B.coe_profiler_usage_probabilities(bad, 6)
+
+
+@pytest.fixture(scope="module")
+def host_checks(B, tmp_path_factory):
+    """Runs tests/native/host_checks.cpp: the library's host code under the sanitizers, kernels from libcoe.so."""
+    exe = str(tmp_path_factory.mktemp("native") / "host_checks")
+    lib_dir = os.path.dirname(B.LIB_PATH)
+    r = subprocess.run(["g++", "-w", "-std=c++17", "-O1", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                        "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", os.path.join(ROOT, "tests", "native", "host_checks.cpp"),
+                        "-o", exe, "-L" + lib_dir, "-lcoe", "-L/opt/rocm/lib", "-lamdhip64", "-lpthread",
+                        "-Wl,-rpath," + lib_dir + ":/opt/rocm/lib"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+    def run(*args, text=""):
+        r = subprocess.run([exe, *map(str, args)], input=text, capture_output=True, text=True, env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
+        assert r.returncode == 0, r.stderr
+        return r.stdout.splitlines()
+    return run
+
+
+def _description(arch, layers):
+    words = [arch.dtype, arch.in_h, arch.in_w, arch.in_c, arch.n_classes, len(layers)] + [v for l in layers for v in l]
+    return " ".join(map(str, words)) + "\n"
+
+
+@pytest.mark.parametrize("make", [lambda: W.detector(27, 64), lambda: W.resnet18(5, 64), lambda: W.resnet50(5, 64), lambda: W.vit(5, 64, dim=128, depth=2, heads=2),
+                                  lambda: W.tiny_cnn(4, 64)])
+def test_plans_ignore_buffers_that_an_operation_does_not_have(host_checks, make):
+    """A description may leave anything in the destination of a head and in the residual of an operation without one: never an index, and
+    the plan is the one with -1 there."""
+    arch = make()
+    clean = [[int(v) for v in l] for l in arch.layers]
+    heads, with_res = (W.OP_HEAD, W.OP_HEAD_CLS, W.OP_HEAD_DET), (W.OP_CONV, W.OP_CONCAT, W.OP_HEAD_DET)
+    text, n = _description(arch, clean), 1
+    for dst, res in ((8, -1), (99, -1), (2 ** 31 - 1, -1), (-9, -9), (7, -1), (-1, 8), (-1, 40), (-1, 2 ** 31 - 1), (3, 7), (99, 99)):
+        stray = [list(l) for l in clean]
+        for l in stray:
+            if l[0] in heads:
+                l[2] = dst
+            if l[0] not in with_res:
+                l[3] = res
+        text += _description(arch, stray)
+        n += 1
+    plans = host_checks("plan", text=text)
+    assert len(plans) == n and plans[0].startswith("rc 0 | ") and set(plans) == {plans[0]}
