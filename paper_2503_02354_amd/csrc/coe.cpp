@@ -596,8 +596,12 @@ int ensure_store(coe_ctx* c)
         c->h_out = nullptr;
         c->out_words = 0;
         if (words * 4 <= kCollectPinned) {
-            HIPCHK(c, hipHostMalloc((void**)&c->h_out, words * 4, hipHostMallocDefault));
-            c->out_words = words;
+            if (hipHostMalloc((void**)&c->h_out, words * 4, hipHostMallocDefault) == hipSuccess) {
+                c->out_words = words;
+            } else {                    // by copies, then
+                (void)hipGetLastError();
+                c->h_out = nullptr;
+            }
         }
     }
     return COE_OK;

@@ -401,3 +401,9 @@ def test_plans_ignore_buffers_that_an_operation_does_not_have(host_checks, make)
         n += 1
     plans = host_checks("plan", text=text)
     assert len(plans) == n and plans[0].startswith("rc 0 | ") and set(plans) == {plans[0]}
+
+
+def test_store_does_without_pinned_memory(host_checks):
+    """Results that find no pinned memory are collected by copies: a refused allocation is no error."""
+    assert host_checks("store", 100, 3, 10, 1 << 30) == ["0 1400 1 "]
+    assert host_checks("store", 100, 3, 10, 5599) == ["0 0 0 "]
