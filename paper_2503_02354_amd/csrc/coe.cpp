@@ -573,7 +573,8 @@ hipError_t dev_malloc(coe_ctx* c, void** p, size_t bytes)
     return hipMalloc(p, bytes);
 }
 
-// Pinned memory for the results of a collect; what does not fit (more than a hundred thousand requests) goes by copies.
+// Pinned memory for the results of a collect.  One whose words (1 + max_stages + max_classes a stored request, those of arrays that the
+// caller does not ask for left out) do not fit goes by copies.
 constexpr size_t kCollectPinned = (size_t)16 << 20;
 
 int ensure_store(coe_ctx* c)
@@ -590,18 +591,16 @@ int ensure_store(coe_ctx* c)
         if (c->d_logits) HIPCHK(c, hipFree(c->d_logits));
         HIPCHK(c, dev_malloc(c, (void**)&c->d_logits, nreq * c->max_classes * sizeof(float)));
         c->logits_alloc_classes = c->max_classes;
-        // results of a collect: next expert, path and logits of every request
-        const size_t words = nreq * (1 + (size_t)c->cfg.max_stages + (size_t)c->max_classes);
+        // results of a collect: next expert, path and logits of every request, or of as many as fit
+        const size_t words = std::min(nreq * (1 + (size_t)c->cfg.max_stages + (size_t)c->max_classes), kCollectPinned / 4);
         if (c->h_out) HIPCHK(c, hipHostFree(c->h_out));
         c->h_out = nullptr;
         c->out_words = 0;
-        if (words * 4 <= kCollectPinned) {
-            if (hipHostMalloc((void**)&c->h_out, words * 4, hipHostMallocDefault) == hipSuccess) {
-                c->out_words = words;
-            } else {                    // by copies, then
-                (void)hipGetLastError();
-                c->h_out = nullptr;
-            }
+        if (hipHostMalloc((void**)&c->h_out, words * 4, hipHostMallocDefault) == hipSuccess) {
+            c->out_words = words;
+        } else {                        // by copies, then
+            (void)hipGetLastError();
+            c->h_out = nullptr;
         }
     }
     return COE_OK;

@@ -667,6 +667,31 @@ def test_device_inputs_and_known_counts(B, n, hw, shift):
     assert np.isfinite(out[0]).all() and all(np.array_equal(out[0], o) for o in out[1:])
 
 
+def test_collects_beyond_the_pinned_memory(B):
+    """A store whose results may exceed the pinned memory (5000 requests, 1000 classes): all at once by copies, in halves through
+    it, the same results."""
+    import torch
+    arch, n = W.tiny_cnn(1000, 8), 5000
+    x = torch.randn((n, 8, 8, 3), generator=torch.Generator().manual_seed(3)).cuda()
+    ctx = B.Context(max_requests=n, max_stages=1, max_batch=512)
+    ctx.coe_register_expert(0, ctx.coe_register_arch(arch), W.make_expert_blob(arch, 7, 0), 1.0)
+    g = W.graph_from_lists([[]])
+    ctx.coe_set_dependency_graph(g.succ_off, g.succ)
+    out = []
+    for parts in ((n,), (n // 2, n // 2)):
+        logits = []
+        for i, m in enumerate(parts):
+            ctx.coe_submit(m, x[i * parts[0]].data_ptr(), True)
+            while ctx.coe_step()[0] != B.COE_DONE:
+                pass
+            ids, lg, path = ctx.coe_collect(m)
+            assert np.array_equal(ids, ids[0] + np.arange(m)) and not path.any()
+            logits.append(lg)
+        out.append(np.concatenate(logits))
+    ctx.close()
+    assert out[0].shape == (n, 1000) and np.isfinite(out[0]).all() and out[0].std() > 0 and np.array_equal(out[0], out[1])
+
+
 @pytest.mark.parametrize("C,hw,n", [(64, 16, 1), (64, 16, 33), (128, 16, 7), (128, 16, 200), (128, 20, 150), (96, 16, 5)])
 def test_independent_convolutions_share_a_launch_with_the_same_bits(B, C, hw, n):
     """Neighbouring convolutions that do not depend on each other run in one launch where both have few tiles (32 x 32 tiles with two or

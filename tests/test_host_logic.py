@@ -407,3 +407,10 @@ def test_store_does_without_pinned_memory(host_checks):
     """Results that find no pinned memory are collected by copies: a refused allocation is no error."""
     assert host_checks("store", 100, 3, 10, 1 << 30) == ["0 1400 1 "]
     assert host_checks("store", 100, 3, 10, 5599) == ["0 0 0 "]
+
+
+def test_store_of_many_results_keeps_what_fits(host_checks):
+    """Up to 16 MB of results in pinned memory; a store that may hold more keeps the 16 MB for the collects that fit."""
+    assert host_checks("store", 4177, 3, 1000, 1 << 30) == ["0 4193708 1 "]
+    assert host_checks("store", 4178, 3, 1000, 1 << 30) == ["0 4194304 1 "]
+    assert host_checks("store", 1 << 20, 3, 10, 1 << 30) == ["0 4194304 1 "]
