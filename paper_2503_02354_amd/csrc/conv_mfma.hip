@@ -1843,16 +1843,21 @@ hipError_t conv_gemm(const void* x, const void* wp, const float* bias, const voi
 
 // The tiles of a launch with few of them; none: not a launch for these tiles
 enum class Ring { none, slab32_9, slab32_3, deep32_9, deep32_4, shallow32, slab64_3, slab64_1, tile64 };
+long long tiles32(const ConvShape& s, const GroupTable& gt)
+{
+    const long long PQ = (long long)s.P * s.Q;
+    return count_tiles(s.N * PQ, PQ, 32, s.K / 32, gt);
+}
 Ring ring_tiles(const ConvShape& s, const GroupTable& gt)
 {
     const bool slab = conv_mfma_uses_slab(s);
     const int cblocks = s.C / 32;
     if (!slab && cblocks % 2) return Ring::none;                 // a stage holds channel blocks of one window position
     const long long M = (long long)s.N * s.P * s.Q, PQ = (long long)s.P * s.Q;
-    const long long tiles32 = count_tiles(M, PQ, 32, s.K / 32, gt);
-    if (tiles32 <= kRingTiles32) {                               // one workgroup per compute unit, or two that share its LDS
-        if (slab) return tiles32 <= 256 ? Ring::slab32_9 : Ring::slab32_3;
-        return cblocks % 4 ? Ring::shallow32 : tiles32 <= 256 ? Ring::deep32_9 : Ring::deep32_4;
+    const long long few = tiles32(s, gt);
+    if (few <= kRingTiles32) {                                   // one workgroup per compute unit, or two that share its LDS
+        if (slab) return few <= 256 ? Ring::slab32_9 : Ring::slab32_3;
+        return cblocks % 4 ? Ring::shallow32 : few <= 256 ? Ring::deep32_9 : Ring::deep32_4;
     }
     const long long tiles64 = count_tiles(M, PQ, 64, s.K / 64, gt);
     if (s.K % 64 == 0 && tiles64 <= (slab ? kRingTiles64Slab : kRingTiles64)) {
@@ -1863,10 +1868,12 @@ Ring ring_tiles(const ConvShape& s, const GroupTable& gt)
     }
     return Ring::none;
 }
-// hipErrorNotSupported: not a launch for these tiles
+// hipErrorNotSupported: not a launch for these tiles.  b: a second convolution, of the same tiles
 hipError_t conv_ring(const ConvArgs& a, hipStream_t stream, const ConvArgs* b = nullptr)
 {
-    switch (ring_tiles(a.s, a.grp.table)) {
+    Ring tiles = ring_tiles(a.s, a.grp.table);
+    if (b && tiles == Ring::deep32_9 && tiles32(a.s, a.grp.table) + tiles32(b->s, b->grp.table) > 256) tiles = Ring::deep32_4;
+    switch (tiles) {
     case Ring::slab32_9: return launch_ring<true, 16, 9, 4>(a, stream);
     case Ring::slab32_3: return launch_ring<true, 16, 3, 6>(a, stream);
     case Ring::deep32_9: return launch_ring<false, 16, 4, 9>(a, stream, b);
@@ -1997,11 +2004,12 @@ hipError_t conv_mfma_grouped(const void* x, const GroupTable& groups, size_t off
     return conv_gemm(x, nullptr, nullptr, res, y, s, stream, grp);
 }
 
-// Two launches of few tiles each leave most of the chip idle, and the second waits for the first for nothing: a launch with the
-// tiles of both takes the time of the longer one.  The tiles are those that each would take by itself, so the bits are the same.
+// Two launches of few tiles each leave most of the chip idle, and the second waits for the first for nothing: one launch has the
+// tiles of both.  The tiles are those that each would take by itself, so the bits are the same; how deep their pipeline is goes by
+// the tiles of both, so that all are resident where they can be.  us, two launches / one, 1x1 512 -> 512 twice on 7 x 7: 1 image 10.4 / 5.4,
+// 8 images (208 tiles each) 10.6 / 6.0, 16 11.4 / 9.5, 24 13.5 / 8.8, 64 18.3 / 15.3; with the depth of one convolution's tiles 8 images took 8.9.
 // Launches that fill the chip gain nothing by sharing it, and pairs whose tiles differ would need a kernel per combination: these
-// stay apart.  Passes with a launch for each / with shared ones, us: one ResNet-18 request (three pairs per expert) 324 / 308, 29 requests
-// 755 / 735.
+// stay apart.
 bool conv_mfma_pairable(const ConvShape& a, const ConvShape& b, const GroupTable* groups)
 {
     const GroupTable none{};

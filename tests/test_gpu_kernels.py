@@ -692,10 +692,10 @@ def test_collects_beyond_the_pinned_memory(B):
     assert out[0].shape == (n, 1000) and np.isfinite(out[0]).all() and out[0].std() > 0 and np.array_equal(out[0], out[1])
 
 
-@pytest.mark.parametrize("C,hw,n", [(64, 16, 1), (64, 16, 33), (128, 16, 7), (128, 16, 200), (128, 20, 150), (96, 16, 5)])
+@pytest.mark.parametrize("C,hw,n", [(64, 16, 1), (64, 16, 33), (128, 16, 7), (128, 16, 20), (128, 16, 200), (128, 20, 150), (96, 16, 5)])
 def test_independent_convolutions_share_a_launch_with_the_same_bits(B, C, hw, n):
     """Neighbouring convolutions that do not depend on each other run in one launch where both have few tiles (32 x 32 tiles with two or
-    four channel blocks to a stage, 64 x 64 tiles), alone and in groups: the bits of a batch of 700, whose launches are apart.  96
+    four channel blocks to a stage, those deep or, where both together are more than the compute units, shallower; 64 x 64 tiles), alone and in groups: the bits of a batch of 700, whose launches are apart.  96
     channels have no such tiles.  Neighbours that read or overwrite each other's outputs stay in order."""
     import torch
     K, many, E = 128, 700, 3
