@@ -368,10 +368,10 @@ __global__ __launch_bounds__(256) void maxpool_bf16x8_kernel(const uint4* __rest
 }
 
 // The same with stride 1 on maps that fit LDS: a workgroup holds CH chunks of 8 channels of one image, takes the maximum along
-// rows, then along columns, so a map is read once.  The kernel above reads it R * S times through the caches, which is what bounds it.
-// us, kernel above / this one: 5x5 on 14 x 14 x 256, 250 images 57.8 / 31.3, 64 images 23.6 / 15.6, one 12.9 / 13.1; on 20 x 20 x 96, 250
-// images 49.6 / 27.9, one 14.4 / 13.9; on 12 x 12 x 64, 250 images 21.0 / 11.5; but 3x3 on 14 x 14 x 64, 64 images 9.6 / 11.1: windows from
-// 5x5 on come here.
+// rows, then along columns, so a map is read once.  The kernel above reads it R * S times through the caches, which is what bounds its
+// long launches; a short launch of this one is bound by what a single workgroup does one after the other (plane_pays).
+// us, kernel above / this one: 5x5 on 14 x 14 x 256, 256 images 54 / 29, 64 images 21 / 14, one 8.0 / 11.0; on 20 x 20 x 96, 256 images
+// 46 / 26, one 8.0 / 11.1; on 7 x 7 x 512, 256 images 29 / 19, one 7.5 / 5.0; 9x9 on 14 x 14 x 256, 256 images 133 / 41, one 19 / 15.
 constexpr int kPlaneThreads = 256;
 constexpr size_t kPlaneLds = 64 * 1024;
 __device__ __forceinline__ void max_bf16x8(float (&best)[8], const uint4& v)
@@ -938,17 +938,29 @@ hipError_t conv_direct(int dtype, const void* x, const void* w, const float* bia
     return hipGetLastError();
 }
 
+// Both kernels' times in us, fitted to launches of 1 to 1024 images with 5x5 to 13x13 windows on maps of 4 x 4 to 22 x 22: what a launch
+// of any size takes, and what each 16 bytes of its output (`vecs` in all) add.  A workgroup of the plane kernel goes over its
+// CH chunks 256 at a time, three times.  Below 5x5 the kernel for all pools is taken throughout (3x3 on 14 x 14 x 64, 64 images: 9.6, plane 11.1).
+static bool plane_pays(size_t vecs, int32_t H, int32_t W, int32_t R, int32_t S, int ch)
+{
+    if (R * S < 25) return false;
+    const double r = std::min(R, H), s = std::min(S, W), turns = (double)H * W * ch / kPlaneThreads;
+    const double plane = 2.5 + turns * (0.4 + 0.095 * (r + s)) + (double)vecs * (6.0 + 0.8 * (r + s)) * 1e-6;
+    const double general = 2.6 + 0.21 * r * s + (double)vecs * 1.15 * r * s * 1e-6;
+    return plane <= general;
+}
+
 hipError_t maxpool(int dtype, const void* x, void* y, int32_t N, int32_t H, int32_t W, int32_t C, int32_t R, int32_t S,
                    int32_t stride, int32_t pad, int32_t P, int32_t Q, hipStream_t stream)
 {
     size_t total = (size_t)N * P * Q * C;
     if (total == 0) return hipSuccess;
-    if (dtype == 1 && C % 32 == 0 && stride == 1 && R * S >= 25) {
+    if (dtype == 1 && C % 32 == 0 && stride == 1) {
         // eight chunks of 8 channels are whole lines; four where eight do not fit
         const size_t chunk = ((size_t)H * W + (size_t)H * Q) * sizeof(uint4);
         const int ch = C % 64 == 0 && 8 * chunk <= kPlaneLds ? 8 : 4 * chunk <= kPlaneLds ? 4 : 0;
         const size_t blocks = ch ? (size_t)N * (C / 8 / ch) : 0;
-        if (ch && blocks <= 0x7FFFFFFFull) {
+        if (ch && blocks <= 0x7FFFFFFFull && plane_pays(total / 8, H, W, R, S, ch)) {
             if (ch == 8)
                 hipLaunchKernelGGL(maxpool_plane_kernel<8>, dim3((unsigned)blocks), dim3(kPlaneThreads), 8 * chunk, stream, (const uint4*)x,
                                    (uint4*)y, H, W, C / 8, R, S, pad, P, Q);

@@ -360,6 +360,31 @@ def test_pools_with_stride_one(B, H, Wd, C, R, pad):
     assert np.array_equal(W.bf16_bits_to_f32(got).reshape(want.shape), want)
 
 
+@pytest.mark.parametrize("H,Wd,C,R,pad,many", [(14, 14, 64, 5, 2, 300), (14, 14, 256, 5, 2, 70), (22, 23, 32, 5, 2, 300), (20, 20, 96, 5, 2, 100),
+                                               (13, 14, 128, 5, 1, 200), (7, 7, 64, 5, 2, 300), (13, 13, 64, 7, 3, 40)])
+def test_pools_of_few_and_many_images_give_the_same_bits(B, H, Wd, C, R, pad, many):
+    """Whether a stride-1 pool runs in LDS goes by the size of the launch too (few images not, many in eight and in four chunks of channels;
+    the last two always): the same bits, of zeros of either sign, infinities and numbers, NaN passed over."""
+    import torch
+    p = W._Prog(H, Wd, C); p.maxpool(0, 1, R, 1, pad); p.head(1, 4)
+    arch = W.Arch("pool", W.DT_BF16, H, Wd, C, 4, np.array(p.layers, dtype=np.int32), p.gains)
+    rng = np.random.default_rng(H * C + R)
+    x = W.bf16_bits_to_f32(_bf16(rng, 4, H, Wd, C)).reshape(4, H, Wd, C).copy()
+    for value, share in ((-np.inf, 0.2), (np.nan, 0.1), (np.inf, 0.002)):
+        x[rng.random(x.shape) < share] = value
+    x[1] = np.where(rng.random(x[1].shape) < 0.1, 0.0, np.where(rng.random(x[1].shape) < 0.5, -0.0, -1.0))
+    x[2, :, :, ::3] = np.nan
+    bits = W.f32_to_bf16_bits(x).reshape(x.shape)[np.arange(many) % 4]
+    dev = torch.from_numpy(bits.view(np.int16)).cuda()
+    P, Q = H + 2 * pad - R + 1, Wd + 2 * pad - R + 1
+    ctx = B.Context(max_requests=many, max_batch=many)
+    ctx.coe_register_expert(0, ctx.coe_register_arch(arch), W.make_expert_blob(arch, 7, 0), 1.0)
+    few, all_of_them = (ctx.coe_debug_layer_output(0, n, dev.data_ptr(), 0, (n, P, Q, C), np.uint16) for n in (4, many))
+    ctx.close()
+    for i in range(many):
+        assert np.array_equal(all_of_them[i], few[i % 4]), i
+
+
 @pytest.mark.parametrize("n,H,Wd,C,K,R,stride,pad,act", [
     (3, 45, 50, 3, 64, 6, 2, 2, 3),      # reduction unrolled, outputs through LDS, ragged tiles
     (2, 16, 16, 3, 64, 6, 2, 2, 1),      # less than a tile
