@@ -479,7 +479,7 @@ __device__ __forceinline__ void store_tile_via_lds_act(f32x16 (&acc)[MB][NB], ui
     constexpr int WN = NB * 32, ROW = WN + 8;             // elements; 16 bytes of padding per staged row
     constexpr int CPR = WN / 8;                            // 16-byte chunks per row
     constexpr int T = 32 * CPR / 64;                       // chunks per lane and 32-row block
-    constexpr int kQuads = 1;                              // accumulator quads that are finished together
+    constexpr int kQuads = ACT == 3 ? 2 : 1;               // accumulator quads that are finished together: SiLU shares a test
     const int frag_row = lane & 31, f_hi = (lane >> 5) * 4;
     // the residual takes the same road in the other direction: row-contiguous 16-byte loads (all issued up front),
     // staged in LDS, picked up in the accumulator layout
@@ -1482,7 +1482,7 @@ __device__ __forceinline__ void store_tile_counted_act(f32x16 (&acc)[MB][NB], ui
     constexpr int WN = NB * 32, ROW = WN + 8;
     constexpr int CPR = WN / 8;
     constexpr int T = 32 * CPR / 64;
-    constexpr int kQuads = ACT == 2 ? 2 : 1;               // accumulator quads that are finished together: GELU shares a test
+    constexpr int kQuads = ACT >= 2 ? 2 : 1;               // accumulator quads that are finished together: GELU and SiLU share a test
     const int frag_row = lane & 31, f_hi = (lane >> 5) * 4;
     auto at = [&](int i, int t) -> uint32_t {
         const int idx = lane + 64 * t, mo = m_wave + i * 32 + idx / CPR;

@@ -326,6 +326,47 @@ def test_silu_rounds_like_the_fp32_path(B, C, K, pixels):
     assert np.all(same | nan) and np.isnan(W.bf16_bits_to_f32(got[nan])).all() and nan[..., 2].all()
 
 
+@pytest.mark.parametrize("beside", [0.0, -20.0])
+@pytest.mark.parametrize("lo,hi", [(-10.0, -1.3), (-1.25, 0.0), (0.0, 10.0), (10.0, 1e6), (-20.0, -10.0), (-79.0, -20.0), (-88.0, -79.0)])
+def test_silu_next_to_rounding_ties(B, lo, hi, beside):
+    """Where SiLU's short form could tip a bf16 rounding: the arguments nearest to the middle of two bf16 values, and 20 on either side.
+    An argument is the sum of three bf16 channels, 24 bits in all, which the matrix cores add without rounding; -20 `beside` the
+    arguments makes every wavefront take the form for low values.  The bits of the plain formula, rounded."""
+    rng = np.random.default_rng(abs(int(lo)) + 1)
+    n = 100000
+    mag = np.exp(rng.uniform(np.log(max(min(abs(lo), abs(hi)), 1e-20)), np.log(max(abs(lo), abs(hi))), n))
+    x = np.where(hi <= 0, -mag, mag)
+    with np.errstate(over="ignore"):
+        for _ in range(4):                               # to the tie next to the result
+            s = 1 / (1 + np.exp(-x))
+            y = (x * s).astype(np.float32)
+            tie = ((y.view(np.uint32) & 0xFFFF0000) | 0x8000).view(np.float32).astype(np.float64)
+            x = np.clip(x + (tie - x * s) / (s * (1 + x * (1 - s))), lo, hi)
+    x = (x.astype(np.float32).view(np.int32)[:, None] + np.arange(-20, 20, dtype=np.int32)).view(np.float32).ravel()
+    x = x[np.isfinite(x)]
+    args = 10                                            # a pixel
+    x = x[:len(x) // args * args].reshape(-1, args)
+    cols = [0, 1, 2, 3, 4, 5, 6, 8, 9, 10]               # of 16 filters; the others are `beside`
+    filters = np.zeros((32, 1, 1, 32), np.float32)
+    pieces, rest = np.zeros((len(x), 32), np.float32), x.copy()
+    for part in range(3):
+        top = (rest.view(np.uint32) & 0xFFFF0000).view(np.float32)
+        pieces[:, part * args:(part + 1) * args] = top
+        rest = rest - top
+        filters[cols, 0, 0, part * args + np.arange(args)] = 1
+    assert not rest.any()
+    bias = np.full(32, beside, np.float32)
+    bias[cols] = 0
+    ctx = B.Context(max_requests=1)
+    bits = lambda a: W.f32_to_bf16_bits(a).reshape(a.shape)
+    got, _ = ctx.coe_debug_conv(1, bits(pieces)[None, :, None, :], bits(filters), bias, None, 1, 0, W.ACT_SILU)
+    eye = np.eye(args, dtype=np.float32).reshape(args, 1, 1, args)
+    plain, _ = ctx.coe_debug_conv(0, x[None, :, None, :], eye, np.zeros(args, np.float32), None, 1, 0, W.ACT_SILU)
+    ctx.close()
+    assert np.abs(plain.view(np.int32) % 65536 - 32768).min() <= 2       # ties were met
+    assert np.array_equal(got[0, :, 0, cols].T, bits(plain)[0, :, 0])
+
+
 @pytest.mark.parametrize("H,Wd,C,R,pad", [(14, 14, 256, 5, 2), (7, 9, 64, 5, 2), (22, 23, 32, 5, 2), (20, 20, 96, 5, 2), (13, 13, 64, 7, 3),
                                           (9, 9, 64, 5, 1), (5, 5, 32, 5, 0), (60, 60, 64, 5, 2), (14, 14, 64, 3, 1), (6, 6, 40, 5, 2)])
 def test_pools_with_stride_one(B, H, Wd, C, R, pad):
