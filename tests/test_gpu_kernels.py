@@ -605,10 +605,11 @@ def test_fp32_head_pooling(B, H, Wd, C):
 
 
 @pytest.mark.parametrize("H,Wd,C,n_cls", [(7, 7, 512, 16), (7, 7, 2048, 65), (1, 1, 64, 1), (8, 16, 64, 5), (43, 3, 64, 17), (4, 4, 2048, 4), (1, 17, 2048, 3),
-                                          (33, 31, 512, 9), (5, 5, 96, 6), (65, 1, 512, 2)])
+                                          (33, 31, 512, 9), (5, 5, 96, 6), (65, 1, 512, 2), (16, 8, 256, 4), (12, 12, 256, 4), (29, 5, 256, 4), (127, 1, 256, 4),
+                                          (11, 11, 256, 4)])
 def test_bf16_head_pooling(B, H, Wd, C, n_cls):
     """Average pool and classifier of bf16 experts: sixteen positions in flight per thread, one less and one more, one position group
-    (2048 channels), more classes than one round of the wavefronts takes, and a channel count that keeps the plain loads (96)."""
+    (2048 channels), remainders of none, two and three rounds of the groups, ones that some groups have and others not, more classes than one round of the wavefronts takes, and a channel count that keeps the plain loads (96)."""
     import torch
     n = 3
     p = W._Prog(H, Wd, C)
