@@ -147,14 +147,21 @@ template <int ACT, int N> __device__ __forceinline__ void activate(float (&v)[N]
 // The activation is a launch parameter, but an epilogue that tests it per element compiles into hundreds of
 // branches: dispatch ONCE per wave to a body specialised for the activation.  GELU's body takes up to 40 registers more than the
 // others and would cost every launch of a kernel a wavefront per SIMD (conv_igemm_dma_kernel<128, 128, 2, 2>: 324 -> 362 us on the
-// stride-2 layers of 4096 images), so it is in kernels of its own, which the launchers choose.
-template <bool GELU, typename F> __device__ __forceinline__ void with_activation(int act, F&& body)
+// stride-2 layers of 4096 images), so it is in kernels of its own, which the launchers choose.  So is SiLU's in the kernels that have no
+// registers left (conv_gemm_persistent_kernel spilled up to 18 for it in every launch: 768 -> 2304, 197 positions of 64 images 49.5 us
+// with, 47.0 without, of 100 images 75.3 / 71.3).
+constexpr int kActsElse = 0,      // none, ReLU and SiLU, as the launch says
+              kActsPlain = 1,     // none and ReLU, as the launch says
+              kActsGelu = 2, kActsSilu = 3;
+template <int ACTS, typename F> __device__ __forceinline__ void with_activation(int act, F&& body)
 {
-    if constexpr (GELU) {
+    if constexpr (ACTS == kActsGelu) {
         body(std::integral_constant<int, 2>{});
+    } else if constexpr (ACTS == kActsSilu) {
+        body(std::integral_constant<int, 3>{});
     } else {
         if (act == 1) body(std::integral_constant<int, 1>{});
-        else if (act == 3) body(std::integral_constant<int, 3>{});
+        else if (ACTS == kActsElse && act == 3) body(std::integral_constant<int, ACTS == kActsElse ? 3 : 0>{});
         else body(std::integral_constant<int, 0>{});
     }
 }
@@ -356,7 +363,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_bf16_kernel
     // Epilogue.  With the filter fragment as the first operand, accumulator element v of lane l belongs to pixel l%32
     // and filter 8*(v/4) + 4*(l/32) + v%4 of the 32x32 block: a quad of v is 4 consecutive channels of one pixel.
     const int f_hi = (lane >> 5) * 4;
-    with_activation<GELU>(s.act, [&](auto act_c) {
+    with_activation<GELU ? kActsGelu : kActsElse>(s.act, [&](auto act_c) {
     constexpr int ACT = decltype(act_c)::value;
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
@@ -538,12 +545,12 @@ __device__ __forceinline__ void store_tile_via_lds_act(f32x16 (&acc)[MB][NB], ui
     }
 }
 
-template <bool GELU, int MB, int NB>
+template <int ACTS, int MB, int NB>
 __device__ __forceinline__ void store_tile_via_lds(f32x16 (&acc)[MB][NB], uint16_t* stage, const float* __restrict__ bias,
                                                    const uint16_t* __restrict__ res, uint16_t* __restrict__ y, int m_wave,
                                                    int n_wave, int M, int K, int act, int lane)
 {
-    with_activation<GELU>(act, [&](auto a) {
+    with_activation<ACTS>(act, [&](auto a) {
         if (res) store_tile_via_lds_act<MB, NB, decltype(a)::value, true>(acc, stage, bias, res, y, m_wave, n_wave, M, K, lane);
         else store_tile_via_lds_act<MB, NB, decltype(a)::value, false>(acc, stage, bias, res, y, m_wave, n_wave, M, K, lane);
     });
@@ -742,7 +749,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_igemm_dma_kern
     }
     wait_before_barrier<0>();
     __builtin_amdgcn_s_barrier();        // every wave is done with the operand stages: LDS is free for the epilogue
-    store_tile_via_lds<GELU, MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
+    store_tile_via_lds<GELU ? kActsGelu : kActsElse, MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
 #endif
 }
 
@@ -787,7 +794,7 @@ hipError_t launch_dma(const void* x, const void* wp, const float* bias, const vo
 // ---------------------------------------------------------------------------------------------------------------
 constexpr int kSlabMaxW = 56;
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool GELU>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int ACTS>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv3x3_slab_kernel(const uint16_t* __restrict__ x,
                                                                     const uint16_t* __restrict__ wp_all,
                                                                     const float* __restrict__ bias_all,
@@ -1081,16 +1088,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv3x3_slab_kernel
     }
     wait_before_barrier<0>();
     __builtin_amdgcn_s_barrier();        // every wave is done with the operand stages: LDS is free for the epilogue
-    store_tile_via_lds<GELU, MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
+    store_tile_via_lds<ACTS, MB, NB>(acc, lds + wid * (32 * (WN + 8)), bias, res, y, m0 + wm * WM, n0 + wn * WN, M, s.K, s.act, lane);
 #endif
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, bool GELU = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int ACTS = kActsPlain>
 hipError_t launch_slab(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
                        hipStream_t stream, const Grouping& grp = Grouping())
 {
-    if constexpr (!GELU)
-        if (s.act == 2) return launch_slab<BM, BN, WAVES_M, WAVES_N, true>(x, wp, bias, res, y, s, stream, grp);
+    if constexpr (ACTS == kActsPlain) {
+        if (s.act == 2) return launch_slab<BM, BN, WAVES_M, WAVES_N, kActsGelu>(x, wp, bias, res, y, s, stream, grp);
+        if (s.act == 3) return launch_slab<BM, BN, WAVES_M, WAVES_N, kActsSilu>(x, wp, bias, res, y, s, stream, grp);
+    }
     long long M = (long long)s.N * s.P * s.Q;
     int tiles_n = s.K / BN;
     long long total = count_tiles(M, (long long)s.P * s.Q, BM, tiles_n, grp.table);
@@ -1102,12 +1111,12 @@ hipError_t launch_slab(const void* x, const void* wp, const float* bias, const v
     constexpr int kThreads = 64 * WAVES_M * WAVES_N;
     static bool configured = false;
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void*)conv3x3_slab_kernel<BM, BN, WAVES_M, WAVES_N, GELU>,
+        hipError_t e = hipFuncSetAttribute((const void*)conv3x3_slab_kernel<BM, BN, WAVES_M, WAVES_N, ACTS>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    hipLaunchKernelGGL((conv3x3_slab_kernel<BM, BN, WAVES_M, WAVES_N, GELU>), dim3((unsigned)total), dim3(kThreads), kLdsBytes, stream,
+    hipLaunchKernelGGL((conv3x3_slab_kernel<BM, BN, WAVES_M, WAVES_N, ACTS>), dim3((unsigned)total), dim3(kThreads), kLdsBytes, stream,
                        (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M, tiles_n,
                        grp.table, grp.off_w, grp.off_b);
     return hipGetLastError();
@@ -1395,7 +1404,7 @@ __global__ __launch_bounds__(64 * kRingWaves) void conv_igemm_ring_kernel(const 
     }
     wait_before_barrier<0>();
     if constexpr (QUARTERS) {
-        with_activation<GELU>(s.act, [&](auto a) {
+        with_activation<GELU ? kActsGelu : kActsElse>(s.act, [&](auto a) {
             float v[4] = {acc[0] + q_bias.x, acc[1] + q_bias.y, acc[2] + q_bias.z, acc[3] + q_bias.w};
             if (res) {
                 v[0] += bf16_to_f32(q_res.x & 0xFFFFu); v[1] += bf16_to_f32(q_res.x >> 16);
@@ -1407,7 +1416,7 @@ __global__ __launch_bounds__(64 * kRingWaves) void conv_igemm_ring_kernel(const 
     } else {
         __builtin_amdgcn_s_barrier();    // every wave is done with the operand stages: LDS is free for the epilogue
         f32x16 (&tile_acc)[1][1] = reinterpret_cast<f32x16 (&)[1][1]>(acc);
-        store_tile_via_lds<GELU, 1, 1>(tile_acc, lds + wid * (32 * (T + 8)), bias, res, y, m0 + wm * T, n0 + wn * T, M, s.K, s.act, lane);
+        store_tile_via_lds<GELU ? kActsGelu : kActsElse, 1, 1>(tile_acc, lds + wid * (32 * (T + 8)), bias, res, y, m0 + wm * T, n0 + wn * T, M, s.K, s.act, lane);
     }
 #endif
 }
@@ -1539,7 +1548,7 @@ __device__ __forceinline__ void store_tile_counted_act(f32x16 (&acc)[MB][NB], ui
     }
 }
 
-template <bool ROWS, int MB, int NB, int WAVES_M, int WAVES_N, bool GELU, bool SOURCES>
+template <bool ROWS, int MB, int NB, int WAVES_M, int WAVES_N, int ACTS, bool SOURCES>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_gemm_persistent_kernel(const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ wp_all,
                                                                    const float* __restrict__ bias_all,
@@ -1734,7 +1743,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_gemm_persisten
         step(no{}, yes{}, no{}, c0{});
         const TileOrigin o = locate_tile<BM>(tile, tiles_n, PQ, M_all, wp_all, bias_all, gt, off_w, off_b);
         uint16_t* const stage = lds + STAGES * STAGE + wid * (32 * (WN + 8) + 128);
-        with_activation<GELU>(s.act, [&](auto a) {
+        with_activation<ACTS>(s.act, [&](auto a) {
             constexpr int ACT = decltype(a)::value;
             const int m = o.m0 + wm * WM, n = o.tile_n * BN + wn * WN;
             if (res) store_tile_counted_act<MB, NB, ACT, true>(acc, stage, o.bias, r_rsrc, y_rsrc, m, n, o.m_end, s.K, lane);
@@ -1750,14 +1759,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void conv_gemm_persisten
 #endif
 }
 
-template <bool ROWS, int MB, int NB, int WAVES_M, int WAVES_N, bool GELU = false, bool SOURCES = false>
+template <bool ROWS, int MB, int NB, int WAVES_M, int WAVES_N, int ACTS = kActsPlain, bool SOURCES = false>
 hipError_t launch_gemm_persistent(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
                        hipStream_t stream, const Grouping& grp = Grouping(), const Sources* from = nullptr)
 {
-    if constexpr (!GELU && !SOURCES && ROWS)
-        if (from) return launch_gemm_persistent<ROWS, MB, NB, WAVES_M, WAVES_N, false, true>(x, wp, bias, res, y, s, stream, grp, from);
-    if constexpr (!GELU && !SOURCES)
-        if (s.act == 2) return launch_gemm_persistent<ROWS, MB, NB, WAVES_M, WAVES_N, true>(x, wp, bias, res, y, s, stream, grp);
+    if constexpr (ACTS == kActsPlain && !SOURCES) {
+        if (s.act == 2) return launch_gemm_persistent<ROWS, MB, NB, WAVES_M, WAVES_N, kActsGelu>(x, wp, bias, res, y, s, stream, grp);
+        if (s.act == 3) return launch_gemm_persistent<ROWS, MB, NB, WAVES_M, WAVES_N, kActsSilu>(x, wp, bias, res, y, s, stream, grp, from);
+    }
+    if constexpr (ACTS != kActsGelu && !SOURCES && ROWS)
+        if (from) return launch_gemm_persistent<ROWS, MB, NB, WAVES_M, WAVES_N, ACTS, true>(x, wp, bias, res, y, s, stream, grp, from);
     constexpr int BM = 32 * MB * WAVES_M, BN = 32 * NB * WAVES_N;
     long long M = (long long)s.N * s.P * s.Q;
     int tiles_n = s.K / BN;
@@ -1766,11 +1777,11 @@ hipError_t launch_gemm_persistent(const void* x, const void* wp, const float* bi
     if (total == 0) return hipSuccess;
     constexpr int NW = WAVES_M * WAVES_N, kRowsLds = (BM / 16 + NW - 1) / NW * NW * 16;
     constexpr size_t kLdsBytes = (3 * (size_t)(kRowsLds + BN) * 32 + WAVES_M * WAVES_N * (32 * (32 * NB + 8) + 128)) * sizeof(uint16_t);
-    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N, GELU, SOURCES>,
+    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N, ACTS, SOURCES>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
     if (configured != hipSuccess) return configured;
     const unsigned grid = (unsigned)(total < 256 ? total : 256);
-    hipLaunchKernelGGL((conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N, GELU, SOURCES>), dim3(grid), dim3(64 * WAVES_M * WAVES_N),
+    hipLaunchKernelGGL((conv_gemm_persistent_kernel<ROWS, MB, NB, WAVES_M, WAVES_N, ACTS, SOURCES>), dim3(grid), dim3(64 * WAVES_M * WAVES_N),
                        kLdsBytes, stream, (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M,
                        tiles_n, (int)total, grp.table, grp.off_w, grp.off_b, from ? *from : Sources{});
     return hipGetLastError();

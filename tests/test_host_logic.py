@@ -414,3 +414,30 @@ def test_store_of_many_results_keeps_what_fits(host_checks):
     assert host_checks("store", 4177, 3, 1000, 1 << 30) == ["0 4193708 1 "]
     assert host_checks("store", 4178, 3, 1000, 1 << 30) == ["0 4194304 1 "]
     assert host_checks("store", 1 << 20, 3, 10, 1 << 30) == ["0 4194304 1 "]
+
+
+@pytest.fixture(scope="module")
+def kernel_scratch(B):
+    """Scratch bytes per lane of every gfx950 kernel in libcoe.so, by demangled name: from the metadata of its code objects."""
+    data, found = open(B.LIB_PATH, "rb").read(), {}
+    for at in (m.start() for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", data)):
+        n, pos = int.from_bytes(data[at + 24:at + 32], "little"), at + 32
+        for _ in range(n):
+            off, size, length = (int.from_bytes(data[pos + 8 * i:pos + 8 * i + 8], "little") for i in range(3))
+            triple = data[pos + 24:pos + 24 + length].decode()
+            pos += 24 + length
+            if not triple.endswith("gfx950") or size == 0:
+                continue
+            notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", "-"], input=data[at + off:at + off + size], capture_output=True)
+            assert notes.returncode == 0, notes.stderr
+            text = notes.stdout.decode()
+            found.update(zip(re.findall(r"^ *\.name: +(_Z\S+)$", text, re.M), map(int, re.findall(r"\.private_segment_fixed_size: +(\d+)", text))))
+    names = subprocess.run(["c++filt"], input="\n".join(found), capture_output=True, text=True).stdout.splitlines()
+    return dict(zip(names, found.values()))
+
+
+def test_plain_epilogues_have_no_spills(kernel_scratch):
+    """The launches without SiLU or GELU of the kernels that have no registers to spare: neither activation's body is compiled into them."""
+    plain = [(n, s) for n, s in kernel_scratch.items() if re.search(r"conv3x3_slab_kernel<\d+, \d+, \d+, \d+, 1>|conv_gemm_persistent_kernel<(true|false), \d+, \d+, \d+, \d+, 1, ", n)]
+    assert len(plain) == 4 + 9
+    assert all(s == 0 for _, s in plain), plain
