@@ -147,9 +147,10 @@ template <int ACT, int N> __device__ __forceinline__ void activate(float (&v)[N]
 // The activation is a launch parameter, but an epilogue that tests it per element compiles into hundreds of
 // branches: dispatch ONCE per wave to a body specialised for the activation.  GELU's body takes up to 40 registers more than the
 // others and would cost every launch of a kernel a wavefront per SIMD (conv_igemm_dma_kernel<128, 128, 2, 2>: 324 -> 362 us on the
-// stride-2 layers of 4096 images), so it is in kernels of its own, which the launchers choose.  So is SiLU's in the kernels that have no
-// registers left (conv_gemm_persistent_kernel spilled up to 18 for it in every launch: 768 -> 2304, 197 positions of 64 images 49.5 us
-// with, 47.0 without, of 100 images 75.3 / 71.3).
+// stride-2 layers of 4096 images), so it is in kernels of its own, which the launchers choose.  So is SiLU's where the others
+// lose by it: conv_gemm_persistent_kernel spilled up to 18 registers for it in every launch (768 -> 2304, 197 positions of 64 images 49.5 us
+// with, 47.0 without, of 100 images 75.3 / 71.3), and in conv_igemm_bf16_kernel it cost launches with ReLU 4 % (128 -> 32 on 17 x 13,
+// 200 images 6.31 / 6.07).
 constexpr int kActsElse = 0,      // none, ReLU and SiLU, as the launch says
               kActsPlain = 1,     // none and ReLU, as the launch says
               kActsGelu = 2, kActsSilu = 3;
@@ -171,7 +172,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool GELU>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int ACTS>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_bf16_kernel(const uint16_t* __restrict__ x,
                                                                     const uint16_t* __restrict__ wp,
                                                                     const float* __restrict__ bias,
@@ -363,8 +364,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_bf16_kernel
     // Epilogue.  With the filter fragment as the first operand, accumulator element v of lane l belongs to pixel l%32
     // and filter 8*(v/4) + 4*(l/32) + v%4 of the 32x32 block: a quad of v is 4 consecutive channels of one pixel.
     const int f_hi = (lane >> 5) * 4;
-    with_activation<GELU ? kActsGelu : kActsElse>(s.act, [&](auto act_c) {
+    with_activation<ACTS>(s.act, [&](auto act_c) {
     constexpr int ACT = decltype(act_c)::value;
+    // no load crosses SiLU's branches: its bias is fetched one quad ahead (192 -> 96, 20 x 20, 16 images 5.9 -> 5.6 us, 250 images 22.7 -> 22.0)
+    constexpr bool kAhead = ACT == 3;
+    auto bias_of = [&](int quad) { return *(const float4*)(bias + n0 + wn * WN + 8 * quad + f_hi); };
+    float4 ahead = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (kAhead) ahead = bias_of(0);
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
         const int m = m0 + wm * WM + i * 32 + frag_row;
@@ -375,7 +381,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_bf16_kernel
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int n = n0 + wn * WN + j * 32 + 8 * g + f_hi;
-                const float4 bv = *(const float4*)(bias + n);
+                const float4 bv = kAhead ? ahead : bias_of(4 * j + g);
+                if (kAhead) ahead = bias_of((4 * j + g + 1) % (4 * NB));
                 float v0 = acc[i][j][4 * g + 0] + bv.x, v1 = acc[i][j][4 * g + 1] + bv.y;
                 float v2 = acc[i][j][4 * g + 2] + bv.z, v3 = acc[i][j][4 * g + 3] + bv.w;
                 if (res) {
@@ -392,12 +399,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_igemm_bf16_kernel
     });
 }
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool GELU = false>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, int ACTS = kActsPlain>
 hipError_t launch(const void* x, const void* wp, const float* bias, const void* res, void* y, const ConvShape& s,
                   hipStream_t stream)
 {
-    if constexpr (!GELU)
-        if (s.act == 2) return launch<BM, BN, BK, WAVES_M, WAVES_N, true>(x, wp, bias, res, y, s, stream);
+    if constexpr (ACTS == kActsPlain) {
+        if (s.act == 2) return launch<BM, BN, BK, WAVES_M, WAVES_N, kActsGelu>(x, wp, bias, res, y, s, stream);
+        if (s.act == 3) return launch<BM, BN, BK, WAVES_M, WAVES_N, kActsSilu>(x, wp, bias, res, y, s, stream);
+    }
     long long M = (long long)s.N * s.P * s.Q;
     int tiles_m = (int)((M + BM - 1) / BM), tiles_n = s.K / BN;
     long long total = (long long)tiles_m * tiles_n;
@@ -406,12 +415,12 @@ hipError_t launch(const void* x, const void* wp, const float* bias, const void* 
     constexpr int kThreads = 64 * WAVES_M * WAVES_N;
     static bool configured = false;
     if (!configured) {   // more than the default 64 KiB of LDS per workgroup needs an explicit opt-in
-        hipError_t e = hipFuncSetAttribute((const void*)conv_igemm_bf16_kernel<BM, BN, BK, WAVES_M, WAVES_N, GELU>,
+        hipError_t e = hipFuncSetAttribute((const void*)conv_igemm_bf16_kernel<BM, BN, BK, WAVES_M, WAVES_N, ACTS>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    hipLaunchKernelGGL((conv_igemm_bf16_kernel<BM, BN, BK, WAVES_M, WAVES_N, GELU>), dim3((unsigned)total), dim3(kThreads), kLdsBytes,
+    hipLaunchKernelGGL((conv_igemm_bf16_kernel<BM, BN, BK, WAVES_M, WAVES_N, ACTS>), dim3((unsigned)total), dim3(kThreads), kLdsBytes,
                        stream, (const uint16_t*)x, (const uint16_t*)wp, bias, (const uint16_t*)res, (uint16_t*)y, s, (int)M,
                        tiles_n);
     return hipGetLastError();
@@ -488,6 +497,14 @@ __device__ __forceinline__ void store_tile_via_lds_act(f32x16 (&acc)[MB][NB], ui
     constexpr int T = 32 * CPR / 64;                       // chunks per lane and 32-row block
     constexpr int kQuads = ACT == 3 ? 2 : 1;               // accumulator quads that are finished together: SiLU shares a test
     const int frag_row = lane & 31, f_hi = (lane >> 5) * 4;
+    // no load crosses SiLU's branches: its bias is fetched one test ahead (256 -> 256, 28 x 28, 12 images 10.4 -> 10.25 us)
+    constexpr bool kAhead = ACT == 3;
+    auto bias_of = [&](int quad) { return *(const float4*)(bias + n_wave + 8 * quad + f_hi); };
+    float4 ahead[kQuads];
+    if (kAhead) {
+#pragma unroll
+        for (int h = 0; h < kQuads; ++h) ahead[h] = bias_of(h);
+    }
     // the residual takes the same road in the other direction: row-contiguous 16-byte loads (all issued up front),
     // staged in LDS, picked up in the accumulator layout
     u32x4 rres[MB][T];
@@ -518,7 +535,8 @@ __device__ __forceinline__ void store_tile_via_lds_act(f32x16 (&acc)[MB][NB], ui
 #pragma unroll
                 for (int h = 0; h < kQuads; ++h) {
                     const int nl = j * 32 + 8 * (g + h) + f_hi;
-                    const float4 bv = *(const float4*)(bias + n_wave + nl);
+                    const float4 bv = kAhead ? ahead[h] : bias_of(4 * j + g + h);
+                    if (kAhead) ahead[h] = bias_of((4 * j + g + kQuads) % (4 * NB) + h);
                     v[4 * h] = acc[i][j][4 * (g + h)] + bv.x; v[4 * h + 1] = acc[i][j][4 * (g + h) + 1] + bv.y;
                     v[4 * h + 2] = acc[i][j][4 * (g + h) + 2] + bv.z; v[4 * h + 3] = acc[i][j][4 * (g + h) + 3] + bv.w;
                     if (RES) {
