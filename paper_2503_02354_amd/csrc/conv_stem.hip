@@ -698,7 +698,12 @@ hipError_t launch(const void* x, const void* w, const float* bias, void* y, cons
         if (e != hipSuccess) return e;
         configured = true;
     }
-    int grid = g.total_tiles < 1024 ? g.total_tiles : 1024;
+    // Workgroups that take tiles in turn: with staged stores of 64 channels the 512 that the chip holds (registers and LDS: two per
+    // compute unit), so that all start at once.  us with 1024 / 512: 7x7/2 (3 -> 64, 224 x 224) 16 images 31 / 25, 44 images 57 / 38, 64
+    // images 67 / 50, 250 images 171 / 168; 6x6/2 with SiLU 64 images 58 / 51.  Of 32 channels the chip holds more: 7x7/2, 224 x 224,
+    // 64 images 37 / 36, 250 images 104 / 110.
+    const int most = g.staged && NB == 2 ? 512 : 1024;
+    const int grid = g.total_tiles < most ? g.total_tiles : most;
     hipLaunchKernelGGL((conv_smallc_bf16_kernel<NB, POOL, CPR_, R_>), dim3(grid), dim3(kThreads), smem, stream, (const uint16_t*)x,
                        (const uint16_t*)w, bias, (uint16_t*)y, s, g, rows);
     return hipGetLastError();

@@ -431,6 +431,8 @@ def test_pools_of_few_and_many_images_give_the_same_bits(B, H, Wd, C, R, pad, ma
     (2, 16, 16, 3, 64, 6, 2, 2, 1),      # less than a tile
     (2, 33, 30, 4, 32, 3, 1, 1, 2),      # 32 filters through LDS
     (2, 20, 20, 4, 64, 9, 1, 4, 0),      # filters and patch leave no room: stores out of the accumulators
+    (60, 40, 40, 4, 64, 3, 1, 1, 1),     # through LDS: workgroups of one tile and of two
+    (116, 40, 40, 4, 32, 3, 1, 1, 3),    # the same with 32 filters
 ])
 def test_few_channels_without_pool(B, oracle, n, H, Wd, C, K, R, stride, pad, act):
     """The kernel for few input channels without the fused pool, every output against the oracle."""
