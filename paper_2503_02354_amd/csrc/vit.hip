@@ -27,11 +27,17 @@ __device__ __forceinline__ float scaled(float a, float b)
 #pragma clang fp contract(off)
     return a * b;
 }
+__device__ __forceinline__ float wave_sum_lds(float v)
+{
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    return v;
+}
 template <int CTRL> __device__ __forceinline__ float dpp(float v)
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
-// v + the value of lane ^ 32, then ^ 16, 8, 4, 2 and 1, as a loop of __shfl_xor would have it
+// the same sum without LDS: v + the value of lane ^ 32, then ^ 16, 8, 4, 2 and 1
 __device__ __forceinline__ float wave_sum(float v)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -106,8 +112,11 @@ __global__ __launch_bounds__(256) void tokens_kernel(const uint4* __restrict__ x
 // A launch of a few requests is a chain of latencies: the token, two sums over the wavefront, scale and shift.  Scale and shift are
 // on their way from the start, up to 1024 channels (beyond, their registers would cost long launches half the wavefronts), and
 // the sums exchange lanes by register operations instead of through LDS, in the same order.  us per launch, 985 tokens of 768 channels:
-// 5.5 / 4.3 (6.3 / 4.6 with a group table); five requests, 48 launches, 1975 / 1877.
+// 5.5 / 4.3 (6.3 / 4.6 with a group table); five requests, 48 launches, 1975 / 1877.  Beyond 1280 channels and the tokens that the chip
+// holds at once, the sums go through LDS again: us in LDS / in registers, 1536 channels 4000 tokens 7.7 / 7.5, 16,000 23.4 / 25.2, 32,000
+// 40.0 / 42.3; 2048 channels 4000 tokens 9.8 / 9.5, 8000 18.6 / 19.6, 32,000 53.8 / 56.9; but 1280 channels 16,000 tokens 20.1 / 20.8, 50,432 50.4 / 48.9.
 constexpr int kLnMaxPairs = 16;     // D <= 64 lanes * 2 * 16 = 2048
+constexpr int kLnAtOnce = 256 * 28; // tokens of more than 1024 channels: seven wavefronts per SIMD
 template <bool GROUPED, int PAIRS>
 __global__ __launch_bounds__(256) void layernorm_kernel(const uint32_t* __restrict__ x, const float* __restrict__ gamma,
                                                         const float* __restrict__ beta, uint32_t* __restrict__ y, int rows,
@@ -147,7 +156,8 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint32_t* __restri
         sum += v[2 * j] + v[2 * j + 1];
     }
     const float inv_d = 1.f / (float)(2 * D2);
-    const float mean = wave_sum(sum) * inv_d;
+    const bool by_lds = !kAhead && D2 > 640 && rows > kLnAtOnce;
+    const float mean = (by_lds ? wave_sum_lds(sum) : wave_sum(sum)) * inv_d;
     float sq = 0.f;
 #pragma unroll
     for (int j = 0; j < PAIRS; ++j) {
@@ -156,7 +166,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint32_t* __restri
             sq += p * p + q * q;
         }
     }
-    const float rstd = rsqrtf(wave_sum(sq) * inv_d + 1e-6f);
+    const float rstd = rsqrtf((by_lds ? wave_sum_lds(sq) : wave_sum(sq)) * inv_d + 1e-6f);
 #pragma unroll
     for (int j = 0; j < PAIRS; ++j) {
         const int c = lane + 64 * j;

@@ -482,6 +482,27 @@ def test_attention_block_counts(B, oracle, T, heads, n):
         assert np.mean(got[i] == want) > 0.9
 
 
+@pytest.mark.parametrize("D", [1024, 1280, 1282, 2048])
+def test_layer_norms_of_few_and_many_tokens_give_the_same_bits(B, D):
+    """Beyond 1280 channels and the tokens that the chip holds at once (7168), the sums of a layer norm take another road, in the same order."""
+    import torch
+    T, few, many = 200, 3, 37
+    p = W._Prog(T, 1, D)
+    p.raw([W.OP_LAYERNORM, 0, 1, -1, D, 0, 0, 0, 0, 0, 0, 0])
+    p.shape[1] = (T, 1, D)
+    p.head(1, 4)
+    arch = W.Arch("layernorm", W.DT_BF16, T, 1, D, 4, np.array(p.layers, dtype=np.int32), p.gains)
+    x = _bf16(np.random.default_rng(D), few, T, 1, D)[np.arange(many) % few]
+    dev = torch.from_numpy(x.view(np.int16)).cuda()
+    ctx = B.Context(max_requests=many, max_batch=many)
+    ctx.coe_register_expert(0, ctx.coe_register_arch(arch), W.make_expert_blob(arch, 7, 0), 1.0)
+    small, large = (ctx.coe_debug_layer_output(0, n, dev.data_ptr(), 0, (n, T, D), np.uint16) for n in (few, many))
+    ctx.close()
+    xf = W.bf16_bits_to_f32(x[:few]).reshape(few, T, D).astype(np.float64)
+    assert W.bf16_bits_to_f32(small).std() > 0.5 * xf.std() > 0
+    assert all(np.array_equal(large[i], small[i % few]) for i in range(many))
+
+
 @pytest.mark.parametrize("H,Wd,n", [
     (224, 224, 3),        # the image of most experts: four strips of 14 pooled columns
     (64, 64, 1300),       # two strips of 8; wavefronts that take several strips
