@@ -247,6 +247,41 @@ def test_few_tiles_give_the_bits_of_many(B, oracle, H, Wd, C, K, R, stride, pad,
     assert np.all(np.abs(got - want) <= np.maximum(np.abs(want) * 2.0 ** -7, 1e-5))
 
 
+@pytest.mark.parametrize("values", ["exponents", "cancelling", "denormal", "bits"])
+@pytest.mark.parametrize("hw,C,K,R,few,some,many", [(14, 128, 256, 1, 1, 40, 300), (14, 64, 128, 3, 1, 60, 400), (7, 512, 512, 3, 2, 60, 150)])
+def test_products_of_few_tiles_sum_like_those_of_many(B, hw, C, K, R, few, some, many, values):
+    """A 16 x 16 x 32 product (32 x 32 tiles: few images) sums in the order of two 32 x 32 x 16 ones (64 x 64 tiles, and the kernels of many
+    tiles), whatever the operands: exponents 24 powers of two apart, terms that cancel but for their last bits, products and sums in
+    fp32's denormals, any finite bit patterns."""
+    rng = np.random.default_rng(hw + C + R)
+
+    def operands(*shape):
+        n = int(np.prod(shape))
+        if values == "bits":
+            b = rng.integers(0, 1 << 16, n).astype(np.uint16)
+            b[(b & 0x7F80) > 0x5D80] &= 0xBFFF                       # below 2^61: products and sums stay finite
+            return b.reshape(shape)
+        v = rng.standard_normal(n).astype(np.float32)
+        if values == "exponents":
+            v *= np.exp2(rng.integers(-12, 13, n)).astype(np.float32)
+        return W.f32_to_bf16_bits(v).reshape(shape)
+    x, w = operands(few + 1, hw, hw, C), operands(K, R, R, C)
+    if values == "cancelling":                                       # neighbouring channels: pixels equal but for a bit, filters opposite
+        x[..., 1::2] = x[..., ::2] ^ (rng.random(x[..., ::2].shape) < 0.3)
+        w[..., 1::2] = w[..., ::2] ^ 0x8000
+    if values == "denormal":
+        x = W.f32_to_bf16_bits(np.ldexp(W.bf16_bits_to_f32(x), -128)).reshape(x.shape)
+        w = W.f32_to_bf16_bits(np.ldexp(W.bf16_bits_to_f32(w), -8)).reshape(w.shape)
+    bias = np.zeros(K, np.float32)
+    ctx = B.Context(max_requests=1)
+    outs = [ctx.coe_debug_conv(1, x[np.arange(n) % (few + 1)], w, bias, None, 1, R // 2, 0)[0] for n in (few, some, many)]
+    ctx.close()
+    assert np.count_nonzero(outs[0] & 0x7FFF) > outs[0].size // 2
+    for y in outs[1:]:
+        for i in range(0, len(y) - few, few + 1):
+            assert np.array_equal(y[i:i + few], outs[0]), i
+
+
 def _tiles(n, P, Q, K, side):
     return -(-n * P * Q // side) * (K // side)
 
