@@ -1814,16 +1814,16 @@ bool conv_mfma_uses_slab(const ConvShape& s)
 
 namespace {
 
-// Launches with few output tiles go to conv_igemm_ring_kernel (same bits).  Measured on single launches, microseconds
-// with 4-5 of launch and event overhead (kernel the shape otherwise takes / 32 x 32 tiles / 64 x 64 tiles):
-//   512 -> 512, 3x3, 7 x 7:   1 image 54 / 13 / 16,  30 images 58 / 20 / 17,  100 images 61 / 63 / 46
-//   256 -> 256, 3x3, 14 x 14: 1 image 32 / 9 / 11,   20 images 33 / 18 / 12,  30 images 34 / 23 / 19
-//   128 -> 128, 3x3, 28 x 28: 1 image 20 / 7 / 9,    30 images 22 / 27 / 20
-//   64 -> 64, 3x3, 56 x 56:   1 image 10 / 6 / 7,    30 images 16 / 36 / 27
-//   3072 -> 768, 1x1, 197 positions: 1 image 34 / 14 / 17,  5 images 35 / 26 / 18
-//   768 -> 2304, 1x1, 197 positions: 1 image 13 / 8 / 9,    5 images 14 / 20 / 15
-// (32 x 32 tiles of one wavefront, as they were then.)  These are ahead while the chip holds all tiles at once at two per compute
-// unit; 64 x 64 tiles, which share operands between four wavefronts, while there are about two of them (three: 3x3) per compute unit.
+// Launches with few output tiles go to conv_igemm_ring_kernel (same bits).  us a launch, launches one behind the other (kernel the shape
+// otherwise takes / 32 x 32 tiles / 64 x 64 tiles; in brackets how many of these):
+//   512 -> 512, 3x3, 7 x 7:   1 image 53 / 7.5 / 12,   20 (496, 128) 57 / 11.8 / 12.3,  24 (592, 152) 57 / 16.6 / 12.3,  100 (2464, 616) 58 / 53 / 39
+//   256 -> 256, 3x3, 14 x 14: 1 image 32 / 5.5 / 7.8,  8 (392, 100) 32 / 7.7 / 8.0,     12 (592, 148) 33 / 10.7 / 8.2,   50 (2456, 616) 33 / 33 / 22
+//   128 -> 128, 3x3, 28 x 28: 1 image 20 / 4.6 / 5.8,  5 (492, 124) 20 / 6.0 / 5.9,     6 (588, 148) 20 / 7.9 / 6.0,     24 (2352, 588) 21 / 21 / 14
+//   64 -> 64, 3x3, 56 x 56:   1 image 8.1 / 4.1 / 4.8, 2 (392, 98) 8.2 / 4.8 / 4.9,     3 (588, 147) 8.2 / 6.4 / 5.0,    12 (2352, 588) 8.9 / 15 / 10.2
+//   3072 -> 768, 1x1, 197 positions: 1 image 32 / 7.9 / 11.8,  3 (456, 120) 33 / 12.1 / 13.4,  4 (600, 156) 33 / 20 / 13.9,  8 (1200, 300) 33 / 37 / 24
+//   768 -> 768, 1x1, 197 positions:  1 image 11.4 / 4.7 / 5.7, 3 (456, 120) 11.5 / 5.2 / 5.8,  4 (600, 156) 11.6 / 7.2 / 5.8, 16 (2376, 600) 12.4 / 25 / 14.2
+// 32 x 32 tiles are ahead while the chip holds all of them at once, two per compute unit; 64 x 64 tiles, which share operands between four
+// wavefronts, while there are about two of them (three: 3x3) per compute unit.
 constexpr long long kRingTiles32 = 512, kRingTiles64 = 512, kRingTiles64Slab = 768;
 
 // Which tiles a long GEMM-like launch takes: height / 64 of conv_gemm_persistent_kernel's tiles, or 0 for the 128 x 128 tiles of
