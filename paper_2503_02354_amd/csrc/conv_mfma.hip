@@ -576,8 +576,8 @@ __device__ __forceinline__ void store_tile_via_lds(f32x16 (&acc)[MB][NB], uint16
 
 // A 1x1 convolution over the concatenation of up to kMaxSources maps of equal shape reads them where they lie (SOURCES): the shape
 // says C channels a map and R maps, and map k takes the place of window position k.  The order of the reduction is that of the
-// concatenated map.  Concatenating cost a read and a write of every map and a launch: in the pass of 1000 requests through detectors,
-// now 12.6 ms, 28 launches of 1.0 ms.
+// concatenated map.  Concatenating cost a read and a write of every map and a launch: in a pass of 1000 requests through detectors, of
+// 13 ms, 28 launches, 1.0 ms in all.
 struct Sources {
     const uint16_t* rest[kMaxSources - 1];      // the maps after the first
 };
@@ -1149,11 +1149,11 @@ hipError_t launch_slab(const void* x, const void* wp, const float* bias, const v
 // shape otherwise takes (slab_order: channel blocks outside, window positions inside), hence the same bits.
 //   * STAGES stages of UN 32-channel steps each in LDS, all but two of them in flight; one barrier per stage.
 //   * operands of a stage are read into registers while the stage before it is multiplied, and the loads of a later one issued,
-//     each between two products: a wave issues in order, and what stands in front of the products delays them.  us, reads, then
-//     loads, then products / this order: 3072 -> 768, 197 rows 11.3 / 9.1, 985 rows 16.0 / 13.9; 3x3 stride 2, 256 -> 512 on 14 x 14,
-//     1 image 9.9 / 8.1, 29 images 13.4 / 11.2; 3x3 stride 1, 512 -> 512 on 7 x 7, 1 image 10.1 / 9.4, 29 images 14.1 / 13.2.
+//     each between two products: a wave issues in order, and what stands in front of the products delays them.  us, 64 x 64
+//     tiles, reads, then loads, then products / this order: 3072 -> 768, 985 rows 16.0 / 13.9; 3x3 stride 2, 256 -> 512 on 14 x 14, 29 images
+//     13.4 / 11.2; 3x3 stride 1, 512 -> 512 on 7 x 7, 29 images 14.1 / 13.2; but 3x3, 64 -> 256 on 14 x 14, 30 images 6.7 / 6.85.
 //   * 32 x 32 tiles are four wavefronts of 16 x 16 (T = 16): a product of 16 x 16 x 32 sums in the order of two of 32 x 32 x 16 one after the
-//     other (no bit of 150,000 sums over 32 to 512 elements differs) and the chain of them, which bounds a tile of one wavefront (144
+//     other (also with exponents far apart, cancelling terms and denormals) and the chain of them, which bounds a tile of one wavefront (144
 //     steps of 64 cycles where 512 channels go into a 3x3 window), takes a quarter of the time; a step's four loads are one per
 //     wavefront, so more of them are in flight; bias and residual are fetched first and 8-byte stores leave straight from the
 //     accumulators.  us per launch, one image, a tile of one wavefront / of four: 3x3 512 -> 512 on 7 x 7 9.3 / 8.1, 256 -> 256 on
@@ -1974,7 +1974,7 @@ hipError_t conv_mfma(const void* x, const void* wp, const float* bias, const voi
 
 bool conv_mfma_sources_supported(const ConvShape& one, int32_t n_sources)
 {
-    // (K = 64 m: every kernel that such a launch may take knows sources; GELU has instantiations of its own, which do not)
+    // (K = 64 m: every kernel that such a launch may take knows sources; GELU's instantiations do not)
     return n_sources >= 2 && n_sources <= kMaxSources && one.R == 1 && one.S == 1 && one.stride == 1 && one.pad == 0 && one.act != 2 &&
            one.C > 0 && one.C % 32 == 0 && one.K > 0 && one.K % 64 == 0;
 }
