@@ -519,6 +519,17 @@ __global__ __launch_bounds__(kHeadThreads) void head_gap_fc_kernel(const T* __re
     constexpr int kWaves = kHeadThreads / kWave;
     const int slot = r.slot ? r.slot[row] : row;
     const int depth = threadIdx.x == 0 && r.cur ? r.depth[slot] : 0;
+    // and so are the weights of phase 2 where its first round takes all classes: an expert's come from memory (one request through
+    // ResNet-18 shapes, 7.1 us a launch without, 6.7 with; weights that are in the cache gain nothing); of 1000 classes they would be a part
+    uint4 first_w[4];
+    const bool ahead = head_vector_path<T>(C) && ncls <= 4 * kWaves;
+    if (ahead) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = wid + u * kWaves;
+            first_w[u] = j < ncls && lane < C / 8 ? *(const uint4*)((const uint16_t*)w + (size_t)j * C + lane * 8) : make_uint4(0, 0, 0, 0);
+        }
+    }
     // phase 1: per-channel sums, lanes run along channels (contiguous in NHWC)
     if (head_vector_path<T>(C)) {
         // bf16, C a multiple of 8 with C/8 dividing the block: 16-byte loads, 8 channels per thread, the positions
@@ -528,7 +539,6 @@ __global__ __launch_bounds__(kHeadThreads) void head_gap_fc_kernel(const T* __re
         // Loads in flight, not their number, bound a workgroup: us a launch, a load at a time / sixteen, 196 positions of 256 channels, one
         // request 8.0 / 6.7, 3136 of 64 channels 18.7 / 10.3, 49 of 2048 channels 30.6 / 26.9.  What is left after whole rounds is loaded only
         // where there is a position (a load for every place, 3136 of 64 channels: 12.1); the others add a zero, which changes no sum.
-        // Weights fetched ahead during this phase gained nothing, and with 1000 classes cost 2 %.
         constexpr int kFlight = 16;
         const uint16_t* const at = (const uint16_t*)xp + chunk * 8;
         float a8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -626,10 +636,15 @@ __global__ __launch_bounds__(kHeadThreads) void head_gap_fc_kernel(const T* __re
             float a[4] = {0.f, 0.f, 0.f, 0.f};
             for (int ch = lane; ch < cpb; ch += kWave) {
                 uint4 wv[4];
+                if (ahead && ch == lane) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int j = j0 + u * kWaves;
-                    wv[u] = j < ncls ? *(const uint4*)(wq + (size_t)j * C + ch * 8) : make_uint4(0, 0, 0, 0);
+                    for (int u = 0; u < 4; ++u) wv[u] = first_w[u];
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int j = j0 + u * kWaves;
+                        wv[u] = j < ncls ? *(const uint4*)(wq + (size_t)j * C + ch * 8) : make_uint4(0, 0, 0, 0);
+                    }
                 }
                 const float4 f0 = *(const float4*)(feat + ch * 8), f1 = *(const float4*)(feat + ch * 8 + 4);
 #pragma unroll
