@@ -27,9 +27,9 @@ PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 # scaled by what the same counters read for the gather kernel's plain copy (profiles/conv3x3_slab_config2_hbm_counters.md).
 # Tied to the kernel source and the launch configuration it was measured on: an edit of that file, another workload,
 # batch cap or grouping threshold make bench.py report null again.
-SLAB_TRAFFIC_BYTES_PER_LAUNCH = 2331.5e6
+SLAB_TRAFFIC_BYTES_PER_LAUNCH = 2332.2e6
 SLAB_TRAFFIC_SOURCE = ("paper_2503_02354_amd/csrc/conv_mfma.hip",
-                       "1860f764d5f528a06c06bc04d64eaf8296f44321947661bb75ccd08042b7f884")
+                       "9c42113171ca34049f913e7a3dd828e4a3531b3c0ff15834ae486001ed0db8e8")
 SLAB_TRAFFIC_LAUNCH_CONFIG = ("config2", 0, 4096, 512, 1, "")   # workload, requests, max_batch, group_small, arrivals per step, window
 
 

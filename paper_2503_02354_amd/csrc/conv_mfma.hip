@@ -150,7 +150,7 @@ template <int ACT, int N> __device__ __forceinline__ void activate(float (&v)[N]
 // stride-2 layers of 4096 images), so it is in kernels of its own, which the launchers choose.  So is SiLU's where the others
 // lose by it: conv_gemm_persistent_kernel spilled up to 18 registers for it in every launch (768 -> 2304, 197 positions of 64 images 49.5 us
 // with, 47.0 without, of 100 images 75.3 / 71.3), and in conv_igemm_bf16_kernel it cost launches with ReLU 4 % (128 -> 32 on 17 x 13,
-// 200 images 6.31 / 6.07).
+// 200 images 6.31 / 6.07); in conv_igemm_ring_kernel a pass of one request through ResNet-18 shapes took 1 to 2 % longer with it.
 constexpr int kActsElse = 0,      // none, ReLU and SiLU, as the launch says
               kActsPlain = 1,     // none and ReLU, as the launch says
               kActsGelu = 2, kActsSilu = 3;
@@ -1179,7 +1179,7 @@ struct RingSecond {
     uint32_t first_tiles;      // tiles of the first convolution
 };
 
-template <bool SLAB_ORDER, int T, int UN, int STAGES, bool GELU, bool PAIR, bool SOURCES>
+template <bool SLAB_ORDER, int T, int UN, int STAGES, int ACTS, bool PAIR, bool SOURCES>
 __global__ __launch_bounds__(64 * kRingWaves) void conv_igemm_ring_kernel(const uint16_t* __restrict__ x,
                                                                    const uint16_t* __restrict__ wp_all,
                                                                    const float* __restrict__ bias_all,
@@ -1422,7 +1422,7 @@ __global__ __launch_bounds__(64 * kRingWaves) void conv_igemm_ring_kernel(const 
     }
     wait_before_barrier<0>();
     if constexpr (QUARTERS) {
-        with_activation<GELU ? kActsGelu : kActsElse>(s.act, [&](auto a) {
+        with_activation<ACTS>(s.act, [&](auto a) {
             float v[4] = {acc[0] + q_bias.x, acc[1] + q_bias.y, acc[2] + q_bias.z, acc[3] + q_bias.w};
             if (res) {
                 v[0] += bf16_to_f32(q_res.x & 0xFFFFu); v[1] += bf16_to_f32(q_res.x >> 16);
@@ -1434,7 +1434,7 @@ __global__ __launch_bounds__(64 * kRingWaves) void conv_igemm_ring_kernel(const 
     } else {
         __builtin_amdgcn_s_barrier();    // every wave is done with the operand stages: LDS is free for the epilogue
         f32x16 (&tile_acc)[1][1] = reinterpret_cast<f32x16 (&)[1][1]>(acc);
-        store_tile_via_lds<GELU ? kActsGelu : kActsElse, 1, 1>(tile_acc, lds + wid * (32 * (T + 8)), bias, res, y, m0 + wm * T, n0 + wn * T, M, s.K, s.act, lane);
+        store_tile_via_lds<ACTS, 1, 1>(tile_acc, lds + wid * (32 * (T + 8)), bias, res, y, m0 + wm * T, n0 + wn * T, M, s.K, s.act, lane);
     }
 #endif
 }
@@ -1450,15 +1450,17 @@ struct ConvArgs {
 };
 
 // b != nullptr: a second convolution, over the same groups, in the same launch
-template <bool SLAB_ORDER, int T, int UN, int STAGES, bool GELU = false, bool PAIR = false, bool SOURCES = false>
+template <bool SLAB_ORDER, int T, int UN, int STAGES, int ACTS = kActsPlain, bool PAIR = false, bool SOURCES = false>
 hipError_t launch_ring(const ConvArgs& a, hipStream_t stream, const ConvArgs* b = nullptr)
 {
-    if constexpr (!GELU && !PAIR && !SOURCES && !SLAB_ORDER)
-        if (a.from) return launch_ring<SLAB_ORDER, T, UN, STAGES, false, false, true>(a, stream);
-    if constexpr (!GELU && !PAIR && !SOURCES)
-        if (a.s.act == 2) return launch_ring<SLAB_ORDER, T, UN, STAGES, true>(a, stream);
-    if constexpr (!GELU && !PAIR && !SOURCES && !SLAB_ORDER)
-        if (b) return launch_ring<SLAB_ORDER, T, UN, STAGES, false, true>(a, stream, b);
+    if constexpr (ACTS == kActsPlain) {                       // (pairs and sources, which never have GELU: the others in one)
+        if constexpr (!SLAB_ORDER) {
+            if (a.from) return launch_ring<SLAB_ORDER, T, UN, STAGES, kActsElse, false, true>(a, stream);
+            if (b) return launch_ring<SLAB_ORDER, T, UN, STAGES, kActsElse, true>(a, stream, b);
+        }
+        if (a.s.act == 2) return launch_ring<SLAB_ORDER, T, UN, STAGES, kActsGelu>(a, stream);
+        if (a.s.act == 3) return launch_ring<SLAB_ORDER, T, UN, STAGES, kActsSilu>(a, stream);
+    }
     constexpr int BM = 2 * T, BN = 2 * T;
     const long long M = (long long)a.s.N * a.s.P * a.s.Q;
     long long total = count_tiles(M, (long long)a.s.P * a.s.Q, BM, a.s.K / BN, a.grp.table);
@@ -1472,10 +1474,10 @@ hipError_t launch_ring(const ConvArgs& a, hipStream_t stream, const ConvArgs* b 
     if (total == 0) return hipSuccess;
     constexpr size_t kLdsBytes = STAGES * UN * (size_t)(BM + BN) * 32 * sizeof(uint16_t);
     static_assert(kLdsBytes <= 160 * 1024 && kLdsBytes >= (T == 16 ? 0 : (size_t)kRingWaves * 32 * (T + 8) * 2), "operand stages and epilogue rows");
-    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_igemm_ring_kernel<SLAB_ORDER, T, UN, STAGES, GELU, PAIR, SOURCES>,
+    static const hipError_t configured = hipFuncSetAttribute((const void*)conv_igemm_ring_kernel<SLAB_ORDER, T, UN, STAGES, ACTS, PAIR, SOURCES>,
                                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
     if (configured != hipSuccess) return configured;
-    hipLaunchKernelGGL((conv_igemm_ring_kernel<SLAB_ORDER, T, UN, STAGES, GELU, PAIR, SOURCES>), dim3((unsigned)total), dim3(64 * kRingWaves),
+    hipLaunchKernelGGL((conv_igemm_ring_kernel<SLAB_ORDER, T, UN, STAGES, ACTS, PAIR, SOURCES>), dim3((unsigned)total), dim3(64 * kRingWaves),
                        kLdsBytes, stream, (const uint16_t*)a.x, (const uint16_t*)a.wp, a.bias, (const uint16_t*)a.res, (uint16_t*)a.y, a.s, (int)M,
                        a.s.K / BN, a.grp.table, a.grp.off_w, a.grp.off_b, b ? (const uint16_t*)b->x : nullptr, b ? (const uint16_t*)b->wp : nullptr,
                        b ? b->bias : nullptr, b ? (const uint16_t*)b->res : nullptr, b ? (uint16_t*)b->y : nullptr, second, a.from ? *a.from : Sources{});
